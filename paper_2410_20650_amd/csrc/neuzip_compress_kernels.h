@@ -150,6 +150,23 @@ struct SourceVec {
         }
     }
     __device__ __forceinline__ void clear() { a = b = make_uint4(0, 0, 0, 0); }
+    // the first `valid` (1..7) elements of a vector that passes the tensor's end, the others zero
+    __device__ __forceinline__ void load_some(const void *__restrict__ src, uint64_t first, uint32_t valid)
+    {
+        uint32_t e[8];
+#pragma unroll
+        for (uint32_t t = 0; t < 8; ++t) {
+            e[t] = 0;
+            if (t < valid)
+                e[t] = WIDE ? static_cast<const uint32_t *>(src)[first + t] : static_cast<const uint16_t *>(src)[first + t];
+        }
+        if constexpr (WIDE) {
+            a = make_uint4(e[0], e[1], e[2], e[3]);
+            b = make_uint4(e[4], e[5], e[6], e[7]);
+        } else {
+            a = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+        }
+    }
     __device__ __forceinline__ void words(uint32_t (&w)[4]) const
     {
         if constexpr (WIDE) {
@@ -849,7 +866,8 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
     float least_rcp = 1.0f;  // 0 once a symbol without room in the table has been met
     uint8_t *__restrict__ sm = it.sm;
 
-    if (m == kChunk) {
+    const bool whole_wave = __all(m == kChunk || m == 0);
+    if (whole_wave && m == kChunk) {
         // One turn: the vector of turn q - 2 is requested into the buffer that is free (the wait for a
         // turn's words then leaves the stores of the turn before -- ring flush, fields -- in flight
         // instead of waiting for them), then turn q is coded from its buffer.
@@ -909,39 +927,91 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
             turn(d0, g0, d2, g2, q);
         if constexpr (kTurns % 3 == 2)
             turn(d1, g1, d0, g0, q - 1);
-    } else if (m > 0) {
-        for (int q = static_cast<int>(kTurns) - 1; q >= 0; --q) {
-            const uint32_t wp_before = st.wp, cur_before = st.cur;
-            uint64_t packed = 0;
-            for (int t = static_cast<int>(kRun) - 1; t >= 0; --t) {
-                const uint32_t i = static_cast<uint32_t>(q) * kTurn + j * kRun + static_cast<uint32_t>(t);
-                if (i < m) {
-                    uint32_t u = source_word<WIDE, (SPLIT >= 0)>(src, low, base + i);
-                    if constexpr (UPD) {
-                        u = update_word(u, grad[base + i], lr);
-                        if (b.keep_new)
-                            static_cast<uint16_t *>(const_cast<void *>(src))[base + i] = static_cast<uint16_t>(u);
+    } else if (!whole_wave && m > 0) {
+        // The wave with the tensor's ragged last chunk: every lane codes the turns its chunk has, the last
+        // one possibly with fewer than 8 elements of its own (read one by one: the source is the caller's and
+        // ends there); a turn's words are requested while the one above it is coded.
+        auto valid_of = [&](int q) -> uint32_t {
+            const uint32_t first = static_cast<uint32_t>(q) * kTurn + j * kRun;
+            return first >= m ? 0u : (m - first < kRun ? m - first : kRun);
+        };
+        auto request = [&](int q, SourceVec<WIDE> &d, uint4 &g) {
+            const uint32_t valid = valid_of(q);
+            const uint64_t first = base + static_cast<uint32_t>(q) * kTurn + j * kRun;
+            if (valid == kRun) {
+                d.load(src4, static_cast<uint32_t>(q) * kStates);
+                if constexpr (UPD)
+                    g = grad4[static_cast<uint32_t>(q) * kStates];
+            } else if (valid > 0) {
+                d.load_some(src, first, valid);
+                if constexpr (UPD) {
+                    SourceVec<false> some;
+                    some.load_some(grad, first, valid);
+                    g = some.a;
+                }
+            }
+        };
+        d0.clear();
+        int q = static_cast<int>((m - 1) / kTurn);
+        request(q, d0, g0);
+        for (; q >= 0; --q) {
+            d1.clear();
+            if (q > 0)
+                request(q - 1, d1, g1);
+            const uint32_t valid = valid_of(q);
+            const uint64_t first = base + static_cast<uint32_t>(q) * kTurn + j * kRun;
+            uint32_t w[4];
+            d0.words(w);
+            if constexpr (UPD) {
+                w[0] = update_pair(w[0], g0.x, lr);
+                w[1] = update_pair(w[1], g0.y, lr);
+                w[2] = update_pair(w[2], g0.z, lr);
+                w[3] = update_pair(w[3], g0.w, lr);
+                if (b.keep_new) {
+                    uint16_t *back = static_cast<uint16_t *>(const_cast<void *>(src)) + first;
+                    if (valid == kRun) {
+                        *reinterpret_cast<uint4 *>(back) = make_uint4(w[0], w[1], w[2], w[3]);
+                    } else {
+#pragma unroll
+                        for (uint32_t t = 0; t < kRun; ++t)
+                            if (t < valid)
+                                back[t] = static_cast<uint16_t>(w[t >> 1] >> (16 * (t & 1)));
                     }
-                    if constexpr (NORM)
-                        u = normalise_word(u, coefficient(coef[(base + i) >> block_shift]));
-                    const EncSym e = enc[symbol_of<HALF>(u)];
+                }
+            }
+            if constexpr (SPLIT >= 0) {
+                // (the sections of the blob are padded by 256 bytes)
+                if (valid > 0) {
+                    uint64_t packed = fields_of<KB, HALF>(w);
+                    if (valid < kRun)  // nothing of the elements past the end: unused bits are zero
+                        packed &= (1ull << (valid * (KB + 1))) - 1ull;
+                    store_fields<KB>(sm, first / 8, packed);
+                    if constexpr (WIDE)
+                        *reinterpret_cast<uint4 *>(low + first) = d0.lows();
+                }
+            }
+            const uint32_t wp_before = st.wp, cur_before = st.cur;
+            float c = 1.0f;
+            if constexpr (NORM) {
+                if (valid > 0)
+                    c = coefficient(coef[first >> block_shift]);
+            }
+#pragma unroll
+            for (int t = static_cast<int>(kRun) - 1; t >= 0; --t) {
+                if (static_cast<uint32_t>(t) < valid) {
+                    const uint32_t raw = (w[t >> 1] >> (16 * (t & 1))) & 0xFFFFu;
+                    const EncSym e = enc[symbol_of<HALF>(NORM ? normalise_word(raw, c) : raw)];
                     if constexpr (SPLIT >= 0) {
                         least_rcp = fminf(least_rcp, e.rcp);
-                        packed |= static_cast<uint64_t>(field_of<KB, HALF>(u)) << (static_cast<uint32_t>(t) * (KB + 1));
+                        asm volatile("" : "+v"(least_rcp));
                     }
                     rans_put(st, e, ring_bytes, lane_ring);
                 }
             }
-            if constexpr (SPLIT >= 0) {
-                // the fields of this lane's run: whole bytes; a last partial byte has zero high bits
-                constexpr uint32_t per_byte = 8 / (KB + 1);
-                const uint32_t first = static_cast<uint32_t>(q) * kTurn + j * kRun;
-                const uint32_t valid = first >= m ? 0u : (m - first < kRun ? m - first : kRun);
-                for (uint32_t t = 0; t < valid; t += per_byte)
-                    sm[(base + first + t) / per_byte] = static_cast<uint8_t>(packed >> (t * (KB + 1)));
-            }
             ring_advance(st, cur_before);
             ring_flush(wp_before, st.wp, ring, chunk_slots, j);
+            d0 = d1;
+            g0 = g1;
         }
     }
     if constexpr (SPLIT >= 0) {

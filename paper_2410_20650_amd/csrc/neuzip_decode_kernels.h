@@ -182,6 +182,102 @@ __device__ __forceinline__ uint32_t denormalise_pair(uint32_t d, float c)
     return r;
 }
 
+// The four output dwords of a turn from its field bits (load_turn) and the eight slot-table entries that
+// decoded its symbols.
+template <int KB, bool NORM, bool HALF>
+__device__ __forceinline__ uint4 merge_turn(uint64_t fields, const uint32_t (&e)[8], const uint2 *__restrict__ spread)
+{
+    uint4 o;
+    if constexpr (HALF) {
+        o.x = merge_pair_half(fields, 0, e[0], e[1]);
+        o.y = merge_pair_half(fields, 1, e[2], e[3]);
+        o.z = merge_pair_half(fields, 2, e[4], e[5]);
+        o.w = merge_pair_half(fields, 3, e[6], e[7]);
+    } else if constexpr (KB <= 1) {
+        o = merge_turn_small<KB>(fields, e, spread);
+    } else {
+        o.x = merge_pair<KB>(fields, 0, e[0], e[1]);
+        o.y = merge_pair<KB>(fields, 1, e[2], e[3]);
+        o.z = merge_pair<KB>(fields, 2, e[4], e[5]);
+        o.w = merge_pair<KB>(fields, 3, e[6], e[7]);
+    }
+    if constexpr (NORM) {
+        const float c = coefficient(static_cast<uint32_t>(fields >> 32) & 0x7Fu);
+        o.x = denormalise_pair(o.x, c);
+        o.y = denormalise_pair(o.y, c);
+        o.z = denormalise_pair(o.z, c);
+        o.w = denormalise_pair(o.w, c);
+    }
+    return o;
+}
+
+// The wave that holds a tensor's ragged last chunk: every lane walks the turns its chunk has (m elements;
+// the other chunks of the wave are whole and walk beside it), the last one possibly with fewer than 8
+// elements of its own.  Fields are read a whole turn at a time and one turn ahead: the sections of the
+// blob they come from are padded by 256 bytes, so the last read may pass the tensor's end.  The gradient is
+// the caller's, so the elements of an incomplete turn are read one by one there, as they are written.
+// (Walked element by element with a field load in front of each, the 1683 elements at the end of a
+// 10 M-element binary32 tensor took as long as the rest of the launch: 50.8 us, 25.1 us now.)
+template <int KB, bool LONE, bool NORM, bool UPD, bool HALF, class WordSrc>
+__device__ __forceinline__ void walk_ragged(const uint32_t *__restrict__ lut, const uint2 *__restrict__ spread,
+                                            const WordSrc &src, uint32_t lone, uint32_t &x, uint32_t &wp,
+                                            const uint8_t *__restrict__ sm, const uint8_t *__restrict__ coef,
+                                            uint32_t block, uint16_t *__restrict__ out, uint64_t base, uint32_t m,
+                                            uint32_t j, const uint16_t *__restrict__ grad, float lr)
+{
+    uint32_t next = LONE ? 0u : src.peek(wp);
+    uint32_t at = j * kRun;  // this lane's run of the turn, inside the chunk
+    uint64_t fields = at < m ? load_turn<KB, NORM>(sm, coef, block, base + at) : 0;
+    for (; at < m; at += kTurn) {
+        const uint64_t here = base + at;
+        uint64_t fields_next = 0;
+        if (at + kTurn < m)
+            fields_next = load_turn<KB, NORM>(sm, coef, block, here + kTurn);
+        const uint32_t valid = m - at < kRun ? m - at : kRun;
+        uint4 g = make_uint4(0, 0, 0, 0);
+        uint32_t e[8];
+        if (valid == kRun) {
+            if constexpr (UPD)
+                g = *reinterpret_cast<const uint4 *>(grad + here);
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                e[t] = LONE ? lone : rans_get(lut, x, wp, next, src);
+        } else {
+            if constexpr (UPD) {
+                uint32_t one[8];
+#pragma unroll
+                for (uint32_t t = 0; t < 8; ++t)
+                    one[t] = t < valid ? grad[here + t] : 0u;
+                g = make_uint4(one[0] | (one[1] << 16), one[2] | (one[3] << 16), one[4] | (one[5] << 16),
+                               one[6] | (one[7] << 16));
+            }
+#pragma unroll
+            for (uint32_t t = 0; t < 8; ++t) {
+                e[t] = 0;
+                if (t < valid)
+                    e[t] = LONE ? lone : rans_get(lut, x, wp, next, src);
+            }
+        }
+        uint4 o = merge_turn<KB, NORM, HALF>(fields, e, spread);
+        if constexpr (UPD) {
+            o.x = update_pair(o.x, g.x, lr);
+            o.y = update_pair(o.y, g.y, lr);
+            o.z = update_pair(o.z, g.z, lr);
+            o.w = update_pair(o.w, g.w, lr);
+        }
+        if (valid == kRun) {
+            *reinterpret_cast<uint4 *>(out + here) = o;
+        } else {
+            const uint32_t d[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+            for (uint32_t t = 0; t < 8; ++t)
+                if (t < valid)
+                    out[here + t] = static_cast<uint16_t>(d[t >> 1] >> (16 * (t & 1)));
+        }
+        fields = fields_next;
+    }
+}
+
 // UPD: the words written are the decoded weights after the update with the gradient `grad` (bf16
 // words, same indexing as the output) and the rate lr.  HALF: the tensor is binary16.
 template <int KB, bool LONE, bool NORM, bool STREAM, bool UPD, bool HALF, class WordSrc>
@@ -198,8 +294,8 @@ __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, con
     static_assert(!(UPD && HALF), "only bf16 weights are trained");
     // `fields` arrives holding the field bits of the state's first turns (full chunks only)
     constexpr uint32_t kGroup = (STREAM && KB == 7 && !UPD) ? kTurnGroupStream : kTurnGroup;
-    uint32_t next = LONE ? 0u : src.peek(wp);
-    if (m == kChunk) {
+    if (__all(m == kChunk)) {  // all chunks of the wave are whole
+        uint32_t next = LONE ? 0u : src.peek(wp);
         uint4 *out4 = reinterpret_cast<uint4 *>(out + base) + j;
         const uint64_t first = base + j * kRun;
         // the gradients of a turn: the 128 bits the lane's output words come from
@@ -234,26 +330,7 @@ __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, con
 #pragma unroll
                 for (int t = 0; t < 8; ++t)
                     e[t] = LONE ? lone : rans_get(lut, x, wp, next, src);
-                if constexpr (HALF) {
-                    o[r].x = merge_pair_half(fields[r], 0, e[0], e[1]);
-                    o[r].y = merge_pair_half(fields[r], 1, e[2], e[3]);
-                    o[r].z = merge_pair_half(fields[r], 2, e[4], e[5]);
-                    o[r].w = merge_pair_half(fields[r], 3, e[6], e[7]);
-                } else if constexpr (KB <= 1) {
-                    o[r] = merge_turn_small<KB>(fields[r], e, spread);
-                } else {
-                    o[r].x = merge_pair<KB>(fields[r], 0, e[0], e[1]);
-                    o[r].y = merge_pair<KB>(fields[r], 1, e[2], e[3]);
-                    o[r].z = merge_pair<KB>(fields[r], 2, e[4], e[5]);
-                    o[r].w = merge_pair<KB>(fields[r], 3, e[6], e[7]);
-                }
-                if constexpr (NORM) {
-                    const float c = coefficient(static_cast<uint32_t>(fields[r] >> 32) & 0x7Fu);
-                    o[r].x = denormalise_pair(o[r].x, c);
-                    o[r].y = denormalise_pair(o[r].y, c);
-                    o[r].z = denormalise_pair(o[r].z, c);
-                    o[r].w = denormalise_pair(o[r].w, c);
-                }
+                o[r] = merge_turn<KB, NORM, HALF>(fields[r], e, spread);
                 if constexpr (UPD) {
                     o[r].x = update_pair(o[r].x, grads[r].x, lr);
                     o[r].y = update_pair(o[r].y, grads[r].y, lr);
@@ -279,25 +356,7 @@ __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, con
             }
         }
     } else {
-        // ragged last chunk: element by element
-        constexpr uint32_t width = KB + 1, per_byte = 8 / width;
-        for (uint32_t q = 0; q < kTurns; ++q) {
-            for (uint32_t t = 0; t < kRun; ++t) {
-                const uint32_t i = q * kTurn + j * kRun + t;
-                if (i >= m)
-                    continue;
-                const uint32_t sym = (LONE ? lone : rans_get(lut, x, wp, next, src)) & 0xFFu;
-                const uint64_t g = base + i;
-                const uint32_t field = (sm[g / per_byte] >> ((g % per_byte) * width)) & ((1u << width) - 1u);
-                uint32_t u = HALF ? (sym << 8) | field
-                                  : ((field >> KB) << 15) | (sym << 7) | ((field & ((1u << KB) - 1u)) << (7 - KB));
-                if constexpr (NORM)
-                    u = denormalise_word(u, coefficient(coef[g >> block]));
-                if constexpr (UPD)
-                    u = update_word(u, grad[g], lr);
-                out[g] = static_cast<uint16_t>(u);
-            }
-        }
+        walk_ragged<KB, LONE, NORM, UPD, HALF>(lut, spread, src, lone, x, wp, sm, coef, block, out, base, m, j, grad, lr);
     }
 }
 
@@ -312,7 +371,7 @@ __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut
 {
     constexpr uint32_t kGroup = kTurnGroup;
     uint32_t next = LONE ? 0u : src.peek(wp);
-    if (m == kChunk) {
+    if (__all(m == kChunk)) {
         // where this lane stores: its own pieces 2j and 2j + 1 of a turn's 32, or, after the exchange
         // described below, pieces (j / 8) * 16 + j % 8 and 8 further
         uint4 *out4 = reinterpret_cast<uint4 *>(out + base) + (STREAM ? (j >> 3) * 16 + (j & 7) : 2 * j);
@@ -400,17 +459,56 @@ __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut
             }
         }
     } else {
-        // ragged last chunk: element by element
-        for (uint32_t q = 0; q < kTurns; ++q) {
-            for (uint32_t t = 0; t < kRun; ++t) {
-                const uint32_t i = q * kTurn + j * kRun + t;
-                if (i >= m)
-                    continue;
-                const uint32_t sym = (LONE ? lone : rans_get(lut, x, wp, next, src)) & 0xFFu;
-                const uint64_t g = base + i;
-                const uint32_t field = sm[g];
-                out[g] = ((field >> 7) << 31) | (sym << 23) | ((field & 0x7Fu) << 16) | low[g];
+        // the wave with the ragged last chunk: see walk_ragged
+        uint32_t at = j * kRun;
+        uint64_t fields = 0;
+        uint4 lows = make_uint4(0, 0, 0, 0);
+        if (at < m) {
+            fields = load_fields<7>(sm, base + at);
+            lows = *reinterpret_cast<const uint4 *>(low + base + at);
+        }
+        for (; at < m; at += kTurn) {
+            const uint64_t here = base + at;
+            uint64_t fields_next = 0;
+            uint4 lows_next = make_uint4(0, 0, 0, 0);
+            if (at + kTurn < m) {
+                fields_next = load_fields<7>(sm, here + kTurn);
+                lows_next = *reinterpret_cast<const uint4 *>(low + here + kTurn);
             }
+            const uint32_t valid = m - at < kRun ? m - at : kRun;
+            uint32_t e[8];
+            if (valid == kRun) {
+#pragma unroll
+                for (int t = 0; t < 8; ++t)
+                    e[t] = LONE ? lone : rans_get(lut, x, wp, next, src);
+            } else {
+#pragma unroll
+                for (uint32_t t = 0; t < 8; ++t) {
+                    e[t] = 0;
+                    if (t < valid)
+                        e[t] = LONE ? lone : rans_get(lut, x, wp, next, src);
+                }
+            }
+            const uint32_t h[4] = {merge_pair<7>(fields, 0, e[0], e[1]), merge_pair<7>(fields, 1, e[2], e[3]),
+                                   merge_pair<7>(fields, 2, e[4], e[5]), merge_pair<7>(fields, 3, e[6], e[7])};
+            const uint32_t l[4] = {lows.x, lows.y, lows.z, lows.w};
+            uint32_t v[8];
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                v[2 * d] = __builtin_amdgcn_perm(h[d], l[d], 0x05040100u);
+                v[2 * d + 1] = __builtin_amdgcn_perm(h[d], l[d], 0x07060302u);
+            }
+            if (valid == kRun) {
+                reinterpret_cast<uint4 *>(out + here)[0] = make_uint4(v[0], v[1], v[2], v[3]);
+                reinterpret_cast<uint4 *>(out + here)[1] = make_uint4(v[4], v[5], v[6], v[7]);
+            } else {
+#pragma unroll
+                for (uint32_t t = 0; t < 8; ++t)
+                    if (t < valid)
+                        out[here + t] = v[t];
+            }
+            fields = fields_next;
+            lows = lows_next;
         }
     }
 }

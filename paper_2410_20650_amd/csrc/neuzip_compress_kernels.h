@@ -358,16 +358,24 @@ __device__ inline uint32_t build_table_wave(const uint32_t (&cnt)[4], uint64_t t
 }
 
 // Encoder constants of a symbol.  A symbol without room in the table (f = 0) gets constants that
-// leave the state as it is and a zero reciprocal, by which the encoder recognises it.
+// leave the state as it is and a zero multiplier, by which the encoder recognises it.
 __device__ inline EncSym encoder_constants(uint32_t f, uint32_t cum)
 {
-    EncSym e = {0.0f, 0xFFFF0000u, 1u, 0};
+    EncSym e = {0u, 0xFFFF0000u, 0u, 0u};
     if (f > 0) {
-        e.rcp = __fmul_rn(__fdiv_rn(1.0f, static_cast<float>(f)), 1.0f - 0x1p-21f);
+        const uint32_t s = 31u - static_cast<uint32_t>(__clz(static_cast<int>(f)));
+        // floor(2^(32+s) / f): the fraction is a multiple of 1/f, so rounding the binary64 quotient (53 bits,
+        // 32 of them before the point) cannot reach the next integer
+        const double power = __longlong_as_double(static_cast<long long>(1023u + 32u + s) << 52);  // 2^(32+s)
+        const uint32_t below = static_cast<uint32_t>(__ddiv_rn(power, static_cast<double>(f)));
+        const uint32_t rest = 0u - below * f;  // 2^(32+s) - below * f, which is less than f
+        const bool single = (f & (f - 1u)) == 0u;  // a power of two: the quotient is 2^32
+        const bool up = !single && 2u * rest >= f;
+        e.mul = single ? 0xFFFFFFFFu : (up ? below + 1u : below);
         // f = 4096 only for a one-symbol tensor: the state stays at 2^16 and never renormalises
         e.limit_cum = (f >= kM ? 0xFFFF0000u : (f << 20)) | cum;
-        e.f = f;
-        e.neg_cmpl = static_cast<int32_t>(f) - static_cast<int32_t>(kM);
+        e.shift_inc = s | (up ? 0u : 0x10000u);
+        e.cmpl = kM - f;
     }
     return e;
 }
@@ -668,37 +676,53 @@ __global__ __launch_bounds__(256) void sgd_update_kernel(uint16_t *__restrict__ 
 // 16-byte pieces (interleaved with the other states' of the chunk, see slot_word), so that the
 // tail of the slot read forwards is the decoder's order.  Final
 // states and run lengths go straight to their place in the blob; the chunk's word count goes to
-// the workspace for the offsets scan.  A turn's 8 bf16 words are requested two turns ahead.
+// the workspace for the offsets scan.  A turn's 8 bf16 words are requested four turns ahead.
 // ------------------------------------------------------------------------------------------
 constexpr uint32_t kEncThreads = 256;
 constexpr uint32_t kChunksPerGroup = kEncThreads / kStates;  // 16 chunks per encoder workgroup
 constexpr uint32_t kRingWords = 16;  // per state; two halves of 8 words = 16 bytes
 
+// The rings of a workgroup lie in LDS as [pair of words][lane][2 words]: lane l's words at positions 2i and
+// 2i + 1 are dword i * kEncThreads + l, so the lanes of a wave are in banks of their own wherever each of
+// them stands in its ring.  (Lane by lane, 32 bytes apart, an unconditional store from all lanes cost the
+// launch its LDS rate: 101 instead of 93 us per compression of 4096 x 14336.)
+constexpr uint32_t kRingMask = ((kRingWords / 2 - 1) * kEncThreads * 4u) | 2u;  // the position's bits in a byte address
+static_assert(kEncThreads == 256, "the position's bits of a ring address, above 8 bits of lane number and 2 of byte");
+__device__ __forceinline__ uint32_t ring_place(uint32_t p) { return ((p & 14u) << 9) | ((p & 1u) << 1); }
+__device__ __forceinline__ uint32_t ring_position(uint32_t at) { return ((at >> 9) & 14u) | ((at >> 1) & 1u); }
+
 struct EncState {
     uint32_t x;
     uint32_t wp;          // next free position in the slot is wp - 1 (words, counts down from kRunCap);
                           // brought up to date once per turn (ring_advance)
-    uint32_t cur;         // byte position of the last word written in the workgroup's ring array:
-                          // lane * 32 + 2 * (wp mod 16)
+    uint32_t cur;         // byte address of the last word written in the workgroup's ring array:
+                          // ring_place(wp mod 16) | lane * 4
 };
 
-// rings: the workgroup's ring array as bytes; lane_ring: this lane's 32-byte ring in it (threadIdx.x * 32)
-__device__ __forceinline__ void rans_put(EncState &st, const EncSym e, uint8_t *__restrict__ rings, uint32_t lane_ring)
+// rings: the workgroup's ring array as bytes; lane_ring: this lane's bits in a ring address; lane_step:
+// lane_ring + 2.
+// What bounds a small tensor, whose waves have a SIMD to themselves, is the number of instructions and what
+// a symbol waits for: the word is stored whether it is needed or not (the place below the last word is free)
+// and nothing branches.  2^20 elements: 144 cycles a symbol before, 113 now (kernel 22.7 -> 18.1 us); tensors
+// beyond the cache are bound by memory and unchanged.
+__device__ __forceinline__ void rans_put(EncState &st, const EncSym e, uint8_t *__restrict__ rings, uint32_t lane_ring,
+                                         uint32_t lane_step)
 {
-    if ((st.x >> 16) >= (e.limit_cum >> 16)) {
-        // one position down, wrapping inside the lane's 16 words: two instructions for the address
-        st.cur = lane_ring | ((st.cur - 2u) & (2u * kRingWords - 2u));
-        *reinterpret_cast<uint16_t *>(rings + st.cur) = static_cast<uint16_t>(st.x);
-        // (the shift as written keeps the compiler from sharing it with the test above, which reads the
-        // state's upper half through an operand select and needs no shift of its own)
-        asm volatile("v_lshrrev_b32 %0, 16, %0" : "+v"(st.x));
-    }
-    // -q or -(q - 1): the conversion truncates toward zero, as it does for the positive product
-    int32_t qn = static_cast<int32_t>(-__fmul_rn(__uint2float_rn(st.x), e.rcp));
-    const uint32_t r = static_cast<uint32_t>(__mul24(qn, static_cast<int32_t>(e.f))) + st.x;
-    qn -= r >= e.f ? 1 : 0;
-    const uint32_t grown = static_cast<uint32_t>(__mul24(qn, e.neg_cmpl)) + st.x;
-    // + cum, the lower half of limit_cum, taken by the add's operand select
+    // one position down, wrapping inside the lane's 16 words: without the lane's bits the borrow out of the
+    // lowest position bit runs through to the next one
+    const uint32_t below = ((st.cur - lane_step) & kRingMask) | lane_ring;
+    *reinterpret_cast<uint16_t *>(rings + below) = static_cast<uint16_t>(st.x);
+    const uint32_t high = st.x >> 16;
+    const bool out = high >= (e.limit_cum >> 16);
+    st.cur = out ? below : st.cur;
+    const uint32_t x = out ? high : st.x;
+    uint32_t inc_x;  // x + inc, the upper half of shift_inc, taken by the add's operand select
+    asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
+        : "=v"(inc_x)
+        : "v"(x), "v"(e.shift_inc));
+    const uint32_t q = __umulhi(inc_x, e.mul) >> (e.shift_inc & 31u);
+    const uint32_t grown = __umul24(q, e.cmpl) + x;
+    // + cum, the lower half of limit_cum
     asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
         : "=v"(st.x)
         : "v"(grown), "v"(e.limit_cum));
@@ -718,18 +742,22 @@ __device__ __forceinline__ uint32_t slot_word(uint32_t j, uint32_t p)
 // The words pushed since `cur_before` (at most 8 per turn, so the ring position tells) come off wp.
 __device__ __forceinline__ void ring_advance(EncState &st, uint32_t cur_before)
 {
-    st.wp -= ((cur_before - st.cur) & (2u * kRingWords - 2u)) >> 1;
+    st.wp -= (ring_position(cur_before) - ring_position(st.cur)) & (kRingWords - 1u);
 }
 
 // Moves the 8-word group completed during the last turn (at most one: a turn pushes at most 8
 // words) from the ring to the slot.  Positions run down from wp_before to wp_after; group g
 // (positions 8g .. 8g+7) is complete once position 8g has been written.
-__device__ __forceinline__ void ring_flush(uint32_t wp_before, uint32_t wp_after, const uint16_t *__restrict__ ring,
-                                           uint16_t *__restrict__ chunk_slots, uint32_t j)
+__device__ __forceinline__ void ring_flush(uint32_t wp_before, uint32_t wp_after, const uint8_t *__restrict__ rings,
+                                           uint32_t lane_ring, uint16_t *__restrict__ chunk_slots, uint32_t j)
 {
     const uint32_t g = (wp_after + 7) >> 3;  // lowest group whose first position is >= wp_after
     if (g * 8 < wp_before) {
-        const uint4 v = *reinterpret_cast<const uint4 *>(ring + ((g * 8) & (kRingWords - 1)));
+        constexpr uint32_t kPair = kEncThreads * 4;
+        const uint8_t *at = rings + (lane_ring | ring_place((g * 8) & (kRingWords - 1)));
+        const uint4 v = make_uint4(*reinterpret_cast<const uint32_t *>(at), *reinterpret_cast<const uint32_t *>(at + kPair),
+                                   *reinterpret_cast<const uint32_t *>(at + 2 * kPair),
+                                   *reinterpret_cast<const uint32_t *>(at + 3 * kPair));
         *reinterpret_cast<uint4 *>(chunk_slots + slot_word(j, g * 8)) = v;
     }
 }
@@ -789,21 +817,29 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
     const bool live = !table_wg && c < n_chunks;
     const uint64_t base = static_cast<uint64_t>(c) * kChunk;
     const uint32_t m = !live ? 0u : ((n - base) < kChunk ? static_cast<uint32_t>(n - base) : kChunk);
-    // The source words of a full chunk are requested two turns ahead, in three buffers used in
-    // rotation; the first two requests go out here, so that they travel while the table is made.
+    // The source words of a full chunk are requested kAhead turns before they are needed, in as many buffers
+    // used in rotation; the first requests go out here, so that they travel while the table is made.
     // This state's first 8-element vector of the chunk; a turn later is kStates vectors on.
     const uint4 *src4 = static_cast<const uint4 *>(src) + (base / 8 + j) * (WIDE ? 2 : 1);
     // the gradients travel with the weights, one 128-bit piece per turn
     const uint4 *grad4 = UPD ? reinterpret_cast<const uint4 *>(grad) + (base / 8 + j) : nullptr;
-    SourceVec<WIDE> d0, d1, d2;
-    uint4 g0 = make_uint4(0, 0, 0, 0), g1 = g0, g2 = g0;
+    constexpr uint32_t kAhead = 4;  // (2: 3 % slower on tensors beyond the cache; 8: registers, 7 % slower with gradients)
+    static_assert(kTurns % kAhead == 0, "whole rotations");
+    SourceVec<WIDE> ahead[kAhead];
+    uint4 grads[kAhead];
+    uint32_t coefs[kAhead];
+    auto request = [&](uint32_t r, int q) {
+        const uint32_t at = static_cast<uint32_t>(q > 0 ? q : 0);  // (past the first turn: a re-read that nobody uses)
+        ahead[r].load(src4, at * kStates);
+        if constexpr (UPD)
+            grads[r] = grad4[at * kStates];
+        if constexpr (NORM)
+            coefs[r] = coef[(base + at * kTurn + j * kRun) >> block_shift];
+    };
     if (m == kChunk) {
-        d0.load(src4, (kTurns - 1) * kStates);
-        d1.load(src4, (kTurns - 2) * kStates);
-        if constexpr (UPD) {
-            g0 = grad4[(kTurns - 1) * kStates];
-            g1 = grad4[(kTurns - 2) * kStates];
-        }
+#pragma unroll
+        for (uint32_t r = 0; r < kAhead; ++r)
+            request(r, static_cast<int>(kTurns - 1 - r));
     }
 
     // ---- encoder constants of the 256 symbols
@@ -821,7 +857,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const EncSym e = encoder_constants(f[i], cum[i]);
-                enc_raw[4 * lane + i] = make_uint4(__float_as_uint(e.rcp), e.limit_cum, e.f, static_cast<uint32_t>(e.neg_cmpl));
+                enc_raw[4 * lane + i] = make_uint4(e.mul, e.limit_cum, e.shift_inc, e.cmpl);
             }
             if (table_wg) {
                 uint32_t *scan = reinterpret_cast<uint32_t *>(rings);  // scan[t] = cum[t + 1]
@@ -848,7 +884,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
     } else {
         // the table the blob holds
         const EncSym e = encoder_constants(tb->freq[threadIdx.x], tb->cum[threadIdx.x]);
-        enc_raw[threadIdx.x] = make_uint4(__float_as_uint(e.rcp), e.limit_cum, e.f, static_cast<uint32_t>(e.neg_cmpl));
+        enc_raw[threadIdx.x] = make_uint4(e.mul, e.limit_cum, e.shift_inc, e.cmpl);
     }
     __syncthreads();
     if (table_wg) {
@@ -859,74 +895,92 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
     const EncSym *enc = reinterpret_cast<const EncSym *>(enc_raw);
 
     uint16_t *chunk_slots = slots + static_cast<uint64_t>(c) * kStates * kRunCap;
-    uint16_t *ring = rings + threadIdx.x * kRingWords;
     uint8_t *ring_bytes = reinterpret_cast<uint8_t *>(rings);
-    const uint32_t lane_ring = threadIdx.x * (2u * kRingWords);
-    EncState st = {kRansL, kRunCap, lane_ring + 2u * (kRunCap % kRingWords)};
-    float least_rcp = 1.0f;  // 0 once a symbol without room in the table has been met
+    const uint32_t lane_ring = threadIdx.x * 4u;
+    uint32_t lane_step = lane_ring + 2u;
+    asm volatile("" : "+v"(lane_step));  // (a register of its own: otherwise the sum is formed again per symbol)
+    EncState st = {kRansL, kRunCap, lane_ring | ring_place(kRunCap % kRingWords)};
+    uint32_t least_mul = 1u;  // 0 once a symbol without room in the table has been met
     uint8_t *__restrict__ sm = it.sm;
 
     const bool whole_wave = __all(m == kChunk || m == 0);
     if (whole_wave && m == kChunk) {
-        // One turn: the vector of turn q - 2 is requested into the buffer that is free (the wait for a
-        // turn's words then leaves the stores of the turn before -- ring flush, fields -- in flight
-        // instead of waiting for them), then turn q is coded from its buffer.
-        auto turn = [&](const SourceVec<WIDE> &d, const uint4 &g, SourceVec<WIDE> &d_after, uint4 &g_after, int q) {
-            d_after.load(src4, (q > 1 ? q - 2 : 0) * kStates);
-            if constexpr (UPD)
-                g_after = grad4[(q > 1 ? q - 2 : 0) * kStates];
-            uint32_t w[4];
-            d.words(w);
+        // the words of turn q from its buffer, with what goes out along with them
+        auto prepare = [&](uint32_t r, int q, uint32_t (&w)[4]) {
+            const uint64_t vec = base / 8 + static_cast<uint32_t>(q) * kStates + j;
+            ahead[r].words(w);
             if constexpr (UPD) {
-                w[0] = update_pair(w[0], g.x, lr);
-                w[1] = update_pair(w[1], g.y, lr);
-                w[2] = update_pair(w[2], g.z, lr);
-                w[3] = update_pair(w[3], g.w, lr);
+                w[0] = update_pair(w[0], grads[r].x, lr);
+                w[1] = update_pair(w[1], grads[r].y, lr);
+                w[2] = update_pair(w[2], grads[r].z, lr);
+                w[3] = update_pair(w[3], grads[r].w, lr);
                 // if the caller wants it, the new weight replaces the old one in its buffer (same lane,
                 // same place)
                 if (b.keep_new)
-                    reinterpret_cast<uint4 *>(const_cast<void *>(src))[base / 8 + static_cast<uint32_t>(q) * kStates + j] =
-                        make_uint4(w[0], w[1], w[2], w[3]);
+                    reinterpret_cast<uint4 *>(const_cast<void *>(src))[vec] = make_uint4(w[0], w[1], w[2], w[3]);
             }
-            const uint32_t wp_before = st.wp, cur_before = st.cur;
             if constexpr (SPLIT >= 0) {
-                store_fields<KB>(sm, base / 8 + static_cast<uint32_t>(q) * kStates + j, fields_of<KB, HALF>(w));
+                store_fields<KB>(sm, vec, fields_of<KB, HALF>(w));
                 if constexpr (WIDE)
-                    reinterpret_cast<uint4 *>(low)[base / 8 + static_cast<uint32_t>(q) * kStates + j] = d.lows();
+                    reinterpret_cast<uint4 *>(low)[vec] = ahead[r].lows();
             }
             // with block-wise normalisation the exponents coded are those of bf16(w / c)
-            float c = 1.0f;
-            if constexpr (NORM)
-                c = coefficient(coef[(base + static_cast<uint32_t>(q) * kTurn + j * kRun) >> block_shift]);
+            if constexpr (NORM) {
+                const float c = coefficient(coefs[r]);
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+                    w[p] = normalise_word(w[p] & 0xFFFFu, c) | (normalise_word(w[p] >> 16, c) << 16);
+            }
+        };
+        uint32_t w[4];
+        // the constants of a pair of symbols are requested while the pair before it is coded: the compiler would
+        // not move these LDS reads over the ring stores by itself, and every pair would wait for its own
+        EncSym e_hi, e_lo;
+        auto fetch = [&](uint32_t d, EncSym &hi, EncSym &lo) {
+            hi = enc[symbol_of<HALF>(d >> 16)];
+            lo = enc[symbol_of<HALF>(d & 0xFFFFu)];
+        };
+        // codes turn q from w, and makes ready the turn after it, whose source is in buffer r
+        auto turn = [&](uint32_t r, int q, bool more) {
+            const uint32_t wp_before = st.wp, cur_before = st.cur;
 #pragma unroll
             for (int p = 3; p >= 0; --p) {
-                const uint32_t hi = NORM ? normalise_word(w[p] >> 16, c) : (w[p] >> 16);
-                const uint32_t lo = NORM ? normalise_word(w[p] & 0xFFFFu, c) : (w[p] & 0xFFFFu);
-                const EncSym e_hi = enc[symbol_of<HALF>(hi)], e_lo = enc[symbol_of<HALF>(lo)];
-                if constexpr (SPLIT >= 0) {
-                    least_rcp = fminf(least_rcp, fminf(e_hi.rcp, e_lo.rcp));
-                    // (taken here and now: left to the scheduler, the minimum is put off to the end of the
-                    // loop body and every symbol's four registers stay occupied until then)
-                    asm volatile("" : "+v"(least_rcp));
+                EncSym n_hi = e_hi, n_lo = e_lo;
+                if (p > 0) {
+                    fetch(w[p - 1], n_hi, n_lo);
+                } else if (more) {
+                    prepare(r, q - 1, w);
+                    fetch(w[3], n_hi, n_lo);
+                    request(r, q - 1 - static_cast<int>(kAhead));
                 }
-                rans_put(st, e_hi, ring_bytes, lane_ring);
-                rans_put(st, e_lo, ring_bytes, lane_ring);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (SPLIT >= 0) {
+                    // (taken here and now: left to the scheduler, the minimum is put off to the end of the
+                    // loop body and every symbol's registers stay occupied until then)
+                    least_mul = min(least_mul, min(e_hi.mul, e_lo.mul));
+                    asm volatile("" : "+v"(least_mul));
+                }
+                rans_put(st, e_hi, ring_bytes, lane_ring, lane_step);
+                rans_put(st, e_lo, ring_bytes, lane_ring, lane_step);
+                e_hi = n_hi;
+                e_lo = n_lo;
             }
             ring_advance(st, cur_before);
-            ring_flush(wp_before, st.wp, ring, chunk_slots, j);
+            ring_flush(wp_before, st.wp, ring_bytes, lane_ring, chunk_slots, j);
         };
-        // turns in groups of three (so that no buffer has to be copied into another); what is left over
-        // when the number of turns is no multiple of three comes last, with the rotation continued
+        prepare(0, static_cast<int>(kTurns) - 1, w);
+        fetch(w[3], e_hi, e_lo);
+        request(0, static_cast<int>(kTurns) - 1 - static_cast<int>(kAhead));
+        // turn q - r codes w; the turn after it is in buffer (r + 1) mod kAhead
         int q = static_cast<int>(kTurns) - 1;
-        for (; q >= 2; q -= 3) {
-            turn(d0, g0, d2, g2, q);
-            turn(d1, g1, d0, g0, q - 1);
-            turn(d2, g2, d1, g1, q - 2);
+        for (; q >= static_cast<int>(kAhead); q -= static_cast<int>(kAhead)) {
+#pragma unroll
+            for (uint32_t r = 0; r < kAhead; ++r)
+                turn((r + 1) % kAhead, q - static_cast<int>(r), true);
         }
-        if constexpr (kTurns % 3 >= 1)
-            turn(d0, g0, d2, g2, q);
-        if constexpr (kTurns % 3 == 2)
-            turn(d1, g1, d0, g0, q - 1);
+#pragma unroll
+        for (uint32_t r = 0; r < kAhead; ++r)
+            turn((r + 1) % kAhead, static_cast<int>(kAhead - 1 - r), r + 1 < kAhead);
     } else if (!whole_wave && m > 0) {
         // The wave with the tensor's ragged last chunk: every lane codes the turns its chunk has, the last
         // one possibly with fewer than 8 elements of its own (read one by one: the source is the caller's and
@@ -935,7 +989,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
             const uint32_t first = static_cast<uint32_t>(q) * kTurn + j * kRun;
             return first >= m ? 0u : (m - first < kRun ? m - first : kRun);
         };
-        auto request = [&](int q, SourceVec<WIDE> &d, uint4 &g) {
+        auto request_some = [&](int q, SourceVec<WIDE> &d, uint4 &g) {
             const uint32_t valid = valid_of(q);
             const uint64_t first = base + static_cast<uint32_t>(q) * kTurn + j * kRun;
             if (valid == kRun) {
@@ -951,13 +1005,15 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
                 }
             }
         };
+        SourceVec<WIDE> d0, d1;
+        uint4 g0 = make_uint4(0, 0, 0, 0), g1 = g0;
         d0.clear();
         int q = static_cast<int>((m - 1) / kTurn);
-        request(q, d0, g0);
+        request_some(q, d0, g0);
         for (; q >= 0; --q) {
             d1.clear();
             if (q > 0)
-                request(q - 1, d1, g1);
+                request_some(q - 1, d1, g1);
             const uint32_t valid = valid_of(q);
             const uint64_t first = base + static_cast<uint32_t>(q) * kTurn + j * kRun;
             uint32_t w[4];
@@ -1002,27 +1058,28 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
                     const uint32_t raw = (w[t >> 1] >> (16 * (t & 1))) & 0xFFFFu;
                     const EncSym e = enc[symbol_of<HALF>(NORM ? normalise_word(raw, c) : raw)];
                     if constexpr (SPLIT >= 0) {
-                        least_rcp = fminf(least_rcp, e.rcp);
-                        asm volatile("" : "+v"(least_rcp));
+                        least_mul = min(least_mul, e.mul);
+                        asm volatile("" : "+v"(least_mul));
                     }
-                    rans_put(st, e, ring_bytes, lane_ring);
+                    rans_put(st, e, ring_bytes, lane_ring, lane_step);
                 }
             }
             ring_advance(st, cur_before);
-            ring_flush(wp_before, st.wp, ring, chunk_slots, j);
+            ring_flush(wp_before, st.wp, ring_bytes, lane_ring, chunk_slots, j);
             d0 = d1;
             g0 = g1;
         }
     }
     if constexpr (SPLIT >= 0) {
-        if (least_rcp == 0.0f)
+        if (least_mul == 0u)
             atomicOr(&state->stale[slot_id.item], 1u);
     }
     const uint32_t len = kRunCap - st.wp;
     if (live) {
         // the incomplete group at the low end: word by word
         for (uint32_t p = st.wp; p < ((st.wp + 7) & ~7u) && p < kRunCap; ++p)
-            chunk_slots[slot_word(j, p)] = ring[p & (kRingWords - 1)];
+            chunk_slots[slot_word(j, p)] =
+                *reinterpret_cast<const uint16_t *>(ring_bytes + (lane_ring | ring_place(p & (kRingWords - 1))));
         states[lane_id] = st.x;
         lens[lane_id] = static_cast<uint8_t>(len);
     }

@@ -59,17 +59,19 @@ static_assert(sizeof(TableBlock) % 256 == 0, "table block keeps later sections a
 //   has no bits in its lower half, so the test compares the upper halves only (x >> 16 against
 //   f << 4) and the lower half of the same dword carries cum (both halves are read through the
 //   sub-dword operand selects of the compare and the add, without an instruction to extract them).
-//   rcp: a float slightly below 1/f, (1/f)(1 - 2^-21).  float(x) * rcp, truncated, is q or q - 1
-//   (three roundings of 2^-24 cannot overcome the 2^-21 bias, and q * 1.5 * 2^-21 < 1); one
-//   compare of the remainder against f settles it.  All of this runs at full VALU rate, unlike a
-//   32-bit multiply-high.  The quotient is formed negated (the sign rides on the float multiply),
-//   so that the remainder x - q f and the new state are one 24-bit multiply-add each:
-//   r = (-q) f + x, x' = (-q)(f - M) + x (+ cum).
+//   mul, shift_inc: with s = floor(log2 f), q is the upper dword of (x + inc) * mul, shifted right by s
+//   (division by an invariant: Granlund and Montgomery 1994, Robison 2005).  For x < f << 20 and f < 2^12
+//   it is exact with mul = ceil(2^(32+s) / f), inc = 0 as long as (mul * f - 2^(32+s)) * f <= 2^(12+s), and
+//   with mul = floor(2^(32+s) / f), inc = 1 as long as (2^(32+s) - mul * f) * f <= 2^(12+s); the two errors
+//   add up to f < 2^(s+1), so the smaller one is at most f / 2 and satisfies its condition.  A power of two
+//   takes mul = 2^32 - 1, inc = 1.  The multiply-high runs at a quarter of the vector rate, but it takes the
+//   place of six instructions that depend on one another (two conversions, a float product, a remainder, its
+//   compare and the correction).
 struct EncSym {
-    float rcp;
+    uint32_t mul;
     uint32_t limit_cum;  // f << 20 | cum (upper half 0xFFFF: never renormalises)
-    uint32_t f;
-    int32_t neg_cmpl;    // f - M
+    uint32_t shift_inc;  // s | inc << 16
+    uint32_t cmpl;       // M - f
 };
 
 // ------------------------------------------------------------------------------------------

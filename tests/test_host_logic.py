@@ -146,3 +146,25 @@ def test_float_reciprocal_division_scheme_of_the_encoder():
         assert np.all((rem >= 0) & (rem < 2 * f)), f
         q = est + (rem >= f)
         assert np.array_equal(q, xs // f), f
+
+
+def test_encoder_multiply_high_division_is_exact():
+    """The encoder's quotient: q = ((x + inc) * mul >> 32) >> s with the constants of EncSym, which must equal
+    integer division for every frequency and every x < f * 2^20.  floor((x + inc) mul / 2^(32+s)) is
+    monotone in x, so it is enough to look at both sides of every quotient that is tried: the smallest, the
+    largest (where the error of mul weighs most) and random ones."""
+    rng = np.random.default_rng(7)
+    for f in range(1, 4096):
+        s = f.bit_length() - 1
+        below = int(np.float64(2.0 ** (32 + s)) / np.float64(f))
+        single = f & (f - 1) == 0
+        if not single:
+            assert below == (1 << (32 + s)) // f and below < 1 << 32     # the binary64 quotient truncates right
+        rest = (-below * f) & 0xFFFFFFFF
+        up = not single and 2 * rest >= f
+        mul, inc = (0xFFFFFFFF, 1) if single else (below + 1, 0) if up else (below, 1)
+        assert mul < 1 << 32
+        q = np.concatenate([np.arange(40), np.arange(2 ** 20 - 40, 2 ** 20), rng.integers(0, 2 ** 20, 40)]).astype(np.uint64)
+        for x in (q * np.uint64(f), q * np.uint64(f) + np.uint64(f - 1)):
+            got = ((x + np.uint64(inc)) * np.uint64(mul) >> np.uint64(32)) >> np.uint64(s)
+            assert np.array_equal(got, q), f

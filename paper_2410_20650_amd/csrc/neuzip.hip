@@ -67,7 +67,7 @@ inline bool valid_block(uint32_t b) { return b == 32 || b == 64 || b == 128 || b
 inline uint64_t block_count(uint64_t n, uint32_t block) { return block ? (n + block - 1) / block : 0; }
 
 struct Layout {
-    uint64_t offsets, states, lens, sm, low, coef, total;  // byte positions inside the fixed allocation
+    uint64_t offsets, states, lens, mid_states, mid_lens, sm, low, coef, total;  // byte positions inside the fixed allocation
 };
 
 // f32: the tensor's elements are binary32; the plane of their lower halves follows the sign|mantissa stream
@@ -75,10 +75,13 @@ Layout fixed_layout(uint64_t n, int k, uint32_t block, bool f32)
 {
     const uint64_t nc = chunks_of(n);
     Layout l;
-    l.offsets = sizeof(TableBlock);
+    l.offsets = table_bytes(nc > 0 && !has_entry_points(chunks_of(n)));
     l.states = l.offsets + pad_to((nc + 2) * 4, 256);
     l.lens = l.states + pad_to(nc * kStates * 4, 256);
-    l.sm = l.lens + pad_to(nc * kStates, 256);
+    const uint64_t entries = has_entry_points(chunks_of(n)) ? nc * kStates : 0;
+    l.mid_states = l.lens + pad_to(nc * kStates, 256);
+    l.mid_lens = l.mid_states + pad_to(entries * 4, 256);
+    l.sm = l.mid_lens + pad_to(entries, 256);
     l.low = l.sm + pad_to(signmant_bytes(n, k), 256) + 256;
     l.coef = l.low + (f32 ? pad_to(n * 2, 256) + 256 : 0);
     l.total = l.coef + pad_to(block_count(n, block), 256);
@@ -136,6 +139,15 @@ inline TableBlock *table_of(const neuzip_blob *b) { return reinterpret_cast<Tabl
 inline uint32_t *offsets_of(const neuzip_blob *b) { return reinterpret_cast<uint32_t *>(b->fixed + b->at.offsets); }
 inline uint32_t *states_of(const neuzip_blob *b) { return reinterpret_cast<uint32_t *>(b->fixed + b->at.states); }
 inline uint8_t *lens_of(const neuzip_blob *b) { return b->fixed + b->at.lens; }
+// (nullptr for blobs without entry points)
+inline uint32_t *mid_states_of(const neuzip_blob *b)
+{
+    return has_entry_points(b->n_chunks) ? reinterpret_cast<uint32_t *>(b->fixed + b->at.mid_states) : nullptr;
+}
+inline uint8_t *mid_lens_of(const neuzip_blob *b)
+{
+    return has_entry_points(b->n_chunks) ? b->fixed + b->at.mid_lens : nullptr;
+}
 inline uint8_t *sm_of(const neuzip_blob *b) { return b->fixed + b->at.sm; }
 inline uint8_t *coef_of(const neuzip_blob *b) { return b->fixed + b->at.coef; }
 inline uint16_t *low_of(const neuzip_blob *b) { return reinterpret_cast<uint16_t *>(b->fixed + b->at.low); }
@@ -359,26 +371,27 @@ inline uint64_t words_room(const neuzip_blob *b)
 }
 
 // Chunks per decoder workgroup.  32 (8 waves) measured best from ~16 M elements up: two such
-// workgroups fill a CU's LDS with 16 waves, and smaller workgroups lower that occupancy.  A small
-// tensor cannot fill the chip either way and is a chain of 256 dependent steps per lane; there
-// workgroups of 16 chunks spread the waves over twice as many CUs (4-7 % faster up to 16 M elements).
+// workgroups fill a CU's LDS with 16 waves, and smaller workgroups lower that occupancy.  A blob with entry
+// points has two lanes per state and cannot fill the chip either way: KEEPME
 // NEUZIP_DECODE_CHUNKS_PER_WG (4..32, multiple of 4) overrides the choice for tuning runs.
 // binary16 symbols carry 5-6 bits each (sign and two mantissa bits ride in the symbol), so only
-// 16 chunks' words fit the LDS window: such blobs always take workgroups of 16 chunks.
+// 16 chunks' words fit the LDS window: such blobs never take more.
 uint32_t decode_chunks_per_wg(uint32_t n_chunks, bool f16 = false)
 {
-    if (f16)
-        return 16u;
     static int forced = -1;
     if (forced < 0) {
         const char *env = std::getenv("NEUZIP_DECODE_CHUNKS_PER_WG");
         const int v = env ? std::atoi(env) : 0;
         forced = (v >= 4 && v <= static_cast<int>(kDecChunksPerWg) && v % 4 == 0) ? v : 0;
     }
-    if (forced > 0)
-        return static_cast<uint32_t>(forced);
-    return n_chunks <= 4096 ? 16u : kDecChunksPerWg;
+    const bool split = has_entry_points(n_chunks);
+    const uint32_t most = f16 || split ? 16u : kDecChunksPerWg;
+    const uint32_t per = forced > 0 ? static_cast<uint32_t>(forced) : (split && n_chunks <= 2048 ? 8u : most);
+    return per < most ? per : most;
 }
+
+// Lanes that walk one chunk.
+inline uint32_t lanes_per_chunk(const neuzip_blob *b) { return has_entry_points(b->n_chunks) ? 2 * kStates : kStates; }
 
 DecodeArgs decode_args(const neuzip_blob *b, void *d_dst)
 {
@@ -387,6 +400,8 @@ DecodeArgs decode_args(const neuzip_blob *b, void *d_dst)
     a.offsets = offsets_of(b);
     a.states = states_of(b);
     a.lens = lens_of(b);
+    a.mid_states = mid_states_of(b);
+    a.mid_lens = mid_lens_of(b);
     a.words = reinterpret_cast<const uint16_t *>(b->words);
     a.sm = sm_of(b);
     a.coef = coef_of(b);
@@ -403,6 +418,7 @@ DecodeArgs decode_args(const neuzip_blob *b, void *d_dst)
     a.n = b->n;
     a.n_chunks = b->n_chunks;
     a.wg_end = 0;
+    a.make_lut = has_entry_points(b->n_chunks) ? 1u : 0u;
     return a;
 }
 
@@ -411,8 +427,11 @@ int launch_decode(const neuzip_blob *b, void *d_dst, hipStream_t stream)
 {
     const uint32_t per = decode_chunks_per_wg(b->n_chunks, b->elem == NEUZIP_F16);
     const uint32_t groups = (b->n_chunks + per - 1) / per;
-    hipLaunchKernelGGL((decode_kernel<KB, NORM, MODE>), dim3(groups), dim3(per * kStates), 0, stream,
-                       decode_args(b, d_dst));
+    const dim3 grid(groups), block(per * lanes_per_chunk(b));
+    if (has_entry_points(b->n_chunks))
+        hipLaunchKernelGGL((decode_kernel<KB, NORM, MODE, true>), grid, block, 0, stream, decode_args(b, d_dst));
+    else
+        hipLaunchKernelGGL((decode_kernel<KB, NORM, MODE, false>), grid, block, 0, stream, decode_args(b, d_dst));
     return hip_ok(hipGetLastError()) ? NEUZIP_OK : NEUZIP_EHIP;
 }
 
@@ -447,23 +466,55 @@ inline int decode_variant(const neuzip_blob *b)
     return b->k + (b->block ? 8 : 0) + (b->elem == NEUZIP_F32 ? 16 : 0) + (b->elem == NEUZIP_F16 ? 32 : 0);
 }
 
-// chunks per workgroup of a batch launch of the given variant
-inline uint32_t batch_chunks_per_wg(int variant) { return variant == 39 ? 16u : kDecChunksPerWg; }
+// threads per workgroup of a batch launch of the given variant
+inline uint32_t batch_threads(int variant) { return variant == 39 ? kDecThreads / 2 : kDecThreads; }
+
+// Deals the workgroups of a batch launch to its tensors; returns their number.  stream_out: the batch as a whole
+// exceeds the last-level cache.  Such a batch has enough waves, and its smaller tensors are walked without their
+// entry points: twice the lanes mean twice the workgroups, each with a slot table to make (the seven weights of a
+// Llama-3-8B layer: 140.0 us, 143.2 us with the entry points).  Below, they shorten the chain (its q, k, v and o
+// with the weight step: 121.5 -> 116.5 us).
+uint32_t place_workgroups(BatchArgs &args, int variant, bool stream_out)
+{
+    uint32_t groups = 0;
+    for (uint32_t t = 0; t < args.count; ++t) {
+        DecodeArgs &a = args.t[t];
+        a.stream_out = stream_out ? 1u : 0u;
+        if (stream_out)
+            a.mid_states = nullptr;
+        const uint32_t per = batch_threads(variant) / (a.mid_states ? 2 * kStates : kStates);
+        groups += (a.n_chunks + per - 1) / per;
+        a.wg_end = groups;
+    }
+    return groups;
+}
+
+template <int KB, bool NORM, int MODE = kPlain>
+void launch_batch_kernel(const BatchArgs &args, dim3 grid, dim3 block, hipStream_t stream)
+{
+    bool entries = false;
+    for (uint32_t t = 0; t < args.count; ++t)
+        entries = entries || args.t[t].mid_states;
+    if (entries)
+        hipLaunchKernelGGL((decode_batch_kernel<KB, NORM, MODE, true>), grid, block, 0, stream, args);
+    else
+        hipLaunchKernelGGL((decode_batch_kernel<KB, NORM, MODE, false>), grid, block, 0, stream, args);
+}
 
 int launch_batch(const BatchArgs &args, int variant, uint32_t groups, hipStream_t stream)
 {
-    const dim3 grid(groups), block(batch_chunks_per_wg(variant) * kStates);
+    const dim3 grid(groups), block(batch_threads(variant));
     switch (variant) {
-    case 7: hipLaunchKernelGGL((decode_batch_kernel<7, false>), grid, block, 0, stream, args); break;
-    case 3: hipLaunchKernelGGL((decode_batch_kernel<3, false>), grid, block, 0, stream, args); break;
-    case 1: hipLaunchKernelGGL((decode_batch_kernel<1, false>), grid, block, 0, stream, args); break;
-    case 0: hipLaunchKernelGGL((decode_batch_kernel<0, false>), grid, block, 0, stream, args); break;
-    case 11: hipLaunchKernelGGL((decode_batch_kernel<3, true>), grid, block, 0, stream, args); break;
-    case 9: hipLaunchKernelGGL((decode_batch_kernel<1, true>), grid, block, 0, stream, args); break;
-    case 23: hipLaunchKernelGGL((decode_batch_kernel<7, false, kWide>), grid, block, 0, stream, args); break;
-    case 39: hipLaunchKernelGGL((decode_batch_kernel<7, false, kHalf>), grid, block, 0, stream, args); break;
-    case kUpdateVariant: hipLaunchKernelGGL((decode_batch_kernel<7, false, kUpdate>), grid, block, 0, stream, args); break;
-    default: hipLaunchKernelGGL((decode_batch_kernel<0, true>), grid, block, 0, stream, args); break;
+    case 7: launch_batch_kernel<7, false>(args, grid, block, stream); break;
+    case 3: launch_batch_kernel<3, false>(args, grid, block, stream); break;
+    case 1: launch_batch_kernel<1, false>(args, grid, block, stream); break;
+    case 0: launch_batch_kernel<0, false>(args, grid, block, stream); break;
+    case 11: launch_batch_kernel<3, true>(args, grid, block, stream); break;
+    case 9: launch_batch_kernel<1, true>(args, grid, block, stream); break;
+    case 23: launch_batch_kernel<7, false, kWide>(args, grid, block, stream); break;
+    case 39: launch_batch_kernel<7, false, kHalf>(args, grid, block, stream); break;
+    case kUpdateVariant: launch_batch_kernel<7, false, kUpdate>(args, grid, block, stream); break;
+    default: launch_batch_kernel<0, true>(args, grid, block, stream); break;
     }
     return hip_ok(hipGetLastError()) ? NEUZIP_OK : NEUZIP_EHIP;
 }
@@ -475,19 +526,13 @@ int launch_batch(const BatchArgs &args, int variant, uint32_t groups, hipStream_
 // 4096 x 14336.
 inline uint32_t linear_columns(uint32_t tokens, uint32_t stride) { return tokens > 16 && stride == 1 ? 32u : 16u; }
 
-// One weight: the plain kernel (its arguments are the first entry); several: the batch kernel.
 template <int KB, bool NORM>
 void launch_linear(const LinearBatchArgs &batch, uint32_t cols, uint32_t wgs, hipStream_t stream)
 {
     const dim3 grid(wgs), block(kLinThreads);
     const uint32_t tokens = batch.t[0].tokens;
-#define NZ_LINEAR(COLS, MT)                                                                                       \
-    do {                                                                                                          \
-        if (batch.count == 1)                                                                                     \
-            hipLaunchKernelGGL((linear_kernel<KB, COLS, MT, NORM>), grid, block, 0, stream, batch.t[0]);          \
-        else                                                                                                      \
-            hipLaunchKernelGGL((linear_batch_kernel<KB, COLS, MT, NORM>), grid, block, 0, stream, batch);         \
-    } while (0)
+#define NZ_LINEAR(COLS, MT) \
+    hipLaunchKernelGGL((linear_batch_kernel<KB, COLS, MT, NORM>), grid, block, 0, stream, batch)
     if (cols == 32) {
         if (tokens <= 32)
             NZ_LINEAR(32, 1);
@@ -508,8 +553,9 @@ void launch_linear(const LinearBatchArgs &batch, uint32_t cols, uint32_t wgs, hi
 // to record into a graph) and a single zero offset.
 int compress_empty(neuzip_blob *b, hipStream_t stream)
 {
-    hipLaunchKernelGGL(fill_u32_kernel, dim3((sizeof(TableBlock) / 4 + 255) / 256), dim3(256), 0, stream,
-                       reinterpret_cast<uint32_t *>(b->fixed), 0u, static_cast<uint32_t>(sizeof(TableBlock) / 4));
+    const uint32_t table_words = static_cast<uint32_t>(b->at.offsets / 4);
+    hipLaunchKernelGGL(fill_u32_kernel, dim3((table_words + 255) / 256), dim3(256), 0, stream,
+                       reinterpret_cast<uint32_t *>(b->fixed), 0u, table_words);
     hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, stream, offsets_of(b), 0u, 2u);
     if (!hip_ok(hipGetLastError()) || !hip_ok(hipStreamSynchronize(stream)))
         return NEUZIP_EHIP;
@@ -713,6 +759,8 @@ int compress_tiled(neuzip_blob *b, const void *d_src, const void *d_grad, int k,
         it.offsets = offsets_of(b) + c0;
         it.states = states_of(b) + static_cast<uint64_t>(c0) * kStates;
         it.lens = lens_of(b) + static_cast<uint64_t>(c0) * kStates;
+        it.mid_states = mid_states_of(b) ? mid_states_of(b) + static_cast<uint64_t>(c0) * kStates : nullptr;
+        it.mid_lens = mid_lens_of(b) ? mid_lens_of(b) + static_cast<uint64_t>(c0) * kStates : nullptr;
         it.sm = sm_of(b) + e0 * static_cast<uint64_t>(k + 1) / 8;
         it.coef = block ? coef_of(b) + e0 / block : coef_of(b);
         it.low = low_of(b) ? low_of(b) + e0 : nullptr;
@@ -731,8 +779,8 @@ int compress_tiled(neuzip_blob *b, const void *d_src, const void *d_grad, int k,
         uint32_t *super_words = ws.super_words + copy * ws.super_cap;
         uint32_t *super_next = ws.super_words + (copy ^ 1u) * ws.super_cap;
         // (the workgroup that fills in the decoder's slot table rides with the first tile)
-        if (!launch_encode(ws, batch, it.enc_end + ((!reuse && g0 == 0) ? 1u : 0u), variant, reuse, elem, block, super_words,
-                           state, stream))
+        if (!launch_encode(ws, batch, it.enc_end + (!reuse && g0 == 0 ? 1u : 0u), variant, reuse, elem, block, super_words, state,
+                           stream))
             return fail(NEUZIP_EHIP);
         bins_dirty = true;  // (sums of this tile; the compaction's report clears them)
         batch.report = 1;
@@ -916,6 +964,8 @@ int compress_some(const void *const *d_srcs, const uint64_t *n_elems, uint32_t c
         it.offsets = offsets_of(b);
         it.states = states_of(b);
         it.lens = lens_of(b);
+        it.mid_states = mid_states_of(b);
+        it.mid_lens = mid_lens_of(b);
         it.sm = sm_of(b);
         it.coef = coef_of(b);
         it.low = low_of(b);
@@ -963,7 +1013,8 @@ int compress_some(const void *const *d_srcs, const uint64_t *n_elems, uint32_t c
 
         // Three launches.  The histogram pass (fresh statistics only).  The encoder, every workgroup of
         // which derives the table from the counts by itself; with fresh tables its launch carries one
-        // more workgroup per tensor, which fills in the decoder's slot table meanwhile.  The compaction,
+        // more workgroup per tensor, which fills in the decoder's slot table meanwhile (of blobs that
+        // hold one).  The compaction,
         // which also works out the chunk offsets, tells the host the stream lengths and returns the
         // workspace's sums to zero.
         const int variant = d_grads ? kUpdateVariant : (elem == NEUZIP_F32 ? 23 : (elem == NEUZIP_F16 ? 39 : k));
@@ -1218,15 +1269,14 @@ int neuzip_update(neuzip_blob *const *blobs, const void *const *d_grads, void *c
         const bool stream_out = batch_elems >= (64ull << 20);
         BatchArgs args;
         args.count = 0;
-        uint32_t groups = 0;
         for (uint32_t i = 0; i <= count; ++i) {
             const bool flush = (i == count) || (args.count == kBatchMax);
             if (flush && args.count > 0) {
+                const uint32_t groups = place_workgroups(args, kUpdateVariant, stream_out);
                 const int rc = launch_batch(args, kUpdateVariant, groups, stream);
                 if (rc != NEUZIP_OK)
                     return rc;
                 args.count = 0;
-                groups = 0;
             }
             if (i == count)
                 break;
@@ -1236,9 +1286,6 @@ int neuzip_update(neuzip_blob *const *blobs, const void *const *d_grads, void *c
             DecodeArgs a = decode_args(b, d_weights[i]);
             a.grad = static_cast<const uint16_t *>(d_grads[i]);
             a.lr = lr;
-            a.stream_out = stream_out ? 1u : 0u;
-            groups += (b->n_chunks + kDecChunksPerWg - 1) / kDecChunksPerWg;
-            a.wg_end = groups;
             args.t[args.count++] = a;
         }
     }
@@ -1315,6 +1362,8 @@ int neuzip_linear_batch(const neuzip_blob *const *weights, const uint64_t *out_f
         a.offsets = offsets_of(w);
         a.states = states_of(w);
         a.lens = lens_of(w);
+        a.mid_states = mid_states_of(w);
+        a.mid_lens = mid_lens_of(w);
         a.words = reinterpret_cast<const uint16_t *>(w->words);
         a.sm = sm_of(w);
         a.status = table_of(w)->status;
@@ -1346,7 +1395,6 @@ int neuzip_linear_batch(const neuzip_blob *const *weights, const uint64_t *out_f
     for (uint32_t t0 = 0; t0 < tokens; t0 += kLinMaxTokens) {
         const uint32_t tile = tokens - t0 < kLinMaxTokens ? tokens - t0 : kLinMaxTokens;
         const uint32_t cols = linear_columns(tile, batch.t[0].stride);  // chunks per group = columns of the matrix instruction
-        const uint32_t groups_per_wg = kDecChunksPerWg / cols;
         uint32_t wgs = 0;
         for (uint32_t i = 0; i < count; ++i) {
             LinearArgs &a = batch.t[i];
@@ -1355,6 +1403,9 @@ int neuzip_linear_batch(const neuzip_blob *const *weights, const uint64_t *out_f
             a.y = d_y[i] + static_cast<uint64_t>(t0) * out_features[i];
             const uint64_t per_block = static_cast<uint64_t>(cols) * a.stride;
             a.n_groups = static_cast<uint32_t>((weights[i]->n_chunks + per_block - 1) / per_block * a.stride);
+            // (the 32-column form walks whole states: its accumulators leave no room for twice the waves)
+            a.split = cols == 16 && a.mid_states ? 1u : 0u;
+            const uint32_t groups_per_wg = (kDecChunksPerWg / cols) >> a.split;
             wgs += (a.n_groups + groups_per_wg - 1) / groups_per_wg;
             batch.wg_end[i] = wgs;
         }
@@ -1542,7 +1593,6 @@ int neuzip_decompress_sequence(const neuzip_blob *const *blobs, uint32_t count, 
     while (first < count) {
         BatchArgs args;
         args.count = 0;
-        uint32_t groups = 0;
         uint64_t at = 0;  // 16-bit words from the start of the space
         const int kind = decode_variant(blobs[first]);
         uint32_t i = first, live = first;  // live: the last blob of the group that has elements
@@ -1553,10 +1603,7 @@ int neuzip_decompress_sequence(const neuzip_blob *const *blobs, uint32_t count, 
             if (h_offsets)
                 h_offsets[i] = at;
             if (b->n > 0) {
-                DecodeArgs a = decode_args(b, static_cast<uint16_t *>(d_scratch) + at);
-                groups += (b->n_chunks + batch_chunks_per_wg(kind) - 1) / batch_chunks_per_wg(kind);
-                a.wg_end = groups;
-                args.t[args.count++] = a;
+                args.t[args.count++] = decode_args(b, static_cast<uint16_t *>(d_scratch) + at);
                 live = i;
             }
             at = pad_to(at + words_of(b), 128);
@@ -1567,9 +1614,8 @@ int neuzip_decompress_sequence(const neuzip_blob *const *blobs, uint32_t count, 
             if (rc != NEUZIP_OK)
                 return rc;
         } else if (args.count > 1) {
-            const bool stream_out = at >= (64ull << 20);  // the group as a whole exceeds the cache
-            for (uint32_t t = 0; t < args.count; ++t)
-                args.t[t].stream_out = stream_out ? 1u : 0u;
+            // (`at`: whether the group as a whole exceeds the cache)
+            const uint32_t groups = place_workgroups(args, kind, at >= (64ull << 20));
             const int rc = launch_batch(args, kind, groups, stream);
             if (rc != NEUZIP_OK)
                 return rc;
@@ -1600,26 +1646,21 @@ int neuzip_decompress_batch(const neuzip_blob *const *blobs, void *const *d_dsts
     for (int k : kinds) {
         BatchArgs args;
         args.count = 0;
-        uint32_t groups = 0;
         for (uint32_t i = 0; i <= count; ++i) {
             const bool flush = (i == count) || (args.count == kBatchMax);
             if (flush && args.count > 0) {
+                const uint32_t groups = place_workgroups(args, k, stream_out);
                 const int rc = launch_batch(args, k, groups, stream);
                 if (rc != NEUZIP_OK)
                     return rc;
                 args.count = 0;
-                groups = 0;
             }
             if (i == count)
                 break;
             const neuzip_blob *b = blobs[i];
             if (decode_variant(b) != k || b->n == 0)
                 continue;
-            DecodeArgs a = decode_args(b, d_dsts[i]);
-            a.stream_out = stream_out ? 1u : 0u;
-            groups += (b->n_chunks + batch_chunks_per_wg(k) - 1) / batch_chunks_per_wg(k);
-            a.wg_end = groups;
-            args.t[args.count++] = a;
+            args.t[args.count++] = decode_args(b, d_dsts[i]);
         }
     }
     return NEUZIP_OK;
@@ -1797,14 +1838,25 @@ int neuzip_import(const void *h_buf, uint64_t len, void *hip_stream, neuzip_blob
     std::memcpy(tb.freq, freq, 512);
     std::memcpy(tb.cum, cum, sizeof(tb.cum));
     tb.lone = 256;
+    uint32_t occupied = 0;
     for (uint32_t sym = 0; sym < 256; ++sym) {
         if (freq[sym] == kM)
             tb.lone = sym;
+        if (freq[sym])
+            tb.steps[occupied++] = (static_cast<uint32_t>(cum[sym]) << 8) | sym;
+    }
+    for (; occupied < kSteps; ++occupied)
+        tb.steps[occupied] = kM << 8;
+    for (uint32_t i = 0, r = 0; n && i < kM / 8; ++i) {
+        while ((tb.steps[r + 1] >> 8) <= 8 * i)
+            ++r;
+        tb.step_of[i] = static_cast<uint8_t>(r);
+    }
+    for (uint32_t sym = 0; sym < 256; ++sym)
         for (uint32_t slot = cum[sym]; slot < static_cast<uint32_t>(cum[sym]) + freq[sym]; ++slot)
             tb.lut[slot] = sym | ((freq[sym] & 0xFFFu) << 8) | ((slot - cum[sym]) << 20);
-    }
     const uint32_t zeros[2] = {0, 0};
-    if (!hip_ok(hipMemcpyAsync(b->fixed, &tb, sizeof(tb), hipMemcpyHostToDevice, stream)) ||
+    if (!hip_ok(hipMemcpyAsync(b->fixed, &tb, b->at.offsets, hipMemcpyHostToDevice, stream)) ||
         !hip_ok(hipMemcpyAsync(offsets_of(b), p + lay.offsets, (nc + 1ull) * 4, hipMemcpyHostToDevice, stream)) ||
         !hip_ok(hipMemcpyAsync(offsets_of(b) + nc + 1, zeros, 4, hipMemcpyHostToDevice, stream)))
         return fail(NEUZIP_EHIP);
@@ -1822,6 +1874,12 @@ int neuzip_import(const void *h_buf, uint64_t len, void *hip_stream, neuzip_blob
             if (p[lay.coef + i] > 127)
                 return fail(NEUZIP_ECORRUPT);
         if (!hip_ok(hipMemcpyAsync(coef_of(b), p + lay.coef, block_count(n, block), hipMemcpyHostToDevice, stream)))
+            return fail(NEUZIP_EHIP);
+    }
+    if (mid_states_of(b)) {
+        hipLaunchKernelGGL(entry_points_kernel, dim3((nc * kStates + 255) / 256), dim3(256), 0, stream, decode_args(b, nullptr),
+                           mid_states_of(b), mid_lens_of(b));
+        if (!hip_ok(hipGetLastError()))
             return fail(NEUZIP_EHIP);
     }
     if (!hip_ok(hipStreamSynchronize(stream)))  // tb and zeros must outlive the copies

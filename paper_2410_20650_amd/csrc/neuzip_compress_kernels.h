@@ -1,7 +1,7 @@
 // Compression kernels of the NeuZip codec for gfx950, three launches per call: histogram +
-// sign|mantissa split (with and without block-wise normalisation), whose last workgroup per tensor
-// builds the frequency table; the chunked rANS encoder, whose last workgroup per tensor turns the
-// word counts into offsets; the compaction.  Every kernel works on a batch of up to 8 tensors
+// sign|mantissa split (with and without block-wise normalisation); the chunked rANS encoder, every
+// workgroup of which derives the frequency table from the counts; the compaction, which works out
+// the chunk offsets.  Every kernel works on a batch of up to 8 tensors
 // described by a CompressBatch.
 #pragma once
 
@@ -380,41 +380,36 @@ __device__ inline EncSym encoder_constants(uint32_t f, uint32_t cum)
     return e;
 }
 
-// Decoder slot table of a tensor: lut[slot] = symbol | f << 8 | (slot - cum[symbol]) << 20.
-// 256 threads; scan[t] = cum[t + 1] (in LDS, complete); thread s fills slots s, s + 256, ...
-__device__ inline void build_slot_table(TableBlock *__restrict__ tb, const uint32_t *__restrict__ scan)
+// The decoder's slot table is made from the tensor's occupied symbols (TableBlock::steps, in LDS) in pieces of
+// eight neighbouring slots.  Which step a piece begins in:
+__device__ __forceinline__ uint32_t step_of_piece(const uint32_t *__restrict__ steps, uint32_t piece)
 {
-    const uint32_t s = threadIdx.x;
-    if (scan[255] != kM)
-        return;  // an empty table: nothing decodes through it
-    // (four searches at a time: this runs beside the encoders in their kernel and must not raise its
-    // register count)
-    constexpr uint32_t kPer = kM / 256, kAtOnce = 4;
-#pragma unroll 1
-    for (uint32_t r0 = 0; r0 < kPer; r0 += kAtOnce) {
-        uint32_t lo[kAtOnce], hi[kAtOnce];
+    uint32_t r = 0;  // the last step that starts at or before the first slot
 #pragma unroll
-        for (uint32_t r = 0; r < kAtOnce; ++r) {
-            lo[r] = 0;
-            hi[r] = 255;
+    for (uint32_t bit = 128; bit > 0; bit >>= 1)
+        r += (steps[r + bit] >> 8) <= piece * 8 ? bit : 0u;
+    return r;
+}
+
+// ... and the piece itself: at most one step further per slot, since every occupied symbol has at least one.
+__device__ __forceinline__ void make_piece(const uint32_t *__restrict__ steps, uint32_t r, uint32_t piece,
+                                           uint32_t *__restrict__ lut)
+{
+    const uint32_t slot0 = piece * 8;
+    uint32_t here = steps[r], there = steps[r + 1];
+    uint32_t e[8];
+#pragma unroll
+    for (uint32_t t = 0; t < 8; ++t) {
+        if (slot0 + t >= (there >> 8)) {
+            here = there;
+            ++r;
+            there = steps[r + 1];
         }
-#pragma unroll
-        for (uint32_t step = 0; step < 8; ++step) {
-#pragma unroll
-            for (uint32_t r = 0; r < kAtOnce; ++r) {  // smallest t with cum[t + 1] > slot
-                const uint32_t mid = (lo[r] + hi[r]) >> 1;
-                const bool above = scan[mid] > s + 256 * (r0 + r);
-                hi[r] = above ? mid : hi[r];
-                lo[r] = above ? lo[r] : (mid < hi[r] ? mid + 1 : hi[r]);
-            }
-        }
-#pragma unroll
-        for (uint32_t r = 0; r < kAtOnce; ++r) {
-            const uint32_t slot = s + 256 * (r0 + r), t = lo[r];
-            const uint32_t begin = t ? scan[t - 1] : 0u;
-            tb->lut[slot] = t | (((scan[t] - begin) & 0xFFFu) << 8) | ((slot - begin) << 20);
-        }
+        const uint32_t cum = here >> 8;
+        e[t] = (here & 0xFFu) | ((((there >> 8) - cum) & 0xFFFu) << 8) | ((slot0 + t - cum) << 20);
     }
+    reinterpret_cast<uint4 *>(lut)[2 * piece] = make_uint4(e[0], e[1], e[2], e[3]);
+    reinterpret_cast<uint4 *>(lut)[2 * piece + 1] = make_uint4(e[4], e[5], e[6], e[7]);
 }
 
 constexpr uint32_t kHistCopies = 32;
@@ -859,13 +854,24 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
                 const EncSym e = encoder_constants(f[i], cum[i]);
                 enc_raw[4 * lane + i] = make_uint4(e.mul, e.limit_cum, e.shift_inc, e.cmpl);
             }
-            if (table_wg) {
-                uint32_t *scan = reinterpret_cast<uint32_t *>(rings);  // scan[t] = cum[t + 1]
+            // the occupied symbols in order, and the end mark behind them: into the blob, and for the slot table
+            if (slot_id.wg == 0) {
+                uint32_t *steps = table_wg ? reinterpret_cast<uint32_t *>(rings) : tb->steps;
+                uint32_t occupied = 0;
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    scan[4 * lane + i] = cum[i] + f[i];
-            } else if (slot_id.wg == 0) {
-                reinterpret_cast<uint4 *>(tb->counts)[lane] = c4;
+                    occupied += f[i] > 0 ? 1u : 0u;
+                const uint32_t upto = wave_scan_u32(occupied, 0u, OpAdd{});
+                uint32_t at = upto - occupied;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (f[i] > 0)
+                        steps[at++] = (cum[i] << 8) | (4 * lane + i);
+                for (uint32_t i = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(upto), 63)) + lane;
+                     i < kSteps; i += 64)
+                    steps[i] = kM << 8;
+            }
+            if (slot_id.wg == 0 && !table_wg) {
                 reinterpret_cast<uint2 *>(tb->freq)[lane] = make_uint2(f[0] | (f[1] << 16), f[2] | (f[3] << 16));
                 reinterpret_cast<uint2 *>(tb->cum)[lane] = make_uint2(cum[0] | (cum[1] << 16), cum[2] | (cum[3] << 16));
                 if (lane == 63)
@@ -888,8 +894,15 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
     }
     __syncthreads();
     if (table_wg) {
-        // fills in the decoder's slot table while the others encode
-        build_slot_table(tb, reinterpret_cast<const uint32_t *>(rings));
+        // fills in the decoder's slot table, or what the decoders need to make it, while the others encode
+        const uint32_t *steps = reinterpret_cast<const uint32_t *>(rings);
+        for (uint32_t piece = threadIdx.x; piece < kM / 8; piece += kEncThreads) {
+            const uint32_t r = step_of_piece(steps, piece);
+            if (it.mid_states)
+                tb->step_of[piece] = static_cast<uint8_t>(r);
+            else
+                make_piece(steps, r, piece, tb->lut);
+        }
         return;
     }
     const EncSym *enc = reinterpret_cast<const EncSym *>(enc_raw);
@@ -900,6 +913,9 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
     uint32_t lane_step = lane_ring + 2u;
     asm volatile("" : "+v"(lane_step));  // (a register of its own: otherwise the sum is formed again per symbol)
     EncState st = {kRansL, kRunCap, lane_ring | ring_place(kRunCap % kRingWords)};
+    // where this state's chain stands between turns kMidTurn and kMidTurn - 1 (nothing coded so far, if the
+    // chunk ends below)
+    uint32_t mid_x = kRansL, mid_wp = kRunCap;
     uint32_t least_mul = 1u;  // 0 once a symbol without room in the table has been met
     uint8_t *__restrict__ sm = it.sm;
 
@@ -977,7 +993,12 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
 #pragma unroll
             for (uint32_t r = 0; r < kAhead; ++r)
                 turn((r + 1) % kAhead, q - static_cast<int>(r), true);
+            if (q + 1 - static_cast<int>(kAhead) == static_cast<int>(kMidTurn)) {
+                mid_x = st.x;
+                mid_wp = st.wp;
+            }
         }
+        static_assert((kTurns - kMidTurn) % kAhead == 0, "the middle lies between two rotations");
 #pragma unroll
         for (uint32_t r = 0; r < kAhead; ++r)
             turn((r + 1) % kAhead, static_cast<int>(kAhead - 1 - r), r + 1 < kAhead);
@@ -1066,6 +1087,10 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
             }
             ring_advance(st, cur_before);
             ring_flush(wp_before, st.wp, ring_bytes, lane_ring, chunk_slots, j);
+            if (q == static_cast<int>(kMidTurn)) {
+                mid_x = st.x;
+                mid_wp = st.wp;
+            }
             d0 = d1;
             g0 = g1;
         }
@@ -1082,6 +1107,10 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
                 *reinterpret_cast<const uint16_t *>(ring_bytes + (lane_ring | ring_place(p & (kRingWords - 1))));
         states[lane_id] = st.x;
         lens[lane_id] = static_cast<uint8_t>(len);
+        if (it.mid_states) {
+            it.mid_states[lane_id] = mid_x;
+            it.mid_lens[lane_id] = static_cast<uint8_t>(mid_wp - st.wp);  // words the decoder has consumed by then
+        }
     }
     // words of the whole chunk (16 neighbouring lanes), then of the workgroup's 16 chunks
     uint32_t sum = len;

@@ -11,11 +11,11 @@ namespace nz {
 // ------------------------------------------------------------------------------------------
 // Kernel 6: fused decoder (Alg. 1 "decompression" + "merge"; Sec. 2.2 Eq. (3)).
 //
-// A workgroup owns blockDim.x / 16 neighbouring chunks (at most 32).  It copies the 4096-entry
-// slot table (symbol | f << 8 | (slot - cum) << 20, prepared once per tensor) and the chunks'
-// word runs -- one contiguous piece of the blob -- into LDS with 128-bit loads behind a single
-// barrier, and then every lane walks one
-// state: 32 turns of 8 symbols; per symbol one table read, one multiply-add, one compare, and
+// A workgroup owns blockDim.x / 16 neighbouring chunks (at most 32; half as many of a blob with entry
+// points).  It copies the 4096-entry slot table (symbol | f << 8 |
+// (slot - cum) << 20), or makes it from the tensor's table, in LDS, copies the chunks' word runs -- one contiguous piece of the blob -- there with
+// 128-bit loads, and then every lane walks one
+// state, or the half of a state before or behind its entry point: 32 (16) turns of 8 symbols; per symbol one table read, one multiply-add, one compare, and
 // a lane-private refill that touches LDS only when a word is consumed.  The 8 decoded
 // exponents are merged with the 8 sign|mantissa fields and leave as one 128-bit store; the
 // fields of the next turn are requested before the current turn is decoded.
@@ -211,8 +211,16 @@ __device__ __forceinline__ uint4 merge_turn(uint64_t fields, const uint32_t (&e)
     return o;
 }
 
-// The wave that holds a tensor's ragged last chunk: every lane walks the turns its chunk has (m elements;
-// the other chunks of the wave are whole and walk beside it), the last one possibly with fewer than 8
+// Marks a loaded value as used here, at the end of a path beside a hot loop: the compiler lays the two out one
+// behind the other, takes the path's loads for outstanding in the loop, and would wait there in every turn for
+// the stores of the turn before (28672 x 8192, k = 3, block 512: 158 us instead of 147).
+__device__ __forceinline__ void settle(uint64_t v)
+{
+    asm volatile("" ::"v"(static_cast<uint32_t>(v)), "v"(static_cast<uint32_t>(v >> 32)));
+}
+
+// The wave that holds a tensor's ragged last chunk: every lane walks the turns its chunk has (m elements, or
+// as many as lie before the lane's entry point; the other chunks of the wave are whole and walk beside it), the last one possibly with fewer than 8
 // elements of its own.  Fields are read a whole turn at a time and one turn ahead: the sections of the
 // blob they come from are padded by 256 bytes, so the last read may pass the tensor's end.  The gradient is
 // the caller's, so the elements of an incomplete turn are read one by one there, as they are written.
@@ -223,10 +231,10 @@ __device__ __forceinline__ void walk_ragged(const uint32_t *__restrict__ lut, co
                                             const WordSrc &src, uint32_t lone, uint32_t &x, uint32_t &wp,
                                             const uint8_t *__restrict__ sm, const uint8_t *__restrict__ coef,
                                             uint32_t block, uint16_t *__restrict__ out, uint64_t base, uint32_t m,
-                                            uint32_t j, const uint16_t *__restrict__ grad, float lr)
+                                            uint32_t j, uint32_t turn0, const uint16_t *__restrict__ grad, float lr)
 {
     uint32_t next = LONE ? 0u : src.peek(wp);
-    uint32_t at = j * kRun;  // this lane's run of the turn, inside the chunk
+    uint32_t at = turn0 * kTurn + j * kRun;  // this lane's run of the turn, inside the chunk
     uint64_t fields = at < m ? load_turn<KB, NORM>(sm, coef, block, base + at) : 0;
     for (; at < m; at += kTurn) {
         const uint64_t here = base + at;
@@ -276,18 +284,19 @@ __device__ __forceinline__ void walk_ragged(const uint32_t *__restrict__ lut, co
         }
         fields = fields_next;
     }
+    settle(fields);
 }
 
 // UPD: the words written are the decoded weights after the update with the gradient `grad` (bf16
 // words, same indexing as the output) and the rate lr.  HALF: the tensor is binary16.
-template <int KB, bool LONE, bool NORM, bool STREAM, bool UPD, bool HALF, class WordSrc>
+template <int KB, bool LONE, bool NORM, bool STREAM, bool UPD, bool HALF, uint32_t turns, class WordSrc>
 __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, const uint2 *__restrict__ spread,
                                            const WordSrc &src, uint32_t lone,
                                            uint32_t &x, uint32_t &wp, const uint8_t *__restrict__ sm,
                                            const uint8_t *__restrict__ coef, uint32_t block,
                                            uint64_t (&fields)[KB == 7 ? kTurnGroupStream : kTurnGroup],
                                            uint16_t *__restrict__ out,
-                                           uint64_t base, uint32_t m, uint32_t j,
+                                           uint64_t base, uint32_t m, uint32_t j, uint32_t turn0,
                                            const uint16_t *__restrict__ grad = nullptr, float lr = 0.0f)
 {
     static_assert(!(UPD || HALF) || (KB == 7 && !NORM), "trained weights and binary16 tensors are lossless only");
@@ -296,10 +305,11 @@ __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, con
     constexpr uint32_t kGroup = (STREAM && KB == 7 && !UPD) ? kTurnGroupStream : kTurnGroup;
     if (__all(m == kChunk)) {  // all chunks of the wave are whole
         uint32_t next = LONE ? 0u : src.peek(wp);
-        uint4 *out4 = reinterpret_cast<uint4 *>(out + base) + j;
-        const uint64_t first = base + j * kRun;
+        const uint64_t from = base + turn0 * kTurn;
+        uint4 *out4 = reinterpret_cast<uint4 *>(out + from) + j;
+        const uint64_t first = from + j * kRun;
         // the gradients of a turn: the 128 bits the lane's output words come from
-        const uint4 *grad4 = UPD ? reinterpret_cast<const uint4 *>(grad + base) + j : nullptr;
+        const uint4 *grad4 = UPD ? reinterpret_cast<const uint4 *>(grad + from) + j : nullptr;
         uint4 grads[kGroup];
         if constexpr (UPD) {
 #pragma unroll
@@ -310,10 +320,10 @@ __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, con
         // the current group is decoded, and the group's 128-bit stores leave back to back, so
         // each state keeps several memory requests in flight and a chunk is written in bursts of
         // kGroup * 256 contiguous bytes.
-        for (uint32_t q0 = 0; q0 < kTurns; q0 += kGroup) {
+        for (uint32_t q0 = 0; q0 < turns; q0 += kGroup) {
             uint64_t fields_next[kGroup];
             // the last group re-reads its own fields (stays in bounds)
-            const uint32_t qn = q0 + kGroup < kTurns ? q0 + kGroup : q0;
+            const uint32_t qn = q0 + kGroup < turns ? q0 + kGroup : q0;
 #pragma unroll
             for (uint32_t r = 0; r < kGroup; ++r)
                 fields_next[r] = load_turn<KB, NORM>(sm, coef, block, first + (qn + r) * kTurn);
@@ -356,30 +366,33 @@ __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, con
             }
         }
     } else {
-        walk_ragged<KB, LONE, NORM, UPD, HALF>(lut, spread, src, lone, x, wp, sm, coef, block, out, base, m, j, grad, lr);
+        const uint32_t end = (turn0 + turns) * kTurn;
+        walk_ragged<KB, LONE, NORM, UPD, HALF>(lut, spread, src, lone, x, wp, sm, coef, block, out, base, m < end ? m : end, j,
+                                               turn0, grad, lr);
     }
 }
 
 // The same walk for a binary32 tensor (lossless only): the decoded bf16 word is the upper half
 // of the element and the lower half comes from the raw plane, so a turn reads 16 B of lower
 // halves next to its 8 B of fields and writes two 128-bit pieces.
-template <bool LONE, bool STREAM, class WordSrc>
+template <bool LONE, bool STREAM, uint32_t turns, class WordSrc>
 __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut, const WordSrc &src, uint32_t lone,
                                                 uint32_t &x, uint32_t &wp, const uint8_t *__restrict__ sm,
                                                 const uint16_t *__restrict__ low, uint32_t *__restrict__ out,
-                                                uint64_t base, uint32_t m, uint32_t j)
+                                                uint64_t base, uint32_t m, uint32_t j, uint32_t turn0)
 {
     constexpr uint32_t kGroup = kTurnGroup;
     uint32_t next = LONE ? 0u : src.peek(wp);
     if (__all(m == kChunk)) {
         // where this lane stores: its own pieces 2j and 2j + 1 of a turn's 32, or, after the exchange
         // described below, pieces (j / 8) * 16 + j % 8 and 8 further
-        uint4 *out4 = reinterpret_cast<uint4 *>(out + base) + (STREAM ? (j >> 3) * 16 + (j & 7) : 2 * j);
+        const uint64_t from = base + turn0 * kTurn;
+        uint4 *out4 = reinterpret_cast<uint4 *>(out + from) + (STREAM ? (j >> 3) * 16 + (j & 7) : 2 * j);
         const uint32_t lane = threadIdx.x & 63u;
         const uint32_t pull[2] = {((lane & ~7u) + ((lane & 7u) >> 1)) * 4u, ((lane & ~7u) + 4u + ((lane & 7u) >> 1)) * 4u};
         const bool odd = lane & 1u;
-        const uint4 *low4 = reinterpret_cast<const uint4 *>(low + base) + j;
-        const uint64_t first = base + j * kRun;
+        const uint4 *low4 = reinterpret_cast<const uint4 *>(low + from) + j;
+        const uint64_t first = from + j * kRun;
         uint64_t fields[kGroup];
         uint4 lows[kGroup];
 #pragma unroll
@@ -387,10 +400,10 @@ __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut
             fields[r] = load_fields<7>(sm, first + r * kTurn);
             lows[r] = low4[r * kStates];
         }
-        for (uint32_t q0 = 0; q0 < kTurns; q0 += kGroup) {
+        for (uint32_t q0 = 0; q0 < turns; q0 += kGroup) {
             uint64_t fields_next[kGroup];
             uint4 lows_next[kGroup];
-            const uint32_t qn = q0 + kGroup < kTurns ? q0 + kGroup : q0;  // the last group re-reads its own
+            const uint32_t qn = q0 + kGroup < turns ? q0 + kGroup : q0;  // the last group re-reads its own
 #pragma unroll
             for (uint32_t r = 0; r < kGroup; ++r) {
                 fields_next[r] = load_fields<7>(sm, first + (qn + r) * kTurn);
@@ -460,7 +473,9 @@ __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut
         }
     } else {
         // the wave with the ragged last chunk: see walk_ragged
-        uint32_t at = j * kRun;
+        const uint32_t end = (turn0 + turns) * kTurn;
+        m = m < end ? m : end;
+        uint32_t at = turn0 * kTurn + j * kRun;
         uint64_t fields = 0;
         uint4 lows = make_uint4(0, 0, 0, 0);
         if (at < m) {
@@ -510,6 +525,8 @@ __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut
             fields = fields_next;
             lows = lows_next;
         }
+        settle(fields);
+        settle(lows.x | (static_cast<uint64_t>(lows.w) << 32));
     }
 }
 
@@ -519,6 +536,8 @@ struct DecodeArgs {
     const uint32_t *offsets;
     const uint32_t *states;
     const uint8_t *lens;
+    const uint32_t *mid_states;  // entry points: two lanes walk a state's two halves (nullptr: one lane per state)
+    const uint8_t *mid_lens;
     const uint16_t *words;
     const uint8_t *sm;
     const uint8_t *coef;  // block coefficients (block-wise normalised blobs only)
@@ -532,6 +551,7 @@ struct DecodeArgs {
     uint32_t block;       // 0: no block-wise normalisation
     uint32_t stream_out;  // non-zero: the output does not fit the last-level cache, store non-temporally
     uint32_t wg_end;      // batches: first workgroup index after this tensor's
+    uint32_t make_lut;    // the blob holds no slot table (it has entry points, used here or not)
 };
 
 // Decodes the chunks of workgroup `wg` of one tensor.
@@ -540,84 +560,127 @@ struct DecodeArgs {
 // binary16 words (kHalf).
 enum DecodeMode { kPlain = 0, kWide = 1, kUpdate = 2, kHalf = 3 };
 
-template <int KB, bool NORM, int MODE>
-__device__ __forceinline__ void decode_workgroup(const TableBlock *__restrict__ tb,
-                                                 const uint32_t *__restrict__ offsets,
-                                                 const uint32_t *__restrict__ states,
-                                                 const uint8_t *__restrict__ lens,
-                                                 const uint16_t *__restrict__ words,
-                                                 const uint8_t *__restrict__ sm,
-                                                 const uint8_t *__restrict__ coef, uint32_t block,
-                                                 const uint16_t *__restrict__ low, void *__restrict__ out_any,
-                                                 const uint16_t *__restrict__ grad, float lr, bool stream_out,
-                                                 uint64_t n, uint32_t n_chunks, uint32_t *__restrict__ status,
-                                                 uint32_t wg, uint32_t *__restrict__ lut, uint8_t *__restrict__ stage,
+// SPLIT: the blob has entry points (the same code with a run-time choice cost the other blobs 2-5 %).
+template <int KB, bool NORM, int MODE, bool SPLIT>
+__device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t wg, uint32_t *__restrict__ lut,
+                                                 uint32_t *__restrict__ steps, uint8_t *__restrict__ stage,
                                                  uint2 *__restrict__ spread)
 {
     constexpr bool WIDE = MODE == kWide, UPD = MODE == kUpdate, HALF = MODE == kHalf;
     static_assert(MODE == kPlain || (KB == 7 && !NORM), "binary32 blobs and trained weights are lossless only");
-    block = 31u - static_cast<uint32_t>(__clz(static_cast<int>(block | 1u)));  // a power of two: from here on its log2
+    const uint32_t block = 31u - static_cast<uint32_t>(__clz(static_cast<int>(a.block | 1u)));  // log2 (a power of two)
+    const uint16_t *__restrict__ words = a.words;
+    const uint8_t *__restrict__ sm = a.sm;
+    const uint8_t *__restrict__ coef = a.coef;
+    const uint16_t *__restrict__ low = a.low;
+    const uint16_t *__restrict__ grad = a.grad;
+    const float lr = a.lr;
+    const bool stream_out = a.stream_out != 0;
+    void *__restrict__ out_any = a.out;
     uint16_t *__restrict__ out = static_cast<uint16_t *>(out_any);
+    const uint32_t n_chunks = a.n_chunks;
     const uint32_t tid = threadIdx.x;
     const uint32_t threads = blockDim.x;            // a multiple of 64, at most kDecThreads
-    const uint32_t chunks_per_wg = threads / kStates;
+    constexpr uint32_t split = SPLIT ? 1u : 0u;     // two lanes per state?
+    const uint32_t chunks_per_wg = (threads / kStates) >> split;
     const uint32_t c0 = wg * chunks_per_wg;
     const uint32_t c1 = c0 + chunks_per_wg < n_chunks ? c0 + chunks_per_wg : n_chunks;
-    const uint32_t c = c0 + tid / kStates;
+    const uint32_t c = c0 + ((tid / kStates) >> split);
     const uint32_t j = tid % kStates;
+    const uint32_t part = SPLIT ? (tid / kStates) & 1u : 0u;  // before (0) or behind (1) the entry point
+    const uint32_t turn0 = part * kMidTurn;
+    constexpr uint32_t turns = SPLIT ? kMidTurn : kTurns;
+    static_assert(kTurns == 2 * kMidTurn, "halves");
     const bool live = c < n_chunks;
     const uint32_t id = c * kStates + j;
     const uint64_t base = static_cast<uint64_t>(c) * kChunk;
-    const uint32_t m = !live ? 0u : ((n - base) < kChunk ? static_cast<uint32_t>(n - base) : kChunk);
+    const uint32_t m = !live ? 0u : ((a.n - base) < kChunk ? static_cast<uint32_t>(a.n - base) : kChunk);
 
     // ---- every load that depends on nothing is issued first, so their latencies overlap
-    const uint32_t off0 = offsets[c0];
-    const uint32_t off1 = offsets[c1];
-    const uint32_t off_c = live ? offsets[c] : 0u;
-    uint32_t x = live ? states[id] : kRansL;
-    const uint32_t len = live ? lens[id] : 0u;
-    const uint32_t lone = tb->lone;
+    const uint32_t off0 = a.offsets[c0];
+    const uint32_t off1 = a.offsets[c1];
+    const uint32_t off_c = live ? a.offsets[c] : 0u;
+    uint32_t x = live ? a.states[id] : kRansL;
+    const uint32_t len = live ? a.lens[id] : 0u;
+    const uint32_t mid_x = live && SPLIT ? a.mid_states[id] : kRansL;
+    const uint32_t mid_len = live && SPLIT ? a.mid_lens[id] : len;
+    const uint32_t lone = a.tb->lone;
+    // the tensor's table: its steps (blobs with entry points) or the slot table itself
+    const bool make_lut = SPLIT || a.make_lut != 0;
+    const uint4 *table_g = reinterpret_cast<const uint4 *>(make_lut ? a.tb->steps : a.tb->lut);
+    const uint32_t table_pieces = make_lut ? kSteps / 4 : kM / 4;  // of 16 bytes
+    uint4 *table_to = reinterpret_cast<uint4 *>(make_lut ? steps : lut);
+    uint4 table_piece[2];  // the slot table has 1024 pieces: 2 per thread at 512 threads
+#pragma unroll
+    for (uint32_t r = 0; r < 2; ++r) {
+        const uint32_t i = tid + r * threads;
+        table_piece[r] = i < table_pieces ? table_g[i] : make_uint4(0, 0, 0, 0);
+    }
+    uint32_t first_step = 0;  // of this thread's first piece of the slot table
+    if (make_lut)
+        first_step = a.tb->step_of[tid];
     constexpr uint32_t kPreload = KB == 7 ? kTurnGroupStream : kTurnGroup;  // the largest group a variant uses
     uint64_t fields0[kPreload];
 #pragma unroll
     for (uint32_t r = 0; r < kPreload; ++r)
-        fields0[r] = !WIDE && m == kChunk ? load_turn<KB, NORM>(sm, coef, block, base + r * kTurn + j * kRun) : 0;
-    const uint4 *lut_g = reinterpret_cast<const uint4 *>(tb->lut);
-    uint4 lut_piece[2];  // 16 KB table / 16 B = 1024 pieces; 2 per thread at 512 threads
-#pragma unroll
-    for (uint32_t r = 0; r < 2; ++r) {
-        const uint32_t i = tid + r * threads;
-        lut_piece[r] = i < kM / 4 ? lut_g[i] : make_uint4(0, 0, 0, 0);
-    }
-
-    // ---- stage the word runs of chunks [c0, c1): one contiguous piece of the blob
+        fields0[r] = !WIDE && m == kChunk ? load_turn<KB, NORM>(sm, coef, block, base + (turn0 + r) * kTurn + j * kRun) : 0;
+    // ---- the word runs of chunks [c0, c1), one contiguous piece of the blob, into LDS.  (Where the slot table has to
+    // be made, the first pieces stay in registers meanwhile.)
     const uint64_t byte0 = static_cast<uint64_t>(off0) * 2;
     const uint64_t byte1 = static_cast<uint64_t>(off1) * 2;
     const uint64_t aligned0 = byte0 & ~static_cast<uint64_t>(15);
     const uint64_t stage_len = byte1 - aligned0;
     const bool staged = stage_len + 16 <= kStageBytesOf<KB>;  // room for the one-word look-ahead
-    if (staged) {
-        const uint4 *from = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint8_t *>(words) + aligned0);
-        uint4 *to = reinterpret_cast<uint4 *>(stage);
-        for (uint32_t i = tid; i * 16 < stage_len; i += threads)
-            to[i] = from[i];
-    }
-    // ---- slot table into LDS (small workgroups loop over the remaining pieces)
+    const uint4 *from = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint8_t *>(words) + aligned0);
+    uint4 *to = reinterpret_cast<uint4 *>(stage);
+    auto table_to_lds = [&]() {
 #pragma unroll
-    for (uint32_t r = 0; r < 2; ++r) {
-        const uint32_t i = tid + r * threads;
-        if (i < kM / 4)
-            reinterpret_cast<uint4 *>(lut)[i] = lut_piece[r];
-    }
-    for (uint32_t i = tid + 2 * threads; i < kM / 4; i += threads)
-        reinterpret_cast<uint4 *>(lut)[i] = lut_g[i];
-    if constexpr (KB <= 1) {
-        for (uint32_t i = tid; i < kSpreadEntries<KB>; i += threads)
-            spread[i] = spread_entry<KB>(i);
+        for (uint32_t r = 0; r < 2; ++r) {
+            const uint32_t i = tid + r * threads;
+            if (i < table_pieces)
+                table_to[i] = table_piece[r];
+        }
+        for (uint32_t i = tid + 2 * threads; i < table_pieces; i += threads)  // (small workgroups)
+            table_to[i] = table_g[i];
+        if constexpr (KB <= 1) {
+            for (uint32_t i = tid; i < kSpreadEntries<KB>; i += threads)
+                spread[i] = spread_entry<KB>(i);
+        }
+    };
+    if (make_lut) {
+        constexpr uint32_t kFirst = 4;
+        uint4 first[kFirst];
+#pragma unroll
+        for (uint32_t r = 0; r < kFirst; ++r) {
+            const uint32_t i = tid + r * threads;
+            first[r] = staged && static_cast<uint64_t>(i) * 16 < stage_len ? from[i] : make_uint4(0, 0, 0, 0);
+        }
+        table_to_lds();
+        __syncthreads();
+        if (lone >= 256) {
+            make_piece(steps, first_step, tid, lut);
+            for (uint32_t piece = tid + threads; piece < kM / 8; piece += threads)  // (small workgroups)
+                make_piece(steps, a.tb->step_of[piece], piece, lut);
+        }
+        if (staged) {
+#pragma unroll
+            for (uint32_t r = 0; r < kFirst; ++r) {
+                const uint32_t i = tid + r * threads;
+                if (static_cast<uint64_t>(i) * 16 < stage_len)
+                    to[i] = first[r];
+            }
+            for (uint32_t i = tid + kFirst * threads; static_cast<uint64_t>(i) * 16 < stage_len; i += threads)
+                to[i] = from[i];
+        }
+    } else {
+        if (staged)
+            for (uint32_t i = tid; static_cast<uint64_t>(i) * 16 < stage_len; i += threads)
+                to[i] = from[i];
+        table_to_lds();
     }
     __syncthreads();
 
-    // ---- one lane, one state
+    // ---- one lane, one state (or half of one)
     if (!live)
         return;
     // start of this state's run: chunk offset + lengths of the states before it (16-lane prefix)
@@ -629,6 +692,14 @@ __device__ __forceinline__ void decode_workgroup(const TableBlock *__restrict__ 
             before += o;
     }
     before -= len;
+    // a well-formed run is consumed exactly and leaves the state where the encoder started; the half before the
+    // entry point ends there
+    const uint32_t x_end = part ? kRansL : mid_x;
+    const uint32_t words_here = part ? len - mid_len : mid_len;
+    if (part) {
+        x = mid_x;
+        before += mid_len;
+    }
     const uint64_t run_byte = (static_cast<uint64_t>(off_c) + before) * 2;
 
     // (the streaming and the cached store variants are separate instantiations: merged into one
@@ -638,58 +709,54 @@ __device__ __forceinline__ void decode_workgroup(const TableBlock *__restrict__ 
         uint32_t *out32 = static_cast<uint32_t *>(out_any);
         if (lone < 256) {
             if (stream_out)
-                walk_state_wide<true, true>(lut, NoWords{}, lone, x, wp, sm, low, out32, base, m, j);
+                walk_state_wide<true, true, turns>(lut, NoWords{}, lone, x, wp, sm, low, out32, base, m, j, turn0);
             else
-                walk_state_wide<true, false>(lut, NoWords{}, lone, x, wp, sm, low, out32, base, m, j);
+                walk_state_wide<true, false, turns>(lut, NoWords{}, lone, x, wp, sm, low, out32, base, m, j, turn0);
         } else if (staged) {
             wp = wp_begin = static_cast<uint32_t>(run_byte - aligned0);
             if (stream_out)
-                walk_state_wide<false, true>(lut, LdsWords{stage}, 0u, x, wp, sm, low, out32, base, m, j);
+                walk_state_wide<false, true, turns>(lut, LdsWords{stage}, 0u, x, wp, sm, low, out32, base, m, j, turn0);
             else
-                walk_state_wide<false, false>(lut, LdsWords{stage}, 0u, x, wp, sm, low, out32, base, m, j);
+                walk_state_wide<false, false, turns>(lut, LdsWords{stage}, 0u, x, wp, sm, low, out32, base, m, j, turn0);
         } else {
             const GlobalWords direct{reinterpret_cast<const uint8_t *>(words) + run_byte};
             if (stream_out)
-                walk_state_wide<false, true>(lut, direct, 0u, x, wp, sm, low, out32, base, m, j);
+                walk_state_wide<false, true, turns>(lut, direct, 0u, x, wp, sm, low, out32, base, m, j, turn0);
             else
-                walk_state_wide<false, false>(lut, direct, 0u, x, wp, sm, low, out32, base, m, j);
+                walk_state_wide<false, false, turns>(lut, direct, 0u, x, wp, sm, low, out32, base, m, j, turn0);
         }
     } else if (lone < 256) {
         if (stream_out)
-            walk_state<KB, true, NORM, true, UPD, HALF>(lut, spread, NoWords{}, lone, x, wp, sm, coef, block, fields0, out, base, m, j, grad, lr);
+            walk_state<KB, true, NORM, true, UPD, HALF, turns>(lut, spread, NoWords{}, lone, x, wp, sm, coef, block, fields0, out, base, m, j, turn0, grad, lr);
         else
-            walk_state<KB, true, NORM, false, UPD, HALF>(lut, spread, NoWords{}, lone, x, wp, sm, coef, block, fields0, out, base, m, j, grad, lr);
+            walk_state<KB, true, NORM, false, UPD, HALF, turns>(lut, spread, NoWords{}, lone, x, wp, sm, coef, block, fields0, out, base, m, j, turn0, grad, lr);
     } else if (staged) {
         wp = wp_begin = static_cast<uint32_t>(run_byte - aligned0);
         if (stream_out)
-            walk_state<KB, false, NORM, true, UPD, HALF>(lut, spread, LdsWords{stage}, 0u, x, wp, sm, coef, block, fields0, out, base, m,
-                                              j, grad, lr);
+            walk_state<KB, false, NORM, true, UPD, HALF, turns>(lut, spread, LdsWords{stage}, 0u, x, wp, sm, coef, block, fields0, out, base, m, j, turn0, grad, lr);
         else
-            walk_state<KB, false, NORM, false, UPD, HALF>(lut, spread, LdsWords{stage}, 0u, x, wp, sm, coef, block, fields0, out, base, m,
-                                               j, grad, lr);
+            walk_state<KB, false, NORM, false, UPD, HALF, turns>(lut, spread, LdsWords{stage}, 0u, x, wp, sm, coef, block, fields0, out, base, m, j, turn0, grad, lr);
     } else {
         // the runs of this workgroup's chunks did not fit the LDS window (more than ~4 bits per
         // symbol): read the words straight from the blob
         const GlobalWords direct{reinterpret_cast<const uint8_t *>(words) + run_byte};
         if (stream_out)
-            walk_state<KB, false, NORM, true, UPD, HALF>(lut, spread, direct, 0u, x, wp, sm, coef, block, fields0, out, base, m, j, grad, lr);
+            walk_state<KB, false, NORM, true, UPD, HALF, turns>(lut, spread, direct, 0u, x, wp, sm, coef, block, fields0, out, base, m, j, turn0, grad, lr);
         else
-            walk_state<KB, false, NORM, false, UPD, HALF>(lut, spread, direct, 0u, x, wp, sm, coef, block, fields0, out, base, m, j, grad, lr);
+            walk_state<KB, false, NORM, false, UPD, HALF, turns>(lut, spread, direct, 0u, x, wp, sm, coef, block, fields0, out, base, m, j, turn0, grad, lr);
     }
-    // a well-formed run is consumed exactly and leaves the state where the encoder started
-    if (x != kRansL || wp - wp_begin != 2 * len)
-        atomicOr(status, 1u);
+    if (x != x_end || wp - wp_begin != 2 * words_here)
+        atomicOr(a.status, 1u);
 }
 
-template <int KB, bool NORM, int MODE = kPlain>
+template <int KB, bool NORM, int MODE, bool SPLIT>
 __global__ __launch_bounds__(kDecThreads) void decode_kernel(const DecodeArgs a)
 {
     __shared__ __align__(16) uint32_t lut[kM];
     __shared__ __align__(16) uint8_t stage[kStageBytesOf<KB>];
     __shared__ uint2 spread[kSpreadEntries<KB>];
-    decode_workgroup<KB, NORM, MODE>(a.tb, a.offsets, a.states, a.lens, a.words, a.sm, a.coef, a.block, a.low, a.out,
-                                     a.grad, a.lr, a.stream_out != 0, a.n, a.n_chunks, a.status, blockIdx.x, lut, stage,
-                                     spread);
+    __shared__ __align__(16) uint32_t steps[kSteps];
+    decode_workgroup<KB, NORM, MODE, SPLIT>(a, blockIdx.x, lut, steps, stage, spread);
 }
 
 // Several tensors in one launch (a layer's weights): workgroups [t[i-1].wg_end, t[i].wg_end)
@@ -699,21 +766,69 @@ struct BatchArgs {
     uint32_t count;
 };
 
-template <int KB, bool NORM, int MODE = kPlain>
+// ENTRIES: blobs are walked from their entry points (those that have them).
+template <int KB, bool NORM, int MODE, bool ENTRIES>
 __global__ __launch_bounds__(kDecThreads) void decode_batch_kernel(const BatchArgs b)
 {
     __shared__ __align__(16) uint32_t lut[kM];
     __shared__ __align__(16) uint8_t stage[kStageBytesOf<KB>];
     __shared__ uint2 spread[kSpreadEntries<KB>];
+    __shared__ __align__(16) uint32_t steps[kSteps];
     uint32_t i = 0, first = 0;
     while (i + 1 < b.count && blockIdx.x >= b.t[i].wg_end) {
         first = b.t[i].wg_end;
         ++i;
     }
-    const DecodeArgs &a = b.t[i];
-    decode_workgroup<KB, NORM, MODE>(a.tb, a.offsets, a.states, a.lens, a.words, a.sm, a.coef, a.block, a.low, a.out,
-                                     a.grad, a.lr, a.stream_out != 0, a.n, a.n_chunks, a.status, blockIdx.x - first, lut,
-                                     stage, spread);
+    if constexpr (ENTRIES) {
+        if (b.t[i].mid_states) {
+            decode_workgroup<KB, NORM, MODE, true>(b.t[i], blockIdx.x - first, lut, steps, stage, spread);
+            return;
+        }
+    }
+    decode_workgroup<KB, NORM, MODE, false>(b.t[i], blockIdx.x - first, lut, steps, stage, spread);
+}
+
+// The entry points of an imported blob: every lane walks its state to them, writing nothing (the words come
+// straight from the blob; a run fed from a damaged container consumes at most one word per symbol and stays
+// inside the slack behind the words).
+__global__ __launch_bounds__(256) void entry_points_kernel(const DecodeArgs a, uint32_t *__restrict__ mid_states,
+                                                           uint8_t *__restrict__ mid_lens)
+{
+    __shared__ __align__(16) uint32_t lut[kM];
+    __shared__ __align__(16) uint32_t steps[kSteps];
+    for (uint32_t i = threadIdx.x; i < kSteps; i += blockDim.x)
+        steps[i] = a.tb->steps[i];
+    __syncthreads();
+    const bool lone = a.tb->lone < 256;
+    if (!lone)
+        for (uint32_t piece = threadIdx.x; piece < kM / 8; piece += blockDim.x)
+            make_piece(steps, a.tb->step_of[piece], piece, lut);
+    __syncthreads();
+    const uint32_t id = blockIdx.x * blockDim.x + threadIdx.x, c = id / kStates, j = id % kStates;
+    if (c >= a.n_chunks)
+        return;
+    const uint32_t len = a.lens[id];
+    uint32_t before = len;
+#pragma unroll
+    for (uint32_t d = 1; d < kStates; d <<= 1) {
+        const uint32_t o = __shfl_up(before, d, kStates);
+        if (j >= d)
+            before += o;
+    }
+    before -= len;
+    const uint64_t base = static_cast<uint64_t>(c) * kChunk;
+    const uint32_t m = (a.n - base) < kChunk ? static_cast<uint32_t>(a.n - base) : kChunk;
+    uint32_t x = a.states[id], wp = 0;
+    if (!lone) {
+        const GlobalWords src{reinterpret_cast<const uint8_t *>(a.words + a.offsets[c] + before)};
+        uint32_t next = src.peek(wp);
+        for (uint32_t q = 0; q < kMidTurn; ++q)
+            for (uint32_t t = 0; t < kRun; ++t)
+                if (q * kTurn + j * kRun + t < m)
+                    rans_get(lut, x, wp, next, src);
+    }
+    mid_states[id] = x;
+    mid_lens[id] = static_cast<uint8_t>(wp / 2);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -37,19 +37,40 @@ constexpr uint32_t kTurnGroupStream = 4;
 static_assert(kTurns % kTurnGroup == 0 && kTurns % kTurnGroupStream == 0, "a chunk is a whole number of turn groups");
 
 
+// Entry points.  A state is a chain of 256 dependent decoding steps, and a tensor of few chunks does not have
+// the waves to hide it: whatever its size, its decoding takes as long as the chain.  A blob of at most
+// kSplitChunks chunks therefore also holds, per state, where the chain stands before turn kMidTurn -- the
+// state (4 bytes) and the words consumed so far (1 byte) -- and two lanes walk the two halves.  It is derived
+// data, like the tables: the encoder passes that point anyway, an import walks to it, and the container does not
+// have it.  It costs 0.16 bits per element, so larger tensors, whose waves fill the chip, go without.
+// Measured (lossless, one launch per tensor): see decode_chunks_per_wg for where the line lies.
+constexpr uint32_t kMidTurn = kTurns / 2;
+constexpr uint32_t kSplitChunks = 4096;
+__host__ __device__ constexpr bool has_entry_points(uint32_t n_chunks) { return n_chunks > 0 && n_chunks <= kSplitChunks; }
+
+constexpr uint32_t kSteps = 264;  // occupied symbols of a table (at most 256) and what a search reads behind them
+
 // ------------------------------------------------------------------------------------------
 // Device-side table block that sits at the start of every blob's fixed allocation.
 // ------------------------------------------------------------------------------------------
 struct TableBlock {
     uint16_t freq[256];    // quantised frequencies (stored in the container)
     uint16_t cum[264];     // exclusive cumulative frequencies, cum[256] = 4096 (derived)
-    uint32_t counts[256];  // exponent histogram of the source tensor
     uint32_t status[4];    // [0] != 0: a decode found a malformed stream
     uint32_t lone;         // the only exponent value of the tensor (its f is 4096), else 256
-    uint32_t pad[55];
-    // decoder slot table (derived): lut[slot] = symbol | f << 8 | (slot - cum[symbol]) << 20
-    uint32_t lut[4096];
+    uint32_t pad[47];
+    // the occupied symbols in order (derived): cum << 8 | symbol; the rest of the array is 4096 << 8
+    uint32_t steps[kSteps];
+    // which of them slot 8i belongs to (derived; blobs with entry points)
+    uint8_t step_of[kM / 8];
+    // decoder slot table (derived): lut[slot] = symbol | f << 8 | (slot - cum[symbol]) << 20.  Blobs with entry
+    // points do not have it (their allocation ends before it): there every workgroup of a decoder makes it from
+    // the steps, which a tensor beyond the size of those blobs, with several rounds of workgroups, would
+    // pay several times (28672 x 8192: 145 us with the table read from the blob, 161 us without).
+    uint32_t lut[kM];
 };
+constexpr uint64_t table_bytes(bool with_lut) { return with_lut ? sizeof(TableBlock) : offsetof(TableBlock, lut); }
+static_assert(offsetof(TableBlock, lut) % 256 == 0, "either way the sections behind it stay aligned");
 static_assert(sizeof(TableBlock) % 256 == 0, "table block keeps later sections aligned");
 
 // Per-symbol encoder constants (16 bytes, one ds_read_b128), derived by every encoder workgroup from
@@ -95,6 +116,8 @@ struct CompressItem {
     uint32_t *offsets;
     uint32_t *states;
     uint8_t *lens;
+    uint32_t *mid_states;  // entry points (nullptr: the blob holds none)
+    uint8_t *mid_lens;
     uint8_t *sm;
     uint8_t *coef;
     uint16_t *low;         // binary32 tensors: the plane of lower halves

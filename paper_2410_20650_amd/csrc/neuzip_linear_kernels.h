@@ -73,6 +73,8 @@ struct LinearArgs {
     const uint32_t *offsets;
     const uint32_t *states;
     const uint8_t *lens;
+    const uint32_t *mid_states;  // entry points (nullptr: none)
+    const uint8_t *mid_lens;
     const uint16_t *words;
     const uint8_t *sm;
     const uint8_t *coef;   // block coefficients (block-wise normalised blobs only)
@@ -88,6 +90,7 @@ struct LinearArgs {
     uint32_t stride;       // chunks between neighbouring columns of a group
     uint32_t rstep;        // rows between neighbouring columns of a group
     uint32_t n_groups;
+    uint32_t split;        // 1: two lanes walk a state's two halves from the entry points
 };
 
 // Several weights applied to the same kind of input in one launch (the q, k and v projections of an
@@ -141,7 +144,7 @@ template <int KB, int COLS, int MT, bool LONE, bool NORM, class WordSrc>
 __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, const WordSrc &src, uint32_t lone,
                                             uint32_t &x, uint32_t &wp, const uint8_t *__restrict__ sm,
                                             const LinearArgs &a, uint64_t base, uint32_t kk, uint32_t turns,
-                                            uint32_t j, uint32_t lane)
+                                            uint32_t all_turns, uint32_t j, uint32_t lane)
 {
     const uint32_t in = a.in_features;
     typedef LinearTile<COLS> Tile;
@@ -178,7 +181,7 @@ __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, co
 
     // the trip count is the same for every lane of the wave (the matrix instruction needs them
     // all); a lane whose chunk is shorter or absent supplies zeros
-    for (uint32_t q = 0; q < kTurns; ++q) {
+    for (uint32_t q = 0; q < all_turns; ++q) {
         const bool mine = q < turns;
         // requests for the next turn go out before this turn is decoded
         const uint32_t kk_next = kk + kTurn == in ? 0u : kk + kTurn;
@@ -223,7 +226,7 @@ __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, co
         // end of a row of the weight (or of the chunk): this wave's partial sums leave for y.
         // (Summing the waves of a group in LDS first was tried: the barriers and the extra
         // registers cost more than the atomics they save.)
-        if (kk_next == 0 || q + 1 == kTurns) {
+        if (kk_next == 0 || q + 1 == all_turns) {
             const bool col_live = mine && row < a.out_features;
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
@@ -247,46 +250,62 @@ __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, co
 
 template <int KB, int COLS, int MT, bool NORM>
 __device__ __forceinline__ void linear_workgroup(const LinearArgs &a, uint32_t wg, uint32_t *__restrict__ lut,
-                                                 uint8_t *__restrict__ stage)
+                                                 uint32_t *__restrict__ steps, uint8_t *__restrict__ stage)
 {
     constexpr uint32_t kLinGroupChunks = COLS;                       // columns of the B operand
-    constexpr uint32_t kGroupsPerWg = kDecChunksPerWg / COLS;        // 2 or 1
-    constexpr uint32_t kWavesPerGroup = kLinThreads / 64 / kGroupsPerWg;  // 4 or 8
     constexpr uint32_t kPerWave = 64 / COLS;                         // states of a chunk per wave: 4 or 2
-    constexpr uint32_t kLinGroupBytes = kStageBytes / kGroupsPerWg;  // LDS window of one group's word runs
-    constexpr uint32_t kColsPerWave = COLS / kWavesPerGroup;         // columns a wave copies: 4
+    const uint32_t split = COLS == 16 ? a.split : 0u;                // two waves for the halves of a wave's states
+    const uint32_t waves_per_group = (kStates / kPerWave) << split;  // 4 (8 with entry points), or 8
+    const uint32_t groups_per_wg = kLinThreads / 64 / waves_per_group;
+    const uint32_t group_window = kStageBytes / groups_per_wg;       // LDS window of one group's word runs
+    const uint32_t cols_per_wave = COLS / waves_per_group;           // columns a wave copies
     const uint32_t tid = threadIdx.x;
     const uint32_t wave = tid >> 6, lane = tid & 63u;
-    const uint32_t g = wave / kWavesPerGroup, sq = wave % kWavesPerGroup;
+    const uint32_t g = wave / waves_per_group, in_group = wave % waves_per_group;
+    const uint32_t part = split ? in_group & 1u : 0u;                // before (0) or behind (1) the entry points
     const uint32_t col = lane & (COLS - 1);
-    const uint32_t j = sq * kPerWave + lane / COLS;
-    const uint32_t group = wg * kGroupsPerWg + g;
+    const uint32_t j = (in_group >> split) * kPerWave + lane / COLS;
+    const uint32_t group = wg * groups_per_wg + g;
     const bool group_live = group < a.n_groups;
     // group -> its COLS chunks: `stride` groups interleave inside a block of COLS * stride chunks
     const uint32_t block_id = group / a.stride, first_in_block = group % a.stride;
     const uint64_t c64 = static_cast<uint64_t>(block_id) * kLinGroupChunks * a.stride + first_in_block +
                          static_cast<uint64_t>(a.stride) * col;
     const bool live = group_live && c64 < a.n_chunks;
+    const uint32_t turn0 = part * kMidTurn, all_turns = split ? kMidTurn : kTurns;
     const uint32_t kk0 = static_cast<uint32_t>(
-        (static_cast<uint64_t>(block_id) * kLinGroupChunks * a.stride + first_in_block) * kChunk % a.in_features);
+        ((static_cast<uint64_t>(block_id) * kLinGroupChunks * a.stride + first_in_block) * kChunk + turn0 * kTurn) % a.in_features);
     const uint32_t c = live ? static_cast<uint32_t>(c64) : 0u;
     const uint64_t base = static_cast<uint64_t>(c) * kChunk;
     const uint32_t m = !live ? 0u : ((a.n - base) < kChunk ? static_cast<uint32_t>(a.n - base) : kChunk);
-    const uint32_t turns = m / kTurn;   // in_features is a multiple of 128, so chunks hold whole turns
+    // in_features is a multiple of 128, so chunks hold whole turns; this lane's share of them
+    const uint32_t upto = m / kTurn < turn0 + all_turns ? m / kTurn : turn0 + all_turns;
+    const uint32_t turns = upto > turn0 ? upto - turn0 : 0u;
 
     // ---- loads that depend on nothing
     const uint32_t off_c = live ? a.offsets[c] : 0u;
     const uint32_t off_c1 = live ? a.offsets[c + 1] : 0u;
     uint32_t x = live ? a.states[c * kStates + j] : kRansL;
+    const uint32_t mid_x = live && split ? a.mid_states[c * kStates + j] : kRansL;
+    const uint32_t mid_len = live && split ? a.mid_lens[c * kStates + j] : 0u;
     uint4 lens16 = make_uint4(0, 0, 0, 0);
     if (live)
         lens16 = *reinterpret_cast<const uint4 *>(a.lens + static_cast<uint64_t>(c) * kStates);
     const uint32_t lone = a.tb->lone;
-    const uint4 *lut_g = reinterpret_cast<const uint4 *>(a.tb->lut);
-    uint4 lut_piece[2];
+    // the tensor's table: its steps (blobs with entry points) or the slot table itself
+    const bool make_lut = a.mid_states != nullptr;
+    static_assert(kLinThreads == kM / 8, "one piece of the slot table per thread");
+    const uint32_t first_step = make_lut ? a.tb->step_of[tid] : 0u;
+    uint4 table_piece[2];
 #pragma unroll
-    for (uint32_t r = 0; r < 2; ++r)
-        lut_piece[r] = lut_g[tid + r * kLinThreads];
+    for (uint32_t r = 0; r < 2; ++r) {
+        const uint32_t i = tid + r * kLinThreads;
+        table_piece[r] = make_uint4(0, 0, 0, 0);
+        if (!make_lut)
+            table_piece[r] = reinterpret_cast<const uint4 *>(a.tb->lut)[i];
+        else if (i < kSteps / 4)
+            table_piece[r] = reinterpret_cast<const uint4 *>(a.tb->steps)[i];
+    }
 
     // ---- stage the word runs of the group's chunks: each chunk's piece of the blob, from the
     // 16-byte boundary below its first word, one after the other in the group's window
@@ -302,12 +321,11 @@ __device__ __forceinline__ void linear_workgroup(const LinearArgs &a, uint32_t w
     }
     const uint32_t group_bytes = __shfl(place, COLS - 1, COLS);
     place -= piece;
-    const bool staged = group_bytes + 16 <= kLinGroupBytes;
-    uint8_t *window = stage + g * kLinGroupBytes;
+    const bool staged = group_bytes + 16 <= group_window;
+    uint8_t *window = stage + g * group_window;
     if (staged && group_live) {
-#pragma unroll
-        for (uint32_t r = 0; r < kColsPerWave; ++r) {
-            const uint32_t from_col = sq * kColsPerWave + r;  // wave sq copies 4 columns
+        for (uint32_t r = 0; r < cols_per_wave; ++r) {
+            const uint32_t from_col = in_group * cols_per_wave + r;
             const uint32_t lo = __shfl(static_cast<uint32_t>(aligned0), from_col, 64);
             const uint32_t hi = __shfl(static_cast<uint32_t>(aligned0 >> 32), from_col, 64);
             const uint32_t len = __shfl(piece, from_col, 64);
@@ -319,9 +337,17 @@ __device__ __forceinline__ void linear_workgroup(const LinearArgs &a, uint32_t w
                 to[i] = from[i];
         }
     }
+    if (make_lut) {
+        if (tid < kSteps / 4)
+            reinterpret_cast<uint4 *>(steps)[tid] = table_piece[0];
+        __syncthreads();
+        if (lone >= 256)
+            make_piece(steps, first_step, tid, lut);
+    } else {
 #pragma unroll
-    for (uint32_t r = 0; r < 2; ++r)
-        reinterpret_cast<uint4 *>(lut)[tid + r * kLinThreads] = lut_piece[r];
+        for (uint32_t r = 0; r < 2; ++r)
+            reinterpret_cast<uint4 *>(lut)[tid + r * kLinThreads] = table_piece[r];
+    }
     __syncthreads();
     if (!group_live)
         return;  // the whole wave leaves together
@@ -335,41 +361,44 @@ __device__ __forceinline__ void linear_workgroup(const LinearArgs &a, uint32_t w
         before += s < j ? l8 : 0u;
         len = s == j ? l8 : len;
     }
+    // the half before the entry point ends there, the other one where the encoder started
+    const uint32_t x_end = split && !part ? mid_x : kRansL;
+    const uint32_t words_here = !split ? len : (part ? len - mid_len : mid_len);
+    if (part) {
+        x = mid_x;
+        before += mid_len;
+    }
     const uint64_t run_byte = (static_cast<uint64_t>(off_c) + before) * 2;
+    const uint64_t from_elem = base + turn0 * kTurn;
 
     uint32_t wp = 0, wp_begin = 0;
     if (lone < 256) {
-        linear_walk<KB, COLS, MT, true, NORM>(lut, NoWords{}, lone, x, wp, a.sm, a, base, kk0, turns, j, lane);
+        linear_walk<KB, COLS, MT, true, NORM>(lut, NoWords{}, lone, x, wp, a.sm, a, from_elem, kk0, turns, all_turns, j, lane);
     } else if (staged) {
-        wp = wp_begin = g * kLinGroupBytes + place + static_cast<uint32_t>(run_byte - aligned0);
-        linear_walk<KB, COLS, MT, false, NORM>(lut, LdsWords{stage}, 0u, x, wp, a.sm, a, base, kk0, turns, j, lane);
+        wp = wp_begin = g * group_window + place + static_cast<uint32_t>(run_byte - aligned0);
+        linear_walk<KB, COLS, MT, false, NORM>(lut, LdsWords{stage}, 0u, x, wp, a.sm, a, from_elem, kk0, turns, all_turns, j, lane);
     } else {
         const GlobalWords direct{reinterpret_cast<const uint8_t *>(a.words) + run_byte};
-        linear_walk<KB, COLS, MT, false, NORM>(lut, direct, 0u, x, wp, a.sm, a, base, kk0, turns, j, lane);
+        linear_walk<KB, COLS, MT, false, NORM>(lut, direct, 0u, x, wp, a.sm, a, from_elem, kk0, turns, all_turns, j, lane);
     }
-    if (live && (x != kRansL || wp - wp_begin != 2 * len))
+    if (live && (x != x_end || wp - wp_begin != 2 * words_here))
         atomicOr(a.status, 1u);
 }
 
+// (Two workgroups of 8 waves share a CU if a lane has at most 128 registers; with the 138 the compiler took
+// for 64 tokens it held one.)
 template <int KB, int COLS, int MT, bool NORM = false>
-__global__ __launch_bounds__(kLinThreads) void linear_kernel(const LinearArgs a)
+__global__ __launch_bounds__(kLinThreads, COLS == 32 && MT == 2 ? 2 : 4) void linear_batch_kernel(const LinearBatchArgs b)
 {
     __shared__ __align__(16) uint32_t lut[kM];
     __shared__ __align__(16) uint8_t stage[kStageBytes];
-    linear_workgroup<KB, COLS, MT, NORM>(a, blockIdx.x, lut, stage);
-}
-
-template <int KB, int COLS, int MT, bool NORM = false>
-__global__ __launch_bounds__(kLinThreads) void linear_batch_kernel(const LinearBatchArgs b)
-{
-    __shared__ __align__(16) uint32_t lut[kM];
-    __shared__ __align__(16) uint8_t stage[kStageBytes];
+    __shared__ __align__(16) uint32_t steps[kSteps];
     uint32_t i = 0, first = 0;
     while (i + 1 < b.count && blockIdx.x >= b.wg_end[i]) {
         first = b.wg_end[i];
         ++i;
     }
-    linear_workgroup<KB, COLS, MT, NORM>(b.t[i], blockIdx.x - first, lut, stage);
+    linear_workgroup<KB, COLS, MT, NORM>(b.t[i], blockIdx.x - first, lut, steps, stage);
 }
 
 }  // namespace nz

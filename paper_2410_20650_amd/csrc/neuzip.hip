@@ -520,11 +520,16 @@ int launch_batch(const BatchArgs &args, int variant, uint32_t groups, hipStream_
 }
 
 // Which form of the kernel: 16 columns (tiles of 16 tokens) or 32 columns (tiles of 32 tokens).
-// The wide form halves the activation traffic per token but doubles the waves that add partial
-// sums to one output, so it pays for more than 16 tokens on shapes whose chunks never straddle
-// rows of the weight (stride 1: no row ends inside a chunk); measured on 14336 x 4096 and
-// 4096 x 14336.
-inline uint32_t linear_columns(uint32_t tokens, uint32_t stride) { return tokens > 16 && stride == 1 ? 32u : 16u; }
+// The wide form halves the activation traffic per token but has twice the sums per wave, and every row
+// that ends inside a chunk sends them to y one by one.  It pays for more than 16 tokens where at most every
+// second chunk has such an end (64 tokens: 4096 x 14336 73 against 88 us, 9000 x 5120 100 against 91), or none
+// (in_features a divisor or a multiple of the chunk).  Weights walked from their entry points have the
+// 16-column form only.
+inline uint32_t linear_columns(uint32_t tokens, uint64_t in_features, bool entries)
+{
+    const bool few_ends = in_features >= 2 * kChunk || kChunk % in_features == 0;
+    return tokens > 16 && few_ends && !entries ? 32u : 16u;
+}
 
 template <int KB, bool NORM>
 void launch_linear(const LinearBatchArgs &batch, uint32_t cols, uint32_t wgs, hipStream_t stream)
@@ -1377,6 +1382,8 @@ int neuzip_linear_batch(const neuzip_blob *const *weights, const uint64_t *out_f
             ++a.block_shift;
         a.stride = static_cast<uint32_t>(in_features / gcd);
         a.rstep = static_cast<uint32_t>(kChunk / gcd);
+        a.whole_rows = in_features == kChunk ? 1u : 0u;
+        a.bias = d_bias ? d_bias[i] : nullptr;
         const uint64_t cells = static_cast<uint64_t>(tokens) * out_features[i];
         init.y[i] = d_y[i];
         init.bias[i] = d_bias ? d_bias[i] : nullptr;
@@ -1384,7 +1391,10 @@ int neuzip_linear_batch(const neuzip_blob *const *weights, const uint64_t *out_f
         init_wgs += static_cast<uint32_t>((cells + 255) / 256);
         init.wg_end[i] = init_wgs;
     }
-    if (count == 1)
+    // (a chunk that is a whole row: its sum is complete in one workgroup, which stores it)
+    if (in_features == kChunk)
+        ;
+    else if (count == 1)
         hipLaunchKernelGGL(linear_init_kernel, dim3(init_wgs), dim3(256), 0, stream, init.y[0], init.bias[0], tokens,
                            init.out_features[0]);
     else
@@ -1394,7 +1404,11 @@ int neuzip_linear_batch(const neuzip_blob *const *weights, const uint64_t *out_f
     const neuzip_blob *first = weights[0];
     for (uint32_t t0 = 0; t0 < tokens; t0 += kLinMaxTokens) {
         const uint32_t tile = tokens - t0 < kLinMaxTokens ? tokens - t0 : kLinMaxTokens;
-        const uint32_t cols = linear_columns(tile, batch.t[0].stride);  // chunks per group = columns of the matrix instruction
+        // chunks per group = columns of the matrix instruction
+        bool entries = false;
+        for (uint32_t i = 0; i < count; ++i)
+            entries = entries || batch.t[i].mid_states;
+        const uint32_t cols = linear_columns(tile, in_features, entries);
         uint32_t wgs = 0;
         for (uint32_t i = 0; i < count; ++i) {
             LinearArgs &a = batch.t[i];
@@ -1403,7 +1417,6 @@ int neuzip_linear_batch(const neuzip_blob *const *weights, const uint64_t *out_f
             a.y = d_y[i] + static_cast<uint64_t>(t0) * out_features[i];
             const uint64_t per_block = static_cast<uint64_t>(cols) * a.stride;
             a.n_groups = static_cast<uint32_t>((weights[i]->n_chunks + per_block - 1) / per_block * a.stride);
-            // (the 32-column form walks whole states: its accumulators leave no room for twice the waves)
             a.split = cols == 16 && a.mid_states ? 1u : 0u;
             const uint32_t groups_per_wg = (kDecChunksPerWg / cols) >> a.split;
             wgs += (a.n_groups + groups_per_wg - 1) / groups_per_wg;

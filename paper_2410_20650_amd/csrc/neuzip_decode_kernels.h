@@ -624,8 +624,9 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
 #pragma unroll
     for (uint32_t r = 0; r < kPreload; ++r)
         fields0[r] = !WIDE && m == kChunk ? load_turn<KB, NORM>(sm, coef, block, base + (turn0 + r) * kTurn + j * kRun) : 0;
-    // ---- the word runs of chunks [c0, c1), one contiguous piece of the blob, into LDS.  (Where the slot table has to
-    // be made, the first pieces stay in registers meanwhile.)
+    // ---- the word runs of chunks [c0, c1), one contiguous piece of the blob, into LDS: the first
+    // three per thread are requested together and stay in registers while the table is copied or made (six, all of
+    // a usual workgroup's, were 0.5 % slower)
     const uint64_t byte0 = static_cast<uint64_t>(off0) * 2;
     const uint64_t byte1 = static_cast<uint64_t>(off1) * 2;
     const uint64_t aligned0 = byte0 & ~static_cast<uint64_t>(15);
@@ -647,8 +648,8 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
                 spread[i] = spread_entry<KB>(i);
         }
     };
-    if (make_lut) {
-        constexpr uint32_t kFirst = 4;
+    {
+        constexpr uint32_t kFirst = 3;
         uint4 first[kFirst];
 #pragma unroll
         for (uint32_t r = 0; r < kFirst; ++r) {
@@ -656,11 +657,13 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
             first[r] = staged && static_cast<uint64_t>(i) * 16 < stage_len ? from[i] : make_uint4(0, 0, 0, 0);
         }
         table_to_lds();
-        __syncthreads();
-        if (lone >= 256) {
-            make_piece(steps, first_step, tid, lut);
-            for (uint32_t piece = tid + threads; piece < kM / 8; piece += threads)  // (small workgroups)
-                make_piece(steps, a.tb->step_of[piece], piece, lut);
+        if (make_lut) {
+            __syncthreads();
+            if (lone >= 256) {
+                make_piece(steps, first_step, tid, lut);
+                for (uint32_t piece = tid + threads; piece < kM / 8; piece += threads)  // (small workgroups)
+                    make_piece(steps, a.tb->step_of[piece], piece, lut);
+            }
         }
         if (staged) {
 #pragma unroll
@@ -672,11 +675,6 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
             for (uint32_t i = tid + kFirst * threads; static_cast<uint64_t>(i) * 16 < stage_len; i += threads)
                 to[i] = from[i];
         }
-    } else {
-        if (staged)
-            for (uint32_t i = tid; static_cast<uint64_t>(i) * 16 < stage_len; i += threads)
-                to[i] = from[i];
-        table_to_lds();
     }
     __syncthreads();
 

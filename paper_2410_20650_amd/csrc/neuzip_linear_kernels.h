@@ -67,6 +67,9 @@ struct LinearTile<32> {
 
 constexpr uint32_t kLinThreads = 512;
 constexpr uint32_t kLinMaxTokens = 64;
+// Up to here the waves of a group add their sums to y by themselves (where they are not complete in the
+// workgroup): 4096 x 14336, 1 token, 35.6 us, with the sums added up in LDS first 37.6; 16 tokens 42.8 and 39.1.
+constexpr uint32_t kLinDirectTokens = 8;
 
 struct LinearArgs {
     const TableBlock *tb;
@@ -91,6 +94,8 @@ struct LinearArgs {
     uint32_t rstep;        // rows between neighbouring columns of a group
     uint32_t n_groups;
     uint32_t split;        // 1: two lanes walk a state's two halves from the entry points
+    uint32_t whole_rows;   // a chunk is a row of the weight: sums are complete in the workgroup
+    const float *bias;     // whole_rows: added to the sums here (nullptr: none); otherwise y holds it on entry
 };
 
 // Several weights applied to the same kind of input in one launch (the q, k and v projections of an
@@ -140,13 +145,16 @@ __device__ __forceinline__ void atomic_add_f32(float *p, float v)
 
 // NORM: the blob is block-wise normalised (Sec. 2.3): the merged words are multiplied by their block's
 // coefficient, as in the decoder, before they enter the matrix instruction.
+// The partial sums of the last row that the walk touched stay in acc, that row in `row`.
 template <int KB, int COLS, int MT, bool LONE, bool NORM, class WordSrc>
 __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, const WordSrc &src, uint32_t lone,
                                             uint32_t &x, uint32_t &wp, const uint8_t *__restrict__ sm,
                                             const LinearArgs &a, uint64_t base, uint32_t kk, uint32_t turns,
-                                            uint32_t all_turns, uint32_t j, uint32_t lane)
+                                            uint32_t all_turns, uint32_t j, uint32_t lane,
+                                            typename LinearTile<COLS>::acc_t (&acc)[MT], uint32_t &row)
 {
-    const uint32_t in = a.in_features;
+    const uint32_t in = a.in_features, out_features = a.out_features, tokens = a.tokens;
+    float *__restrict__ y = a.y;
     typedef LinearTile<COLS> Tile;
     constexpr uint32_t kPerWave = 64 / COLS;         // states of a chunk held by one wave (4 or 2)
     const uint32_t col = lane & (COLS - 1);          // column of B and of D: this lane's chunk
@@ -155,7 +163,7 @@ __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, co
     // Position in the matrix: the row is the lane's own (its chunk's); the input-feature offset kk
     // is that of the group's first chunk, which all 16 chunks share -- lanes without a chunk use
     // it too, because every lane supplies activations to A.
-    uint32_t row = static_cast<uint32_t>(base / in);
+    row = static_cast<uint32_t>(base / in);
     // rows of the activations this lane supplies to A (clamped: rows past `tokens` are never stored)
     const uint16_t *xrow[MT];
 #pragma unroll
@@ -164,13 +172,6 @@ __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, co
         t = t < a.tokens ? t : a.tokens - 1;
         xrow[mt] = a.x + static_cast<uint64_t>(t) * in + ksq + kq;
     }
-    typename Tile::acc_t acc[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int r = 0; r < Tile::kRegs; ++r)
-            acc[mt][r] = 0.0f;
-
     uint32_t next = LONE ? 0u : src.peek(wp);
     const uint64_t first = base + j * kRun;
     uint64_t fields = turns > 0 ? load_turn<KB, NORM>(sm, a.coef, a.block_shift, first) : 0;
@@ -223,22 +224,27 @@ __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, co
             av.q4 = xa[mt];
             acc[mt] = Tile::mma(av.v, b.v, acc[mt]);
         }
-        // end of a row of the weight (or of the chunk): this wave's partial sums leave for y.
-        // (Summing the waves of a group in LDS first was tried: the barriers and the extra
-        // registers cost more than the atomics they save.)
-        if (kk_next == 0 || q + 1 == all_turns) {
-            const bool col_live = mine && row < a.out_features;
+        // end of a row of the weight inside the walk: this wave's partial sums leave for y
+        if (kk_next == 0 && q + 1 < all_turns) {
+            const bool col_live = mine && row < out_features;
+            // (one running offset: the compiler would hold an address per register of the tile otherwise, and
+            // with them a second workgroup's worth of registers)
+            uint64_t at = static_cast<uint64_t>(Tile::row(lane, 0)) * out_features + row;
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
                 for (int r = 0; r < Tile::kRegs; ++r) {
                     const uint32_t t = mt * COLS + Tile::row(lane, r);
-                    if (col_live && t < a.tokens)
-                        atomic_add_f32(a.y + static_cast<uint64_t>(t) * a.out_features + row, acc[mt][r]);
+                    if (col_live && t < tokens)
+                        atomic_add_f32(y + at, acc[mt][r]);
                     acc[mt][r] = 0.0f;
+                    const int beyond = r + 1 < Tile::kRegs ? static_cast<int>(Tile::row(0, r + 1) - Tile::row(0, r))
+                                                           : COLS - static_cast<int>(Tile::row(0, r));
+                    at += static_cast<uint64_t>(beyond) * out_features;
+                    asm volatile("" : "+v"(at));
                 }
             }
-            row += kk_next == 0 ? 1u : 0u;
+            ++row;
         }
         kk = kk_next;
         fields = fields_next;
@@ -260,7 +266,9 @@ __device__ __forceinline__ void linear_workgroup(const LinearArgs &a, uint32_t w
     const uint32_t group_window = kStageBytes / groups_per_wg;       // LDS window of one group's word runs
     const uint32_t cols_per_wave = COLS / waves_per_group;           // columns a wave copies
     const uint32_t tid = threadIdx.x;
-    const uint32_t wave = tid >> 6, lane = tid & 63u;
+    // (the same for all lanes, and told so: what follows from it stays in scalar registers)
+    const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(tid >> 6)));
+    const uint32_t lane = tid & 63u;
     const uint32_t g = wave / waves_per_group, in_group = wave % waves_per_group;
     const uint32_t part = split ? in_group & 1u : 0u;                // before (0) or behind (1) the entry points
     const uint32_t col = lane & (COLS - 1);
@@ -323,18 +331,32 @@ __device__ __forceinline__ void linear_workgroup(const LinearArgs &a, uint32_t w
     place -= piece;
     const bool staged = group_bytes + 16 <= group_window;
     uint8_t *window = stage + g * group_window;
-    if (staged && group_live) {
-        for (uint32_t r = 0; r < cols_per_wave; ++r) {
-            const uint32_t from_col = in_group * cols_per_wave + r;
-            const uint32_t lo = __shfl(static_cast<uint32_t>(aligned0), from_col, 64);
-            const uint32_t hi = __shfl(static_cast<uint32_t>(aligned0 >> 32), from_col, 64);
-            const uint32_t len = __shfl(piece, from_col, 64);
-            const uint32_t at = __shfl(place, from_col, 64);
-            const uint4 *from = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint8_t *>(a.words) +
-                                                                ((static_cast<uint64_t>(hi) << 32) | lo));
-            uint4 *to = reinterpret_cast<uint4 *>(window + at);
-            for (uint32_t i = lane; i * 16 < len; i += 64)
-                to[i] = from[i];
+    // A wave copies kMostCols columns (or half as many, with entry points).  The first 2 KB of each, usually all of
+    // it, are requested together: column after column the copies were a chain of eight memory latencies, a sixth
+    // of the kernel's time.
+    constexpr uint32_t kMostCols = COLS / (kStates / kPerWave), kFirst = 2;
+    uint4 pieces[kMostCols][kFirst];
+    auto of_column = [&](uint32_t v, uint32_t r) {
+        return static_cast<uint32_t>(
+            __builtin_amdgcn_readlane(static_cast<int>(v), static_cast<int>((in_group * cols_per_wave + r) & 63u)));
+    };
+    auto column = [&](uint32_t r, const uint4 *&from, uint4 *&to, uint32_t &len) {
+        const uint64_t at = of_column(static_cast<uint32_t>(aligned0), r) |
+                            (static_cast<uint64_t>(of_column(static_cast<uint32_t>(aligned0 >> 32), r)) << 32);
+        len = staged && group_live && r < cols_per_wave ? of_column(piece, r) : 0u;
+        from = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint8_t *>(a.words) + at);
+        to = reinterpret_cast<uint4 *>(window + of_column(place, r));
+    };
+#pragma unroll
+    for (uint32_t r = 0; r < kMostCols; ++r) {
+        const uint4 *from;
+        uint4 *to;
+        uint32_t len;
+        column(r, from, to, len);
+#pragma unroll
+        for (uint32_t h = 0; h < kFirst; ++h) {
+            const uint32_t i = lane + 64 * h;
+            pieces[r][h] = i * 16 < len ? from[i] : make_uint4(0, 0, 0, 0);
         }
     }
     if (make_lut) {
@@ -348,10 +370,22 @@ __device__ __forceinline__ void linear_workgroup(const LinearArgs &a, uint32_t w
         for (uint32_t r = 0; r < 2; ++r)
             reinterpret_cast<uint4 *>(lut)[tid + r * kLinThreads] = table_piece[r];
     }
+#pragma unroll
+    for (uint32_t r = 0; r < kMostCols; ++r) {
+        const uint4 *from;
+        uint4 *to;
+        uint32_t len;
+        column(r, from, to, len);
+#pragma unroll
+        for (uint32_t h = 0; h < kFirst; ++h) {
+            const uint32_t i = lane + 64 * h;
+            if (i * 16 < len)
+                to[i] = pieces[r][h];
+        }
+        for (uint32_t i = lane + 64 * kFirst; i * 16 < len; i += 64)
+            to[i] = from[i];
+    }
     __syncthreads();
-    if (!group_live)
-        return;  // the whole wave leaves together
-
     // ---- start of this state's run: the chunk's offset plus the lengths of the states before it
     const uint32_t lw[4] = {lens16.x, lens16.y, lens16.z, lens16.w};
     uint32_t before = 0, len = 0;
@@ -371,24 +405,78 @@ __device__ __forceinline__ void linear_workgroup(const LinearArgs &a, uint32_t w
     const uint64_t run_byte = (static_cast<uint64_t>(off_c) + before) * 2;
     const uint64_t from_elem = base + turn0 * kTurn;
 
-    uint32_t wp = 0, wp_begin = 0;
-    if (lone < 256) {
-        linear_walk<KB, COLS, MT, true, NORM>(lut, NoWords{}, lone, x, wp, a.sm, a, from_elem, kk0, turns, all_turns, j, lane);
-    } else if (staged) {
-        wp = wp_begin = g * group_window + place + static_cast<uint32_t>(run_byte - aligned0);
-        linear_walk<KB, COLS, MT, false, NORM>(lut, LdsWords{stage}, 0u, x, wp, a.sm, a, from_elem, kk0, turns, all_turns, j, lane);
-    } else {
-        const GlobalWords direct{reinterpret_cast<const uint8_t *>(a.words) + run_byte};
-        linear_walk<KB, COLS, MT, false, NORM>(lut, direct, 0u, x, wp, a.sm, a, from_elem, kk0, turns, all_turns, j, lane);
+    typedef LinearTile<COLS> Tile;
+    typename Tile::acc_t acc[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int r = 0; r < Tile::kRegs; ++r)
+            acc[mt][r] = 0.0f;
+    uint32_t row = 0;
+    if (group_live) {
+        uint32_t wp = 0, wp_begin = 0;
+        if (lone < 256) {
+            linear_walk<KB, COLS, MT, true, NORM>(lut, NoWords{}, lone, x, wp, a.sm, a, from_elem, kk0, turns, all_turns, j,
+                                                  lane, acc, row);
+        } else if (staged) {
+            wp = wp_begin = g * group_window + place + static_cast<uint32_t>(run_byte - aligned0);
+            linear_walk<KB, COLS, MT, false, NORM>(lut, LdsWords{stage}, 0u, x, wp, a.sm, a, from_elem, kk0, turns, all_turns,
+                                                   j, lane, acc, row);
+        } else {
+            const GlobalWords direct{reinterpret_cast<const uint8_t *>(a.words) + run_byte};
+            linear_walk<KB, COLS, MT, false, NORM>(lut, direct, 0u, x, wp, a.sm, a, from_elem, kk0, turns, all_turns, j, lane,
+                                                   acc, row);
+        }
+        if (live && (x != x_end || wp - wp_begin != 2 * words_here))
+            atomicOr(a.status, 1u);
     }
-    if (live && (x != x_end || wp - wp_begin != 2 * words_here))
-        atomicOr(a.status, 1u);
+
+    // ---- the waves that hold partial sums of the same row (those of the group, or of its half when a chunk is not
+    // a whole row) add them up in LDS, tile of tokens by tile of tokens, one sum per thread; then they are complete
+    // and go to y with the bias, or leave by one atomic per sum instead of one per wave
+    constexpr uint32_t kSums = Tile::kRegs * 64;                // of one tile
+    const uint32_t half = split && !a.whole_rows ? part : 0u;   // waves of the two halves end in different rows
+    const uint32_t sharing = split && !a.whole_rows ? waves_per_group / 2 : waves_per_group;
+    const uint32_t place_in = split && !a.whole_rows ? in_group >> 1 : in_group;
+    const uint32_t set = split && !a.whole_rows ? g * 2 + half : g;
+    static_assert(kLinThreads / 64 * kSums * sizeof(float) <= kStageBytes, "the sums of a tile take the words' place");
+    float *sums = reinterpret_cast<float *>(stage) + set * sharing * kSums;
+    const uint32_t chunk_turns = m / kTurn;
+    const bool row_live = live && chunk_turns > turn0 && row < a.out_features;
+    if (MT == 1 && !a.whole_rows && !split && a.tokens <= kLinDirectTokens) {
+#pragma unroll
+        for (int r = 0; r < Tile::kRegs; ++r)
+            if (row_live && Tile::row(lane, r) < a.tokens)
+                atomic_add_f32(a.y + static_cast<uint64_t>(Tile::row(lane, r)) * a.out_features + row, acc[0][r]);
+        return;
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < Tile::kRegs; ++r)
+            sums[place_in * kSums + r * 64 + lane] = acc[mt][r];
+        __syncthreads();
+        for (uint32_t r = place_in; r < Tile::kRegs; r += sharing) {
+            float total = 0.0f;
+            for (uint32_t w = 0; w < sharing; ++w)
+                total += sums[w * kSums + r * 64 + lane];
+            const uint32_t t = mt * COLS + Tile::row(lane, static_cast<int>(r));
+            if (row_live && t < a.tokens) {
+                float *at = a.y + static_cast<uint64_t>(t) * a.out_features + row;
+                if (a.whole_rows)
+                    *at = total + (a.bias ? a.bias[row] : 0.0f);
+                else
+                    atomic_add_f32(at, total);
+            }
+        }
+    }
 }
 
 // (Two workgroups of 8 waves share a CU if a lane has at most 128 registers; with the 138 the compiler took
 // for 64 tokens it held one.)
 template <int KB, int COLS, int MT, bool NORM = false>
-__global__ __launch_bounds__(kLinThreads, COLS == 32 && MT == 2 ? 2 : 4) void linear_batch_kernel(const LinearBatchArgs b)
+__global__ __launch_bounds__(kLinThreads, 4) void linear_batch_kernel(const LinearBatchArgs b)
 {
     __shared__ __align__(16) uint32_t lut[kM];
     __shared__ __align__(16) uint8_t stage[kStageBytes];

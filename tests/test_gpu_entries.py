@@ -1,0 +1,102 @@
+"""GPU parity of what entry points and the linear layer's forms choose between (-m gpu): blobs on both sides of
+the size up to which states are walked in two halves, imported ones (whose entry points a kernel finds), batches
+beyond the cache, and the linear layer with rows that are, hold, or straddle chunks, for every tile of tokens.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2410_20650_amd import inputs
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+LINE = 4096 * 4096   # elements of the largest blob with entry points
+
+
+@pytest.fixture(scope="module")
+def nz():
+    from paper_2410_20650_amd import binding
+    return binding
+
+
+def decoded(nz, blob, like):
+    out = torch.full_like(like, float("nan"))
+    nz.neuzip_decompress(blob, out)
+    nz.neuzip_check(blob)
+    return out
+
+
+@pytest.mark.parametrize("n", [2048, 2049, 4096 + 2048, 17 * 4096 + 2047, LINE, LINE + 1])
+def test_both_sides_of_the_line_compressed_recompressed_and_imported(nz, n):
+    w = inputs.gaussian_bf16(n, 900 + n % 1000, device=DEV)
+    blob = nz.neuzip_compress(w, 7)
+    container = nz.neuzip_export(blob)
+    assert np.array_equal(container, O.compress(inputs.bits(w), 7, threads=8))
+    assert torch.equal(decoded(nz, blob, w).view(torch.int16), w.view(torch.int16))
+    assert torch.equal(decoded(nz, nz.neuzip_import(container), w).view(torch.int16), w.view(torch.int16))
+    (kept,) = nz.neuzip_compress_guarded([w], 7, 8)
+    v = inputs.synthetic_update(w, 901)
+    nz.neuzip_recompress([v], [kept])
+    assert torch.equal(decoded(nz, kept, v).view(torch.int16), v.view(torch.int16))
+    if n > LINE:
+        assert blob.device_bytes < 1.01 * blob.compressed_bytes + 32768      # no entry points, one slot table
+    else:
+        assert blob.device_bytes < 1.025 * blob.compressed_bytes + 8192      # 0.16 bits per element of entry points
+
+
+def test_symbols_with_gaps_and_a_full_table(nz):
+    # the slot table is made from the occupied symbols: all 256, two at the ends, one, one with a rare other
+    every = inputs.random_bits_bf16(60_001, 31, device=DEV)
+    ends = inputs.from_bits(np.resize(np.array([0x0003, 0x7F81, 0x7F82], np.uint16), 50_003), device=DEV)
+    alone = inputs.constant_bf16(30_000, 1.5, device=DEV)
+    rare = alone.clone()
+    rare[12_345] = 2.0 ** 100
+    for w in (every, ends, alone, rare):
+        blob = nz.neuzip_compress(w, 7)
+        assert np.array_equal(nz.neuzip_export(blob), O.compress(inputs.bits(w), 7, threads=8))
+        assert torch.equal(decoded(nz, blob, w).view(torch.int16), w.view(torch.int16))
+        (kept,) = nz.neuzip_compress_guarded([w], 7, 8)   # the band adds symbols that do not occur
+        assert torch.equal(decoded(nz, kept, w).view(torch.int16), w.view(torch.int16))
+
+
+def test_a_batch_beyond_the_cache_walks_small_tensors_whole(nz):
+    ws = [inputs.gaussian_bf16(n, 910 + i, device=DEV) for i, n in enumerate((70_000_001, 1_000_003, 4097, LINE))]
+    blobs = [nz.neuzip_compress(w, 3) for w in ws]
+    outs = [torch.full_like(w, float("nan")) for w in ws]
+    nz.neuzip_decompress_batch(blobs, outs)
+    for b, o, w in zip(blobs, outs, ws):
+        nz.neuzip_check(b)
+        assert torch.equal(o.view(torch.int16), w.view(torch.int16) & ~0xF)
+
+
+@pytest.mark.parametrize("out_f, in_f", [(1, 4096), (17, 4096), (100, 4096), (4100, 4096),   # a chunk is a row
+                                         (33, 2048), (130, 128),                            # a chunk holds rows
+                                         (50, 8192), (2100, 8192),                          # a row is two chunks
+                                         (30, 5120), (3300, 5120), (14, 14336), (1200, 14336), (200, 1152)])
+def test_linear_forms(nz, out_f, in_f):
+    w = inputs.gaussian_bf16((out_f, in_f), 920 + out_f, device=DEV)
+    blob = nz.neuzip_compress(w, 7)
+    exact_w = w.double()
+    bias = torch.randn(out_f, device=DEV, dtype=torch.float32)
+    for tokens in (1, 8, 9, 16, 17, 32, 33, 48, 49, 64, 65):
+        x = inputs.gaussian_bf16((tokens, in_f), 930 + tokens, std=1.0, device=DEV)
+        y = torch.full((tokens, out_f), float("nan"), device=DEV)
+        nz.neuzip_linear(blob, out_f, in_f, x, bias, y)
+        want = x.double() @ exact_w.t() + bias.double()
+        # float32 sums in any order: 2 (terms) 2^-24 sum |w x|
+        bound = 2 * (in_f + 64) * 2.0 ** -24 * (x.double().abs() @ exact_w.abs().t() + bias.double().abs())
+        assert bool(((y.double() - want).abs() <= bound).all()), (tokens, float((y.double() - want).abs().max()))
+    nz.neuzip_check(blob)
+
+
+@pytest.mark.parametrize("tokens", [3, 20, 64])
+def test_linear_batch_of_weights_on_both_sides_of_the_line(nz, tokens):
+    in_f, outs = 4096, (40, 4100, 7)
+    ws = [inputs.gaussian_bf16((o, in_f), 940 + o, device=DEV) for o in outs]
+    blobs = [nz.neuzip_compress(w, 7) for w in ws]
+    x = inputs.gaussian_bf16((tokens, in_f), 941, std=1.0, device=DEV)
+    for y, w in zip(nz.neuzip_linear_batch(blobs, outs, in_f, x), ws):
+        want = x.double() @ w.double().t()
+        bound = 2 * (in_f + 64) * 2.0 ** -24 * (x.double().abs() @ w.double().abs().t())
+        assert bool(((y.double() - want).abs() <= bound).all())

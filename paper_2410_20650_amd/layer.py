@@ -39,8 +39,9 @@ class CompressedLinear:
         tokens = x.shape[0]
         if tokens <= 64 and self.in_features % 128 == 0:
             return nz.neuzip_linear(self.blob, self.out_features, self.in_features, x.contiguous(), self.bias)
-        y = torch.matmul(x, self.weight_into(space).t()).float()
-        return y if self.bias is None else y + self.bias
+        y = torch.matmul(x, self.weight_into(space).t())
+        # (the sum of a bf16 and a float32 tensor is float32: widening and addition in one launch)
+        return y.float() if self.bias is None else y + self.bias
 
     def backward_and_update(self, x: torch.Tensor, grad_y: torch.Tensor, lr: float, space: torch.Tensor,
                             grad_space: torch.Tensor):
@@ -54,7 +55,7 @@ class CompressedLinear:
         grad_w = grad_space.view(-1)[:n].view(self.out_features, self.in_features)
         torch.matmul(grad_y.t(), x, out=grad_w)                           # out_features x in_features, bf16
         if self.bias is not None:
-            self.bias -= lr * grad_y.float().sum(dim=0)
+            self.bias.sub_(grad_y.sum(dim=0, dtype=torch.float32), alpha=lr)
         # `space` still holds W_hat from the decompression above: the step and the coding are one pass,
         # and nobody needs the new weight uncompressed
         (rebuilt,) = nz.neuzip_update([self.blob], [grad_w.view(-1)], [space.view(-1)[:n]], lr, weights_ready=2)

@@ -320,7 +320,8 @@ void neuzip_free(neuzip_blob *blob);
 uint64_t neuzip_compressed_bytes(const neuzip_blob *blob);
 
 /* Bytes of device memory the blob actually holds (container sections plus
- * alignment padding and the derived cumulative and slot tables). */
+ * alignment padding and what the decoder derives: the cumulative table, and the slot table or, for
+ * tensors of at most 2^24 elements, an entry point half way into each state, 5 bytes per 256 elements). */
 uint64_t neuzip_device_bytes(const neuzip_blob *blob);
 
 /* Element count, mantissa bits, normalisation block size (0 = none), guard band of the table

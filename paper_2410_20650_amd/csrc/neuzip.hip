@@ -372,7 +372,10 @@ inline uint64_t words_room(const neuzip_blob *b)
 
 // Chunks per decoder workgroup.  32 (8 waves) measured best from ~16 M elements up: two such
 // workgroups fill a CU's LDS with 16 waves, and smaller workgroups lower that occupancy.  A blob with entry
-// points has two lanes per state and cannot fill the chip either way: KEEPME
+// points has two lanes per state and cannot fill the chip either way: workgroups of 8 chunks (4 waves) spread it
+// over more CUs up to 2048 chunks (4 M elements: 4 / 8 / 12 / 16 chunks 15.8 / 14.9 / 15.2 / 15.0 us; 8 M: 18.1 /
+// 15.7 / 16.3 / 15.9), from there on the slot table that every workgroup makes weighs more (16.8 M: 32.9 / 19.0 /
+// 20.4 / 18.0).
 // NEUZIP_DECODE_CHUNKS_PER_WG (4..32, multiple of 4) overrides the choice for tuning runs.
 // binary16 symbols carry 5-6 bits each (sign and two mantissa bits ride in the symbol), so only
 // 16 chunks' words fit the LDS window: such blobs never take more.

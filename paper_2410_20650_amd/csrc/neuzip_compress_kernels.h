@@ -740,21 +740,27 @@ __device__ __forceinline__ void ring_advance(EncState &st, uint32_t cur_before)
     st.wp -= (ring_position(cur_before) - ring_position(st.cur)) & (kRingWords - 1u);
 }
 
-// Moves the 8-word group completed during the last turn (at most one: a turn pushes at most 8
-// words) from the ring to the slot.  Positions run down from wp_before to wp_after; group g
-// (positions 8g .. 8g+7) is complete once position 8g has been written.
+// Moves the 8-word group g (positions 8g .. 8g+7) from the ring to the slot.
+__device__ __forceinline__ void store_group(uint32_t g, const uint8_t *__restrict__ rings, uint32_t lane_ring,
+                                            uint16_t *__restrict__ chunk_slots, uint32_t j)
+{
+    constexpr uint32_t kPair = kEncThreads * 4;
+    const uint8_t *at = rings + (lane_ring | ring_place((g * 8) & (kRingWords - 1)));
+    const uint4 v = make_uint4(*reinterpret_cast<const uint32_t *>(at), *reinterpret_cast<const uint32_t *>(at + kPair),
+                               *reinterpret_cast<const uint32_t *>(at + 2 * kPair),
+                               *reinterpret_cast<const uint32_t *>(at + 3 * kPair));
+    *reinterpret_cast<uint4 *>(chunk_slots + slot_word(j, g * 8)) = v;
+}
+
+// ... the group completed during the last turn, if there is one (at most one: a turn pushes at most 8
+// words).  Positions run down from wp_before to wp_after; a group is complete once its lowest position has been
+// written.
 __device__ __forceinline__ void ring_flush(uint32_t wp_before, uint32_t wp_after, const uint8_t *__restrict__ rings,
                                            uint32_t lane_ring, uint16_t *__restrict__ chunk_slots, uint32_t j)
 {
     const uint32_t g = (wp_after + 7) >> 3;  // lowest group whose first position is >= wp_after
-    if (g * 8 < wp_before) {
-        constexpr uint32_t kPair = kEncThreads * 4;
-        const uint8_t *at = rings + (lane_ring | ring_place((g * 8) & (kRingWords - 1)));
-        const uint4 v = make_uint4(*reinterpret_cast<const uint32_t *>(at), *reinterpret_cast<const uint32_t *>(at + kPair),
-                                   *reinterpret_cast<const uint32_t *>(at + 2 * kPair),
-                                   *reinterpret_cast<const uint32_t *>(at + 3 * kPair));
-        *reinterpret_cast<uint4 *>(chunk_slots + slot_word(j, g * 8)) = v;
-    }
+    if (g * 8 < wp_before)
+        store_group(g, rings, lane_ring, chunk_slots, j);
 }
 
 // SPLIT >= 0: the one-pass variant used for recompression with an existing table.  There is no
@@ -1101,10 +1107,10 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
     }
     const uint32_t len = kRunCap - st.wp;
     if (live) {
-        // the incomplete group at the low end: word by word
-        for (uint32_t p = st.wp; p < ((st.wp + 7) & ~7u) && p < kRunCap; ++p)
-            chunk_slots[slot_word(j, p)] =
-                *reinterpret_cast<const uint16_t *>(ring_bytes + (lane_ring | ring_place(p & (kRingWords - 1))));
+        // the incomplete group at the low end, whole: what its lower positions hold is never looked at (the
+        // compaction takes a run from its first word on).  Word by word it was a loop of up to seven stores.
+        if (st.wp & 7u)
+            store_group(st.wp >> 3, ring_bytes, lane_ring, chunk_slots, j);
         states[lane_id] = st.x;
         lens[lane_id] = static_cast<uint8_t>(len);
         if (it.mid_states) {

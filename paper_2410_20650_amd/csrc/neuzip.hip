@@ -75,7 +75,7 @@ Layout fixed_layout(uint64_t n, int k, uint32_t block, bool f32)
 {
     const uint64_t nc = chunks_of(n);
     Layout l;
-    l.offsets = table_bytes(nc > 0 && !has_entry_points(chunks_of(n)));
+    l.offsets = table_bytes(holds_table(chunks_of(n)));
     l.states = l.offsets + pad_to((nc + 2) * 4, 256);
     l.lens = l.states + pad_to(nc * kStates * 4, 256);
     const uint64_t entries = has_entry_points(chunks_of(n)) ? nc * kStates : 0;
@@ -421,7 +421,6 @@ DecodeArgs decode_args(const neuzip_blob *b, void *d_dst)
     a.n = b->n;
     a.n_chunks = b->n_chunks;
     a.wg_end = 0;
-    a.make_lut = has_entry_points(b->n_chunks) ? 1u : 0u;
     return a;
 }
 
@@ -474,7 +473,7 @@ inline uint32_t batch_threads(int variant) { return variant == 39 ? kDecThreads 
 
 // Deals the workgroups of a batch launch to its tensors; returns their number.  stream_out: the batch as a whole
 // exceeds the last-level cache.  Such a batch has enough waves, and its smaller tensors are walked without their
-// entry points: twice the lanes mean twice the workgroups, each with a slot table to make (the seven weights of a
+// entry points: twice the lanes mean twice the workgroups (the seven weights of a
 // Llama-3-8B layer: 140.0 us, 143.2 us with the entry points).  Below, they shorten the chain (its q, k, v and o
 // with the weight step: 121.5 -> 116.5 us).
 uint32_t place_workgroups(BatchArgs &args, int variant, bool stream_out)
@@ -483,9 +482,7 @@ uint32_t place_workgroups(BatchArgs &args, int variant, bool stream_out)
     for (uint32_t t = 0; t < args.count; ++t) {
         DecodeArgs &a = args.t[t];
         a.stream_out = stream_out ? 1u : 0u;
-        if (stream_out)
-            a.mid_states = nullptr;
-        const uint32_t per = batch_threads(variant) / (a.mid_states ? 2 * kStates : kStates);
+        const uint32_t per = batch_threads(variant) / (a.mid_states && !stream_out ? 2 * kStates : kStates);
         groups += (a.n_chunks + per - 1) / per;
         a.wg_end = groups;
     }
@@ -495,13 +492,17 @@ uint32_t place_workgroups(BatchArgs &args, int variant, bool stream_out)
 template <int KB, bool NORM, int MODE = kPlain>
 void launch_batch_kernel(const BatchArgs &args, dim3 grid, dim3 block, hipStream_t stream)
 {
-    bool entries = false;
-    for (uint32_t t = 0; t < args.count; ++t)
+    bool entries = false, tables = true;
+    for (uint32_t t = 0; t < args.count; ++t) {
         entries = entries || args.t[t].mid_states;
-    if (entries)
-        hipLaunchKernelGGL((decode_batch_kernel<KB, NORM, MODE, true>), grid, block, 0, stream, args);
+        tables = tables && holds_table(args.t[t].n_chunks);
+    }
+    if (entries && !args.t[0].stream_out)  // (as place_workgroups decided)
+        hipLaunchKernelGGL((decode_batch_kernel<KB, NORM, MODE, kEntries>), grid, block, 0, stream, args);
+    else if (!tables)
+        hipLaunchKernelGGL((decode_batch_kernel<KB, NORM, MODE, kMakeTable>), grid, block, 0, stream, args);
     else
-        hipLaunchKernelGGL((decode_batch_kernel<KB, NORM, MODE, false>), grid, block, 0, stream, args);
+        hipLaunchKernelGGL((decode_batch_kernel<KB, NORM, MODE, kReadTable>), grid, block, 0, stream, args);
 }
 
 int launch_batch(const BatchArgs &args, int variant, uint32_t groups, hipStream_t stream)
@@ -1863,12 +1864,12 @@ int neuzip_import(const void *h_buf, uint64_t len, void *hip_stream, neuzip_blob
     }
     for (; occupied < kSteps; ++occupied)
         tb.steps[occupied] = kM << 8;
-    for (uint32_t i = 0, r = 0; n && i < kM / 8; ++i) {
+    for (uint32_t i = 0, r = 0; has_entry_points(nc) && i < kM / 8; ++i) {
         while ((tb.steps[r + 1] >> 8) <= 8 * i)
             ++r;
         tb.step_of[i] = static_cast<uint8_t>(r);
     }
-    for (uint32_t sym = 0; sym < 256; ++sym)
+    for (uint32_t sym = 0; holds_table(nc) && sym < 256; ++sym)
         for (uint32_t slot = cum[sym]; slot < static_cast<uint32_t>(cum[sym]) + freq[sym]; ++slot)
             tb.lut[slot] = sym | ((freq[sym] & 0xFFFu) << 8) | ((slot - cum[sym]) << 20);
     const uint32_t zeros[2] = {0, 0};

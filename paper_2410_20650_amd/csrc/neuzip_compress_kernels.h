@@ -900,13 +900,15 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
     }
     __syncthreads();
     if (table_wg) {
-        // fills in the decoder's slot table, or what the decoders need to make it, while the others encode
+        // fills in the decoder's slot table, and what decoders from the entry points need to make it, while the others
+        // encode
         const uint32_t *steps = reinterpret_cast<const uint32_t *>(rings);
+        const bool with_table = holds_table(static_cast<uint32_t>((it.table_n + kChunk - 1) / kChunk));  // (not the tile's chunks)
         for (uint32_t piece = threadIdx.x; piece < kM / 8; piece += kEncThreads) {
             const uint32_t r = step_of_piece(steps, piece);
             if (it.mid_states)
                 tb->step_of[piece] = static_cast<uint8_t>(r);
-            else
+            if (with_table)
                 make_piece(steps, r, piece, tb->lut);
         }
         return;

@@ -536,7 +536,7 @@ struct DecodeArgs {
     const uint32_t *offsets;
     const uint32_t *states;
     const uint8_t *lens;
-    const uint32_t *mid_states;  // entry points: two lanes walk a state's two halves (nullptr: one lane per state)
+    const uint32_t *mid_states;  // entry points (nullptr: the blob has none)
     const uint8_t *mid_lens;
     const uint16_t *words;
     const uint8_t *sm;
@@ -551,7 +551,6 @@ struct DecodeArgs {
     uint32_t block;       // 0: no block-wise normalisation
     uint32_t stream_out;  // non-zero: the output does not fit the last-level cache, store non-temporally
     uint32_t wg_end;      // batches: first workgroup index after this tensor's
-    uint32_t make_lut;    // the blob holds no slot table (it has entry points, used here or not)
 };
 
 // Decodes the chunks of workgroup `wg` of one tensor.
@@ -560,13 +559,23 @@ struct DecodeArgs {
 // binary16 words (kHalf).
 enum DecodeMode { kPlain = 0, kWide = 1, kUpdate = 2, kHalf = 3 };
 
-// SPLIT: the blob has entry points (the same code with a run-time choice cost the other blobs 2-5 %).
-template <int KB, bool NORM, int MODE, bool SPLIT>
+// How a workgroup comes by the tensor's slot table and how many lanes walk a state, settled at compile time: with a
+// run-time choice of one or two lanes the other blobs lost 2-5 %, and with a run-time choice of the table (a second
+// barrier, 14 registers and 1 KB of LDS that only a made table needs) a binary16 tensor of 58.7 M elements took 61.8 us
+// (60.2 now), the k = 3 weights of a Llama-3-8B layer 136.0 (135.0), 20 M elements 24.5 (24.1).
+enum DecodeForm {
+    kReadTable,  // one lane per state; the slot table is copied from the blob
+    kMakeTable,  // one lane per state; the blob is too small to hold the table (its entry points are not used)
+    kEntries,    // two lanes per state, from the entry points; the slot table is made
+};
+
+template <int KB, bool NORM, int MODE, int FORM>
 __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t wg, uint32_t *__restrict__ lut,
                                                  uint32_t *__restrict__ steps, uint8_t *__restrict__ stage,
                                                  uint2 *__restrict__ spread)
 {
     constexpr bool WIDE = MODE == kWide, UPD = MODE == kUpdate, HALF = MODE == kHalf;
+    constexpr bool SPLIT = FORM == kEntries, make_lut = FORM != kReadTable;
     static_assert(MODE == kPlain || (KB == 7 && !NORM), "binary32 blobs and trained weights are lossless only");
     const uint32_t block = 31u - static_cast<uint32_t>(__clz(static_cast<int>(a.block | 1u)));  // log2 (a power of two)
     const uint16_t *__restrict__ words = a.words;
@@ -575,7 +584,8 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
     const uint16_t *__restrict__ low = a.low;
     const uint16_t *__restrict__ grad = a.grad;
     const float lr = a.lr;
-    const bool stream_out = a.stream_out != 0;
+    // (blobs of at most 2^24 elements are never beyond the cache, and in a batch that is they are walked whole)
+    const bool stream_out = FORM == kMakeTable || (FORM == kReadTable && a.stream_out != 0);
     void *__restrict__ out_any = a.out;
     uint16_t *__restrict__ out = static_cast<uint16_t *>(out_any);
     const uint32_t n_chunks = a.n_chunks;
@@ -606,9 +616,8 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
     const uint32_t mid_len = live && SPLIT ? a.mid_lens[id] : len;
     const uint32_t lone = a.tb->lone;
     // the tensor's table: its steps (blobs with entry points) or the slot table itself
-    const bool make_lut = SPLIT || a.make_lut != 0;
     const uint4 *table_g = reinterpret_cast<const uint4 *>(make_lut ? a.tb->steps : a.tb->lut);
-    const uint32_t table_pieces = make_lut ? kSteps / 4 : kM / 4;  // of 16 bytes
+    constexpr uint32_t table_pieces = make_lut ? kSteps / 4 : kM / 4;  // of 16 bytes
     uint4 *table_to = reinterpret_cast<uint4 *>(make_lut ? steps : lut);
     uint4 table_piece[2];  // the slot table has 1024 pieces: 2 per thread at 512 threads
 #pragma unroll
@@ -617,16 +626,14 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
         table_piece[r] = i < table_pieces ? table_g[i] : make_uint4(0, 0, 0, 0);
     }
     uint32_t first_step = 0;  // of this thread's first piece of the slot table
-    if (make_lut)
+    if constexpr (make_lut)
         first_step = a.tb->step_of[tid];
     constexpr uint32_t kPreload = KB == 7 ? kTurnGroupStream : kTurnGroup;  // the largest group a variant uses
     uint64_t fields0[kPreload];
 #pragma unroll
     for (uint32_t r = 0; r < kPreload; ++r)
         fields0[r] = !WIDE && m == kChunk ? load_turn<KB, NORM>(sm, coef, block, base + (turn0 + r) * kTurn + j * kRun) : 0;
-    // ---- the word runs of chunks [c0, c1), one contiguous piece of the blob, into LDS: the first
-    // three per thread are requested together and stay in registers while the table is copied or made (six, all of
-    // a usual workgroup's, were 0.5 % slower)
+    // ---- the word runs of chunks [c0, c1), one contiguous piece of the blob, into LDS
     const uint64_t byte0 = static_cast<uint64_t>(off0) * 2;
     const uint64_t byte1 = static_cast<uint64_t>(off1) * 2;
     const uint64_t aligned0 = byte0 & ~static_cast<uint64_t>(15);
@@ -648,7 +655,15 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
                 spread[i] = spread_entry<KB>(i);
         }
     };
-    {
+    if constexpr (!make_lut) {
+        if (staged) {
+            for (uint32_t i = tid; static_cast<uint64_t>(i) * 16 < stage_len; i += threads)
+                to[i] = from[i];
+        }
+        table_to_lds();
+    } else {
+        // the first three per thread are requested together and stay in registers while the table is made (six, all
+        // of a usual workgroup's, were 0.5 % slower)
         constexpr uint32_t kFirst = 3;
         uint4 first[kFirst];
 #pragma unroll
@@ -657,13 +672,11 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
             first[r] = staged && static_cast<uint64_t>(i) * 16 < stage_len ? from[i] : make_uint4(0, 0, 0, 0);
         }
         table_to_lds();
-        if (make_lut) {
-            __syncthreads();
-            if (lone >= 256) {
-                make_piece(steps, first_step, tid, lut);
-                for (uint32_t piece = tid + threads; piece < kM / 8; piece += threads)  // (small workgroups)
-                    make_piece(steps, a.tb->step_of[piece], piece, lut);
-            }
+        __syncthreads();
+        if (lone >= 256) {
+            make_piece(steps, first_step, tid, lut);
+            for (uint32_t piece = tid + threads; piece < kM / 8; piece += threads)  // (small workgroups)
+                make_piece(steps, a.tb->step_of[piece], piece, lut);
         }
         if (staged) {
 #pragma unroll
@@ -753,8 +766,8 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(const DecodeArgs a)
     __shared__ __align__(16) uint32_t lut[kM];
     __shared__ __align__(16) uint8_t stage[kStageBytesOf<KB>];
     __shared__ uint2 spread[kSpreadEntries<KB>];
-    __shared__ __align__(16) uint32_t steps[kSteps];
-    decode_workgroup<KB, NORM, MODE, SPLIT>(a, blockIdx.x, lut, steps, stage, spread);
+    __shared__ __align__(16) uint32_t steps[SPLIT ? kSteps : 4];
+    decode_workgroup<KB, NORM, MODE, SPLIT ? kEntries : kReadTable>(a, blockIdx.x, lut, steps, stage, spread);
 }
 
 // Several tensors in one launch (a layer's weights): workgroups [t[i-1].wg_end, t[i].wg_end)
@@ -764,26 +777,28 @@ struct BatchArgs {
     uint32_t count;
 };
 
-// ENTRIES: blobs are walked from their entry points (those that have them).
-template <int KB, bool NORM, int MODE, bool ENTRIES>
+// FORM: how the blobs of the batch that have entry points (kEntries) or no slot table (kMakeTable) are walked; the
+// others read theirs.
+template <int KB, bool NORM, int MODE, int FORM>
 __global__ __launch_bounds__(kDecThreads) void decode_batch_kernel(const BatchArgs b)
 {
     __shared__ __align__(16) uint32_t lut[kM];
     __shared__ __align__(16) uint8_t stage[kStageBytesOf<KB>];
     __shared__ uint2 spread[kSpreadEntries<KB>];
-    __shared__ __align__(16) uint32_t steps[kSteps];
+    __shared__ __align__(16) uint32_t steps[FORM == kReadTable ? 4 : kSteps];
     uint32_t i = 0, first = 0;
     while (i + 1 < b.count && blockIdx.x >= b.t[i].wg_end) {
         first = b.t[i].wg_end;
         ++i;
     }
-    if constexpr (ENTRIES) {
-        if (b.t[i].mid_states) {
-            decode_workgroup<KB, NORM, MODE, true>(b.t[i], blockIdx.x - first, lut, steps, stage, spread);
+    const DecodeArgs a = b.t[i];
+    if constexpr (FORM != kReadTable) {
+        if (FORM == kEntries ? a.mid_states != nullptr : !holds_table(a.n_chunks)) {
+            decode_workgroup<KB, NORM, MODE, FORM>(a, blockIdx.x - first, lut, steps, stage, spread);
             return;
         }
     }
-    decode_workgroup<KB, NORM, MODE, false>(b.t[i], blockIdx.x - first, lut, steps, stage, spread);
+    decode_workgroup<KB, NORM, MODE, kReadTable>(a, blockIdx.x - first, lut, steps, stage, spread);
 }
 
 // The entry points of an imported blob: every lane walks its state to them, writing nothing (the words come

@@ -52,6 +52,14 @@ constexpr uint32_t kMidTurn = kTurns / 2;
 constexpr uint32_t kSplitChunks = 4096;
 __host__ __device__ constexpr bool has_entry_points(uint32_t n_chunks) { return n_chunks > 0 && n_chunks <= kSplitChunks; }
 
+// The decoder's slot table (16 KB) is held by blobs without entry points, whose decoders copy it, and by those of
+// them that have at least kTableChunks chunks: in a batch beyond the cache these are walked whole beside larger
+// ones, and with the table in the blob that launch is the plain one, which makes no tables (5 tensors of 16.8 M:
+// 55.8 us, 56.9 with every workgroup making its own; 0.3 % of such a blob, of smaller ones it would be more).
+constexpr uint32_t kTableChunks = 1024;
+__host__ __device__ constexpr bool holds_table(uint32_t n_chunks) { return n_chunks >= kTableChunks; }
+static_assert(kTableChunks <= kSplitChunks, "a blob without entry points holds the table");
+
 constexpr uint32_t kSteps = 264;  // occupied symbols of a table (at most 256) and what a search reads behind them
 
 // ------------------------------------------------------------------------------------------
@@ -67,9 +75,9 @@ struct TableBlock {
     uint32_t steps[kSteps];
     // which of them slot 8i belongs to (derived; blobs with entry points)
     uint8_t step_of[kM / 8];
-    // decoder slot table (derived): lut[slot] = symbol | f << 8 | (slot - cum[symbol]) << 20.  Blobs with entry
-    // points do not have it (their allocation ends before it): there every workgroup of a decoder makes it from
-    // the steps, which a tensor beyond the size of those blobs, with several rounds of workgroups, would
+    // decoder slot table (derived): lut[slot] = symbol | f << 8 | (slot - cum[symbol]) << 20.  Small blobs do not
+    // have it (their allocation ends before it, see holds_table); from the entry points every workgroup of a decoder
+    // makes it from the steps, which a tensor beyond the size of those blobs, with several rounds of workgroups, would
     // pay several times (28672 x 8192: 145 us with the table read from the blob, 161 us without).
     uint32_t lut[kM];
 };

@@ -523,16 +523,47 @@ int launch_batch(const BatchArgs &args, int variant, uint32_t groups, hipStream_
     return hip_ok(hipGetLastError()) ? NEUZIP_OK : NEUZIP_EHIP;
 }
 
-// Which form of the kernel: 16 columns (tiles of 16 tokens) or 32 columns (tiles of 32 tokens).
-// The wide form halves the activation traffic per token but has twice the sums per wave, and every row
-// that ends inside a chunk sends them to y one by one.  It pays for more than 16 tokens where at most every
-// second chunk has such an end (64 tokens: 4096 x 14336 73 against 88 us, 9000 x 5120 100 against 91), or none
-// (in_features a divisor or a multiple of the chunk).  Weights walked from their entry points have the
-// 16-column form only.
-inline uint32_t linear_columns(uint32_t tokens, uint64_t in_features, bool entries)
+// Which form of the linear kernel a launch takes: 16 columns (tiles of 16 tokens) or 32 columns (tiles of 32 tokens),
+// and whether weights that have entry points are walked from them (16 columns only) or whole.
+//
+// Columns, more than 16 tokens: the wide form halves the activation traffic per token but has twice the sums per
+// wave, and every row that ends inside a chunk sends them to y one by one.  It pays where at most every second chunk
+// has such an end, or none, and for rows of 2048, which end once inside each (64 tokens, 32 / 16 columns:
+// 4096 x 14336 69 / 86 us, 14336 x 4096 62 / 81, 20000 x 2048 85 / 90; 9000 x 5120 95 / 90, 18000 x 1024 106 / 77).
+//
+// Entry points: two lanes per state halve the chain and double the workgroups.  With up to 16 tokens that pays while
+// these run at once (two per CU, 512), and beyond one round of whole walks, whose last round the half ones fill
+// (1 token, halves / whole: three weights of 1000 x 8192 23.4 / 28.2 us, two of 4096 x 4096 21.0 / 26.6, four
+// 39.5 / 34.3; 4000 x 14336 with 1000 x 14336 48.3 / 55.2); the longer walk of normalised weights gains a little further
+// (three of 4096 x 4096, k = 3, block 512: 39.3 / 41.5).  With more tokens the activations weigh, and 16 columns
+// read them twice as often: weights that leave CUs empty are walked in halves, beyond that, or beside a larger one, the
+// launch whole, a little later for few tokens (4096 x 4096, 64 tokens: 26 / 30; two of them, 20 tokens: 26.2 / 26.8, 24:
+// 28.1 / 27.1, 64: 45.9 / 31.5; q, k and v of a Llama-3-8B attention block, 64 tokens: 45.6 / 31.1; 14336 x 4096 with
+// 1024 x 4096, 32 tokens: 53.7 / 38.4; 20000 x 2048 with 500 x 2048, 32 tokens: 59.1 / 54.4).  Rows shorter than a chunk end inside it, and half a walk has half the ends to send one
+// after the other: always in halves there (four weights of 16000 x 1024, 64 tokens: 173 / 200; 5000 x 2048: 70 / 90).
+struct LinearForm {
+    uint32_t cols;
+    bool entries;
+};
+inline LinearForm linear_form(uint32_t tokens, uint64_t in_features, const neuzip_blob *const *weights, uint32_t count)
 {
-    const bool few_ends = in_features >= 2 * kChunk || kChunk % in_features == 0;
-    return tokens > 16 && few_ends && !entries ? 32u : 16u;
+    constexpr uint32_t kAtOnce = 512;  // workgroups the chip runs at once: two on each of its 256 CUs
+    uint32_t whole = 0, halves = 0;    // workgroups of the launch
+    bool any = false, all = true;
+    for (uint32_t i = 0; i < count; ++i) {
+        const bool has = has_entry_points(weights[i]->n_chunks);
+        any = any || has;
+        all = all && has;
+        whole += (weights[i]->n_chunks + kDecChunksPerWg - 1) / kDecChunksPerWg;
+        halves += (weights[i]->n_chunks + (kDecChunksPerWg >> has) - 1) / (kDecChunksPerWg >> has);
+    }
+    if (tokens <= 16)
+        return {16u, any && (halves <= (weights[0]->block ? kAtOnce + kAtOnce / 2 : kAtOnce) || whole > kAtOnce)};
+    const bool few_ends = in_features >= 2 * kChunk || in_features == kChunk || in_features == kChunk / 2;
+    const bool worth = in_features < kChunk || halves <= (tokens <= 20 ? kAtOnce : kAtOnce / 2);
+    if (any && worth && (all || (in_features < kChunk && !few_ends)))
+        return {16u, true};
+    return {few_ends ? 32u : 16u, false};
 }
 
 template <int KB, bool NORM>
@@ -540,8 +571,16 @@ void launch_linear(const LinearBatchArgs &batch, uint32_t cols, uint32_t wgs, hi
 {
     const dim3 grid(wgs), block(kLinThreads);
     const uint32_t tokens = batch.t[0].tokens;
-#define NZ_LINEAR(COLS, MT) \
-    hipLaunchKernelGGL((linear_batch_kernel<KB, COLS, MT, NORM>), grid, block, 0, stream, batch)
+    bool read = true;  // all weights walked whole, with tables to read
+    for (uint32_t i = 0; i < batch.count; ++i)
+        read = read && !batch.t[i].split && holds_table(batch.t[i].n_chunks);
+#define NZ_LINEAR(COLS, MT)                                                                                        \
+    do {                                                                                                           \
+        if (read)                                                                                                  \
+            hipLaunchKernelGGL((linear_batch_kernel<KB, COLS, MT, NORM, true>), grid, block, 0, stream, batch);    \
+        else                                                                                                       \
+            hipLaunchKernelGGL((linear_batch_kernel<KB, COLS, MT, NORM, false>), grid, block, 0, stream, batch);   \
+    } while (0)
     if (cols == 32) {
         if (tokens <= 32)
             NZ_LINEAR(32, 1);
@@ -1408,11 +1447,8 @@ int neuzip_linear_batch(const neuzip_blob *const *weights, const uint64_t *out_f
     const neuzip_blob *first = weights[0];
     for (uint32_t t0 = 0; t0 < tokens; t0 += kLinMaxTokens) {
         const uint32_t tile = tokens - t0 < kLinMaxTokens ? tokens - t0 : kLinMaxTokens;
-        // chunks per group = columns of the matrix instruction
-        bool entries = false;
-        for (uint32_t i = 0; i < count; ++i)
-            entries = entries || batch.t[i].mid_states;
-        const uint32_t cols = linear_columns(tile, in_features, entries);
+        const LinearForm form = linear_form(tile, in_features, weights, count);
+        const uint32_t cols = form.cols;  // chunks per group = columns of the matrix instruction
         uint32_t wgs = 0;
         for (uint32_t i = 0; i < count; ++i) {
             LinearArgs &a = batch.t[i];
@@ -1421,7 +1457,7 @@ int neuzip_linear_batch(const neuzip_blob *const *weights, const uint64_t *out_f
             a.y = d_y[i] + static_cast<uint64_t>(t0) * out_features[i];
             const uint64_t per_block = static_cast<uint64_t>(cols) * a.stride;
             a.n_groups = static_cast<uint32_t>((weights[i]->n_chunks + per_block - 1) / per_block * a.stride);
-            a.split = cols == 16 && a.mid_states ? 1u : 0u;
+            a.split = form.entries && a.mid_states ? 1u : 0u;
             const uint32_t groups_per_wg = (kDecChunksPerWg / cols) >> a.split;
             wgs += (a.n_groups + groups_per_wg - 1) / groups_per_wg;
             batch.wg_end[i] = wgs;

@@ -254,13 +254,15 @@ __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, co
     }
 }
 
-template <int KB, int COLS, int MT, bool NORM>
+// READ: every weight of the launch is walked whole and holds its slot table (with the choice of both left to run time
+// 4096 x 14336, 1 token, took 36.4 us, 35.7 now, and 8192 x 8192 36.7, 35.9 now).
+template <int KB, int COLS, int MT, bool NORM, bool READ>
 __device__ __forceinline__ void linear_workgroup(const LinearArgs &a, uint32_t wg, uint32_t *__restrict__ lut,
                                                  uint32_t *__restrict__ steps, uint8_t *__restrict__ stage)
 {
     constexpr uint32_t kLinGroupChunks = COLS;                       // columns of the B operand
     constexpr uint32_t kPerWave = 64 / COLS;                         // states of a chunk per wave: 4 or 2
-    const uint32_t split = COLS == 16 ? a.split : 0u;                // two waves for the halves of a wave's states
+    const uint32_t split = COLS == 16 && !READ ? a.split : 0u;                // two waves for the halves of a wave's states
     const uint32_t waves_per_group = (kStates / kPerWave) << split;  // 4 (8 with entry points), or 8
     const uint32_t groups_per_wg = kLinThreads / 64 / waves_per_group;
     const uint32_t group_window = kStageBytes / groups_per_wg;       // LDS window of one group's word runs
@@ -300,8 +302,8 @@ __device__ __forceinline__ void linear_workgroup(const LinearArgs &a, uint32_t w
     if (live)
         lens16 = *reinterpret_cast<const uint4 *>(a.lens + static_cast<uint64_t>(c) * kStates);
     const uint32_t lone = a.tb->lone;
-    // the tensor's table: its steps (blobs with entry points) or the slot table itself
-    const bool make_lut = a.mid_states != nullptr;
+    // the tensor's table: its steps (walked from the entry points, or too small to hold the table) or the slot table itself
+    const bool make_lut = !READ && (split || !holds_table(a.n_chunks));
     static_assert(kLinThreads == kM / 8, "one piece of the slot table per thread");
     const uint32_t first_step = make_lut ? a.tb->step_of[tid] : 0u;
     uint4 table_piece[2];
@@ -475,18 +477,18 @@ __device__ __forceinline__ void linear_workgroup(const LinearArgs &a, uint32_t w
 
 // (Two workgroups of 8 waves share a CU if a lane has at most 128 registers; with the 138 the compiler took
 // for 64 tokens it held one.)
-template <int KB, int COLS, int MT, bool NORM = false>
+template <int KB, int COLS, int MT, bool NORM, bool READ>
 __global__ __launch_bounds__(kLinThreads, 4) void linear_batch_kernel(const LinearBatchArgs b)
 {
     __shared__ __align__(16) uint32_t lut[kM];
     __shared__ __align__(16) uint8_t stage[kStageBytes];
-    __shared__ __align__(16) uint32_t steps[kSteps];
+    __shared__ __align__(16) uint32_t steps[READ ? 4 : kSteps];
     uint32_t i = 0, first = 0;
     while (i + 1 < b.count && blockIdx.x >= b.wg_end[i]) {
         first = b.wg_end[i];
         ++i;
     }
-    linear_workgroup<KB, COLS, MT, NORM>(b.t[i], blockIdx.x - first, lut, steps, stage);
+    linear_workgroup<KB, COLS, MT, NORM, READ>(b.t[i], blockIdx.x - first, lut, steps, stage);
 }
 
 }  // namespace nz

@@ -100,3 +100,24 @@ def test_linear_batch_of_weights_on_both_sides_of_the_line(nz, tokens):
         want = x.double() @ w.double().t()
         bound = 2 * (in_f + 64) * 2.0 ** -24 * (x.double().abs() @ w.double().abs().t())
         assert bool(((y.double() - want).abs() <= bound).all())
+
+
+# (out_features of the weights, in_features, tokens): a small weight, which makes its slot table, beside one that
+# holds it and one without entry points, walked whole in the wide form and in the narrow one; batches that fill the
+# chip at half a state per lane, and one that does so beyond one round of whole states
+@pytest.mark.parametrize("outs, in_f, tokens", [((9000, 40), 4096, 21), ((4096, 4096, 1000), 4096, 33), ((6000, 3000, 40), 8192, 64),
+                                                ((4096, 4096, 4000, 500), 4096, 1), ((4096, 4096, 4000, 500), 4096, 16),
+                                                ((4096, 4096, 4000, 500), 4096, 20), ((17000, 900), 4096, 8),
+                                                ((5000, 5000, 300), 2048, 40), ((3300, 100), 5120, 24)])
+@pytest.mark.parametrize("k, block", [(7, 0), (3, 512)])
+def test_linear_batches_walked_whole_and_in_halves(nz, k, block, outs, in_f, tokens):
+    ws = [inputs.gaussian_bf16((o, in_f), 950 + o, device=DEV) for o in outs]
+    blobs = [nz.neuzip_compress_blockwise(w, k, block) for w in ws]
+    held = [nz.neuzip_decompress(b, torch.empty_like(w)).double() for b, w in zip(blobs, ws)]
+    biases = [torch.randn(o, device=DEV, dtype=torch.float32) for o in outs]
+    x = inputs.gaussian_bf16((tokens, in_f), 951, std=1.0, device=DEV)
+    for y, w, b, blob in zip(nz.neuzip_linear_batch(blobs, outs, in_f, x, biases), held, biases, blobs):
+        want = x.double() @ w.t() + b.double()
+        bound = 2 * (in_f + 64) * 2.0 ** -24 * (x.double().abs() @ w.abs().t() + b.double().abs())
+        assert bool(((y.double() - want).abs() <= bound).all())
+        nz.neuzip_check(blob)

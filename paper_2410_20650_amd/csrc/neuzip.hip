@@ -1859,12 +1859,16 @@ int neuzip_import(const void *h_buf, uint64_t len, void *hip_stream, neuzip_blob
     for (uint32_t c = 0; c < nc; ++c) {
         if (get32(lay.offsets + 4ull * c) != run)
             return NEUZIP_ECORRUPT;
+        // (without a way out of the loop, so that it is a few vector instructions)
+        const uint8_t *lens = p + lay.lens + static_cast<uint64_t>(c) * kStates;
+        uint32_t words = 0, longest = 0;
         for (uint32_t j = 0; j < kStates; ++j) {
-            const uint32_t l = p[lay.lens + static_cast<uint64_t>(c) * kStates + j];
-            if (l > kRunCap)
-                return NEUZIP_ECORRUPT;
-            run += l;
+            words += lens[j];
+            longest = lens[j] > longest ? lens[j] : longest;
         }
+        if (longest > kRunCap)
+            return NEUZIP_ECORRUPT;
+        run += words;
     }
     if (get32(lay.offsets + 4ull * nc) != run || run != total_words)
         return NEUZIP_ECORRUPT;
@@ -1909,15 +1913,35 @@ int neuzip_import(const void *h_buf, uint64_t len, void *hip_stream, neuzip_blob
         for (uint32_t slot = cum[sym]; slot < static_cast<uint32_t>(cum[sym]) + freq[sym]; ++slot)
             tb.lut[slot] = sym | ((freq[sym] & 0xFFFu) << 8) | ((slot - cum[sym]) << 20);
     const uint32_t zeros[2] = {0, 0};
-    if (!hip_ok(hipMemcpyAsync(b->fixed, &tb, b->at.offsets, hipMemcpyHostToDevice, stream)) ||
-        !hip_ok(hipMemcpyAsync(offsets_of(b), p + lay.offsets, (nc + 1ull) * 4, hipMemcpyHostToDevice, stream)) ||
-        !hip_ok(hipMemcpyAsync(offsets_of(b) + nc + 1, zeros, 4, hipMemcpyHostToDevice, stream)))
+    // Table, offsets, states and lengths of a tensor with entry points go up as they lie in the blob, in one copy: it
+    // saves what the walk to the entry points costs (3 M elements: 194 us without entry points, with them 269 in five
+    // copies, 209 in one).
+    static thread_local uint8_t image[sizeof(TableBlock) + kSplitChunks * (4 + 4 * kStates + kStates) + 1024];
+    if (nc <= kSplitChunks) {
+        std::memcpy(image, &tb, b->at.offsets);
+        std::memcpy(image + b->at.offsets, p + lay.offsets, (nc + 1ull) * 4);
+        std::memcpy(image + b->at.offsets + (nc + 1ull) * 4, zeros, 4);
+        std::memcpy(image + b->at.states, p + lay.states, nc * kStates * 4ull);
+        std::memcpy(image + b->at.lens, p + lay.lens, nc * static_cast<uint64_t>(kStates));
+        if (!hip_ok(hipMemcpyAsync(b->fixed, image, b->at.lens + nc * kStates, hipMemcpyHostToDevice, stream)))
+            return fail(NEUZIP_EHIP);
+    } else if (!hip_ok(hipMemcpyAsync(b->fixed, &tb, b->at.offsets, hipMemcpyHostToDevice, stream)) ||
+               !hip_ok(hipMemcpyAsync(offsets_of(b), p + lay.offsets, (nc + 1ull) * 4, hipMemcpyHostToDevice, stream)) ||
+               !hip_ok(hipMemcpyAsync(offsets_of(b) + nc + 1, zeros, 4, hipMemcpyHostToDevice, stream)) ||
+               !hip_ok(hipMemcpyAsync(states_of(b), p + lay.states, nc * kStates * 4ull, hipMemcpyHostToDevice, stream)) ||
+               !hip_ok(hipMemcpyAsync(lens_of(b), p + lay.lens, nc * static_cast<uint64_t>(kStates), hipMemcpyHostToDevice, stream))) {
         return fail(NEUZIP_EHIP);
-    if (nc && (!hip_ok(hipMemcpyAsync(states_of(b), p + lay.states, nc * kStates * 4ull, hipMemcpyHostToDevice, stream)) ||
-               !hip_ok(hipMemcpyAsync(lens_of(b), p + lay.lens, nc * static_cast<uint64_t>(kStates), hipMemcpyHostToDevice, stream))))
-        return fail(NEUZIP_EHIP);
+    }
     if (total_words && !hip_ok(hipMemcpyAsync(b->words, p + lay.words, total_words * 2, hipMemcpyHostToDevice, stream)))
         return fail(NEUZIP_EHIP);
+    // (what the walk needs is there: it runs while the host makes the next copy ready)
+    if (mid_states_of(b)) {
+        const uint32_t chunks = kEntryThreads / kStates;
+        hipLaunchKernelGGL(entry_points_kernel, dim3((nc + chunks - 1) / chunks), dim3(kEntryThreads), 0, stream,
+                           decode_args(b, nullptr), mid_states_of(b), mid_lens_of(b));
+        if (!hip_ok(hipGetLastError()))
+            return fail(NEUZIP_EHIP);
+    }
     if (n && !hip_ok(hipMemcpyAsync(sm_of(b), p + lay.sm, signmant_bytes(n, k), hipMemcpyHostToDevice, stream)))
         return fail(NEUZIP_EHIP);
     if (n && f32 && !hip_ok(hipMemcpyAsync(low_of(b), p + lay.low, n * 2, hipMemcpyHostToDevice, stream)))
@@ -1929,13 +1953,7 @@ int neuzip_import(const void *h_buf, uint64_t len, void *hip_stream, neuzip_blob
         if (!hip_ok(hipMemcpyAsync(coef_of(b), p + lay.coef, block_count(n, block), hipMemcpyHostToDevice, stream)))
             return fail(NEUZIP_EHIP);
     }
-    if (mid_states_of(b)) {
-        hipLaunchKernelGGL(entry_points_kernel, dim3((nc * kStates + 255) / 256), dim3(256), 0, stream, decode_args(b, nullptr),
-                           mid_states_of(b), mid_lens_of(b));
-        if (!hip_ok(hipGetLastError()))
-            return fail(NEUZIP_EHIP);
-    }
-    if (!hip_ok(hipStreamSynchronize(stream)))  // tb and zeros must outlive the copies
+    if (!hip_ok(hipStreamSynchronize(stream)))  // tb, zeros and image must outlive the copies
         return fail(NEUZIP_EHIP);
     b->has_table = true;
     *blob = b;

@@ -801,23 +801,57 @@ __global__ __launch_bounds__(kDecThreads) void decode_batch_kernel(const BatchAr
     decode_workgroup<KB, NORM, MODE, kReadTable>(a, blockIdx.x - first, lut, steps, stage, spread);
 }
 
-// The entry points of an imported blob: every lane walks its state to them, writing nothing (the words come
-// straight from the blob; a run fed from a damaged container consumes at most one word per symbol and stays
-// inside the slack behind the words).
-__global__ __launch_bounds__(256) void entry_points_kernel(const DecodeArgs a, uint32_t *__restrict__ mid_states,
-                                                           uint8_t *__restrict__ mid_lens)
+// The entry points of an imported blob: every lane walks its state to them, writing nothing.  A workgroup's words go
+// through LDS, as in the decoder (with every word fetched from the blob behind the one before it, the launch was a chain
+// of memory latencies: the import of 50 000 elements took 94 us).  A run fed from a damaged container consumes at most
+// one word per symbol and stays inside the slack behind the words, here and in the window; the decoder reports it.
+constexpr uint32_t kEntryThreads = 256;
+constexpr uint32_t kEntryOverrun = (kMidTurn * kRun + 1) * 2;  // bytes a walk can pass the end of its run by
+
+template <class WordSrc>
+__device__ __forceinline__ void walk_to_entry(const uint32_t *__restrict__ lut, const WordSrc &src, uint32_t m, uint32_t j,
+                                              uint32_t &x, uint32_t &wp)
+{
+    uint32_t next = src.peek(wp);
+    for (uint32_t at = j * kRun; at < m && at < kMidTurn * kTurn; at += kTurn) {
+        if (m - at >= kRun) {
+#pragma unroll
+            for (uint32_t t = 0; t < kRun; ++t)
+                rans_get(lut, x, wp, next, src);
+        } else {
+            for (uint32_t t = 0; t < m - at; ++t)
+                rans_get(lut, x, wp, next, src);
+        }
+    }
+}
+
+__global__ __launch_bounds__(kEntryThreads) void entry_points_kernel(const DecodeArgs a, uint32_t *__restrict__ mid_states,
+                                                                     uint8_t *__restrict__ mid_lens)
 {
     __shared__ __align__(16) uint32_t lut[kM];
     __shared__ __align__(16) uint32_t steps[kSteps];
-    for (uint32_t i = threadIdx.x; i < kSteps; i += blockDim.x)
-        steps[i] = a.tb->steps[i];
-    __syncthreads();
+    __shared__ __align__(16) uint8_t stage[kStageBytes];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t c0 = blockIdx.x * (kEntryThreads / kStates);
+    const uint32_t c1 = c0 + kEntryThreads / kStates < a.n_chunks ? c0 + kEntryThreads / kStates : a.n_chunks;
+    const uint64_t byte0 = static_cast<uint64_t>(a.offsets[c0]) * 2, byte1 = static_cast<uint64_t>(a.offsets[c1]) * 2;
+    const uint64_t aligned0 = byte0 & ~static_cast<uint64_t>(15);
+    const uint64_t stage_len = byte1 - aligned0;
+    const bool staged = stage_len + 16 + kEntryOverrun <= kStageBytes;
     const bool lone = a.tb->lone < 256;
+    for (uint32_t i = tid; i < kSteps; i += kEntryThreads)
+        steps[i] = a.tb->steps[i];
+    if (staged) {
+        const uint4 *from = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint8_t *>(a.words) + aligned0);
+        for (uint32_t i = tid; static_cast<uint64_t>(i) * 16 < stage_len; i += kEntryThreads)
+            reinterpret_cast<uint4 *>(stage)[i] = from[i];
+    }
+    __syncthreads();
     if (!lone)
-        for (uint32_t piece = threadIdx.x; piece < kM / 8; piece += blockDim.x)
+        for (uint32_t piece = tid; piece < kM / 8; piece += kEntryThreads)
             make_piece(steps, a.tb->step_of[piece], piece, lut);
     __syncthreads();
-    const uint32_t id = blockIdx.x * blockDim.x + threadIdx.x, c = id / kStates, j = id % kStates;
+    const uint32_t c = c0 + tid / kStates, j = tid % kStates, id = c * kStates + j;
     if (c >= a.n_chunks)
         return;
     const uint32_t len = a.lens[id];
@@ -831,17 +865,16 @@ __global__ __launch_bounds__(256) void entry_points_kernel(const DecodeArgs a, u
     before -= len;
     const uint64_t base = static_cast<uint64_t>(c) * kChunk;
     const uint32_t m = (a.n - base) < kChunk ? static_cast<uint32_t>(a.n - base) : kChunk;
-    uint32_t x = a.states[id], wp = 0;
-    if (!lone) {
-        const GlobalWords src{reinterpret_cast<const uint8_t *>(a.words + a.offsets[c] + before)};
-        uint32_t next = src.peek(wp);
-        for (uint32_t q = 0; q < kMidTurn; ++q)
-            for (uint32_t t = 0; t < kRun; ++t)
-                if (q * kTurn + j * kRun + t < m)
-                    rans_get(lut, x, wp, next, src);
+    const uint64_t run_byte = (static_cast<uint64_t>(a.offsets[c]) + before) * 2;
+    uint32_t x = a.states[id], wp = 0, wp_begin = 0;
+    if (!lone && staged) {
+        wp = wp_begin = static_cast<uint32_t>(run_byte - aligned0);
+        walk_to_entry(lut, LdsWords{stage}, m, j, x, wp);
+    } else if (!lone) {
+        walk_to_entry(lut, GlobalWords{reinterpret_cast<const uint8_t *>(a.words) + run_byte}, m, j, x, wp);
     }
     mid_states[id] = x;
-    mid_lens[id] = static_cast<uint8_t>(wp / 2);
+    mid_lens[id] = static_cast<uint8_t>((wp - wp_begin) / 2);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -60,6 +60,22 @@ def test_symbols_with_gaps_and_a_full_table(nz):
         assert torch.equal(decoded(nz, kept, w).view(torch.int16), w.view(torch.int16))
 
 
+@pytest.mark.parametrize("chunks, rest", [(0, 5), (15, 4095), (16, 0), (17, 77), (600, 129)])
+def test_imported_entry_points_with_and_without_the_lds_window(nz, chunks, rest):
+    # random bits code to 8 bits per symbol: the 16 chunks of a workgroup of the import's walk come to 64 KiB of
+    # words, more than its window of 62 KiB; Gaussian ones to a third of it
+    n = chunks * 4096 + rest
+    for w, wide in ((inputs.random_bits_bf16(n, 905, device=DEV), True), (inputs.gaussian_bf16(n, 906, device=DEV), False)):
+        blob = nz.neuzip_compress(w, 7)
+        container = nz.neuzip_export(blob)
+        if wide and chunks >= 16:
+            words = int(container[40:48].view(np.uint64)[0])
+            assert 2 * words * 16 * 4096 // n > 62 * 1024
+        again = nz.neuzip_import(container)
+        assert torch.equal(decoded(nz, again, w).view(torch.int16), w.view(torch.int16))
+        assert np.array_equal(nz.neuzip_export(again), container)
+
+
 def test_a_batch_beyond_the_cache_walks_small_tensors_whole(nz):
     ws = [inputs.gaussian_bf16(n, 910 + i, device=DEV) for i, n in enumerate((70_000_001, 1_000_003, 4097, LINE))]
     blobs = [nz.neuzip_compress(w, 3) for w in ws]

@@ -40,8 +40,9 @@ class CompressedLinear:
         if tokens <= 64 and self.in_features % 128 == 0:
             return nz.neuzip_linear(self.blob, self.out_features, self.in_features, x.contiguous(), self.bias)
         y = torch.matmul(x, self.weight_into(space).t())
-        # (the sum of a bf16 and a float32 tensor is float32: widening and addition in one launch)
-        return y.float() if self.bias is None else y + self.bias
+        # (the sum of a bf16 and a float32 tensor is float32, widening and addition in one launch, unless one of them has
+        # no dimensions, which counts for less in torch's choice of the result's type)
+        return y.float() if self.bias is None else y + torch.atleast_1d(self.bias)
 
     def backward_and_update(self, x: torch.Tensor, grad_y: torch.Tensor, lr: float, space: torch.Tensor,
                             grad_space: torch.Tensor):

@@ -1,0 +1,25 @@
+"""The bias arithmetic of the layer wrapper (torch only; the codec's calls are stood in for on the CPU)."""
+import pytest
+import torch
+
+from paper_2410_20650_amd import layer
+
+
+def a_layer(out_features, in_features, bias):
+    made = layer.CompressedLinear.__new__(layer.CompressedLinear)
+    made.out_features, made.in_features = out_features, in_features
+    made.blob, made.bias = None, bias
+    made.held = torch.randn(out_features, in_features, generator=torch.Generator().manual_seed(3)).to(torch.bfloat16)
+    made.weight_into = lambda space: made.held
+    return made
+
+
+@pytest.mark.parametrize("shape", [(), (1,), (5,), (1, 5)])
+def test_forward_of_a_training_batch_is_float32_for_every_shape_of_bias(shape):
+    out_features = 1 if shape in ((), (1,)) else 5
+    bias = torch.full(shape, 1.0 + 2.0 ** -20)          # more bits than bf16 has
+    made = a_layer(out_features, 128, bias)
+    x = torch.randn(65, 128, generator=torch.Generator().manual_seed(4)).to(torch.bfloat16)
+    y = made.forward(x, None)
+    want = torch.matmul(x, made.held.t()).float() + bias
+    assert y.dtype == torch.float32 and y.shape == (65, out_features) and torch.equal(y, want)

@@ -56,7 +56,7 @@ class CompressedLinear:
         grad_w = grad_space.view(-1)[:n].view(self.out_features, self.in_features)
         torch.matmul(grad_y.t(), x, out=grad_w)                           # out_features x in_features, bf16
         if self.bias is not None:
-            self.bias.sub_(grad_y.sum(dim=0, dtype=torch.float32), alpha=lr)
+            self.bias.sub_(grad_y.sum(dim=0, dtype=torch.float32), alpha=float(lr))
         # `space` still holds W_hat from the decompression above: the step and the coding are one pass,
         # and nobody needs the new weight uncompressed
         (rebuilt,) = nz.neuzip_update([self.blob], [grad_w.view(-1)], [space.view(-1)[:n]], lr, weights_ready=2)

@@ -373,9 +373,9 @@ inline uint64_t words_room(const neuzip_blob *b)
 // Chunks per decoder workgroup.  32 (8 waves) measured best from ~16 M elements up: two such
 // workgroups fill a CU's LDS with 16 waves, and smaller workgroups lower that occupancy.  A blob with entry
 // points has two lanes per state and cannot fill the chip either way: workgroups of 8 chunks (4 waves) spread it
-// over more CUs up to 2048 chunks (4 M elements: 4 / 8 / 12 / 16 chunks 15.8 / 14.9 / 15.2 / 15.0 us; 8 M: 18.1 /
-// 15.7 / 16.3 / 15.9), from there on the slot table that every workgroup makes weighs more (16.8 M: 32.9 / 19.0 /
-// 20.4 / 18.0).
+// over more CUs up to 2048 chunks (4 M elements: 4 / 8 / 12 / 16 chunks 13.8 / 13.0 / 13.5 / 13.1 us; 8 M: 15.7 /
+// 14.1 / 14.4 / 14.2), from there on the slot table that every workgroup makes weighs more (16.8 M: 29.3 / 16.5 /
+// 18.6 / 15.8).
 // NEUZIP_DECODE_CHUNKS_PER_WG (4..32, multiple of 4) overrides the choice for tuning runs.
 // binary16 symbols carry 5-6 bits each (sign and two mantissa bits ride in the symbol), so only
 // 16 chunks' words fit the LDS window: such blobs never take more.
@@ -1424,7 +1424,6 @@ int neuzip_linear_batch(const neuzip_blob *const *weights, const uint64_t *out_f
         while (w->block && (1u << a.block_shift) < w->block)
             ++a.block_shift;
         a.stride = static_cast<uint32_t>(in_features / gcd);
-        a.rstep = static_cast<uint32_t>(kChunk / gcd);
         a.whole_rows = in_features == kChunk ? 1u : 0u;
         a.bias = d_bias ? d_bias[i] : nullptr;
         const uint64_t cells = static_cast<uint64_t>(tokens) * out_features[i];

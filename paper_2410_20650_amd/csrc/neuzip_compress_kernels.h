@@ -120,13 +120,6 @@ __device__ __forceinline__ uint32_t normalise_word(uint32_t u, float c)
     return bf16_of(__uint_as_float(u << 16) / c);
 }
 
-__device__ __forceinline__ uint32_t denormalise_word(uint32_t u, float c)
-{
-    if (bf16_is_nan(u))
-        return u | 0x40u;
-    return bf16_of(__fmul_rn(__uint_as_float(u << 16), c));
-}
-
 __device__ __forceinline__ float coefficient(uint32_t coef) { return 1.0f + static_cast<float>(coef) * 0.0078125f; }
 
 // ------------------------------------------------------------------------------------------

@@ -165,7 +165,7 @@ __device__ __forceinline__ uint64_t load_turn(const uint8_t *__restrict__ sm, co
 }
 
 // bf16(stored * c) on the two halves of a merged dword: two multiplies, one packed conversion;
-// a NaN keeps its bits and gets the quiet bit, as in denormalise_word
+// a NaN keeps its bits and gets the quiet bit, as in normalise_word
 __device__ __forceinline__ uint32_t denormalise_pair(uint32_t d, float c)
 {
     typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2_t;

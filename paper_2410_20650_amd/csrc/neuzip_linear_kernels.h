@@ -10,15 +10,19 @@
 // float (lane l holds column l % 16, rows 4 * (l / 16) .. + 3).  A = 16 tokens of the
 // activations, B = 16 rows of the weight, both over the same 32 input features.
 //
-// Lane assignment.  A workgroup of 512 threads walks 32 chunks as two groups of 16.  In a group,
+// Lane assignment.  A workgroup of 512 threads walks 32 chunks as two groups of 16, or, from the entry
+// points, one group of 16 with two waves where there was one, for the two halves of its states.  In a group,
 // wave sq (0..3) and lane l own state j = 4 * sq + l / 16 of chunk number l % 16 of the group.
 // At turn t that state holds the weights at flat index chunk * 4096 + t * 128 + j * 8 .. + 7, so
 // a wave holds, for 16 chunks, the 32 neighbouring input features t * 128 + sq * 32 .. + 31:
 // exactly a B operand, provided the 16 chunks sit at the same input-feature offset.  Chunks that
 // are `stride` = in_features / gcd(in_features, 4096) apart do (stride * 4096 is a whole number of
-// rows), so a group is chunks first + stride * (0..15); its columns are rows `rstep` apart.
-// Every wave accumulates its own share of the input features of a row piece and adds the
-// partial sums to y with float atomics when the row ends (y starts as the bias, or zero).
+// rows), so a group is chunks first + stride * (0..15).
+// Every wave accumulates its own share of the input features of a row piece.  Where a row ends inside the
+// walk, its partial sums go to y with float atomics (y then starts as the bias, or zero).  At the end of
+// the walk the waves of a group add theirs up in LDS first (unless the tokens are few, see
+// kLinDirectTokens) and one atomic leaves per sum; and where a chunk is a whole row the sum is complete
+// there and is stored with the bias, without atomics and without y set up before.
 //
 // Two forms, template parameter COLS.  COLS = 16 is the above.  COLS = 32 uses
 // v_mfma_f32_32x32x16_bf16 (A 32 x 16, B 16 x 32, lane l: row / column l % 32, k = 8 * (l / 32)
@@ -68,8 +72,9 @@ struct LinearTile<32> {
 constexpr uint32_t kLinThreads = 512;
 constexpr uint32_t kLinMaxTokens = 64;
 // Up to here the waves of a group add their sums to y by themselves (where they are not complete in the
-// workgroup): 4096 x 14336, 1 token, 35.6 us, with the sums added up in LDS first 37.6; 16 tokens 42.8 and 39.1.
-constexpr uint32_t kLinDirectTokens = 8;
+// workgroup): 4096 x 14336, 1 token, 35.6 us, with the sums added up in LDS first 35.8; 8 tokens 36.5 and 35.9, 16
+// tokens 43.1 and 38.4.
+constexpr uint32_t kLinDirectTokens = 4;
 
 struct LinearArgs {
     const TableBlock *tb;
@@ -83,7 +88,7 @@ struct LinearArgs {
     const uint8_t *coef;   // block coefficients (block-wise normalised blobs only)
     uint32_t block_shift;  // log2 of the block size of the normalisation
     const uint16_t *x;     // [tokens][in_features] bf16
-    float *y;              // [tokens][out_features], holds the bias (or zero) on entry
+    float *y;              // [tokens][out_features], holds the bias (or zero) on entry unless whole_rows
     uint32_t *status;
     uint64_t n;
     uint32_t n_chunks;
@@ -91,7 +96,6 @@ struct LinearArgs {
     uint32_t out_features;
     uint32_t tokens;
     uint32_t stride;       // chunks between neighbouring columns of a group
-    uint32_t rstep;        // rows between neighbouring columns of a group
     uint32_t n_groups;
     uint32_t split;        // 1: two lanes walk a state's two halves from the entry points
     uint32_t whole_rows;   // a chunk is a row of the weight: sums are complete in the workgroup

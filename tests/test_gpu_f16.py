@@ -70,7 +70,7 @@ def test_f16_every_pattern_and_extremes(nz):
     blob = nz.neuzip_compress(c, 7)
     same_container(nz.neuzip_export(blob), O.compress_f16(inputs.bits16(c)), "single symbol")
     assert np.array_equal(decoded(nz, blob, c), inputs.bits16(c))
-    # uniformly random words: 8 bits per symbol, the words do not fit the LDS window
+    # uniformly random words: 8 bits per symbol
     r = inputs.from_bits16(inputs.bits(inputs.random_bits_bf16(300_000, 12_100)), DEV)
     blob = nz.neuzip_compress(r, 7)
     same_container(nz.neuzip_export(blob), O.compress_f16(inputs.bits16(r), threads=8), "random bits")

@@ -81,7 +81,7 @@ def test_f32_single_exponent_and_wide_spread(nz):
     blob = nz.neuzip_compress(c, 7)
     same_container(nz.neuzip_export(blob), O.compress_f32(words), "single exponent")
     assert np.array_equal(decoded(nz, blob, c), words)
-    # random 32-bit patterns: over 5 bits per exponent, the decoder reads the words from the blob
+    # random 32-bit patterns: 8 bits per exponent
     g = torch.Generator(device=DEV).manual_seed(9811)
     v = torch.randint(-2 ** 31, 2 ** 31, (300_000,), generator=g, device=DEV, dtype=torch.int64)
     w = v.to(torch.int32).view(torch.float32)

@@ -143,8 +143,7 @@ def test_linear_single_exponent_and_wide_exponent_weights(nz):
     sign = torch.where(torch.arange(out_f * in_f, device=DEV) % 3 == 0, -1.0, 1.0)
     w = (sign * 0.75).to(torch.bfloat16)
     check_linear(nz, w, out_f, in_f, 4, seed=9400)
-    # exponents spread over 40 values (over 5 bits per symbol): the word runs do not fit the LDS
-    # window and are read from the blob
+    # exponents spread over 40 values (over 5 bits per symbol)
     g = torch.Generator(device=DEV).manual_seed(9401)
     n = 64 * 2048
     expo = torch.randint(100, 140, (n,), generator=g, device=DEV, dtype=torch.int32)

@@ -102,8 +102,9 @@ def test_heavy_tailed(nz, k):
 
 
 @pytest.mark.parametrize("n", [5, 4096, 40_000, 300_000])
-def test_uniform_exponents_take_the_unstaged_path(nz, n):
-    # 8 bits per symbol: the word runs of 32 chunks exceed the LDS window
+def test_uniform_exponents(nz, n):
+    # 8 bits per symbol (the workgroups of tensors this small hold 8 chunks, whose words still fit the LDS window;
+    # test_gpu_large_forms.py goes beyond it)
     w = inputs.random_bits_bf16(n, 99 + n, device=DEV)
     roundtrip_and_compare(nz, w, 7)
     roundtrip_and_compare(nz, w, 0)

@@ -38,7 +38,7 @@ PROFILE_CASES = ("decode_config2", "decode_config4_k7", "decode_config4_k3", "de
                  "decode_config4_k3_block512",
                  "decode_embedding", "decode_batch_layer",
                  "decode_small_kv", "compress_config2", "recompress_config2", "compress_embedding",
-                 "recompress_embedding", "update_config2", "linear_q", "linear_qkv")
+                 "recompress_embedding", "update_config2", "linear_q", "linear_qkv", "linear_down_k3")
 
 
 def parse_args():
@@ -227,6 +227,12 @@ def profile_case(args, torch, nz, inputs, np, dev, stream):
         ys = [torch.empty((1, o), dtype=torch.float32, device=dev) for o in outs]
         run(lambda: nz.neuzip_linear_batch(blobs, outs, 4096, x, None, ys), sum(b.compressed_bytes for b in blobs),
             sum(t.numel() for t in ws))
+    elif case == "linear_down_k3":         # the MLP's down projection, lossy, a full decoding batch
+        t = inputs.gaussian_bf16((4096, 14336), inputs.seed_for(8, 710), device=dev)
+        blob = nz.neuzip_compress(t, 3)
+        x = inputs.gaussian_bf16((64, 14336), inputs.seed_for(8, 502), std=1.0, device=dev)
+        y = torch.empty((64, 4096), dtype=torch.float32, device=dev)
+        run(lambda: nz.neuzip_linear(blob, 4096, 14336, x, None, y), blob.compressed_bytes, t.numel())
     elif case == "linear_q":
         blob = nz.neuzip_compress(w, 7)
         x = inputs.gaussian_bf16((1, 4096), inputs.seed_for(8, 501), std=1.0, device=dev)
@@ -291,7 +297,7 @@ def main():
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": read_traffic_note(),
                 "traffic_source": "profiles/decode_config2.txt (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, a separate run; not measured in this one)",
-                "kernel": "decode_kernel<7, false, 0>", "avg_launch_us": round(kernel_ms * 1e3, 2),
+                "kernel": "decode_kernel<7, false, 0, false>", "avg_launch_us": round(kernel_ms * 1e3, 2),
                 "algorithmic_bytes_per_elem": round(algo_bytes / n, 4),
                 "working_set": "196 MB: fits the 256 MB last-level cache, so this figure is cache assisted; "
                                "see roofline_hbm_resident for a tensor that streams through HBM"}
@@ -399,7 +405,7 @@ def main():
                 result["roofline_hbm_resident"] = {
                     "bound": "hbm", "achieved": round((b4.compressed_bytes + 2.0 * n4) / us / 1e3, 1),
                     "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": hbm_frac(b4.compressed_bytes + 2.0 * n4, us),
-                    "kernel": "decode_kernel<7, false, 0> (non-temporal stores)", "avg_launch_us": round(us, 2),
+                    "kernel": "decode_kernel<7, false, 0, false> (non-temporal stores)", "avg_launch_us": round(us, 2),
                     "workload": "config 4 tensor (bf16 28672x8192, Student-t), lossless: 783 MB per launch, "
                                 "beyond the last-level cache", "launches": 50}
             else:

@@ -320,8 +320,9 @@ void neuzip_free(neuzip_blob *blob);
 uint64_t neuzip_compressed_bytes(const neuzip_blob *blob);
 
 /* Bytes of device memory the blob actually holds (container sections plus
- * alignment padding and what the decoder derives: the cumulative table, and the slot table or, for
- * tensors of at most 2^24 elements, an entry point half way into each state, 5 bytes per 256 elements). */
+ * alignment padding and what the decoder derives: the cumulative table, for tensors of 1024 chunks (2^22
+ * elements) and more the 16 KB slot table, and for tensors of at most 2^24 elements an entry point half way
+ * into each state, 5 bytes per 256 elements). */
 uint64_t neuzip_device_bytes(const neuzip_blob *blob);
 
 /* Element count, mantissa bits, normalisation block size (0 = none), guard band of the table

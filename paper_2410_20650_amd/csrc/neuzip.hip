@@ -25,6 +25,7 @@
 #include <cstdlib>
 #include <chrono>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 
@@ -1916,14 +1917,19 @@ int neuzip_import(const void *h_buf, uint64_t len, void *hip_stream, neuzip_blob
     // Table, offsets, states and lengths of a tensor with entry points go up as they lie in the blob, in one copy: it
     // saves what the walk to the entry points costs (3 M elements: 194 us without entry points, with them 269 in five
     // copies, 209 in one).
-    static thread_local uint8_t image[table_bytes(kSplitChunks) + kSplitChunks * (4 + 4 * kStates + kStates) + 1024];
+    std::unique_ptr<uint8_t, void (*)(void *)> held(nullptr, std::free);
     if (nc <= kSplitChunks) {
+        const uint64_t image_bytes = b->at.lens + nc * kStates;
+        held.reset(static_cast<uint8_t *>(std::malloc(image_bytes)));
+        uint8_t *image = held.get();
+        if (!image)
+            return fail(NEUZIP_ENOMEM);
         std::memcpy(image, block_of, b->at.offsets);
         std::memcpy(image + b->at.offsets, p + lay.offsets, (nc + 1ull) * 4);
         std::memcpy(image + b->at.offsets + (nc + 1ull) * 4, zeros, 4);
         std::memcpy(image + b->at.states, p + lay.states, nc * kStates * 4ull);
         std::memcpy(image + b->at.lens, p + lay.lens, nc * static_cast<uint64_t>(kStates));
-        if (!hip_ok(hipMemcpyAsync(b->fixed, image, b->at.lens + nc * kStates, hipMemcpyHostToDevice, stream)))
+        if (!hip_ok(hipMemcpyAsync(b->fixed, image, image_bytes, hipMemcpyHostToDevice, stream)))
             return fail(NEUZIP_EHIP);
     } else if (!hip_ok(hipMemcpyAsync(b->fixed, block_of, b->at.offsets, hipMemcpyHostToDevice, stream)) ||
                !hip_ok(hipMemcpyAsync(offsets_of(b), p + lay.offsets, (nc + 1ull) * 4, hipMemcpyHostToDevice, stream)) ||

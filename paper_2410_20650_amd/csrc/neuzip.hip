@@ -76,7 +76,7 @@ Layout fixed_layout(uint64_t n, int k, uint32_t block, bool f32)
 {
     const uint64_t nc = chunks_of(n);
     Layout l;
-    l.offsets = table_bytes(chunks_of(n));
+    l.offsets = table_bytes(holds_table(chunks_of(n)));
     l.states = l.offsets + pad_to((nc + 2) * 4, 256);
     l.lens = l.states + pad_to(nc * kStates * 4, 256);
     const uint64_t entries = has_entry_points(chunks_of(n)) ? nc * kStates : 0;
@@ -1890,9 +1890,8 @@ int neuzip_import(const void *h_buf, uint64_t len, void *hip_stream, neuzip_blob
     b->have_counts = false;
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    alignas(TableBlock) static thread_local uint8_t block_of[sizeof(TableBlock) + kM / 8];  // 19 KB: off the stack
-    std::memset(block_of, 0, sizeof(block_of));
-    TableBlock &tb = *reinterpret_cast<TableBlock *>(block_of);
+    static thread_local TableBlock tb;  // 18 KB: off the stack
+    std::memset(&tb, 0, sizeof(tb));
     std::memcpy(tb.freq, freq, 512);
     std::memcpy(tb.cum, cum, sizeof(tb.cum));
     tb.lone = 256;
@@ -1908,7 +1907,7 @@ int neuzip_import(const void *h_buf, uint64_t len, void *hip_stream, neuzip_blob
     for (uint32_t i = 0, r = 0; has_entry_points(nc) && i < kM / 8; ++i) {
         while ((tb.steps[r + 1] >> 8) <= 8 * i)
             ++r;
-        step_of(&tb, holds_table(nc))[i] = static_cast<uint8_t>(r);
+        tb.step_of[i] = static_cast<uint8_t>(r);
     }
     for (uint32_t sym = 0; holds_table(nc) && sym < 256; ++sym)
         for (uint32_t slot = cum[sym]; slot < static_cast<uint32_t>(cum[sym]) + freq[sym]; ++slot)
@@ -1924,14 +1923,14 @@ int neuzip_import(const void *h_buf, uint64_t len, void *hip_stream, neuzip_blob
         uint8_t *image = held.get();
         if (!image)
             return fail(NEUZIP_ENOMEM);
-        std::memcpy(image, block_of, b->at.offsets);
+        std::memcpy(image, &tb, b->at.offsets);
         std::memcpy(image + b->at.offsets, p + lay.offsets, (nc + 1ull) * 4);
         std::memcpy(image + b->at.offsets + (nc + 1ull) * 4, zeros, 4);
         std::memcpy(image + b->at.states, p + lay.states, nc * kStates * 4ull);
         std::memcpy(image + b->at.lens, p + lay.lens, nc * static_cast<uint64_t>(kStates));
         if (!hip_ok(hipMemcpyAsync(b->fixed, image, image_bytes, hipMemcpyHostToDevice, stream)))
             return fail(NEUZIP_EHIP);
-    } else if (!hip_ok(hipMemcpyAsync(b->fixed, block_of, b->at.offsets, hipMemcpyHostToDevice, stream)) ||
+    } else if (!hip_ok(hipMemcpyAsync(b->fixed, &tb, b->at.offsets, hipMemcpyHostToDevice, stream)) ||
                !hip_ok(hipMemcpyAsync(offsets_of(b), p + lay.offsets, (nc + 1ull) * 4, hipMemcpyHostToDevice, stream)) ||
                !hip_ok(hipMemcpyAsync(offsets_of(b) + nc + 1, zeros, 4, hipMemcpyHostToDevice, stream)) ||
                !hip_ok(hipMemcpyAsync(states_of(b), p + lay.states, nc * kStates * 4ull, hipMemcpyHostToDevice, stream)) ||
@@ -1959,7 +1958,7 @@ int neuzip_import(const void *h_buf, uint64_t len, void *hip_stream, neuzip_blob
         if (!hip_ok(hipMemcpyAsync(coef_of(b), p + lay.coef, block_count(n, block), hipMemcpyHostToDevice, stream)))
             return fail(NEUZIP_EHIP);
     }
-    if (!hip_ok(hipStreamSynchronize(stream)))  // the tables and zeros must outlive the copies
+    if (!hip_ok(hipStreamSynchronize(stream)))  // tb, zeros and image must outlive the copies
         return fail(NEUZIP_EHIP);
     b->has_table = true;
     *blob = b;

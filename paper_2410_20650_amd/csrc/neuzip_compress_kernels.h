@@ -900,7 +900,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
         for (uint32_t piece = threadIdx.x; piece < kM / 8; piece += kEncThreads) {
             const uint32_t r = step_of_piece(steps, piece);
             if (it.mid_states)
-                step_of(tb, with_table)[piece] = static_cast<uint8_t>(r);
+                tb->step_of[piece] = static_cast<uint8_t>(r);
             if (with_table)
                 make_piece(steps, r, piece, tb->lut);
         }

@@ -625,10 +625,9 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
         const uint32_t i = tid + r * threads;
         table_piece[r] = i < table_pieces ? table_g[i] : make_uint4(0, 0, 0, 0);
     }
-    const uint8_t *pieces_of = step_of(a.tb, holds_table(n_chunks));
     uint32_t first_step = 0;  // of this thread's first piece of the slot table
     if constexpr (make_lut)
-        first_step = pieces_of[tid];
+        first_step = a.tb->step_of[tid];
     constexpr uint32_t kPreload = KB == 7 ? kTurnGroupStream : kTurnGroup;  // the largest group a variant uses
     uint64_t fields0[kPreload];
 #pragma unroll
@@ -677,7 +676,7 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
         if (lone >= 256) {
             make_piece(steps, first_step, tid, lut);
             for (uint32_t piece = tid + threads; piece < kM / 8; piece += threads)  // (small workgroups)
-                make_piece(steps, pieces_of[piece], piece, lut);
+                make_piece(steps, a.tb->step_of[piece], piece, lut);
         }
         if (staged) {
 #pragma unroll
@@ -850,7 +849,7 @@ __global__ __launch_bounds__(kEntryThreads) void entry_points_kernel(const Decod
     __syncthreads();
     if (!lone)
         for (uint32_t piece = tid; piece < kM / 8; piece += kEntryThreads)
-            make_piece(steps, step_of(a.tb, holds_table(a.n_chunks))[piece], piece, lut);
+            make_piece(steps, a.tb->step_of[piece], piece, lut);
     __syncthreads();
     const uint32_t c = c0 + tid / kStates, j = tid % kStates, id = c * kStates + j;
     if (c >= a.n_chunks)

@@ -73,28 +73,16 @@ struct TableBlock {
     uint32_t pad[47];
     // the occupied symbols in order (derived): cum << 8 | symbol; the rest of the array is 4096 << 8
     uint32_t steps[kSteps];
+    // which of them slot 8i belongs to (derived; blobs with entry points)
+    uint8_t step_of[kM / 8];
     // decoder slot table (derived): lut[slot] = symbol | f << 8 | (slot - cum[symbol]) << 20.  Small blobs do not
     // have it (their allocation ends before it, see holds_table); from the entry points every workgroup of a decoder
     // makes it from the steps, which a tensor beyond the size of those blobs, with several rounds of workgroups, would
     // pay several times (28672 x 8192: 145 us with the table read from the blob, 161 us without).
     uint32_t lut[kM];
 };
-// Which of the steps slot 8i belongs to, kM / 8 bytes (derived; blobs with entry points): behind the slot table, or in its
-// place where the blob does not hold it.
-constexpr uint64_t step_of_place(bool with_table) { return offsetof(TableBlock, lut) + (with_table ? sizeof(TableBlock::lut) : 0); }
-__host__ __device__ inline uint8_t *step_of(TableBlock *tb, bool with_table)
-{
-    return reinterpret_cast<uint8_t *>(tb) + step_of_place(with_table);
-}
-__host__ __device__ inline const uint8_t *step_of(const TableBlock *tb, bool with_table)
-{
-    return reinterpret_cast<const uint8_t *>(tb) + step_of_place(with_table);
-}
-constexpr uint64_t table_bytes(uint32_t n_chunks)
-{
-    return step_of_place(holds_table(n_chunks)) + (has_entry_points(n_chunks) ? kM / 8 : 0);
-}
-static_assert(offsetof(TableBlock, lut) % 256 == 0 && kM / 8 % 256 == 0, "the sections behind the table stay aligned");
+constexpr uint64_t table_bytes(bool with_lut) { return with_lut ? sizeof(TableBlock) : offsetof(TableBlock, lut); }
+static_assert(offsetof(TableBlock, lut) % 256 == 0, "either way the sections behind it stay aligned");
 static_assert(sizeof(TableBlock) % 256 == 0, "table block keeps later sections aligned");
 
 // Per-symbol encoder constants (16 bytes, one ds_read_b128), derived by every encoder workgroup from

@@ -309,7 +309,7 @@ __device__ __forceinline__ void linear_workgroup(const LinearArgs &a, uint32_t w
     // the tensor's table: its steps (walked from the entry points, or too small to hold the table) or the slot table itself
     const bool make_lut = !READ && (split || !holds_table(a.n_chunks));
     static_assert(kLinThreads == kM / 8, "one piece of the slot table per thread");
-    const uint32_t first_step = make_lut ? step_of(a.tb, holds_table(a.n_chunks))[tid] : 0u;
+    const uint32_t first_step = make_lut ? a.tb->step_of[tid] : 0u;
     uint4 table_piece[2];
 #pragma unroll
     for (uint32_t r = 0; r < 2; ++r) {

@@ -373,14 +373,25 @@ inline uint64_t words_room(const neuzip_blob *b)
 
 // Chunks per decoder workgroup.  32 (8 waves) measured best from ~16 M elements up: two such
 // workgroups fill a CU's LDS with 16 waves, and smaller workgroups lower that occupancy.  A blob with entry
-// points has two lanes per state and cannot fill the chip either way: workgroups of 8 chunks (4 waves) spread it
-// over more CUs up to 2048 chunks (4 M elements: 4 / 8 / 12 / 16 chunks 13.8 / 13.0 / 13.5 / 13.1 us; 8 M: 15.7 /
-// 14.1 / 14.4 / 14.2), from there on the slot table that every workgroup makes weighs more (16.8 M: 29.3 / 16.5 /
-// 18.6 / 15.8).
+// points has two lanes per state: as many chunks as spread it over the 256 CUs, between 8, below which the slot table that
+// every workgroup makes has too few threads to be made by (0.05 M elements 10.0 us at 4 chunks, 9.5 at 8; 4 M 11.5 / 10.7;
+// 16 chunks 10.2 / 11.7), and 16, the most a workgroup of 8 waves has lanes for (10 M binary32 elements at 8 / 12 / 16 chunks:
+// 19.7 / 16.4 / 18.1 us; 12 M bf16 13.6 / 12.6 / 12.7; 16.8 M 14.4 / 17.1 / 14.0).
 // NEUZIP_DECODE_CHUNKS_PER_WG (4..32, multiple of 4) overrides the choice for tuning runs.
-// binary16 symbols carry 5-6 bits each (sign and two mantissa bits ride in the symbol), so only
-// 16 chunks' words fit the LDS window: such blobs never take more.
-uint32_t decode_chunks_per_wg(uint32_t n_chunks, bool f16 = false)
+// At most so many that their words fit the LDS window (at their average length and 3 % more): a walk whose words come from
+// memory waits for every one of them.  Exponents of 4 bits, 58.7 M elements: 32 chunks 143.7 us, 16 58.8; of 5 bits, 100 M:
+// 251.6 and, with 20, 90.5; of 8 bits, 30 M: 85.2 and, with 12, 73.7; so are weights coded with a table that they have moved away
+// from.  binary16 symbols carry 5-6 bits each (sign and two mantissa bits ride in the symbol) and never take more than 16.
+constexpr uint32_t kFitBytes = 58 * 1024;
+static_assert(kFitBytes + kFitBytes / 33 < kStageBytesOf<1> && kStageBytesOf<1> <= kStageBytesOf<0>, "the smallest window");
+inline uint32_t chunks_that_fit(const neuzip_blob *b)
+{
+    const uint64_t bytes = b->total_words * 2 / b->n_chunks + 1;  // of a chunk's words
+    const uint64_t fit = kFitBytes / bytes / 4 * 4;
+    return fit < 4 ? 4u : (fit < kDecChunksPerWg ? static_cast<uint32_t>(fit) : kDecChunksPerWg);
+}
+
+uint32_t decode_chunks_per_wg(const neuzip_blob *b)
 {
     static int forced = -1;
     if (forced < 0) {
@@ -388,10 +399,13 @@ uint32_t decode_chunks_per_wg(uint32_t n_chunks, bool f16 = false)
         const int v = env ? std::atoi(env) : 0;
         forced = (v >= 4 && v <= static_cast<int>(kDecChunksPerWg) && v % 4 == 0) ? v : 0;
     }
-    const bool split = has_entry_points(n_chunks);
-    const uint32_t most = f16 || split ? 16u : kDecChunksPerWg;
-    const uint32_t per = forced > 0 ? static_cast<uint32_t>(forced) : (split && n_chunks <= 2048 ? 8u : most);
-    return per < most ? per : most;
+    const bool split = has_entry_points(b->n_chunks);
+    const uint32_t most = b->elem == NEUZIP_F16 || split ? 16u : kDecChunksPerWg;
+    if (forced > 0)
+        return static_cast<uint32_t>(forced) < most ? static_cast<uint32_t>(forced) : most;
+    const uint32_t spread = static_cast<uint32_t>(pad_to((b->n_chunks + 255) / 256, 4)), fit = chunks_that_fit(b);
+    const uint32_t per = split && spread < most ? (spread < 8 ? 8u : spread) : most;
+    return per < fit ? per : fit;
 }
 
 // Lanes that walk one chunk.
@@ -422,19 +436,34 @@ DecodeArgs decode_args(const neuzip_blob *b, void *d_dst)
     a.n = b->n;
     a.n_chunks = b->n_chunks;
     a.wg_end = 0;
+    a.fit = b->n_chunks ? chunks_that_fit(b) : 0u;
     return a;
 }
+
+// Whether the words of a launch of whole walks go straight into LDS: where nearly every CU is given two workgroups at once
+// and no more come behind them, so that nothing but their own requests keeps memory busy while the words are awaited (58.7 M
+// elements 46.2 us, through registers 47.8; 62 M 48.8 / 50.0; 55 M 46.6 / 46.6).  With fewer workgroups it gives nothing or
+// costs (45 M 42.3 / 42.4, 36 M 40.6 / 39.4), and in a launch of several rounds the burst of a workgroup's words is in the way
+// of those that walk (28672 x 8192, k = 3: 151 / 146; a Llama-3-8B layer 143.7 / 140.9).
+inline bool copies_directly(uint32_t workgroups) { return workgroups >= 416 && workgroups <= 512; }
 
 template <int KB, bool NORM, int MODE = kPlain>
 int launch_decode(const neuzip_blob *b, void *d_dst, hipStream_t stream)
 {
-    const uint32_t per = decode_chunks_per_wg(b->n_chunks, b->elem == NEUZIP_F16);
+    const uint32_t per = decode_chunks_per_wg(b);
     const uint32_t groups = (b->n_chunks + per - 1) / per;
     const dim3 grid(groups), block(per * lanes_per_chunk(b));
+    const DecodeArgs args = decode_args(b, d_dst);
+    if constexpr (MODE == kPlain) {  // (binary32 and binary16 tensors of so many workgroups were not measured, or stream)
+        if (!has_entry_points(b->n_chunks) && !args.stream_out && per == kDecChunksPerWg && copies_directly(groups)) {
+            hipLaunchKernelGGL((decode_direct_kernel<KB, NORM>), grid, block, 0, stream, args);
+            return hip_ok(hipGetLastError()) ? NEUZIP_OK : NEUZIP_EHIP;
+        }
+    }
     if (has_entry_points(b->n_chunks))
-        hipLaunchKernelGGL((decode_kernel<KB, NORM, MODE, true>), grid, block, 0, stream, decode_args(b, d_dst));
+        hipLaunchKernelGGL((decode_kernel<KB, NORM, MODE, true>), grid, block, 0, stream, args);
     else
-        hipLaunchKernelGGL((decode_kernel<KB, NORM, MODE, false>), grid, block, 0, stream, decode_args(b, d_dst));
+        hipLaunchKernelGGL((decode_kernel<KB, NORM, MODE, false>), grid, block, 0, stream, args);
     return hip_ok(hipGetLastError()) ? NEUZIP_OK : NEUZIP_EHIP;
 }
 
@@ -469,8 +498,23 @@ inline int decode_variant(const neuzip_blob *b)
     return b->k + (b->block ? 8 : 0) + (b->elem == NEUZIP_F32 ? 16 : 0) + (b->elem == NEUZIP_F16 ? 32 : 0);
 }
 
-// threads per workgroup of a batch launch of the given variant
-inline uint32_t batch_threads(int variant) { return variant == 39 ? kDecThreads / 2 : kDecThreads; }
+// Threads per workgroup of a batch launch of the given variant: the most, or as few as the words of the tensors that do not
+// fit the LDS window otherwise ask for (see chunks_that_fit), if those are at least half of the batch: the others are better
+// off with full workgroups.
+uint32_t batch_threads(const BatchArgs &args, int variant, bool stream_out)
+{
+    const uint32_t most = variant == 39 ? kDecThreads / 2 : kDecThreads;
+    uint32_t threads = most;
+    uint64_t all = 0, beyond = 0;
+    for (uint32_t t = 0; t < args.count; ++t) {
+        const DecodeArgs &a = args.t[t];
+        const uint32_t needs = a.fit * (a.mid_states && !stream_out ? 2 * kStates : kStates);
+        all += a.n;
+        beyond += needs < most ? a.n : 0;
+        threads = needs < threads ? needs : threads;
+    }
+    return 2 * beyond >= all ? threads : most;
+}
 
 // Deals the workgroups of a batch launch to its tensors; returns their number.  stream_out: the batch as a whole
 // exceeds the last-level cache.  Such a batch has enough waves, and its smaller tensors are walked without their
@@ -480,10 +524,11 @@ inline uint32_t batch_threads(int variant) { return variant == 39 ? kDecThreads 
 uint32_t place_workgroups(BatchArgs &args, int variant, bool stream_out)
 {
     uint32_t groups = 0;
+    args.threads = batch_threads(args, variant, stream_out);
     for (uint32_t t = 0; t < args.count; ++t) {
         DecodeArgs &a = args.t[t];
         a.stream_out = stream_out ? 1u : 0u;
-        const uint32_t per = batch_threads(variant) / (a.mid_states && !stream_out ? 2 * kStates : kStates);
+        const uint32_t per = args.threads / (a.mid_states && !stream_out ? 2 * kStates : kStates);
         groups += (a.n_chunks + per - 1) / per;
         a.wg_end = groups;
     }
@@ -508,7 +553,7 @@ void launch_batch_kernel(const BatchArgs &args, dim3 grid, dim3 block, hipStream
 
 int launch_batch(const BatchArgs &args, int variant, uint32_t groups, hipStream_t stream)
 {
-    const dim3 grid(groups), block(batch_threads(variant));
+    const dim3 grid(groups), block(args.threads);
     switch (variant) {
     case 7: launch_batch_kernel<7, false>(args, grid, block, stream); break;
     case 3: launch_batch_kernel<3, false>(args, grid, block, stream); break;
@@ -1702,8 +1747,9 @@ int neuzip_decompress_batch(const neuzip_blob *const *blobs, void *const *d_dsts
         for (uint32_t i = 0; i <= count; ++i) {
             const bool flush = (i == count) || (args.count == kBatchMax);
             if (flush && args.count > 0) {
-                const uint32_t groups = place_workgroups(args, k, stream_out);
-                const int rc = launch_batch(args, k, groups, stream);
+                // (a tensor on its own: the single-tensor launch, whose form follows the tensor's size)
+                const int rc = count == 1 ? decode_dispatch(blobs[0], d_dsts[0], stream)
+                                          : launch_batch(args, k, place_workgroups(args, k, stream_out), stream);
                 if (rc != NEUZIP_OK)
                     return rc;
                 args.count = 0;

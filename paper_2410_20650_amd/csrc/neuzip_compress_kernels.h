@@ -215,7 +215,7 @@ __device__ __forceinline__ void wait_for_memory_acks() { asm volatile("s_waitcnt
 // shifts of 1, 2, 4, 8 (a lane without a source keeps the identity), then the last lane of rows 0
 // and 2 is added into rows 1 and 3, then lane 31 into rows 2 and 3.  All 64 lanes must be active.
 template <class Op>
-__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v, uint32_t identity, Op op)
+__device__ __forceinline__ uint32_t row_scan_u32(uint32_t v, uint32_t identity, Op op)
 {
 #define NZ_DPP(ctrl, rows) \
     static_cast<uint32_t>(__builtin_amdgcn_update_dpp(static_cast<int>(identity), static_cast<int>(v), ctrl, rows, 0xf, false))
@@ -223,6 +223,13 @@ __device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v, uint32_t identity,
     v = op(v, NZ_DPP(0x112, 0xf));  // row_shr:2
     v = op(v, NZ_DPP(0x114, 0xf));  // row_shr:4
     v = op(v, NZ_DPP(0x118, 0xf));  // row_shr:8
+    return v;
+}
+
+template <class Op>
+__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v, uint32_t identity, Op op)
+{
+    v = row_scan_u32(v, identity, op);
     v = op(v, NZ_DPP(0x142, 0xa));  // row_bcast:15 into rows 1 and 3
     v = op(v, NZ_DPP(0x143, 0xc));  // row_bcast:31 into rows 2 and 3
 #undef NZ_DPP
@@ -235,6 +242,9 @@ struct OpAdd {
 struct OpMax {
     __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return a > b ? a : b; }
 };
+
+// Inclusive sum over the lanes of a row of 16 (all of them active).
+__device__ __forceinline__ uint32_t row_scan_u32(uint32_t v) { return row_scan_u32(v, 0u, OpAdd{}); }
 
 // Sum / maximum over the wave, the same value in every lane (lane 63 of the scan, read out as a scalar).
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v)

@@ -134,17 +134,31 @@ struct NoWords {
 
 // One rANS decoding step of a lane's state; returns the slot-table entry (symbol in its low
 // byte).  `next` always holds the word at byte position wp of the lane's word source, so a
-// refill is a shift-or; the following word is fetched only then.
-template <class WordSrc>
+// refill is a shift-or.
+//   EAGER = false: the following word is fetched only where one has been consumed, behind a branch over the wave's mask.
+//   EAGER = true: no branch; the refilled state is selected and the word at wp is fetched again whether it moved or not.
+// A wave that has its SIMD to itself issues an instruction about every 8 cycles whatever it depends on, and the mask's
+// save, branch and restore cost more there than the two selects: 116 cycles a symbol without them, 139 with (the loop alone,
+// 1 to 4 waves per CU; at 8 waves 132 and 147).  With four waves per SIMD the vector unit's time counts, and the branch skips
+// some of it: 30 M elements walked whole, k = 3, 26.3 us, without the branch 28.7.
+template <bool EAGER, class WordSrc>
 __device__ __forceinline__ uint32_t rans_get(const uint32_t *__restrict__ lut, uint32_t &x, uint32_t &wp,
                                              uint32_t &next, const WordSrc &src)
 {
     const uint32_t e = lut[x & (kM - 1)];
-    x = __umul24((e >> 8) & 0xFFFu, x >> kProbBits) + (e >> 20);
-    if (x < kRansL) {
-        x = (x << 16) | next;
-        wp += 2;
+    const uint32_t y = __umul24((e >> 8) & 0xFFFu, x >> kProbBits) + (e >> 20);
+    if constexpr (EAGER) {
+        const bool refill = y < kRansL;
+        x = refill ? (y << 16) | next : y;
+        wp = refill ? wp + 2 : wp;
         next = src.peek(wp);
+    } else {
+        x = y;
+        if (x < kRansL) {
+            x = (x << 16) | next;
+            wp += 2;
+            next = src.peek(wp);
+        }
     }
     return e;
 }
@@ -211,6 +225,15 @@ __device__ __forceinline__ uint4 merge_turn(uint64_t fields, const uint32_t (&e)
     return o;
 }
 
+// What a workgroup's beginning has requested of a state's first turns (whole chunks only): the fields, and the lower halves of
+// a binary32 tensor that is walked from the entry points.
+constexpr uint32_t kTurnsAhead = 4;
+static_assert(kTurnsAhead >= kTurnGroup && kTurnsAhead >= kTurnGroupStream, "at least a group of turns");
+struct TurnsAhead {
+    uint64_t fields[kTurnsAhead];
+    uint4 lows[kTurnsAhead];
+};
+
 // Marks a loaded value as used here, at the end of a path beside a hot loop: the compiler lays the two out one
 // behind the other, takes the path's loads for outstanding in the loop, and would wait there in every turn for
 // the stores of the turn before (28672 x 8192, k = 3, block 512: 158 us instead of 147).
@@ -226,7 +249,7 @@ __device__ __forceinline__ void settle(uint64_t v)
 // the caller's, so the elements of an incomplete turn are read one by one there, as they are written.
 // (Walked element by element with a field load in front of each, the 1683 elements at the end of a
 // 10 M-element binary32 tensor took as long as the rest of the launch: 50.8 us, 25.1 us now.)
-template <int KB, bool LONE, bool NORM, bool UPD, bool HALF, class WordSrc>
+template <int KB, bool LONE, bool NORM, bool UPD, bool HALF, bool EAGER, class WordSrc>
 __device__ __forceinline__ void walk_ragged(const uint32_t *__restrict__ lut, const uint2 *__restrict__ spread,
                                             const WordSrc &src, uint32_t lone, uint32_t &x, uint32_t &wp,
                                             const uint8_t *__restrict__ sm, const uint8_t *__restrict__ coef,
@@ -249,7 +272,7 @@ __device__ __forceinline__ void walk_ragged(const uint32_t *__restrict__ lut, co
                 g = *reinterpret_cast<const uint4 *>(grad + here);
 #pragma unroll
             for (int t = 0; t < 8; ++t)
-                e[t] = LONE ? lone : rans_get(lut, x, wp, next, src);
+                e[t] = LONE ? lone : rans_get<EAGER>(lut, x, wp, next, src);
         } else {
             if constexpr (UPD) {
                 uint32_t one[8];
@@ -263,7 +286,7 @@ __device__ __forceinline__ void walk_ragged(const uint32_t *__restrict__ lut, co
             for (uint32_t t = 0; t < 8; ++t) {
                 e[t] = 0;
                 if (t < valid)
-                    e[t] = LONE ? lone : rans_get(lut, x, wp, next, src);
+                    e[t] = LONE ? lone : rans_get<EAGER>(lut, x, wp, next, src);
             }
         }
         uint4 o = merge_turn<KB, NORM, HALF>(fields, e, spread);
@@ -287,14 +310,15 @@ __device__ __forceinline__ void walk_ragged(const uint32_t *__restrict__ lut, co
     settle(fields);
 }
 
+// SPLIT: the lane walks one half of its state, from or up to the entry point (see rans_get for the step).
 // UPD: the words written are the decoded weights after the update with the gradient `grad` (bf16
 // words, same indexing as the output) and the rate lr.  HALF: the tensor is binary16.
-template <int KB, bool LONE, bool NORM, bool STREAM, bool UPD, bool HALF, uint32_t turns, class WordSrc>
+template <int KB, bool LONE, bool NORM, bool STREAM, bool UPD, bool HALF, bool SPLIT, bool EAGER, class WordSrc>
 __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, const uint2 *__restrict__ spread,
                                            const WordSrc &src, uint32_t lone,
                                            uint32_t &x, uint32_t &wp, const uint8_t *__restrict__ sm,
                                            const uint8_t *__restrict__ coef, uint32_t block,
-                                           uint64_t (&fields)[KB == 7 ? kTurnGroupStream : kTurnGroup],
+                                           uint64_t (&fields)[kTurnsAhead],
                                            uint16_t *__restrict__ out,
                                            uint64_t base, uint32_t m, uint32_t j, uint32_t turn0,
                                            const uint16_t *__restrict__ grad = nullptr, float lr = 0.0f)
@@ -303,6 +327,7 @@ __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, con
     static_assert(!(UPD && HALF), "only bf16 weights are trained");
     // `fields` arrives holding the field bits of the state's first turns (full chunks only)
     constexpr uint32_t kGroup = (STREAM && KB == 7 && !UPD) ? kTurnGroupStream : kTurnGroup;
+    constexpr uint32_t turns = SPLIT ? kMidTurn : kTurns;
     if (__all(m == kChunk)) {  // all chunks of the wave are whole
         uint32_t next = LONE ? 0u : src.peek(wp);
         const uint64_t from = base + turn0 * kTurn;
@@ -339,7 +364,7 @@ __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, con
                 uint32_t e[8];
 #pragma unroll
                 for (int t = 0; t < 8; ++t)
-                    e[t] = LONE ? lone : rans_get(lut, x, wp, next, src);
+                    e[t] = LONE ? lone : rans_get<EAGER>(lut, x, wp, next, src);
                 o[r] = merge_turn<KB, NORM, HALF>(fields[r], e, spread);
                 if constexpr (UPD) {
                     o[r].x = update_pair(o[r].x, grads[r].x, lr);
@@ -367,7 +392,7 @@ __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, con
         }
     } else {
         const uint32_t end = (turn0 + turns) * kTurn;
-        walk_ragged<KB, LONE, NORM, UPD, HALF>(lut, spread, src, lone, x, wp, sm, coef, block, out, base, m < end ? m : end, j,
+        walk_ragged<KB, LONE, NORM, UPD, HALF, EAGER>(lut, spread, src, lone, x, wp, sm, coef, block, out, base, m < end ? m : end, j,
                                                turn0, grad, lr);
     }
 }
@@ -375,13 +400,20 @@ __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, con
 // The same walk for a binary32 tensor (lossless only): the decoded bf16 word is the upper half
 // of the element and the lower half comes from the raw plane, so a turn reads 16 B of lower
 // halves next to its 8 B of fields and writes two 128-bit pieces.
-template <bool LONE, bool STREAM, uint32_t turns, class WordSrc>
+template <bool LONE, bool STREAM, bool SPLIT, bool EAGER, class WordSrc>
 __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut, const WordSrc &src, uint32_t lone,
                                                 uint32_t &x, uint32_t &wp, const uint8_t *__restrict__ sm,
                                                 const uint16_t *__restrict__ low, uint32_t *__restrict__ out,
-                                                uint64_t base, uint32_t m, uint32_t j, uint32_t turn0)
+                                                uint64_t base, uint32_t m, uint32_t j, uint32_t turn0,
+                                                const TurnsAhead &ahead)
 {
     constexpr uint32_t kGroup = kTurnGroup;
+    constexpr uint32_t turns = SPLIT ? kMidTurn : kTurns;
+    // Groups of turns whose inputs are held: one, and the next is requested before it is decoded and moves up behind it; or
+    // two that are used in rotation, each requested again once it is merged (from the entry points, with a wave or two per
+    // SIMD to wait for memory with: 10 M elements 18.5 us with one, 17.6 with two).
+    constexpr uint32_t kDepth = SPLIT ? 2 : 1;
+    static_assert(turns % (kGroup * kDepth) == 0, "whole rotations");
     uint32_t next = LONE ? 0u : src.peek(wp);
     if (__all(m == kChunk)) {
         // where this lane stores: its own pieces 2j and 2j + 1 of a turn's 32, or, after the exchange
@@ -393,82 +425,103 @@ __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut
         const bool odd = lane & 1u;
         const uint4 *low4 = reinterpret_cast<const uint4 *>(low + from) + j;
         const uint64_t first = from + j * kRun;
-        uint64_t fields[kGroup];
-        uint4 lows[kGroup];
-#pragma unroll
-        for (uint32_t r = 0; r < kGroup; ++r) {
-            fields[r] = load_fields<7>(sm, first + r * kTurn);
-            lows[r] = low4[r * kStates];
-        }
-        for (uint32_t q0 = 0; q0 < turns; q0 += kGroup) {
-            uint64_t fields_next[kGroup];
-            uint4 lows_next[kGroup];
-            const uint32_t qn = q0 + kGroup < turns ? q0 + kGroup : q0;  // the last group re-reads its own
+        uint64_t fields[kDepth][kGroup];
+        uint4 lows[kDepth][kGroup];
+        auto request = [&](uint64_t (&f)[kGroup], uint4 (&l)[kGroup], uint32_t q) {
 #pragma unroll
             for (uint32_t r = 0; r < kGroup; ++r) {
-                fields_next[r] = load_fields<7>(sm, first + (qn + r) * kTurn);
-                lows_next[r] = low4[(qn + r) * kStates];
+                f[r] = load_fields<7>(sm, first + (q + r) * kTurn);
+                l[r] = low4[(q + r) * kStates];
             }
-            uint4 o[2 * kGroup];
+        };
+        static_assert(kDepth == 1 || kDepth * kGroup == kTurnsAhead, "requested by the workgroup's beginning");
 #pragma unroll
-            for (uint32_t r = 0; r < kGroup; ++r) {
-                uint32_t e[8];
+        for (uint32_t d = 0; d < kDepth; ++d) {
+            if constexpr (kDepth == 1)
+                request(fields[d], lows[d], 0);
 #pragma unroll
-                for (int t = 0; t < 8; ++t)
-                    e[t] = LONE ? lone : rans_get(lut, x, wp, next, src);
-                const uint32_t h[4] = {merge_pair<7>(fields[r], 0, e[0], e[1]), merge_pair<7>(fields[r], 1, e[2], e[3]),
-                                       merge_pair<7>(fields[r], 2, e[4], e[5]), merge_pair<7>(fields[r], 3, e[6], e[7])};
-                const uint32_t l[4] = {lows[r].x, lows[r].y, lows[r].z, lows[r].w};
-                // element = upper half << 16 | lower half: this lane's 8 elements as 16-byte pieces 2j, 2j + 1
-                // of the turn's 32
-                uint32_t mine[2][4];
+            for (uint32_t r = 0; kDepth > 1 && r < kGroup; ++r) {
+                fields[d][r] = ahead.fields[d * kGroup + r];
+                lows[d][r] = ahead.lows[d * kGroup + r];
+            }
+        }
+        for (uint32_t q0 = 0; q0 < turns; q0 += kGroup * kDepth) {
 #pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    mine[d >> 1][2 * (d & 1)] = __builtin_amdgcn_perm(h[d], l[d], 0x05040100u);
-                    mine[d >> 1][2 * (d & 1) + 1] = __builtin_amdgcn_perm(h[d], l[d], 0x07060302u);
-                }
-                // A 128-bit store of piece 2j by every lane leaves every other 16 bytes of a cache line
-                // to a second instruction.  In the cache that is harmless, but once the tensor streams
-                // to HBM such half-written lines cost a third of the store rate.  There the 8 lanes of
-                // an octet trade pieces: store `half` of lane t writes piece 8 * half + t of the
-                // octet's 16, which lane 4 * half + t / 2 holds (its first piece for even t), and each
-                // store instruction covers whole 128-byte lines.  (The 16 lane exchanges per turn cost
-                // 20 % of the rate of a cache-resident tensor, which therefore keeps the plain stores.)
+            for (uint32_t d = 0; d < kDepth; ++d) {
+                const uint32_t q = q0 + d * kGroup;
+                uint64_t (&f)[kGroup] = fields[d];
+                uint4 (&l)[kGroup] = lows[d];
+                uint64_t fields_next[kGroup];
+                uint4 lows_next[kGroup];
+                // (behind the last group: its own again, in bounds and not used)
+                const uint32_t qn = q + kDepth * kGroup < turns ? q + kDepth * kGroup : q;
+                if constexpr (kDepth == 1)
+                    request(fields_next, lows_next, qn);
+                uint4 o[2 * kGroup];
 #pragma unroll
-                for (int half = 0; half < 2; ++half) {
-                    uint32_t got[4];
+                for (uint32_t r = 0; r < kGroup; ++r) {
+                    uint32_t e[8];
+#pragma unroll
+                    for (int t = 0; t < 8; ++t)
+                        e[t] = LONE ? lone : rans_get<EAGER>(lut, x, wp, next, src);
+                    const uint32_t h[4] = {merge_pair<7>(f[r], 0, e[0], e[1]), merge_pair<7>(f[r], 1, e[2], e[3]),
+                                           merge_pair<7>(f[r], 2, e[4], e[5]), merge_pair<7>(f[r], 3, e[6], e[7])};
+                    const uint32_t lo[4] = {l[r].x, l[r].y, l[r].z, l[r].w};
+                    // element = upper half << 16 | lower half: this lane's 8 elements as 16-byte pieces 2j, 2j + 1
+                    // of the turn's 32
+                    uint32_t mine[2][4];
 #pragma unroll
                     for (int d = 0; d < 4; ++d) {
+                        mine[d >> 1][2 * (d & 1)] = __builtin_amdgcn_perm(h[d], lo[d], 0x05040100u);
+                        mine[d >> 1][2 * (d & 1) + 1] = __builtin_amdgcn_perm(h[d], lo[d], 0x07060302u);
+                    }
+                    // A 128-bit store of piece 2j by every lane leaves every other 16 bytes of a cache line
+                    // to a second instruction.  In the cache that is harmless, but once the tensor streams
+                    // to HBM such half-written lines cost a third of the store rate.  There the 8 lanes of
+                    // an octet trade pieces: store `half` of lane t writes piece 8 * half + t of the
+                    // octet's 16, which lane 4 * half + t / 2 holds (its first piece for even t), and each
+                    // store instruction covers whole 128-byte lines.  (The 16 lane exchanges per turn cost
+                    // 20 % of the rate of a cache-resident tensor, which therefore keeps the plain stores.)
+#pragma unroll
+                    for (int half = 0; half < 2; ++half) {
+                        uint32_t got[4];
+#pragma unroll
+                        for (int d = 0; d < 4; ++d) {
+                            if constexpr (STREAM) {
+                                const uint32_t first = __builtin_amdgcn_ds_bpermute(static_cast<int>(pull[half]),
+                                                                                    static_cast<int>(mine[0][d]));
+                                const uint32_t second = __builtin_amdgcn_ds_bpermute(static_cast<int>(pull[half]),
+                                                                                     static_cast<int>(mine[1][d]));
+                                got[d] = odd ? second : first;
+                            } else {
+                                got[d] = mine[half][d];
+                            }
+                        }
+                        o[2 * r + half] = make_uint4(got[0], got[1], got[2], got[3]);
+                    }
+                }
+                if constexpr (kDepth > 1)
+                    request(f, l, qn);
+#pragma unroll
+                for (uint32_t r = 0; r < kGroup; ++r) {
+#pragma unroll
+                    for (uint32_t half = 0; half < 2; ++half) {
+                        uint4 *dst = &out4[(q + r) * kStates * 2 + half * (STREAM ? 8 : 1)];
+                        const uint4 v = o[2 * r + half];
                         if constexpr (STREAM) {
-                            const uint32_t first = __builtin_amdgcn_ds_bpermute(static_cast<int>(pull[half]),
-                                                                                static_cast<int>(mine[0][d]));
-                            const uint32_t second = __builtin_amdgcn_ds_bpermute(static_cast<int>(pull[half]),
-                                                                                 static_cast<int>(mine[1][d]));
-                            got[d] = odd ? second : first;
+                            __builtin_nontemporal_store(v.x, &dst->x);
+                            __builtin_nontemporal_store(v.y, &dst->y);
+                            __builtin_nontemporal_store(v.z, &dst->z);
+                            __builtin_nontemporal_store(v.w, &dst->w);
                         } else {
-                            got[d] = mine[half][d];
+                            *dst = v;
                         }
                     }
-                    o[2 * r + half] = make_uint4(got[0], got[1], got[2], got[3]);
-                }
-            }
-#pragma unroll
-            for (uint32_t r = 0; r < kGroup; ++r) {
-#pragma unroll
-                for (uint32_t half = 0; half < 2; ++half) {
-                    uint4 *dst = &out4[(q0 + r) * kStates * 2 + half * (STREAM ? 8 : 1)];
-                    const uint4 v = o[2 * r + half];
-                    if constexpr (STREAM) {
-                        __builtin_nontemporal_store(v.x, &dst->x);
-                        __builtin_nontemporal_store(v.y, &dst->y);
-                        __builtin_nontemporal_store(v.z, &dst->z);
-                        __builtin_nontemporal_store(v.w, &dst->w);
-                    } else {
-                        *dst = v;
+                    if constexpr (kDepth == 1) {
+                        f[r] = fields_next[r];
+                        l[r] = lows_next[r];
                     }
                 }
-                fields[r] = fields_next[r];
-                lows[r] = lows_next[r];
             }
         }
     } else {
@@ -495,13 +548,13 @@ __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut
             if (valid == kRun) {
 #pragma unroll
                 for (int t = 0; t < 8; ++t)
-                    e[t] = LONE ? lone : rans_get(lut, x, wp, next, src);
+                    e[t] = LONE ? lone : rans_get<EAGER>(lut, x, wp, next, src);
             } else {
 #pragma unroll
                 for (uint32_t t = 0; t < 8; ++t) {
                     e[t] = 0;
                     if (t < valid)
-                        e[t] = LONE ? lone : rans_get(lut, x, wp, next, src);
+                        e[t] = LONE ? lone : rans_get<EAGER>(lut, x, wp, next, src);
                 }
             }
             const uint32_t h[4] = {merge_pair<7>(fields, 0, e[0], e[1]), merge_pair<7>(fields, 1, e[2], e[3]),
@@ -551,13 +604,85 @@ struct DecodeArgs {
     uint32_t block;       // 0: no block-wise normalisation
     uint32_t stream_out;  // non-zero: the output does not fit the last-level cache, store non-temporally
     uint32_t wg_end;      // batches: first workgroup index after this tensor's
+    uint32_t fit;         // (for the host: chunks whose words fit a workgroup's LDS window)
 };
 
-// Decodes the chunks of workgroup `wg` of one tensor.
-// MODE: what is written -- the decoded bf16 words (kPlain), binary32 words joined with their
+// MODE: what a decoder writes -- the decoded bf16 words (kPlain), binary32 words joined with their
 // lower halves (kWide), the decoded weights after the update of the backward loop (kUpdate), or
 // binary16 words (kHalf).
 enum DecodeMode { kPlain = 0, kWide = 1, kUpdate = 2, kHalf = 3 };
+
+// The walk of the mode.
+template <int KB, bool LONE, bool NORM, bool STREAM, int MODE, bool SPLIT, class WordSrc>
+__device__ __forceinline__ void walk_mode(const uint32_t *__restrict__ lut, const uint2 *__restrict__ spread,
+                                          const WordSrc &src, uint32_t lone, uint32_t &x, uint32_t &wp, const DecodeArgs &a,
+                                          uint32_t block, TurnsAhead &ahead, uint64_t base, uint32_t m, uint32_t j,
+                                          uint32_t turn0)
+{
+    // (a word read from memory is fetched only when it is needed)
+    constexpr bool EAGER = SPLIT && !std::is_same<WordSrc, GlobalWords>::value;
+    if constexpr (MODE == kWide)
+        walk_state_wide<LONE, STREAM, SPLIT, EAGER>(lut, src, lone, x, wp, a.sm, a.low, static_cast<uint32_t *>(a.out), base, m, j,
+                                             turn0, ahead);
+    else
+        walk_state<KB, LONE, NORM, STREAM, MODE == kUpdate, MODE == kHalf, SPLIT, EAGER>(
+            lut, spread, src, lone, x, wp, a.sm, a.coef, block, ahead.fields, static_cast<uint16_t *>(a.out), base, m, j, turn0,
+            a.grad, a.lr);
+}
+
+// 16 bytes per lane from memory straight into LDS: lane l's piece goes to `to` (the same for the wave) + 16 l.
+__device__ __forceinline__ void copy_to_lds(const uint4 *from, uint8_t *to)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(from),
+                                     (__attribute__((address_space(3))) void *)(to), 16, 0, 0);
+}
+
+// A barrier for what the workgroup's waves have written to LDS themselves, which does not wait for direct copies.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// The slot table from the occupied symbols (TableBlock::steps, in LDS), by the whole workgroup; begins: the steps that pieces
+// threadIdx.x and threadIdx.x + blockDim.x (of eight neighbouring slots) begin in.  First every piece is written as if the
+// step it begins in filled it, then every step that starts inside a piece writes its slots of that piece over that: some 60
+// instructions per thread of 256 and a barrier, while a search slot by slot (make_piece) takes 200 for each of its two pieces,
+// and these tables are made by waves that wait for nothing else.  (The caller's barrier is still to come.)
+__device__ __forceinline__ void make_table(const uint32_t *__restrict__ steps, const uint32_t (&begins)[2],
+                                           const TableBlock *__restrict__ tb, uint32_t *__restrict__ lut)
+{
+    const uint32_t tid = threadIdx.x, threads = blockDim.x;
+    auto entry = [](uint32_t here, uint32_t there, uint32_t slot) {
+        return (here & 0xFFu) | ((((there >> 8) - (here >> 8)) & 0xFFFu) << 8) | ((slot - (here >> 8)) << 20);
+    };
+    auto fill = [&](uint32_t piece, uint32_t r) {
+        const uint32_t e = entry(steps[r], steps[r + 1], piece * 8);
+        uint4 *at = reinterpret_cast<uint4 *>(lut) + 2 * piece;
+        at[0] = make_uint4(e, e + (1u << 20), e + (2u << 20), e + (3u << 20));
+        at[1] = make_uint4(e + (4u << 20), e + (5u << 20), e + (6u << 20), e + (7u << 20));
+    };
+#pragma unroll
+    for (uint32_t r = 0; r < 2; ++r)
+        if (tid + r * threads < kM / 8)
+            fill(tid + r * threads, begins[r]);
+    for (uint32_t piece = tid + 2 * threads; piece < kM / 8; piece += threads)  // (small workgroups)
+        fill(piece, tb->step_of[piece]);
+    lds_barrier();
+    for (uint32_t i = tid; i + 1 < kSteps; i += threads) {
+        const uint32_t here = steps[i], there = steps[i + 1];
+        const uint32_t from = here >> 8, piece_end = (from + 7) & ~7u;  // (nothing to write where a piece begins with it)
+        const uint32_t upto = (there >> 8) < piece_end ? there >> 8 : piece_end;
+        for (uint32_t slot = from; slot < upto; ++slot)
+            lut[slot] = entry(here, there, slot);
+    }
+}
+
+// `pieces` such pieces by the workgroup.  The copies are under way when this returns: wait_for_memory_acks, then a barrier.
+__device__ __forceinline__ void copy_run_to_lds(const uint4 *from, uint8_t *to, uint32_t pieces)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    for (uint32_t i = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x & ~63u))); i < pieces;
+         i += blockDim.x)
+        if (i + lane < pieces)
+            copy_to_lds(from + i + lane, to + i * 16);
+}
 
 // How a workgroup comes by the tensor's slot table and how many lanes walk a state, settled at compile time: with a
 // run-time choice of one or two lanes the other blobs lost 2-5 %, and with a run-time choice of the table (a second
@@ -567,6 +692,7 @@ enum DecodeForm {
     kReadTable,  // one lane per state; the slot table is copied from the blob
     kMakeTable,  // one lane per state; the blob is too small to hold the table (its entry points are not used)
     kEntries,    // two lanes per state, from the entry points; the slot table is made
+    kReadDirect, // like kReadTable, cached; the words are copied straight into LDS
 };
 
 template <int KB, bool NORM, int MODE, int FORM>
@@ -574,33 +700,24 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
                                                  uint32_t *__restrict__ steps, uint8_t *__restrict__ stage,
                                                  uint2 *__restrict__ spread)
 {
-    constexpr bool WIDE = MODE == kWide, UPD = MODE == kUpdate, HALF = MODE == kHalf;
-    constexpr bool SPLIT = FORM == kEntries, make_lut = FORM != kReadTable;
+    constexpr bool WIDE = MODE == kWide;
+    constexpr bool make_lut = FORM == kMakeTable;
     static_assert(MODE == kPlain || (KB == 7 && !NORM), "binary32 blobs and trained weights are lossless only");
     const uint32_t block = 31u - static_cast<uint32_t>(__clz(static_cast<int>(a.block | 1u)));  // log2 (a power of two)
     const uint16_t *__restrict__ words = a.words;
     const uint8_t *__restrict__ sm = a.sm;
     const uint8_t *__restrict__ coef = a.coef;
-    const uint16_t *__restrict__ low = a.low;
-    const uint16_t *__restrict__ grad = a.grad;
-    const float lr = a.lr;
     // (blobs of at most 2^24 elements are never beyond the cache, and in a batch that is they are walked whole)
     const bool stream_out = FORM == kMakeTable || (FORM == kReadTable && a.stream_out != 0);
-    void *__restrict__ out_any = a.out;
-    uint16_t *__restrict__ out = static_cast<uint16_t *>(out_any);
+    static_assert(FORM != kEntries, "see decode_from_entries");
     const uint32_t n_chunks = a.n_chunks;
     const uint32_t tid = threadIdx.x;
     const uint32_t threads = blockDim.x;            // a multiple of 64, at most kDecThreads
-    constexpr uint32_t split = SPLIT ? 1u : 0u;     // two lanes per state?
-    const uint32_t chunks_per_wg = (threads / kStates) >> split;
+    const uint32_t chunks_per_wg = threads / kStates;
     const uint32_t c0 = wg * chunks_per_wg;
     const uint32_t c1 = c0 + chunks_per_wg < n_chunks ? c0 + chunks_per_wg : n_chunks;
-    const uint32_t c = c0 + ((tid / kStates) >> split);
+    const uint32_t c = c0 + tid / kStates;
     const uint32_t j = tid % kStates;
-    const uint32_t part = SPLIT ? (tid / kStates) & 1u : 0u;  // before (0) or behind (1) the entry point
-    const uint32_t turn0 = part * kMidTurn;
-    constexpr uint32_t turns = SPLIT ? kMidTurn : kTurns;
-    static_assert(kTurns == 2 * kMidTurn, "halves");
     const bool live = c < n_chunks;
     const uint32_t id = c * kStates + j;
     const uint64_t base = static_cast<uint64_t>(c) * kChunk;
@@ -612,8 +729,6 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
     const uint32_t off_c = live ? a.offsets[c] : 0u;
     uint32_t x = live ? a.states[id] : kRansL;
     const uint32_t len = live ? a.lens[id] : 0u;
-    const uint32_t mid_x = live && SPLIT ? a.mid_states[id] : kRansL;
-    const uint32_t mid_len = live && SPLIT ? a.mid_lens[id] : len;
     const uint32_t lone = a.tb->lone;
     // the tensor's table: its steps (blobs with entry points) or the slot table itself
     const uint4 *table_g = reinterpret_cast<const uint4 *>(make_lut ? a.tb->steps : a.tb->lut);
@@ -628,11 +743,12 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
     uint32_t first_step = 0;  // of this thread's first piece of the slot table
     if constexpr (make_lut)
         first_step = a.tb->step_of[tid];
-    constexpr uint32_t kPreload = KB == 7 ? kTurnGroupStream : kTurnGroup;  // the largest group a variant uses
-    uint64_t fields0[kPreload];
+    TurnsAhead ahead;
 #pragma unroll
-    for (uint32_t r = 0; r < kPreload; ++r)
-        fields0[r] = !WIDE && m == kChunk ? load_turn<KB, NORM>(sm, coef, block, base + (turn0 + r) * kTurn + j * kRun) : 0;
+    for (uint32_t r = 0; r < kTurnsAhead; ++r)
+        ahead.fields[r] = !WIDE && m == kChunk && r < (KB == 7 ? kTurnGroupStream : kTurnGroup)  // (the largest group of the width)
+                              ? load_turn<KB, NORM>(sm, coef, block, base + r * kTurn + j * kRun)
+                              : 0;
     // ---- the word runs of chunks [c0, c1), one contiguous piece of the blob, into LDS
     const uint64_t byte0 = static_cast<uint64_t>(off0) * 2;
     const uint64_t byte1 = static_cast<uint64_t>(off1) * 2;
@@ -655,7 +771,12 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
                 spread[i] = spread_entry<KB>(i);
         }
     };
-    if constexpr (!make_lut) {
+    if constexpr (FORM == kReadDirect) {
+        if (staged)
+            copy_run_to_lds(from, stage, static_cast<uint32_t>(stage_len + 15) / 16);
+        table_to_lds();
+        wait_for_memory_acks();
+    } else if constexpr (!make_lut) {
         if (staged) {
             for (uint32_t i = tid; static_cast<uint64_t>(i) * 16 < stage_len; i += threads)
                 to[i] = from[i];
@@ -691,7 +812,7 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
     }
     __syncthreads();
 
-    // ---- one lane, one state (or half of one)
+    // ---- one lane, one state
     if (!live)
         return;
     // start of this state's run: chunk offset + lengths of the states before it (16-lane prefix)
@@ -703,71 +824,170 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
             before += o;
     }
     before -= len;
+    const uint64_t run_byte = (static_cast<uint64_t>(off_c) + before) * 2;
+
+    uint32_t wp = 0, wp_begin = 0;
+    // (the streaming and the cached store variants are separate instantiations: merged into one
+    // loop the compiler drops the non-temporal hint)
+    auto walk = [&](auto alone, const auto &src, uint32_t only) {
+        constexpr bool LONE = decltype(alone)::value;
+        if (stream_out)
+            walk_mode<KB, LONE, NORM, true, MODE, false>(lut, spread, src, only, x, wp, a, block, ahead, base, m, j, 0u);
+        else
+            walk_mode<KB, LONE, NORM, false, MODE, false>(lut, spread, src, only, x, wp, a, block, ahead, base, m, j, 0u);
+    };
+    if (lone < 256) {
+        walk(std::true_type{}, NoWords{}, lone);
+    } else if (staged) {
+        wp = wp_begin = static_cast<uint32_t>(run_byte - aligned0);
+        walk(std::false_type{}, LdsWords{stage}, 0u);
+    } else {
+        // the runs of this workgroup's chunks did not fit the LDS window (more than ~4 bits per
+        // symbol): read the words straight from the blob
+        walk(std::false_type{}, GlobalWords{reinterpret_cast<const uint8_t *>(words) + run_byte}, 0u);
+    }
+    // a well-formed run is consumed exactly and leaves the state where the encoder started
+    if (x != kRansL || wp - wp_begin != 2 * len)
+        atomicOr(a.status, 1u);
+}
+
+// The same from the entry points: two lanes walk the halves of a state.  A launch of such blobs has a wave or two per SIMD,
+// so its time is the workgroup's beginning -- a chain of memory latencies: arguments, tables and offsets, words -- and the
+// walk's instructions, one after the other.  So nothing in the beginning is behind a branch (lanes without a chunk read the
+// last one's: a masked load made the wave wait for the loads before it), the words go to LDS without passing through
+// registers while the slot table is made, and the start of a lane's run is worked out meanwhile.  With the steps of the walk
+// without a branch (see rans_get) and the table made by make_table: 4 M elements 13.5 -> 10.7 us, of which the beginning
+// 3.9 -> 2.7 and the walk 9.5 -> 7.7, 0.05 M 11.8 -> 9.5, 16.8 M 15.8 -> 14.0, 10 M binary32 elements 20.3 -> 16.4; words
+// through registers 11.8 (4 M), 15.5 (16.8 M).
+template <int KB, bool NORM, int MODE>
+__device__ __forceinline__ void decode_from_entries(const DecodeArgs &a, uint32_t wg, uint32_t *__restrict__ lut,
+                                                    uint32_t *__restrict__ steps, uint8_t *__restrict__ stage,
+                                                    uint2 *__restrict__ spread)
+{
+    static_assert(MODE == kPlain || (KB == 7 && !NORM), "binary32 blobs and trained weights are lossless only");
+    static_assert(kTurns == 2 * kMidTurn, "halves");
+    const uint32_t block = 31u - static_cast<uint32_t>(__clz(static_cast<int>(a.block | 1u)));  // log2 (a power of two)
+    const uint32_t n_chunks = a.n_chunks, tid = threadIdx.x, threads = blockDim.x;
+    const uint32_t chunks_per_wg = threads / (2 * kStates);
+    const uint32_t c0 = wg * chunks_per_wg;
+    const uint32_t c1 = c0 + chunks_per_wg < n_chunks ? c0 + chunks_per_wg : n_chunks;
+    const uint32_t c = c0 + tid / (2 * kStates);
+    const uint32_t j = tid % kStates;
+    const uint32_t part = (tid / kStates) & 1u;  // before (0) or behind (1) the entry point
+    const uint32_t turn0 = part * kMidTurn;
+    const bool live = c < n_chunks;
+    const uint64_t base = static_cast<uint64_t>(c) * kChunk;
+    const uint32_t m = !live ? 0u : ((a.n - base) < kChunk ? static_cast<uint32_t>(a.n - base) : kChunk);
+
+    // ---- every load that depends on nothing
+    const uint32_t off0 = a.offsets[c0];
+    const uint32_t off1 = a.offsets[c1];
+    const uint32_t c_in = live ? c : n_chunks - 1;
+    const uint32_t id = c_in * kStates + j;
+    const uint32_t off_c = a.offsets[c_in];
+    const uint32_t first_x = a.states[id], mid_x = a.mid_states[id];
+    const uint32_t len = a.lens[id], mid_len = a.mid_lens[id];
+    const uint32_t lone = a.tb->lone;
+    const uint4 *steps_g = reinterpret_cast<const uint4 *>(a.tb->steps);
+    constexpr uint32_t kStepPieces = kSteps / 4;  // of 16 bytes
+    const uint4 step_piece = steps_g[tid < kStepPieces ? tid : kStepPieces - 1];
+    // the steps that this thread's first two pieces of the slot table begin in (512 pieces: all, from 256 threads on)
+    uint32_t begins[2];
+#pragma unroll
+    for (uint32_t r = 0; r < 2; ++r)
+        begins[r] = a.tb->step_of[min(tid + r * threads, kM / 8 - 1)];
+    // the first turns' inputs (addresses stay inside the tensor; a lane whose chunk is not whole makes no use of what it gets)
+    TurnsAhead ahead = {};
+    const uint32_t last_run = static_cast<uint32_t>(a.n - 1) & ~(kRun - 1);  // (such tensors have at most 2^24 elements)
+    auto request_ahead = [&]() {
+#pragma unroll
+        for (uint32_t r = 0; r < kTurnsAhead; ++r) {
+            const uint32_t at = min(c_in * kChunk + (turn0 + r) * kTurn + j * kRun, last_run);
+            if (MODE == kWide || r < kTurnGroup)
+                ahead.fields[r] = load_turn<KB, NORM>(a.sm, a.coef, block, at);
+            if constexpr (MODE == kWide)
+                ahead.lows[r] = *reinterpret_cast<const uint4 *>(a.low + at);
+        }
+    };
+    __builtin_amdgcn_sched_barrier(0);  // (behind what the table is made of, which is waited for first)
+    if constexpr (MODE != kWide)
+        request_ahead();
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- the steps, then (as soon as the offsets are there) the word runs of chunks [c0, c1), one contiguous piece of the
+    // blob, into LDS
+    if (tid < kStepPieces)
+        reinterpret_cast<uint4 *>(steps)[tid] = step_piece;
+    for (uint32_t i = tid + threads; i < kStepPieces; i += threads)  // (workgroups of one wave)
+        reinterpret_cast<uint4 *>(steps)[i] = steps_g[i];
+    const uint64_t byte0 = static_cast<uint64_t>(off0) * 2, byte1 = static_cast<uint64_t>(off1) * 2;
+    const uint64_t aligned0 = byte0 & ~static_cast<uint64_t>(15);
+    const uint64_t stage_len = byte1 - aligned0;
+    const bool staged = stage_len + 16 <= kStageBytesOf<KB>;  // room for the one-word look-ahead
+    asm volatile("" : "+v"(begins[0]), "+v"(begins[1]));  // (taken here, and not waited for behind the words)
+    if (staged)
+        copy_run_to_lds(reinterpret_cast<const uint4 *>(reinterpret_cast<const uint8_t *>(a.words) + aligned0), stage,
+                        static_cast<uint32_t>(stage_len + 15) / 16);
+    if constexpr (KB <= 1) {
+        for (uint32_t i = tid; i < kSpreadEntries<KB>; i += threads)
+            spread[i] = spread_entry<KB>(i);
+    }
+    // where this lane begins and ends: the run starts behind those of the states before it in the chunk (a row of 16 lanes)
+    const uint32_t before = row_scan_u32(len) - len + (part ? mid_len : 0u);
+    const uint64_t run_byte = (static_cast<uint64_t>(off_c) + before) * 2;
+    uint32_t x = part ? mid_x : first_x;
     // a well-formed run is consumed exactly and leaves the state where the encoder started; the half before the
     // entry point ends there
     const uint32_t x_end = part ? kRansL : mid_x;
     const uint32_t words_here = part ? len - mid_len : mid_len;
-    if (part) {
-        x = mid_x;
-        before += mid_len;
-    }
-    const uint64_t run_byte = (static_cast<uint64_t>(off_c) + before) * 2;
-
-    // (the streaming and the cached store variants are separate instantiations: merged into one
-    // loop the compiler drops the non-temporal hint)
+    lds_barrier();
+    if (lone >= 256)
+        make_table(steps, begins, a.tb, lut);
+    wait_for_memory_acks();  // the words
+    __syncthreads();
+    if (!live)
+        return;
+    if constexpr (MODE == kWide)  // (four times the bytes, which in front of the words are in their way: 10 M elements 18.7 / 18.1 us)
+        request_ahead();
     uint32_t wp = 0, wp_begin = 0;
-    if constexpr (WIDE) {
-        uint32_t *out32 = static_cast<uint32_t *>(out_any);
-        if (lone < 256) {
-            if (stream_out)
-                walk_state_wide<true, true, turns>(lut, NoWords{}, lone, x, wp, sm, low, out32, base, m, j, turn0);
-            else
-                walk_state_wide<true, false, turns>(lut, NoWords{}, lone, x, wp, sm, low, out32, base, m, j, turn0);
-        } else if (staged) {
-            wp = wp_begin = static_cast<uint32_t>(run_byte - aligned0);
-            if (stream_out)
-                walk_state_wide<false, true, turns>(lut, LdsWords{stage}, 0u, x, wp, sm, low, out32, base, m, j, turn0);
-            else
-                walk_state_wide<false, false, turns>(lut, LdsWords{stage}, 0u, x, wp, sm, low, out32, base, m, j, turn0);
-        } else {
-            const GlobalWords direct{reinterpret_cast<const uint8_t *>(words) + run_byte};
-            if (stream_out)
-                walk_state_wide<false, true, turns>(lut, direct, 0u, x, wp, sm, low, out32, base, m, j, turn0);
-            else
-                walk_state_wide<false, false, turns>(lut, direct, 0u, x, wp, sm, low, out32, base, m, j, turn0);
-        }
-    } else if (lone < 256) {
-        if (stream_out)
-            walk_state<KB, true, NORM, true, UPD, HALF, turns>(lut, spread, NoWords{}, lone, x, wp, sm, coef, block, fields0, out, base, m, j, turn0, grad, lr);
-        else
-            walk_state<KB, true, NORM, false, UPD, HALF, turns>(lut, spread, NoWords{}, lone, x, wp, sm, coef, block, fields0, out, base, m, j, turn0, grad, lr);
+    if (lone < 256) {
+        walk_mode<KB, true, NORM, false, MODE, true>(lut, spread, NoWords{}, lone, x, wp, a, block, ahead, base, m, j, turn0);
     } else if (staged) {
         wp = wp_begin = static_cast<uint32_t>(run_byte - aligned0);
-        if (stream_out)
-            walk_state<KB, false, NORM, true, UPD, HALF, turns>(lut, spread, LdsWords{stage}, 0u, x, wp, sm, coef, block, fields0, out, base, m, j, turn0, grad, lr);
-        else
-            walk_state<KB, false, NORM, false, UPD, HALF, turns>(lut, spread, LdsWords{stage}, 0u, x, wp, sm, coef, block, fields0, out, base, m, j, turn0, grad, lr);
+        walk_mode<KB, false, NORM, false, MODE, true>(lut, spread, LdsWords{stage}, 0u, x, wp, a, block, ahead, base, m, j, turn0);
     } else {
-        // the runs of this workgroup's chunks did not fit the LDS window (more than ~4 bits per
-        // symbol): read the words straight from the blob
-        const GlobalWords direct{reinterpret_cast<const uint8_t *>(words) + run_byte};
-        if (stream_out)
-            walk_state<KB, false, NORM, true, UPD, HALF, turns>(lut, spread, direct, 0u, x, wp, sm, coef, block, fields0, out, base, m, j, turn0, grad, lr);
-        else
-            walk_state<KB, false, NORM, false, UPD, HALF, turns>(lut, spread, direct, 0u, x, wp, sm, coef, block, fields0, out, base, m, j, turn0, grad, lr);
+        const GlobalWords direct{reinterpret_cast<const uint8_t *>(a.words) + run_byte};
+        walk_mode<KB, false, NORM, false, MODE, true>(lut, spread, direct, 0u, x, wp, a, block, ahead, base, m, j, turn0);
     }
     if (x != x_end || wp - wp_begin != 2 * words_here)
         atomicOr(a.status, 1u);
 }
 
+// The LDS of a workgroup.  The words come first: a direct copy's LDS address has 16 bits.
+template <int KB, bool MADE>
+struct DecodeLds {
+    uint8_t stage[kStageBytesOf<KB>];
+    uint32_t lut[kM];
+    uint2 spread[kSpreadEntries<KB>];
+    uint32_t steps[MADE ? kSteps : 2];
+    static_assert(kStageBytesOf<KB> <= 65536 && kStageBytesOf<KB> % 16 == 0, "within reach, and the table behind it aligned");
+};
+
 template <int KB, bool NORM, int MODE, bool SPLIT>
 __global__ __launch_bounds__(kDecThreads) void decode_kernel(const DecodeArgs a)
 {
-    __shared__ __align__(16) uint32_t lut[kM];
-    __shared__ __align__(16) uint8_t stage[kStageBytesOf<KB>];
-    __shared__ uint2 spread[kSpreadEntries<KB>];
-    __shared__ __align__(16) uint32_t steps[SPLIT ? kSteps : 4];
-    decode_workgroup<KB, NORM, MODE, SPLIT ? kEntries : kReadTable>(a, blockIdx.x, lut, steps, stage, spread);
+    __shared__ __align__(16) DecodeLds<KB, SPLIT> lds;
+    if constexpr (SPLIT)
+        decode_from_entries<KB, NORM, MODE>(a, blockIdx.x, lds.lut, lds.steps, lds.stage, lds.spread);
+    else
+        decode_workgroup<KB, NORM, MODE, kReadTable>(a, blockIdx.x, lds.lut, lds.steps, lds.stage, lds.spread);
+}
+
+// The launch whose workgroups nearly all run at once, two on every CU (see copies_directly).
+template <int KB, bool NORM>
+__global__ __launch_bounds__(kDecThreads) void decode_direct_kernel(const DecodeArgs a)
+{
+    __shared__ __align__(16) DecodeLds<KB, false> lds;
+    decode_workgroup<KB, NORM, kPlain, kReadDirect>(a, blockIdx.x, lds.lut, lds.steps, lds.stage, lds.spread);
 }
 
 // Several tensors in one launch (a layer's weights): workgroups [t[i-1].wg_end, t[i].wg_end)
@@ -775,6 +995,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(const DecodeArgs a)
 struct BatchArgs {
     DecodeArgs t[kBatchMax];
     uint32_t count;
+    uint32_t threads;  // (for the host: of a workgroup)
 };
 
 // FORM: how the blobs of the batch that have entry points (kEntries) or no slot table (kMakeTable) are walked; the
@@ -782,23 +1003,26 @@ struct BatchArgs {
 template <int KB, bool NORM, int MODE, int FORM>
 __global__ __launch_bounds__(kDecThreads) void decode_batch_kernel(const BatchArgs b)
 {
-    __shared__ __align__(16) uint32_t lut[kM];
-    __shared__ __align__(16) uint8_t stage[kStageBytesOf<KB>];
-    __shared__ uint2 spread[kSpreadEntries<KB>];
-    __shared__ __align__(16) uint32_t steps[FORM == kReadTable ? 4 : kSteps];
+    __shared__ __align__(16) DecodeLds<KB, FORM != kReadTable> lds;
     uint32_t i = 0, first = 0;
     while (i + 1 < b.count && blockIdx.x >= b.t[i].wg_end) {
         first = b.t[i].wg_end;
         ++i;
     }
     const DecodeArgs a = b.t[i];
-    if constexpr (FORM != kReadTable) {
-        if (FORM == kEntries ? a.mid_states != nullptr : !holds_table(a.n_chunks)) {
-            decode_workgroup<KB, NORM, MODE, FORM>(a, blockIdx.x - first, lut, steps, stage, spread);
+    if constexpr (FORM == kEntries) {
+        if (a.mid_states) {
+            decode_from_entries<KB, NORM, MODE>(a, blockIdx.x - first, lds.lut, lds.steps, lds.stage, lds.spread);
             return;
         }
     }
-    decode_workgroup<KB, NORM, MODE, kReadTable>(a, blockIdx.x - first, lut, steps, stage, spread);
+    if constexpr (FORM == kMakeTable) {
+        if (!holds_table(a.n_chunks)) {
+            decode_workgroup<KB, NORM, MODE, kMakeTable>(a, blockIdx.x - first, lds.lut, lds.steps, lds.stage, lds.spread);
+            return;
+        }
+    }
+    decode_workgroup<KB, NORM, MODE, kReadTable>(a, blockIdx.x - first, lds.lut, lds.steps, lds.stage, lds.spread);
 }
 
 // The entry points of an imported blob: every lane walks its state to them, writing nothing.  A workgroup's words go
@@ -812,15 +1036,16 @@ template <class WordSrc>
 __device__ __forceinline__ void walk_to_entry(const uint32_t *__restrict__ lut, const WordSrc &src, uint32_t m, uint32_t j,
                                               uint32_t &x, uint32_t &wp)
 {
+    constexpr bool EAGER = !std::is_same<WordSrc, GlobalWords>::value;
     uint32_t next = src.peek(wp);
     for (uint32_t at = j * kRun; at < m && at < kMidTurn * kTurn; at += kTurn) {
         if (m - at >= kRun) {
 #pragma unroll
             for (uint32_t t = 0; t < kRun; ++t)
-                rans_get(lut, x, wp, next, src);
+                rans_get<EAGER>(lut, x, wp, next, src);
         } else {
             for (uint32_t t = 0; t < m - at; ++t)
-                rans_get(lut, x, wp, next, src);
+                rans_get<EAGER>(lut, x, wp, next, src);
         }
     }
 }

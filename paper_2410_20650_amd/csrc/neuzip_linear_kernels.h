@@ -207,7 +207,7 @@ __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, co
             uint32_t e[8];
 #pragma unroll
             for (int t = 0; t < 8; ++t)
-                e[t] = LONE ? lone : rans_get(lut, x, wp, next, src);
+                e[t] = LONE ? lone : rans_get<false>(lut, x, wp, next, src);
             b.u[0] = merge_pair<KB>(fields, 0, e[0], e[1]);
             b.u[1] = merge_pair<KB>(fields, 1, e[2], e[3]);
             b.u[2] = merge_pair<KB>(fields, 2, e[4], e[5]);

@@ -167,9 +167,8 @@ inline bool on_current_device(const neuzip_blob *b)
 struct Workspace {
     int device = -1;
     uint32_t *counts = nullptr;       // kBatchMax x 256 histogram bins, zero between compress calls; behind them, in
-                                      // the same allocation, the two copies of the call state and a counter
+                                      // the same allocation, the two copies of the call state
     CallState *state = nullptr;       // [2], used by alternate calls (stamp & 1)
-    uint32_t *all_done = nullptr;     // tensors of the batch that have been reported to the host
     uint32_t *super_words = nullptr;  // [2][super_cap] words per 64 encoder groups, used by alternate calls
     uint32_t super_cap = 0;
     uint32_t *chunk_words = nullptr;  // words per chunk
@@ -210,15 +209,20 @@ int release_workspace_locked()
     return rc;
 }
 
-// Waits until the encode kernel of call `seq` has published its record.  The stamp arrives a
-// few microseconds after the kernel's last store, well before a blocking stream synchronise would
+// Waits until the encode kernel of call `seq` has published its record.  The stamp arrives when its last
+// workgroup ends, before the compaction behind it and well before a blocking stream synchronise would
 // wake up; after a bounded spin the stream is synchronised anyway, which also surfaces errors.
-bool wait_for_record(uint32_t seq, hipStream_t stream)
+bool wait_for_record(uint32_t seq, uint32_t items, hipStream_t stream)
 {
-    const volatile uint32_t *stamp = &g_ws.pinned->seq;
+    auto complete = [&]() {
+        for (uint32_t i = 0; i < items; ++i)
+            if (told_stamp(__atomic_load_n(&g_ws.pinned->item[i].told, __ATOMIC_ACQUIRE)) != (seq & kStampMask))
+                return false;
+        return true;
+    };
     const auto start = std::chrono::steady_clock::now();
     for (uint32_t spins = 0;; ++spins) {
-        if (__atomic_load_n(stamp, __ATOMIC_ACQUIRE) == seq)
+        if (complete())
             return true;
         if ((spins & 1023u) == 1023u &&
             std::chrono::steady_clock::now() - start > std::chrono::milliseconds(20))
@@ -226,11 +230,11 @@ bool wait_for_record(uint32_t seq, hipStream_t stream)
     }
     if (!hip_ok(hipStreamSynchronize(stream)))
         return false;
-    return __atomic_load_n(stamp, __ATOMIC_ACQUIRE) == seq;
+    return complete();
 }
 
-// Words of the small allocation: the histogram bins of a batch, two call states, a counter (padded).
-constexpr uint32_t kSmallWords = kBatchMax * 256 + 2 * sizeof(CallState) / 4 + 16;
+// Words of the small allocation: the histogram bins of a batch, two call states.
+constexpr uint32_t kSmallWords = kBatchMax * 256 + 2 * sizeof(CallState) / 4;
 // Entries of one copy of the per-64-groups array for a batch of n_groups encoder groups in all: every
 // tensor of the batch may end with a partial block.
 inline uint32_t super_entries(uint64_t n_groups) { return static_cast<uint32_t>(n_groups / kSuperGroups + kBatchMax + 1); }
@@ -253,7 +257,6 @@ int create_workspace(int device, hipStream_t stream)
     g_ws.device = device;
     NZ_HIP(hipMalloc(reinterpret_cast<void **>(&g_ws.counts), kSmallWords * sizeof(uint32_t)));
     g_ws.state = reinterpret_cast<CallState *>(g_ws.counts + kBatchMax * 256);
-    g_ws.all_done = g_ws.counts + kBatchMax * 256 + 2 * sizeof(CallState) / 4;
     NZ_HIP(hipHostMalloc(reinterpret_cast<void **>(&g_ws.pinned), sizeof(HostRecord), hipHostMallocDefault));
     std::memset(g_ws.pinned, 0, sizeof(HostRecord));
     g_ws.seq = 0;
@@ -753,8 +756,7 @@ bool launch_compaction(const Workspace &ws, const CompressBatch &batch, uint32_t
                        CallState *state, CallState *state_next, uint32_t *super_next, hipStream_t stream)
 {
     hipLaunchKernelGGL(compact_kernel, dim3(workgroups), dim3(kCompactThreads), 0, stream, batch, ws.slots, ws.chunk_words,
-                       ws.group_words, super_words, state, ws.counts, state_next, super_next, ws.super_cap, ws.all_done,
-                       ws.pinned);
+                       ws.group_words, super_words, state, ws.counts, state_next, super_next, ws.super_cap);
     return hip_ok(hipGetLastError());
 }
 
@@ -876,15 +878,15 @@ int compress_tiled(neuzip_blob *b, const void *d_src, const void *d_grad, int k,
         if (!launch_encode(ws, batch, it.enc_end + (!reuse && g0 == 0 ? 1u : 0u), variant, reuse, elem, block, super_words, state,
                            stream))
             return fail(NEUZIP_EHIP);
-        bins_dirty = true;  // (sums of this tile; the compaction's report clears them)
-        batch.report = 1;
+        bins_dirty = true;  // (sums of this tile; the compaction clears them)
+        batch.tidy = 1;
         if (!launch_compaction(ws, batch, it.compact_end, super_words, state, state_next, super_next, stream))
             return fail(NEUZIP_EHIP);
-        if (!wait_for_record(batch.seq, stream))
+        if (!wait_for_record(batch.seq, batch.count, stream))
             return fail(NEUZIP_EHIP);
         bins_dirty = !reuse && !last;  // the histogram bins stay until the last tile has been encoded
         const HostRecord::Item &r = ws.pinned->item[0];
-        if (reuse && r.stale) {
+        if (reuse && told_stale(r.told)) {
             // The table does not cover this tile: the tensor will be compressed afresh.  A weight step
             // that writes the new weights back still has to reach the remaining tiles.
             *stale = true;
@@ -894,9 +896,9 @@ int compress_tiled(neuzip_blob *b, const void *d_src, const void *d_grad, int k,
                 return NEUZIP_OK;
             }
         }
-        if (r.total_words[1] != 0)
+        if (told_beyond(r.told))
             return fail(NEUZIP_EUNSUPPORTED);
-        const uint64_t upto = words_before + r.total_words[0];
+        const uint64_t upto = words_before + told_words(r.told);
         if (upto >= (1ull << 32))
             return fail(NEUZIP_EUNSUPPORTED);  // more than 2^32 words
         if (!*stale && upto > it.words_cap) {
@@ -907,7 +909,7 @@ int compress_tiled(neuzip_blob *b, const void *d_src, const void *d_grad, int k,
                 return fail(rc);
             it.words = reinterpret_cast<uint16_t *>(b->words);
             it.words_cap = words_room(b);
-            batch.report = 0;
+            batch.tidy = 0;
             if (!launch_compaction(ws, batch, it.compact_end, super_words, state, state_next, super_next, stream))
                 return fail(NEUZIP_EHIP);
         }
@@ -1108,9 +1110,8 @@ int compress_some(const void *const *d_srcs, const uint64_t *n_elems, uint32_t c
         // Three launches.  The histogram pass (fresh statistics only).  The encoder, every workgroup of
         // which derives the table from the counts by itself; with fresh tables its launch carries one
         // more workgroup per tensor, which fills in the decoder's slot table meanwhile (of blobs that
-        // hold one).  The compaction,
-        // which also works out the chunk offsets, tells the host the stream lengths and returns the
-        // workspace's sums to zero.
+        // hold one); its last workgroup tells the host the stream lengths.  The compaction,
+        // which also works out the chunk offsets and returns the workspace's sums to zero.
         const int variant = d_grads ? kUpdateVariant : (elem == NEUZIP_F32 ? 23 : (elem == NEUZIP_F16 ? 39 : k));
         if (!reuse) {
             launch_histogram(ws, batch, variant, block != 0, hist_groups, hist_threads, stream);
@@ -1126,15 +1127,15 @@ int compress_some(const void *const *d_srcs, const uint64_t *n_elems, uint32_t c
         // The stream lengths are data dependent.  The compaction is launched right away all the same:
         // a blob that already has a word section (one that is compressed into again, as in a training
         // loop) has its words moved into the room it has, and the kernel itself leaves a tensor alone
-        // whose words turn out not to fit, or whose kept table turned out stale.  It also writes the
-        // lengths into pinned host memory, the stamp last, which is what the host then waits for.
+        // whose words turn out not to fit, or whose kept table turned out stale.  The lengths come from
+        // the encoder, through pinned host memory, the stamp last, which is what the host then waits for.
         for (uint32_t j = 0; j < batch.count; ++j) {
             const neuzip_blob *b = work[owner[j]];
             batch.it[j].words = reinterpret_cast<uint16_t *>(b->words);
             batch.it[j].words_cap = words_room(b);
         }
-        auto launch_compact = [&](bool report) {
-            batch.report = report ? 1u : 0u;
+        auto launch_compact = [&](bool tidy) {
+            batch.tidy = tidy ? 1u : 0u;
             return launch_compaction(ws, batch, compact_groups, super_words, state, state_next, super_next, stream);
         };
         if (!launch_compact(true))
@@ -1146,7 +1147,7 @@ int compress_some(const void *const *d_srcs, const uint64_t *n_elems, uint32_t c
                                        hipMemcpyDeviceToHost, stream)) ||
                 !hip_ok(hipStreamSynchronize(stream)))
                 return fail(NEUZIP_EHIP);
-        } else if (!wait_for_record(batch.seq, stream)) {
+        } else if (!wait_for_record(batch.seq, batch.count, stream)) {
             return fail(NEUZIP_EHIP);
         }
         uint32_t n_stale = 0;
@@ -1154,7 +1155,7 @@ int compress_some(const void *const *d_srcs, const uint64_t *n_elems, uint32_t c
         for (uint32_t j = 0; j < batch.count; ++j) {
             const HostRecord::Item &r = fixed_ws ? fetched[j] : ws.pinned->item[j];
             neuzip_blob *b = work[owner[j]];
-            if (reuse && r.stale) {
+            if (reuse && told_stale(r.told)) {
                 // its table does not cover the new values: nothing of this pass is kept (the
                 // compaction has left such a tensor alone); it is compressed afresh below
                 stale_src[n_stale] = d_srcs[owner[j]];
@@ -1166,21 +1167,21 @@ int compress_some(const void *const *d_srcs, const uint64_t *n_elems, uint32_t c
                 batch.it[j].n_chunks = 0;
                 continue;
             }
-            if (r.total_words[1] != 0)
+            if (told_beyond(r.told))
                 return fail(NEUZIP_EUNSUPPORTED);  // more than 2^32 words
-            if (r.total_words[0] <= batch.it[j].words_cap) {
+            if (told_words(r.told) <= batch.it[j].words_cap) {
                 batch.it[j].n_chunks = 0;  // in place already: the kernel took the same decision
             } else {
                 if (fixed_ws)  // no allocation: the stream must fit the room the blob has
                     return fail(NEUZIP_ENOMEM);
-                rc = reserve_words(b, r.total_words[0]);
+                rc = reserve_words(b, told_words(r.told));
                 if (rc != NEUZIP_OK)
                     return fail(rc);
                 batch.it[j].words = reinterpret_cast<uint16_t *>(b->words);
                 batch.it[j].words_cap = words_room(b);
                 late = true;
             }
-            b->total_words = r.total_words[0];
+            b->total_words = told_words(r.told);
             if (!reuse) {
                 std::memcpy(b->h_counts, r.counts, 1024);
                 std::memcpy(b->h_freq, r.freq, 512);
@@ -1581,7 +1582,7 @@ namespace {
 constexpr uint32_t kFixedChunks = static_cast<uint32_t>(NEUZIP_NOALLOC_MAX_ELEMS / kChunk);
 constexpr uint32_t kFixedGroups = kFixedChunks / kChunksPerGroup;
 static_assert(NEUZIP_NOALLOC_MAX_ELEMS % (kChunk * kChunksPerGroup) == 0, "whole encoder groups");
-constexpr uint64_t kFixedCountsAt = 0;                                                     // bins, call states, counter
+constexpr uint64_t kFixedCountsAt = 0;                                                     // bins, call states
 constexpr uint64_t kFixedRecordAt = kFixedCountsAt + pad_to(kSmallWords * 4, 256);
 constexpr uint64_t kFixedChunkWordsAt = kFixedRecordAt + pad_to(sizeof(HostRecord), 256);
 constexpr uint64_t kFixedGroupWordsAt = kFixedChunkWordsAt + pad_to((kFixedChunks + 4) * 4, 256);
@@ -1644,7 +1645,6 @@ int neuzip_compress_noalloc(const void *d_src, uint64_t n_elems, int dtype, int 
     ws.device = device;
     ws.counts = reinterpret_cast<uint32_t *>(base + kFixedCountsAt);
     ws.state = reinterpret_cast<CallState *>(ws.counts + kBatchMax * 256);
-    ws.all_done = ws.counts + kBatchMax * 256 + 2 * sizeof(CallState) / 4;
     ws.super_words = reinterpret_cast<uint32_t *>(base + kFixedSuperAt);
     ws.super_cap = kFixedSuperCap;
     ws.pinned = reinterpret_cast<HostRecord *>(base + kFixedRecordAt);  // device memory here: copied out, not read in place

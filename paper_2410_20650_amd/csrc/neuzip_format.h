@@ -152,15 +152,17 @@ struct CompressBatch {
     uint32_t seq;  // stamp of this call
     float lr;      // learning rate of the fused weight step
     uint32_t keep_new;  // fused weight step: write the new weight back over the source
-    uint32_t report;    // compaction launch: also report the stream lengths to the host and tidy the workspace
+    uint32_t tidy;      // compaction launch: also close the offsets and tidy the workspace
     uint32_t keep_counts;  // ... but leave the histogram bins: further tiles of the tensor need them
 };
 
-// What the encoder workgroups of a call add up for the compaction and for the host, in the workspace.
+// What the encoder workgroups of a call add up for the compaction and for the host, in the workspace.  (A tensor's words
+// are fewer than 2^32 and its encoder workgroups at most 2^16: both fit one atomic, whose result tells who is last.)
 // There are two copies, used by alternate calls: while one call's compaction reads its copy, it
 // returns the other one (and the histogram bins) to zero for the call that follows.
+constexpr unsigned long long kOneDone = 1ull << 40;
 struct CallState {
-    unsigned long long total[kBatchMax];  // words of tensor i
+    unsigned long long total[kBatchMax];  // words of tensor i, + kOneDone per workgroup that has added its own
     uint32_t stale[kBatchMax];            // recompression met an exponent without room in tensor i's table
     uint32_t pad[8];
 };
@@ -168,16 +170,26 @@ constexpr uint32_t kSuperGroups = 64;  // encoder groups whose words are also ad
 
 // Host-visible results of one compress call (pinned host memory the kernels write directly).
 struct HostRecord {
-    uint32_t seq;  // stamp of the compress call whose results are complete (written last)
-    uint32_t pad[3];  // (the items, and the arrays in them, are 16-byte aligned)
     struct Item {
-        uint32_t total_words[2];
-        uint32_t stale;    // recompression only: an exponent had no room in the blob's table
-        uint32_t pad;
+        // the words of this item alone (the host adds up the tiles of a tensor), flags, and the stamp of the compress call
+        // whose results are complete: written last, in one piece
+        unsigned long long told;
+        uint32_t pad[2];  // (the arrays are 16-byte aligned)
         uint32_t counts[256];
         uint16_t freq[256];
     } item[kBatchMax];
 };
+constexpr uint32_t kStampMask = (1u << 30) - 1;
+__host__ __device__ inline unsigned long long told_of(unsigned long long words, uint32_t stale, uint32_t seq)
+{
+    const unsigned long long beyond = words >> 32 ? 1u : 0u;  // too long for 32-bit offsets
+    return (words & 0xFFFFFFFFull) | (beyond << 32) | (static_cast<unsigned long long>(stale ? 1u : 0u) << 33) |
+           (static_cast<unsigned long long>(seq & kStampMask) << 34);
+}
+__host__ __device__ inline uint32_t told_words(unsigned long long told) { return static_cast<uint32_t>(told); }
+__host__ __device__ inline bool told_beyond(unsigned long long told) { return told >> 32 & 1u; }
+__host__ __device__ inline bool told_stale(unsigned long long told) { return told >> 33 & 1u; }  // recompression only: an exponent had no room in the blob's table
+__host__ __device__ inline uint32_t told_stamp(unsigned long long told) { return static_cast<uint32_t>(told >> 34); }
 static_assert(sizeof(HostRecord::Item) % 16 == 0 && offsetof(HostRecord, item) % 16 == 0, "whole-wave 128-bit stores");
 
 }  // namespace nz

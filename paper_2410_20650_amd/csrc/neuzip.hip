@@ -615,6 +615,11 @@ inline LinearForm linear_form(uint32_t tokens, uint64_t in_features, const neuzi
     return {few_ends ? 32u : 16u, false};
 }
 
+// Workgroups up to which the walks step without a branch (see rans_get): at most one per CU, two waves per SIMD (4096 x 4096,
+// 1 token, 15.5 us, with the branch 16.1; 1000 x 1024 17.0 / 17.7; 2048 x 4096, 16 tokens, k = 3, 15.5 / 16.4), while with more
+// (q, k and v of a Llama-3-8B attention block, 8 tokens: 20.9 / 20.0; two of 4096 x 4096, 12 tokens: 20.8 / 19.9) the vector unit has the branch's savings.
+constexpr uint32_t kLinEager = 256;
+
 template <int KB, bool NORM>
 void launch_linear(const LinearBatchArgs &batch, uint32_t cols, uint32_t wgs, hipStream_t stream)
 {
@@ -626,9 +631,11 @@ void launch_linear(const LinearBatchArgs &batch, uint32_t cols, uint32_t wgs, hi
 #define NZ_LINEAR(COLS, MT)                                                                                        \
     do {                                                                                                           \
         if (read)                                                                                                  \
-            hipLaunchKernelGGL((linear_batch_kernel<KB, COLS, MT, NORM, true>), grid, block, 0, stream, batch);    \
+            hipLaunchKernelGGL((linear_batch_kernel<KB, COLS, MT, NORM, true, false>), grid, block, 0, stream, batch);  \
+        else if (wgs <= kLinEager)                                                                                 \
+            hipLaunchKernelGGL((linear_batch_kernel<KB, COLS, MT, NORM, false, true>), grid, block, 0, stream, batch);  \
         else                                                                                                       \
-            hipLaunchKernelGGL((linear_batch_kernel<KB, COLS, MT, NORM, false>), grid, block, 0, stream, batch);   \
+            hipLaunchKernelGGL((linear_batch_kernel<KB, COLS, MT, NORM, false, false>), grid, block, 0, stream, batch); \
     } while (0)
     if (cols == 32) {
         if (tokens <= 32)

@@ -256,6 +256,14 @@ struct OpMax {
 // Inclusive sum over the lanes of a row of 16 (all of them active).
 __device__ __forceinline__ uint32_t row_scan_u32(uint32_t v) { return row_scan_u32(v, 0u, OpAdd{}); }
 
+// ... and of a half of 32.
+__device__ __forceinline__ uint32_t half_scan_u32(uint32_t v)
+{
+    v = row_scan_u32(v);
+    // row_bcast:15 into rows 1 and 3
+    return v + static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x142, 0xa, 0xf, false));
+}
+
 // Sum / maximum over the wave, the same value in every lane (lane 63 of the scan, read out as a scalar).
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v)
 {

@@ -150,7 +150,7 @@ __device__ __forceinline__ void atomic_add_f32(float *p, float v)
 // NORM: the blob is block-wise normalised (Sec. 2.3): the merged words are multiplied by their block's
 // coefficient, as in the decoder, before they enter the matrix instruction.
 // The partial sums of the last row that the walk touched stay in acc, that row in `row`.
-template <int KB, int COLS, int MT, bool LONE, bool NORM, class WordSrc>
+template <int KB, int COLS, int MT, bool LONE, bool NORM, bool EAGER, class WordSrc>
 __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, const WordSrc &src, uint32_t lone,
                                             uint32_t &x, uint32_t &wp, const uint8_t *__restrict__ sm,
                                             const LinearArgs &a, uint64_t base, uint32_t kk, uint32_t turns,
@@ -177,90 +177,100 @@ __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, co
         xrow[mt] = a.x + static_cast<uint64_t>(t) * in + ksq + kq;
     }
     uint32_t next = LONE ? 0u : src.peek(wp);
-    const uint64_t first = base + j * kRun;
-    uint64_t fields = turns > 0 ? load_turn<KB, NORM>(sm, a.coef, a.block_shift, first) : 0;
-    uint4 xa[MT];
+    // The inputs of DEPTH turns are held in buffers used in rotation, each requested again once its turn is done, so that with
+    // one they travel while the next turn's eight symbols are decoded.  (Requested a whole turn earlier, or more, they only take
+    // registers and places in the queue: 4096 x 14336, 32 tokens, 43.2 us, with two buffers 48.8; 4096 x 4096, 64 tokens,
+    // 25.8 / 26.9; 9000 x 5120, 64 tokens, 86.7 / 89.3.)  A lane without turns of its own reads those of the tensor's first
+    // chunk; a turn behind the last reads the last again.
+    constexpr uint32_t DEPTH = 1;
+    const uint64_t first = (turns > 0 ? base : 0u) + j * kRun;
+    const uint32_t last = turns > 0 ? turns - 1 : 0u;
+    uint64_t fields[DEPTH];
+    uint4 xa[DEPTH][MT];
+    uint32_t ahead = kk;  // the input-feature offset of the turn requested next
+    auto request = [&](uint32_t d, uint32_t q) {
+        fields[d] = load_turn<KB, NORM>(sm, a.coef, a.block_shift, first + min(q, last) * kTurn);
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-        xa[mt] = *reinterpret_cast<const uint4 *>(xrow[mt] + kk);
+        for (int mt = 0; mt < MT; ++mt)
+            xa[d][mt] = *reinterpret_cast<const uint4 *>(xrow[mt] + ahead);
+        ahead = ahead + kTurn == in ? 0u : ahead + kTurn;
+    };
+#pragma unroll
+    for (uint32_t d = 0; d < DEPTH; ++d)
+        request(d, d);
 
     // the trip count is the same for every lane of the wave (the matrix instruction needs them
     // all); a lane whose chunk is shorter or absent supplies zeros
-    for (uint32_t q = 0; q < all_turns; ++q) {
-        const bool mine = q < turns;
-        // requests for the next turn go out before this turn is decoded
-        const uint32_t kk_next = kk + kTurn == in ? 0u : kk + kTurn;
-        uint64_t fields_next = 0;
-        if (q + 1 < turns)
-            fields_next = load_turn<KB, NORM>(sm, a.coef, a.block_shift, first + (q + 1) * kTurn);
-        uint4 xa_next[MT];
+    static_assert(kTurns % DEPTH == 0 && kMidTurn % DEPTH == 0, "whole rotations");
+    for (uint32_t q0 = 0; q0 < all_turns; q0 += DEPTH) {
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-            xa_next[mt] = *reinterpret_cast<const uint4 *>(xrow[mt] + kk_next);
+        for (uint32_t d = 0; d < DEPTH; ++d) {
+            const uint32_t q = q0 + d;
+            const bool mine = q < turns;
+            const uint32_t kk_next = kk + kTurn == in ? 0u : kk + kTurn;
 
-        union {
-            uint32_t u[4];
-            bf16x8_t v;
-        } b;
-        b.u[0] = b.u[1] = b.u[2] = b.u[3] = 0;
-        if (mine) {
-            uint32_t e[8];
-#pragma unroll
-            for (int t = 0; t < 8; ++t)
-                e[t] = LONE ? lone : rans_get<false>(lut, x, wp, next, src);
-            b.u[0] = merge_pair<KB>(fields, 0, e[0], e[1]);
-            b.u[1] = merge_pair<KB>(fields, 1, e[2], e[3]);
-            b.u[2] = merge_pair<KB>(fields, 2, e[4], e[5]);
-            b.u[3] = merge_pair<KB>(fields, 3, e[6], e[7]);
-            if constexpr (NORM) {
-                const float c = coefficient(static_cast<uint32_t>(fields >> 32) & 0x7Fu);
-#pragma unroll
-                for (int d = 0; d < 4; ++d)
-                    b.u[d] = denormalise_pair(b.u[d], c);
-            }
-        }
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
             union {
-                uint4 q4;
+                uint32_t u[4];
                 bf16x8_t v;
-            } av;
-            av.q4 = xa[mt];
-            acc[mt] = Tile::mma(av.v, b.v, acc[mt]);
-        }
-        // end of a row of the weight inside the walk: this wave's partial sums leave for y
-        if (kk_next == 0 && q + 1 < all_turns) {
-            const bool col_live = mine && row < out_features;
-            // (one running offset: the compiler would hold an address per register of the tile otherwise, and
-            // with them a second workgroup's worth of registers)
-            uint64_t at = static_cast<uint64_t>(Tile::row(lane, 0)) * out_features + row;
+            } b;
+            b.u[0] = b.u[1] = b.u[2] = b.u[3] = 0;
+            if (mine) {
+                uint32_t e[8];
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
+                for (int t = 0; t < 8; ++t)
+                    e[t] = LONE ? lone : rans_get<EAGER>(lut, x, wp, next, src);
+                b.u[0] = merge_pair<KB>(fields[d], 0, e[0], e[1]);
+                b.u[1] = merge_pair<KB>(fields[d], 1, e[2], e[3]);
+                b.u[2] = merge_pair<KB>(fields[d], 2, e[4], e[5]);
+                b.u[3] = merge_pair<KB>(fields[d], 3, e[6], e[7]);
+                if constexpr (NORM) {
+                    const float c = coefficient(static_cast<uint32_t>(fields[d] >> 32) & 0x7Fu);
 #pragma unroll
-                for (int r = 0; r < Tile::kRegs; ++r) {
-                    const uint32_t t = mt * COLS + Tile::row(lane, r);
-                    if (col_live && t < tokens)
-                        atomic_add_f32(y + at, acc[mt][r]);
-                    acc[mt][r] = 0.0f;
-                    const int beyond = r + 1 < Tile::kRegs ? static_cast<int>(Tile::row(0, r + 1) - Tile::row(0, r))
-                                                           : COLS - static_cast<int>(Tile::row(0, r));
-                    at += static_cast<uint64_t>(beyond) * out_features;
-                    asm volatile("" : "+v"(at));
+                    for (int p = 0; p < 4; ++p)
+                        b.u[p] = denormalise_pair(b.u[p], c);
                 }
             }
-            ++row;
-        }
-        kk = kk_next;
-        fields = fields_next;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-            xa[mt] = xa_next[mt];
+            for (int mt = 0; mt < MT; ++mt) {
+                union {
+                    uint4 q4;
+                    bf16x8_t v;
+                } av;
+                av.q4 = xa[d][mt];
+                acc[mt] = Tile::mma(av.v, b.v, acc[mt]);
+            }
+            request(d, q + DEPTH);
+            // end of a row of the weight inside the walk: this wave's partial sums leave for y
+            if (kk_next == 0 && q + 1 < all_turns) {
+                const bool col_live = mine && row < out_features;
+                // (one running offset: the compiler would hold an address per register of the tile otherwise, and
+                // with them a second workgroup's worth of registers)
+                uint64_t at = static_cast<uint64_t>(Tile::row(lane, 0)) * out_features + row;
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+                    for (int r = 0; r < Tile::kRegs; ++r) {
+                        const uint32_t t = mt * COLS + Tile::row(lane, r);
+                        if (col_live && t < tokens)
+                            atomic_add_f32(y + at, acc[mt][r]);
+                        acc[mt][r] = 0.0f;
+                        const int beyond = r + 1 < Tile::kRegs ? static_cast<int>(Tile::row(0, r + 1) - Tile::row(0, r))
+                                                               : COLS - static_cast<int>(Tile::row(0, r));
+                        at += static_cast<uint64_t>(beyond) * out_features;
+                        asm volatile("" : "+v"(at));
+                    }
+                }
+                ++row;
+            }
+            kk = kk_next;
+        }
     }
 }
 
 // READ: every weight of the launch is walked whole and holds its slot table (with the choice of both left to run time
 // 4096 x 14336, 1 token, took 36.4 us, 35.7 now, and 8192 x 8192 36.7, 35.9 now).
-template <int KB, int COLS, int MT, bool NORM, bool READ>
+// EAGER: the step of the walk without a branch (see rans_get).
+template <int KB, int COLS, int MT, bool NORM, bool READ, bool EAGER>
 __device__ __forceinline__ void linear_workgroup(const LinearArgs &a, uint32_t wg, uint32_t *__restrict__ lut,
                                                  uint32_t *__restrict__ steps, uint8_t *__restrict__ stage)
 {
@@ -297,19 +307,21 @@ __device__ __forceinline__ void linear_workgroup(const LinearArgs &a, uint32_t w
     const uint32_t turns = upto > turn0 ? upto - turn0 : 0u;
 
     // ---- loads that depend on nothing
-    const uint32_t off_c = live ? a.offsets[c] : 0u;
-    const uint32_t off_c1 = live ? a.offsets[c + 1] : 0u;
-    uint32_t x = live ? a.states[c * kStates + j] : kRansL;
-    const uint32_t mid_x = live && split ? a.mid_states[c * kStates + j] : kRansL;
-    const uint32_t mid_len = live && split ? a.mid_lens[c * kStates + j] : 0u;
-    uint4 lens16 = make_uint4(0, 0, 0, 0);
-    if (live)
-        lens16 = *reinterpret_cast<const uint4 *>(a.lens + static_cast<uint64_t>(c) * kStates);
+    // (lanes without a chunk read the first one's: no branch, and no wait in front of the loads behind it)
+    const uint32_t off_c = a.offsets[c];
+    const uint32_t off_c1 = a.offsets[c + 1];
+    uint32_t x = a.states[c * kStates + j];
+    const uint4 lens16 = *reinterpret_cast<const uint4 *>(a.lens + static_cast<uint64_t>(c) * kStates);
+    uint32_t mid_x = kRansL, mid_len = 0;
+    if (split) {
+        mid_x = a.mid_states[c * kStates + j];
+        mid_len = a.mid_lens[c * kStates + j];
+    }
     const uint32_t lone = a.tb->lone;
     // the tensor's table: its steps (walked from the entry points, or too small to hold the table) or the slot table itself
     const bool make_lut = !READ && (split || !holds_table(a.n_chunks));
     static_assert(kLinThreads == kM / 8, "one piece of the slot table per thread");
-    const uint32_t first_step = make_lut ? a.tb->step_of[tid] : 0u;
+    const uint32_t begins[2] = {make_lut ? a.tb->step_of[tid] : 0u, 0u};  // the step that this thread's piece begins in
     uint4 table_piece[2];
 #pragma unroll
     for (uint32_t r = 0; r < 2; ++r) {
@@ -326,71 +338,41 @@ __device__ __forceinline__ void linear_workgroup(const LinearArgs &a, uint32_t w
     const uint64_t byte0 = static_cast<uint64_t>(off_c) * 2, byte1 = static_cast<uint64_t>(off_c1) * 2;
     const uint64_t aligned0 = byte0 & ~static_cast<uint64_t>(15);
     const uint32_t piece = live ? static_cast<uint32_t>((byte1 - aligned0 + 15) & ~static_cast<uint64_t>(15)) : 0u;
-    uint32_t place = piece;  // exclusive prefix over the columns (lanes with equal lane / COLS agree)
-#pragma unroll
-    for (uint32_t d = 1; d < COLS; d <<= 1) {
-        const uint32_t o = __shfl_up(place, d, COLS);
-        if (col >= d)
-            place += o;
-    }
-    const uint32_t group_bytes = __shfl(place, COLS - 1, COLS);
+    // exclusive prefix over the columns (lanes with equal lane / COLS agree)
+    uint32_t place = COLS == 16 ? row_scan_u32(piece) : half_scan_u32(piece);
+    const uint32_t group_bytes = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(place), COLS - 1));
     place -= piece;
     const bool staged = group_bytes + 16 <= group_window;
     uint8_t *window = stage + g * group_window;
-    // A wave copies kMostCols columns (or half as many, with entry points).  The first 2 KB of each, usually all of
-    // it, are requested together: column after column the copies were a chain of eight memory latencies, a sixth
-    // of the kernel's time.
-    constexpr uint32_t kMostCols = COLS / (kStates / kPerWave), kFirst = 2;
-    uint4 pieces[kMostCols][kFirst];
+    // A wave copies cols_per_wave columns straight into LDS (kMostCols, or half as many with entry points), all of them
+    // requested together, while the table is made.
     auto of_column = [&](uint32_t v, uint32_t r) {
         return static_cast<uint32_t>(
             __builtin_amdgcn_readlane(static_cast<int>(v), static_cast<int>((in_group * cols_per_wave + r) & 63u)));
     };
-    auto column = [&](uint32_t r, const uint4 *&from, uint4 *&to, uint32_t &len) {
+    if (make_lut && tid < kSteps / 4)
+        reinterpret_cast<uint4 *>(steps)[tid] = table_piece[0];
+    asm volatile("" ::"v"(begins[0]));  // (taken here, and not waited for behind the words)
+    for (uint32_t r = 0; r < cols_per_wave; ++r) {
         const uint64_t at = of_column(static_cast<uint32_t>(aligned0), r) |
                             (static_cast<uint64_t>(of_column(static_cast<uint32_t>(aligned0 >> 32), r)) << 32);
-        len = staged && group_live && r < cols_per_wave ? of_column(piece, r) : 0u;
-        from = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint8_t *>(a.words) + at);
-        to = reinterpret_cast<uint4 *>(window + of_column(place, r));
-    };
-#pragma unroll
-    for (uint32_t r = 0; r < kMostCols; ++r) {
-        const uint4 *from;
-        uint4 *to;
-        uint32_t len;
-        column(r, from, to, len);
-#pragma unroll
-        for (uint32_t h = 0; h < kFirst; ++h) {
-            const uint32_t i = lane + 64 * h;
-            pieces[r][h] = i * 16 < len ? from[i] : make_uint4(0, 0, 0, 0);
-        }
+        const uint32_t len = staged && group_live ? of_column(piece, r) : 0u;
+        const uint4 *from = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint8_t *>(a.words) + at);
+        uint8_t *to = window + of_column(place, r);
+        for (uint32_t i = 0; i * 16 < len; i += 64)
+            if ((i + lane) * 16 < len)
+                copy_to_lds(from + i + lane, to + i * 16);
     }
     if (make_lut) {
-        if (tid < kSteps / 4)
-            reinterpret_cast<uint4 *>(steps)[tid] = table_piece[0];
-        __syncthreads();
+        lds_barrier();
         if (lone >= 256)
-            make_piece(steps, first_step, tid, lut);
+            make_table(steps, begins, a.tb, lut);
     } else {
 #pragma unroll
         for (uint32_t r = 0; r < 2; ++r)
             reinterpret_cast<uint4 *>(lut)[tid + r * kLinThreads] = table_piece[r];
     }
-#pragma unroll
-    for (uint32_t r = 0; r < kMostCols; ++r) {
-        const uint4 *from;
-        uint4 *to;
-        uint32_t len;
-        column(r, from, to, len);
-#pragma unroll
-        for (uint32_t h = 0; h < kFirst; ++h) {
-            const uint32_t i = lane + 64 * h;
-            if (i * 16 < len)
-                to[i] = pieces[r][h];
-        }
-        for (uint32_t i = lane + 64 * kFirst; i * 16 < len; i += 64)
-            to[i] = from[i];
-    }
+    wait_for_memory_acks();  // the words
     __syncthreads();
     // ---- start of this state's run: the chunk's offset plus the lengths of the states before it
     const uint32_t lw[4] = {lens16.x, lens16.y, lens16.z, lens16.w};
@@ -422,15 +404,15 @@ __device__ __forceinline__ void linear_workgroup(const LinearArgs &a, uint32_t w
     if (group_live) {
         uint32_t wp = 0, wp_begin = 0;
         if (lone < 256) {
-            linear_walk<KB, COLS, MT, true, NORM>(lut, NoWords{}, lone, x, wp, a.sm, a, from_elem, kk0, turns, all_turns, j,
+            linear_walk<KB, COLS, MT, true, NORM, EAGER>(lut, NoWords{}, lone, x, wp, a.sm, a, from_elem, kk0, turns, all_turns, j,
                                                   lane, acc, row);
         } else if (staged) {
             wp = wp_begin = g * group_window + place + static_cast<uint32_t>(run_byte - aligned0);
-            linear_walk<KB, COLS, MT, false, NORM>(lut, LdsWords{stage}, 0u, x, wp, a.sm, a, from_elem, kk0, turns, all_turns,
+            linear_walk<KB, COLS, MT, false, NORM, EAGER>(lut, LdsWords{stage}, 0u, x, wp, a.sm, a, from_elem, kk0, turns, all_turns,
                                                    j, lane, acc, row);
         } else {
             const GlobalWords direct{reinterpret_cast<const uint8_t *>(a.words) + run_byte};
-            linear_walk<KB, COLS, MT, false, NORM>(lut, direct, 0u, x, wp, a.sm, a, from_elem, kk0, turns, all_turns, j, lane,
+            linear_walk<KB, COLS, MT, false, NORM, false>(lut, direct, 0u, x, wp, a.sm, a, from_elem, kk0, turns, all_turns, j, lane,
                                                    acc, row);
         }
         if (live && (x != x_end || wp - wp_begin != 2 * words_here))
@@ -481,18 +463,20 @@ __device__ __forceinline__ void linear_workgroup(const LinearArgs &a, uint32_t w
 
 // (Two workgroups of 8 waves share a CU if a lane has at most 128 registers; with the 138 the compiler took
 // for 64 tokens it held one.)
-template <int KB, int COLS, int MT, bool NORM, bool READ>
+template <int KB, int COLS, int MT, bool NORM, bool READ, bool EAGER>
 __global__ __launch_bounds__(kLinThreads, 4) void linear_batch_kernel(const LinearBatchArgs b)
 {
-    __shared__ __align__(16) uint32_t lut[kM];
-    __shared__ __align__(16) uint8_t stage[kStageBytes];
-    __shared__ __align__(16) uint32_t steps[READ ? 4 : kSteps];
+    __shared__ __align__(16) struct {
+        uint8_t stage[kStageBytes];  // first: a direct copy's LDS address has 16 bits
+        uint32_t lut[kM];
+        uint32_t steps[READ ? 4 : kSteps];
+    } lds;
     uint32_t i = 0, first = 0;
     while (i + 1 < b.count && blockIdx.x >= b.wg_end[i]) {
         first = b.wg_end[i];
         ++i;
     }
-    linear_workgroup<KB, COLS, MT, NORM, READ>(b.t[i], blockIdx.x - first, lut, steps, stage);
+    linear_workgroup<KB, COLS, MT, NORM, READ, EAGER>(b.t[i], blockIdx.x - first, lds.lut, lds.steps, lds.stage);
 }
 
 }  // namespace nz

@@ -134,3 +134,22 @@ def test_a_kept_table_that_the_weights_have_left(nz):
     assert nz.neuzip_recompress([moved], [blob]) == [0]
     assert 8 * blob.compressed_bytes > 14 * w.numel()
     assert torch.equal(decoded(nz, blob, moved).view(torch.int16), moved.view(torch.int16))
+
+
+# the linear layer's walks with and without a branch (launches of at most 256 workgroups, and of more), lanes without a chunk
+# and without a turn of their own in the half behind the entry point, columns that are copied in more than one piece
+@pytest.mark.parametrize("shapes, k", [([(1, 128)], 7), ([(17, 128)], 3), ([(15, 384)], 7), ([(33, 2176)], 7), ([(130, 1152)], 0),
+                                       ([(2048, 4096)], 1), ([(2100, 4096), (2100, 4096)], 7), ([(700, 8192), (3, 8192)], 3)])
+@pytest.mark.parametrize("tokens", [1, 16, 40])
+def test_linear_walks_at_the_edges_of_their_launches(nz, shapes, k, tokens):
+    in_f = shapes[0][1]
+    mask = ~((1 << (7 - k)) - 1)
+    ws = [inputs.gaussian_bf16(s, 5400 + i, device=DEV) for i, s in enumerate(shapes)]
+    held = [(w.view(torch.int16) & mask).view(torch.bfloat16) for w in ws]
+    blobs = [nz.neuzip_compress(w, k) for w in ws]
+    g = torch.Generator(device=DEV).manual_seed(5500)
+    x = torch.randn((tokens, in_f), generator=g, device=DEV).to(torch.bfloat16)
+    for y, w, blob in zip(nz.neuzip_linear_batch(blobs, [s[0] for s in shapes], in_f, x), held, blobs):
+        nz.neuzip_check(blob)
+        want, size = x.double() @ w.double().t(), x.double().abs() @ w.double().abs().t()
+        assert bool(((y.double() - want).abs() <= 2 * (in_f + 64) * 2.0 ** -24 * size + 1e-30).all())   # float32 sums, any order

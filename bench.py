@@ -297,7 +297,7 @@ def main():
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": read_traffic_note(),
                 "traffic_source": "profiles/decode_config2.txt (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, a separate run; not measured in this one)",
-                "kernel": "decode_kernel<7, false, 0, false>", "avg_launch_us": round(kernel_ms * 1e3, 2),
+                "kernel": "decode_direct_kernel<7, false>", "avg_launch_us": round(kernel_ms * 1e3, 2),
                 "algorithmic_bytes_per_elem": round(algo_bytes / n, 4),
                 "working_set": "196 MB: fits the 256 MB last-level cache, so this figure is cache assisted; "
                                "see roofline_hbm_resident for a tensor that streams through HBM"}

@@ -590,6 +590,7 @@ int launch_batch(const BatchArgs &args, int variant, uint32_t groups, hipStream_
 // 28.1 / 27.1, 64: 45.9 / 31.5; q, k and v of a Llama-3-8B attention block, 64 tokens: 45.6 / 31.1; 14336 x 4096 with
 // 1024 x 4096, 32 tokens: 53.7 / 38.4; 20000 x 2048 with 500 x 2048, 32 tokens: 59.1 / 54.4).  Rows shorter than a chunk end inside it, and half a walk has half the ends to send one
 // after the other: always in halves there (four weights of 16000 x 1024, 64 tokens: 173 / 200; 5000 x 2048: 70 / 90).
+// (Figures of the kernel whose words went through registers; both sides are 3-10 % lower now.)
 struct LinearForm {
     uint32_t cols;
     bool entries;

@@ -11,14 +11,12 @@ namespace nz {
 // ------------------------------------------------------------------------------------------
 // Kernel 6: fused decoder (Alg. 1 "decompression" + "merge"; Sec. 2.2 Eq. (3)).
 //
-// A workgroup owns blockDim.x / 16 neighbouring chunks (at most 32; half as many of a blob with entry
-// points).  It copies the 4096-entry slot table (symbol | f << 8 |
-// (slot - cum) << 20), or makes it from the tensor's table, in LDS, copies the chunks' word runs -- one contiguous piece of the blob -- there with
-// 128-bit loads, and then every lane walks one
-// state, or the half of a state before or behind its entry point: 32 (16) turns of 8 symbols; per symbol one table read, one multiply-add, one compare, and
-// a lane-private refill that touches LDS only when a word is consumed.  The 8 decoded
-// exponents are merged with the 8 sign|mantissa fields and leave as one 128-bit store; the
-// fields of the next turn are requested before the current turn is decoded.
+// A workgroup owns blockDim.x / 16 neighbouring chunks (at most 32; half as many of a blob with entry points).  It copies
+// the 4096-entry slot table (symbol | f << 8 | (slot - cum) << 20), or makes it from the tensor's table, in LDS, copies the
+// chunks' word runs -- one contiguous piece of the blob -- there with 128-bit loads, through registers or straight, and then
+// every lane walks one state, or the half of a state before or behind its entry point: 32 (16) turns of 8 symbols; per symbol
+// one table read, one multiply-add, one compare, and a lane-private refill.  The 8 decoded exponents are merged with the 8
+// sign|mantissa fields and leave as one 128-bit store; the fields of the next turns are requested before a turn is decoded.
 // ------------------------------------------------------------------------------------------
 template <int KB>
 __device__ __forceinline__ uint64_t load_fields(const uint8_t *__restrict__ sm, uint64_t first_elem)

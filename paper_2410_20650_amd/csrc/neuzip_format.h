@@ -42,8 +42,8 @@ static_assert(kTurns % kTurnGroup == 0 && kTurns % kTurnGroupStream == 0, "a chu
 // kSplitChunks chunks therefore also holds, per state, where the chain stands before turn kMidTurn -- the
 // state (4 bytes) and the words consumed so far (1 byte) -- and two lanes walk the two halves.  It is derived
 // data, like the tables: the encoder passes that point anyway, an import walks to it, and the container does not
-// have it.  Measured, lossless, one launch per tensor, whole states / halves: 1 M elements 19.7 / 12.3 us, 4 M
-// 20.4 / 13.0, 16.8 M 23.0 / 15.8; linear layer 4096 x 4096, 1 token, 28.2 / 17.0.  The line lies where the lanes
+// have it.  Measured, lossless, one launch per tensor, whole states / halves: 1 M elements 19.7 / 9.8 us, 4 M
+// 20.4 / 10.7, 16.8 M 23.0 / 14.0; linear layer 4096 x 4096, 1 token, 28.2 / 15.3.  The line lies where the lanes
 // of whole states come to one wave per SIMD (1024 waves of 64 states): beyond it the launch has waves to hide the
 // chain behind (58.7 M elements with twice the lanes: no faster), and the 0.16 bits per element the entry points
 // cost would be held by the matrices that make up most of a model (on an 8B-shaped layer they are 0.3 % of the

@@ -546,7 +546,13 @@ void launch_batch_kernel(const BatchArgs &args, dim3 grid, dim3 block, hipStream
         entries = entries || args.t[t].mid_states;
         tables = tables && holds_table(args.t[t].n_chunks);
     }
-    if (entries && !args.t[0].stream_out)  // (as place_workgroups decided)
+    // From the entry points (as place_workgroups decided), without a branch in the step where every CU has one workgroup at
+    // most: 13 M elements in four tensors (205 workgroups) 13.9 us, with the branch 15.1; beyond, CUs with two have four waves
+    // per SIMD, and with the branch 21 M in four tensors (321) take 19.4 instead of 23.1, 22 M (338) 18.5 instead of 21.1, 28 M in
+    // two (428) 24.3 and 23.8.
+    if (entries && !args.t[0].stream_out && grid.x <= 256)
+        hipLaunchKernelGGL((decode_batch_kernel<KB, NORM, MODE, kEntriesAlone>), grid, block, 0, stream, args);
+    else if (entries && !args.t[0].stream_out)
         hipLaunchKernelGGL((decode_batch_kernel<KB, NORM, MODE, kEntries>), grid, block, 0, stream, args);
     else if (!tables)
         hipLaunchKernelGGL((decode_batch_kernel<KB, NORM, MODE, kMakeTable>), grid, block, 0, stream, args);

@@ -611,14 +611,14 @@ struct DecodeArgs {
 enum DecodeMode { kPlain = 0, kWide = 1, kUpdate = 2, kHalf = 3 };
 
 // The walk of the mode.
-template <int KB, bool LONE, bool NORM, bool STREAM, int MODE, bool SPLIT, class WordSrc>
+template <int KB, bool LONE, bool NORM, bool STREAM, int MODE, bool SPLIT, bool ALONE, class WordSrc>
 __device__ __forceinline__ void walk_mode(const uint32_t *__restrict__ lut, const uint2 *__restrict__ spread,
                                           const WordSrc &src, uint32_t lone, uint32_t &x, uint32_t &wp, const DecodeArgs &a,
                                           uint32_t block, TurnsAhead &ahead, uint64_t base, uint32_t m, uint32_t j,
                                           uint32_t turn0)
 {
     // (a word read from memory is fetched only when it is needed)
-    constexpr bool EAGER = SPLIT && !std::is_same<WordSrc, GlobalWords>::value;
+    constexpr bool EAGER = ALONE && !std::is_same<WordSrc, GlobalWords>::value;
     if constexpr (MODE == kWide)
         walk_state_wide<LONE, STREAM, SPLIT, EAGER>(lut, src, lone, x, wp, a.sm, a.low, static_cast<uint32_t *>(a.out), base, m, j,
                                              turn0, ahead);
@@ -691,6 +691,7 @@ enum DecodeForm {
     kMakeTable,  // one lane per state; the blob is too small to hold the table (its entry points are not used)
     kEntries,    // two lanes per state, from the entry points; the slot table is made
     kReadDirect, // like kReadTable, cached; the words are copied straight into LDS
+    kEntriesAlone, // like kEntries, at most one workgroup per CU
 };
 
 template <int KB, bool NORM, int MODE, int FORM>
@@ -707,7 +708,7 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
     const uint8_t *__restrict__ coef = a.coef;
     // (blobs of at most 2^24 elements are never beyond the cache, and in a batch that is they are walked whole)
     const bool stream_out = FORM == kMakeTable || (FORM == kReadTable && a.stream_out != 0);
-    static_assert(FORM != kEntries, "see decode_from_entries");
+    static_assert(FORM != kEntries && FORM != kEntriesAlone, "see decode_from_entries");
     const uint32_t n_chunks = a.n_chunks;
     const uint32_t tid = threadIdx.x;
     const uint32_t threads = blockDim.x;            // a multiple of 64, at most kDecThreads
@@ -830,9 +831,9 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
     auto walk = [&](auto alone, const auto &src, uint32_t only) {
         constexpr bool LONE = decltype(alone)::value;
         if (stream_out)
-            walk_mode<KB, LONE, NORM, true, MODE, false>(lut, spread, src, only, x, wp, a, block, ahead, base, m, j, 0u);
+            walk_mode<KB, LONE, NORM, true, MODE, false, false>(lut, spread, src, only, x, wp, a, block, ahead, base, m, j, 0u);
         else
-            walk_mode<KB, LONE, NORM, false, MODE, false>(lut, spread, src, only, x, wp, a, block, ahead, base, m, j, 0u);
+            walk_mode<KB, LONE, NORM, false, MODE, false, false>(lut, spread, src, only, x, wp, a, block, ahead, base, m, j, 0u);
     };
     if (lone < 256) {
         walk(std::true_type{}, NoWords{}, lone);
@@ -857,7 +858,8 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
 // without a branch (see rans_get) and the table made by make_table: 4 M elements 13.5 -> 10.7 us, of which the beginning
 // 3.9 -> 2.7 and the walk 9.5 -> 7.7, 0.05 M 11.8 -> 9.5, 16.8 M 15.8 -> 14.0, 10 M binary32 elements 20.3 -> 16.4; words
 // through registers 11.8 (4 M), 15.5 (16.8 M).
-template <int KB, bool NORM, int MODE>
+// ALONE: the launch has at most one workgroup per CU, and the step no branch (see launch_batch_kernel).
+template <int KB, bool NORM, int MODE, bool ALONE>
 __device__ __forceinline__ void decode_from_entries(const DecodeArgs &a, uint32_t wg, uint32_t *__restrict__ lut,
                                                     uint32_t *__restrict__ steps, uint8_t *__restrict__ stage,
                                                     uint2 *__restrict__ spread)
@@ -948,13 +950,13 @@ __device__ __forceinline__ void decode_from_entries(const DecodeArgs &a, uint32_
         request_ahead();
     uint32_t wp = 0, wp_begin = 0;
     if (lone < 256) {
-        walk_mode<KB, true, NORM, false, MODE, true>(lut, spread, NoWords{}, lone, x, wp, a, block, ahead, base, m, j, turn0);
+        walk_mode<KB, true, NORM, false, MODE, true, ALONE>(lut, spread, NoWords{}, lone, x, wp, a, block, ahead, base, m, j, turn0);
     } else if (staged) {
         wp = wp_begin = static_cast<uint32_t>(run_byte - aligned0);
-        walk_mode<KB, false, NORM, false, MODE, true>(lut, spread, LdsWords{stage}, 0u, x, wp, a, block, ahead, base, m, j, turn0);
+        walk_mode<KB, false, NORM, false, MODE, true, ALONE>(lut, spread, LdsWords{stage}, 0u, x, wp, a, block, ahead, base, m, j, turn0);
     } else {
         const GlobalWords direct{reinterpret_cast<const uint8_t *>(a.words) + run_byte};
-        walk_mode<KB, false, NORM, false, MODE, true>(lut, spread, direct, 0u, x, wp, a, block, ahead, base, m, j, turn0);
+        walk_mode<KB, false, NORM, false, MODE, true, ALONE>(lut, spread, direct, 0u, x, wp, a, block, ahead, base, m, j, turn0);
     }
     if (x != x_end || wp - wp_begin != 2 * words_here)
         atomicOr(a.status, 1u);
@@ -975,7 +977,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(const DecodeArgs a)
 {
     __shared__ __align__(16) DecodeLds<KB, SPLIT> lds;
     if constexpr (SPLIT)
-        decode_from_entries<KB, NORM, MODE>(a, blockIdx.x, lds.lut, lds.steps, lds.stage, lds.spread);
+        decode_from_entries<KB, NORM, MODE, true>(a, blockIdx.x, lds.lut, lds.steps, lds.stage, lds.spread);
     else
         decode_workgroup<KB, NORM, MODE, kReadTable>(a, blockIdx.x, lds.lut, lds.steps, lds.stage, lds.spread);
 }
@@ -996,7 +998,7 @@ struct BatchArgs {
     uint32_t threads;  // (for the host: of a workgroup)
 };
 
-// FORM: how the blobs of the batch that have entry points (kEntries) or no slot table (kMakeTable) are walked; the
+// FORM: how the blobs of the batch that have entry points (kEntries, kEntriesAlone) or no slot table (kMakeTable) are walked; the
 // others read theirs.
 template <int KB, bool NORM, int MODE, int FORM>
 __global__ __launch_bounds__(kDecThreads) void decode_batch_kernel(const BatchArgs b)
@@ -1008,9 +1010,9 @@ __global__ __launch_bounds__(kDecThreads) void decode_batch_kernel(const BatchAr
         ++i;
     }
     const DecodeArgs a = b.t[i];
-    if constexpr (FORM == kEntries) {
+    if constexpr (FORM == kEntries || FORM == kEntriesAlone) {
         if (a.mid_states) {
-            decode_from_entries<KB, NORM, MODE>(a, blockIdx.x - first, lds.lut, lds.steps, lds.stage, lds.spread);
+            decode_from_entries<KB, NORM, MODE, FORM == kEntriesAlone>(a, blockIdx.x - first, lds.lut, lds.steps, lds.stage, lds.spread);
             return;
         }
     }

@@ -177,7 +177,7 @@ struct Workspace {
     uint16_t *slots = nullptr;
     HostRecord *pinned = nullptr;     // pinned host memory, written by the encode kernel
     uint32_t seq = 0;                 // stamp of the last compress call
-    hipEvent_t idle = nullptr;        // recorded after the last kernel that uses the workspace
+    hipEvent_t idle = nullptr;        // recorded behind the last kernel of every call that uses the workspace
     hipStream_t last_stream = nullptr; // ... on this stream
 };
 std::mutex g_ws_mutex;
@@ -249,6 +249,16 @@ void reset_workspace(const Workspace &ws, hipStream_t stream)
         hipLaunchKernelGGL(fill_u32_kernel, dim3((2 * ws.super_cap + 255) / 256), dim3(256), 0, stream, ws.super_words, 0u,
                            2 * ws.super_cap);
     (void)hipGetLastError();
+}
+
+// Every way out of a call that may have launched kernels on the shared workspace, behind the last of them, failures included:
+// the next call on another stream waits for this event.
+bool leave_workspace(hipStream_t stream)
+{
+    if (hip_ok(hipEventRecord(g_ws.idle, stream)))
+        return true;
+    (void)hipStreamSynchronize(stream);
+    return false;
 }
 
 // First use on a device: the arrays whose size does not depend on the tensors.
@@ -823,6 +833,7 @@ int compress_tiled(neuzip_blob *b, const void *d_src, const void *d_grad, int k,
     auto fail = [&](int code) {
         if (bins_dirty)
             reset_workspace(ws, stream);
+        (void)leave_workspace(stream);
         b->has_table = false;
         return code;
     };
@@ -906,7 +917,7 @@ int compress_tiled(neuzip_blob *b, const void *d_src, const void *d_grad, int k,
             *stale = true;
             b->has_table = false;
             if (!(d_grad && keep_new)) {
-                (void)hipEventRecord(ws.idle, stream);
+                (void)leave_workspace(stream);
                 return NEUZIP_OK;
             }
         }
@@ -938,9 +949,7 @@ int compress_tiled(neuzip_blob *b, const void *d_src, const void *d_grad, int k,
         b->total_words = words_before;
         b->has_table = true;
     }
-    if (!hip_ok(hipEventRecord(ws.idle, stream)))
-        return NEUZIP_EHIP;
-    return NEUZIP_OK;
+    return leave_workspace(stream) ? NEUZIP_OK : NEUZIP_EHIP;
 }
 
 int compress_some(const void *const *d_srcs, const uint64_t *n_elems, uint32_t count, int k, uint32_t block, int elem,
@@ -992,9 +1001,12 @@ int compress_some(const void *const *d_srcs, const uint64_t *n_elems, uint32_t c
     }
     bool touched = false;     // kernels that write into the blobs have been launched
     bool ws_dirty = false;    // kernels have run whose sums in the workspace no later kernel has cleared
+    bool ws_used = false;     // kernels on the shared workspace may have been launched (its lock is held)
     auto fail = [&](int rc) {
         if (ws_dirty)
             reset_workspace(ws, stream);
+        if (ws_used)
+            (void)leave_workspace(stream);
         for (uint32_t i = 0; i < count; ++i) {
             if (fresh[i])
                 neuzip_free(work[i]);
@@ -1110,6 +1122,7 @@ int compress_some(const void *const *d_srcs, const uint64_t *n_elems, uint32_t c
             rc = ensure_workspace(work[owner[0]]->device, enc_groups, stream);
             if (rc != NEUZIP_OK)
                 return fail(rc);
+            ws_used = true;
         }
         batch.seq = ++ws.seq;
         batch.lr = lr;
@@ -1206,7 +1219,7 @@ int compress_some(const void *const *d_srcs, const uint64_t *n_elems, uint32_t c
         // the tensors that had no room (or no word section yet), now that it is allocated
         if (late && !launch_compact(false))
             return fail(NEUZIP_EHIP);
-        if (!fixed_ws && !hip_ok(hipEventRecord(ws.idle, stream)))
+        if (!fixed_ws && !leave_workspace(stream))
             return fail(NEUZIP_EHIP);
         stale_count = n_stale;
     }

@@ -1,0 +1,211 @@
+// Drives the library's host code on a runtime double: the HIP calls it makes are answered here, nothing runs on a GPU.
+// Kernels are not executed; an encoder launch tells the host its stream lengths as the kernel would.  What is kept is what
+// each stream has been ordered behind (launches and copies per stream, carried by events), so that the order a call leaves
+// behind can be checked.  Run as: host_order SCENARIO; prints "ok" or what is out of order.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <functional>
+#include <map>
+#include <string>
+#include <vector>
+#include <hip/hip_runtime.h>
+#include "neuzip_format.h"
+
+namespace {
+
+using Clock = std::map<hipStream_t, uint64_t>;  // work of a stream: how many pieces of it have gone before
+struct Event { Clock at; };
+
+// (the library registers its kernels before this program's own variables are initialised)
+std::map<const void *, std::string> &names() { static auto *n = new std::map<const void *, std::string>; return *n; }
+std::map<hipStream_t, Clock> g_seen;            // what the next piece of work on a stream is ordered behind
+std::map<hipStream_t, uint64_t> g_work;         // pieces of work given to a stream
+std::map<hipStream_t, std::vector<Clock>> g_behind;  // per piece of work: what it was ordered behind
+Clock g_host;                                   // what the host has waited for
+nz::HostRecord *g_record = nullptr;
+uint64_t g_words = 1000;                        // stream length that the encoder reports for every tensor
+int g_mallocs_until_failure = -1;
+int g_waits = 0;
+bool g_capturing = false;
+std::vector<std::string> g_launched;
+struct { dim3 grid, block; size_t shared; hipStream_t stream; } g_call;
+
+void join(Clock &into, const Clock &from)
+{
+    for (const auto &e : from)
+        if (into[e.first] < e.second)
+            into[e.first] = e.second;
+}
+
+void work(hipStream_t s)
+{
+    join(g_seen[s], g_host);
+    g_behind[s].push_back(g_seen[s]);
+    g_seen[s][s] = ++g_work[s];
+}
+
+void wait_for(const Clock &c) { join(g_host, c); }
+
+[[noreturn]] void wrong(const std::string &what)
+{
+    std::printf("%s\n", what.c_str());
+    std::fflush(stdout);
+    std::_Exit(1);
+}
+void expect(bool ok, const std::string &what)
+{
+    if (!ok)
+        wrong(what);
+}
+
+}  // namespace
+
+extern "C" {
+void **__hipRegisterFatBinary(const void *) { static void *handle; return &handle; }
+void __hipUnregisterFatBinary(void **) {}
+void __hipRegisterFunction(void **, const void *fn, char *, const char *name, unsigned, void *, void *, void *, void *, int *)
+{
+    names()[fn] = name;
+}
+void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t shared, hipStream_t stream)
+{
+    g_call = {grid, block, shared, stream};
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *shared, hipStream_t *stream)
+{
+    *grid = g_call.grid, *block = g_call.block, *shared = g_call.shared, *stream = g_call.stream;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *fn, dim3, dim3, void **args, size_t, hipStream_t stream)
+{
+    const std::string &name = names()[fn];
+    g_launched.push_back(name);
+    work(stream);
+    if (name.find("encode_kernel") != std::string::npos) {
+        const nz::CompressBatch &b = *static_cast<const nz::CompressBatch *>(args[0]);
+        for (uint32_t i = 0; i < b.count && g_record; ++i)
+            g_record->item[i].told = nz::told_of(g_words, 0, b.seq);
+    }
+    return hipSuccess;
+}
+hipError_t hipMalloc(void **p, size_t n)
+{
+    if (g_mallocs_until_failure == 0)
+        return hipErrorOutOfMemory;
+    if (g_mallocs_until_failure > 0)
+        --g_mallocs_until_failure;
+    *p = std::calloc(1, 64);  // (an address: nothing reads or writes it)
+    (void)n;
+    return hipSuccess;
+}
+hipError_t hipFree(void *p)
+{
+    for (const auto &w : g_work)  // waits for the device
+        g_host[w.first] = w.second;
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipHostMalloc(void **p, size_t n, unsigned)
+{
+    *p = std::calloc(1, n);
+    g_record = static_cast<nz::HostRecord *>(*p);
+    return hipSuccess;
+}
+hipError_t hipHostFree(void *p)
+{
+    g_record = nullptr;
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipGetSymbolAddress(void **p, const void *) { static uint64_t somewhere[4]; *p = somewhere; return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { *e = reinterpret_cast<hipEvent_t>(new Event); return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { delete reinterpret_cast<Event *>(e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
+{
+    join(g_seen[s], g_host);
+    reinterpret_cast<Event *>(e)->at = g_seen[s];
+    return hipSuccess;
+}
+hipError_t hipEventSynchronize(hipEvent_t e) { wait_for(reinterpret_cast<Event *>(e)->at); return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned)
+{
+    expect(!g_capturing, "an event of another stream in a stream under capture");
+    ++g_waits;
+    join(g_seen[s], reinterpret_cast<Event *>(e)->at);
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t s) { wait_for(g_seen[s]); return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *st)
+{
+    *st = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void *to, const void *, size_t n, hipMemcpyKind kind, hipStream_t s)
+{
+    if (kind == hipMemcpyDeviceToHost)
+        std::memset(to, 0, n);
+    work(s);
+    return hipSuccess;
+}
+}
+
+namespace {
+
+const hipStream_t A = reinterpret_cast<hipStream_t>(0x1000), B = reinterpret_cast<hipStream_t>(0x2000);
+void *const kSomewhere = reinterpret_cast<void *>(0x100000);
+constexpr uint64_t kElems = 1000000;
+
+neuzip_blob *compressed(hipStream_t s, neuzip_blob *blob = nullptr, uint64_t n = kElems)
+{
+    expect(neuzip_compress(kSomewhere, n, NEUZIP_BF16, 7, s, &blob) == NEUZIP_OK, "compress");
+    return blob;
+}
+
+// `call` gives work to B: every piece of it is behind all that A has been given by now.
+void expect_behind(const char *what, const std::function<int()> &call)
+{
+    const size_t first = g_behind[B].size();
+    const uint64_t before = g_work[A];
+    expect(call() == NEUZIP_OK, std::string(what) + " failed");
+    expect(g_behind[B].size() > first, std::string(what) + " did nothing");
+    for (size_t i = first; i < g_behind[B].size(); ++i)
+        expect(g_behind[B][i][A] >= before, std::string(what) + " is not ordered behind the other stream's work");
+}
+
+// A compress call into an existing blob fails on A for want of memory after its kernels have been launched; a call on B uses
+// the workspace next.  (Twice, since the first failure gives the old word section back, and a free waits for the device.)
+void after_a_failure()
+{
+    g_words = 0;
+    neuzip_blob *blob = compressed(A);
+    g_words = 500000;
+    g_mallocs_until_failure = 0;
+    for (int i = 0; i < 2; ++i)
+        expect(neuzip_compress(kSomewhere, kElems, NEUZIP_BF16, 7, A, &blob) == NEUZIP_ENOMEM, "the failing call");
+    g_mallocs_until_failure = -1;
+    g_words = 1000;
+    expect_behind("the next call", [] { compressed(B); return 0; });
+}
+
+}  // namespace
+
+int main(int argc, char **argv)
+{
+    const std::string s = argc > 1 ? argv[1] : "";
+    if (s == "failure") {
+        after_a_failure();
+    } else if (s == "failure_in_a_tile") {
+        expect(neuzip_set_workspace_limit(102400) == NEUZIP_OK, "limit");
+        after_a_failure();
+    } else {
+        wrong("unknown scenario " + s);
+    }
+    std::printf("ok\n");
+    return 0;
+}

@@ -20,6 +20,13 @@
  *     words for NEUZIP_F32); the shape of the matrix is irrelevant to the
  *     codec.  d_src / d_dst must be aligned to 16 bytes.  n_elems must be
  *     below 2^32.
+ *   - A compress, recompress or update call waits for the lengths of the streams, which depend on the
+ *     data, and returns while its last kernels, which complete the blobs, may still run on hip_stream.
+ *     The calls of this library that read such a blob are ordered behind them, on the same stream by
+ *     its own order, on another one by an event that the library makes that stream wait for (the host
+ *     does not wait).  A stream under capture is not made to wait: a blob that was filled on another
+ *     stream has to be complete before a capture that reads it begins.  The other direction is the
+ *     caller's: a blob is not compressed into, or freed, while calls on other streams still read it.
  *   - Errors are reported through the return code only (no exceptions, no
  *     aborts, nothing is printed).  On error no output argument is modified
  *     unless stated otherwise.
@@ -96,7 +103,8 @@ enum {
  * sign|mantissa stream in device memory sized for this tensor (the word
  * section with 1/64 of headroom, 0.3 % of the container, so that a blob which
  * is compressed into again after an update seldom has to be re-allocated).
- * Synchronises hip_stream once (the stream length is data dependent).
+ * The host waits once, for the stream's length; the blob is complete in the order of hip_stream (see
+ * the conventions).
  * n_elems == 0 yields a valid empty blob.
  */
 int neuzip_compress(const void *d_src, uint64_t n_elems, int dtype, int mantissa_bits,
@@ -160,8 +168,8 @@ int neuzip_compress_batch(const void *const *d_srcs, const uint64_t *n_elems, ui
  *       the blob's guard) and rebuilt[i] is set to 1, else 0 (rebuilt may be NULL).  Block-wise
  *       normalised blobs always take the second route.  After a table has been reused
  *       neuzip_histogram reports EINVAL for the blob (no counts were taken).
- *   Both work on host arrays of count entries like neuzip_compress_batch and synchronise the
- *   stream once per group of up to 8 tensors.  A caller that wants a fresh table every N steps
+ *   Both work on host arrays of count entries like neuzip_compress_batch, and the host waits
+ *   once per group of up to 8 tensors.  A caller that wants a fresh table every N steps
  *   calls neuzip_compress_guarded then.
  */
 int neuzip_compress_guarded(const void *const *d_srcs, const uint64_t *n_elems, uint32_t count, int dtype,
@@ -204,7 +212,7 @@ int neuzip_recompress(const void *const *d_srcs, uint32_t count, void *hip_strea
  * weight is never written) and the new weight is then coded as by neuzip_recompress; otherwise the
  * one-pass encoder of neuzip_recompress reads weight and gradient, forms the new weight, writes it
  * back to d_weights and codes it.  Either way the table the blob holds is used, with the fallback
- * to fresh statistics.  Synchronises the stream once per group of up to 8 weights.
+ * to fresh statistics.  The host waits once per group of up to 8 weights.
  */
 enum {
     NEUZIP_UPDATE_FROM_BLOB = 0,
@@ -395,7 +403,7 @@ int neuzip_check(const neuzip_blob *blob, void *hip_stream);
  *   - all calls on one GPU share that GPU's array: calls that overlap in time on one GPU (from
  *     several host threads or streams) race and must be serialised by the caller.  The array
  *     keeps the last call's contents; the call clears what has to start at zero.
- * Synchronises hip_stream once, like neuzip_compress.
+ * Synchronises hip_stream once: the blob is complete when the call returns.
  */
 #define NEUZIP_NOALLOC_MAX_ELEMS (1ull << 22)
 int neuzip_compress_noalloc(const void *d_src, uint64_t n_elems, int dtype, int mantissa_bits,

@@ -21,6 +21,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 #include <cstdlib>
 #include <chrono>
@@ -126,6 +127,8 @@ struct neuzip_blob {
     uint64_t fixed_bytes;
     uint8_t *words;
     uint64_t words_bytes;  // capacity of the word allocation
+    uint64_t filled_by;    // number of the compress call that filled it, whose last kernels may still run ...
+    hipStream_t filled_on; // ... on this stream (0 and nullptr: the host has waited for them)
     Layout at;
     bool have_counts;
     uint32_t h_counts[256];
@@ -177,11 +180,54 @@ struct Workspace {
     uint16_t *slots = nullptr;
     HostRecord *pinned = nullptr;     // pinned host memory, written by the encode kernel
     uint32_t seq = 0;                 // stamp of the last compress call
-    hipEvent_t idle = nullptr;        // recorded behind the last kernel of every call that uses the workspace
-    hipStream_t last_stream = nullptr; // ... on this stream
+    hipStream_t last_stream = nullptr; // of the last call
 };
 std::mutex g_ws_mutex;
 Workspace g_ws;
+
+// Compress calls on the shared workspace are numbered, and each comes behind the one before it, on whatever streams they are.
+// A call returns while its last kernels may still run, but once its encoder has reported, every call before it is complete.
+uint64_t g_calls = 0;                          // (under g_ws_mutex)
+std::atomic<uint64_t> g_calls_complete{0};     // calls up to this number are
+std::mutex g_idle_mutex;                       // taken behind g_ws_mutex, or alone
+hipEvent_t g_idle = nullptr;                   // recorded behind the last kernel of every call; nullptr without a workspace
+
+// (the handle of the per-thread default stream is another stream in every thread)
+inline bool same_stream(hipStream_t a, hipStream_t b) { return a == b && a != hipStreamPerThread; }
+
+// Orders what `stream` is given next behind the calls that filled the blobs.  Calls that read a blob on the stream that it was
+// filled on, or after the next compress call has reported, find nothing to do.  A stream under capture is left as it is.
+int follow(const neuzip_blob *const *blobs, uint32_t count, hipStream_t stream)
+{
+    uint64_t last = 0;
+    for (uint32_t i = 0; i < count; ++i)
+        if (blobs[i]->filled_by > last && !same_stream(blobs[i]->filled_on, stream))
+            last = blobs[i]->filled_by;
+    if (last <= g_calls_complete.load(std::memory_order_acquire))
+        return NEUZIP_OK;
+    std::lock_guard<std::mutex> lock(g_idle_mutex);
+    if (!g_idle)
+        return NEUZIP_OK;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return NEUZIP_OK;
+    }
+    NZ_HIP(hipStreamWaitEvent(stream, g_idle, 0));
+    return NEUZIP_OK;
+}
+inline int follow(const neuzip_blob *blob, hipStream_t stream) { return follow(&blob, 1, stream); }
+
+// Every way out of a call that may have launched kernels on the shared workspace, behind the last of them, failures included:
+// calls on other streams wait for this event.
+bool leave_workspace(hipStream_t stream)
+{
+    std::lock_guard<std::mutex> lock(g_idle_mutex);
+    if (hip_ok(hipEventRecord(g_idle, stream)))
+        return true;
+    (void)hipStreamSynchronize(stream);
+    return false;
+}
 
 int release_workspace_locked()
 {
@@ -192,11 +238,16 @@ int release_workspace_locked()
             return NEUZIP_EHIP;
         if (!hip_ok(hipSetDevice(g_ws.device)))
             return NEUZIP_EHIP;
-        if (g_ws.idle) {
-            if (!hip_ok(hipEventSynchronize(g_ws.idle)))
-                rc = NEUZIP_EHIP;
-            (void)hipEventDestroy(g_ws.idle);
+        {
+            std::lock_guard<std::mutex> lock(g_idle_mutex);
+            if (g_idle) {
+                if (!hip_ok(hipEventSynchronize(g_idle)))
+                    rc = NEUZIP_EHIP;
+                (void)hipEventDestroy(g_idle);
+                g_idle = nullptr;
+            }
         }
+        g_calls_complete.store(g_calls, std::memory_order_release);
         void *device_arrays[] = {g_ws.counts, g_ws.chunk_words, g_ws.group_words, g_ws.super_words, g_ws.slots};
         for (void *ptr : device_arrays)
             if (ptr)
@@ -251,16 +302,6 @@ void reset_workspace(const Workspace &ws, hipStream_t stream)
     (void)hipGetLastError();
 }
 
-// Every way out of a call that may have launched kernels on the shared workspace, behind the last of them, failures included:
-// the next call on another stream waits for this event.
-bool leave_workspace(hipStream_t stream)
-{
-    if (hip_ok(hipEventRecord(g_ws.idle, stream)))
-        return true;
-    (void)hipStreamSynchronize(stream);
-    return false;
-}
-
 // First use on a device: the arrays whose size does not depend on the tensors.
 int create_workspace(int device, hipStream_t stream)
 {
@@ -270,11 +311,15 @@ int create_workspace(int device, hipStream_t stream)
     NZ_HIP(hipHostMalloc(reinterpret_cast<void **>(&g_ws.pinned), sizeof(HostRecord), hipHostMallocDefault));
     std::memset(g_ws.pinned, 0, sizeof(HostRecord));
     g_ws.seq = 0;
-    NZ_HIP(hipEventCreateWithFlags(&g_ws.idle, hipEventDisableTiming));
+    {
+        std::lock_guard<std::mutex> lock(g_idle_mutex);
+        NZ_HIP(hipEventCreateWithFlags(&g_idle, hipEventDisableTiming));
+    }
     hipLaunchKernelGGL(fill_u32_kernel, dim3((kSmallWords + 255) / 256), dim3(256), 0, stream, g_ws.counts, 0u,
                        kSmallWords);
     NZ_HIP(hipGetLastError());
-    NZ_HIP(hipEventRecord(g_ws.idle, stream));
+    if (!leave_workspace(stream))
+        return NEUZIP_EHIP;
     g_ws.last_stream = stream;
     return NEUZIP_OK;
 }
@@ -295,11 +340,11 @@ int ensure_workspace(int device, uint64_t n_groups, hipStream_t stream)
     }
     // the previous user of the workspace may still be running on another stream (on the same one, the
     // stream's own order does)
-    if (stream != g_ws.last_stream)
-        NZ_HIP(hipStreamWaitEvent(stream, g_ws.idle, 0));
+    if (!same_stream(stream, g_ws.last_stream))
+        NZ_HIP(hipStreamWaitEvent(stream, g_idle, 0));
     g_ws.last_stream = stream;
     if (g_ws.group_cap < n_groups) {
-        NZ_HIP(hipEventSynchronize(g_ws.idle));
+        NZ_HIP(hipEventSynchronize(g_idle));
         void *old_arrays[] = {g_ws.chunk_words, g_ws.group_words, g_ws.super_words, g_ws.slots};
         for (void *ptr : old_arrays)
             if (ptr)
@@ -827,6 +872,8 @@ int compress_tiled(neuzip_blob *b, const void *d_src, const void *d_grad, int k,
     int rc = ensure_workspace(b->device, tile_groups, stream);
     if (rc != NEUZIP_OK)
         return rc;
+    const uint64_t call = b->filled_by = ++g_calls;
+    b->filled_on = stream;
     const int variant = d_grad ? kUpdateVariant : (elem == NEUZIP_F32 ? 23 : (elem == NEUZIP_F16 ? 39 : k));
     const uint32_t src_bytes = elem == NEUZIP_F32 ? 4u : 2u;
     bool bins_dirty = false;
@@ -909,6 +956,7 @@ int compress_tiled(neuzip_blob *b, const void *d_src, const void *d_grad, int k,
             return fail(NEUZIP_EHIP);
         if (!wait_for_record(batch.seq, batch.count, stream))
             return fail(NEUZIP_EHIP);
+        g_calls_complete.store(call - 1, std::memory_order_release);
         bins_dirty = !reuse && !last;  // the histogram bins stay until the last tile has been encoded
         const HostRecord::Item &r = ws.pinned->item[0];
         if (reuse && told_stale(r.told)) {
@@ -1113,9 +1161,13 @@ int compress_some(const void *const *d_srcs, const uint64_t *n_elems, uint32_t c
     if (batch.count > 0) {
         std::lock_guard<std::mutex> lock(g_ws_mutex);
         int rc = NEUZIP_OK;
+        uint64_t call = 0;
         if (fixed_ws) {
             if (enc_groups > ws.group_cap)
                 return fail(NEUZIP_EUNSUPPORTED);
+            rc = follow(work, count, stream);
+            if (rc != NEUZIP_OK)
+                return fail(rc);
             // the static array keeps what the last call left: bins, call states and sums start at zero
             reset_workspace(ws, stream);
         } else {
@@ -1123,6 +1175,11 @@ int compress_some(const void *const *d_srcs, const uint64_t *n_elems, uint32_t c
             if (rc != NEUZIP_OK)
                 return fail(rc);
             ws_used = true;
+            call = ++g_calls;
+        }
+        for (uint32_t j = 0; j < batch.count; ++j) {
+            work[owner[j]]->filled_by = call;
+            work[owner[j]]->filled_on = fixed_ws ? nullptr : stream;
         }
         batch.seq = ++ws.seq;
         batch.lr = lr;
@@ -1174,8 +1231,10 @@ int compress_some(const void *const *d_srcs, const uint64_t *n_elems, uint32_t c
                                        hipMemcpyDeviceToHost, stream)) ||
                 !hip_ok(hipStreamSynchronize(stream)))
                 return fail(NEUZIP_EHIP);
-        } else if (!wait_for_record(batch.seq, batch.count, stream)) {
-            return fail(NEUZIP_EHIP);
+        } else {
+            if (!wait_for_record(batch.seq, batch.count, stream))
+                return fail(NEUZIP_EHIP);
+            g_calls_complete.store(call - 1, std::memory_order_release);
         }
         uint32_t n_stale = 0;
         bool late = false;
@@ -1371,6 +1430,9 @@ int neuzip_update(neuzip_blob *const *blobs, const void *const *d_grads, void *c
         for (uint32_t i = 0; i < count; ++i)
             rebuilt[i] = 0;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    const int behind = follow(blobs, count, stream);
+    if (behind != NEUZIP_OK)
+        return behind;
     // Two routes, chosen by what the caller holds (measured on a 4096 x 14336 weight: 148 and 122 us;
     // either route in the other's place costs 10-20 % more, because of the bytes it moves).
     // a) Only the blob: the decoder applies the step on its way out, so that d_weights receives the
@@ -1464,6 +1526,9 @@ int neuzip_linear_batch(const neuzip_blob *const *weights, const uint64_t *out_f
             return NEUZIP_EINVAL;
     }
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    const int behind = follow(weights, count, stream);
+    if (behind != NEUZIP_OK)
+        return behind;
     uint64_t gcd = in_features, r = kChunk;
     while (r) {
         const uint64_t t = gcd % r;
@@ -1694,7 +1759,8 @@ int neuzip_decompress(const neuzip_blob *blob, void *d_dst, uint64_t n_elems, in
         return NEUZIP_EINVAL;
     if (n_elems > 0 && (!d_dst || (reinterpret_cast<uintptr_t>(d_dst) & 15u)))
         return NEUZIP_EINVAL;
-    return decode_dispatch(blob, d_dst, static_cast<hipStream_t>(hip_stream));
+    const int behind = follow(blob, static_cast<hipStream_t>(hip_stream));
+    return behind == NEUZIP_OK ? decode_dispatch(blob, d_dst, static_cast<hipStream_t>(hip_stream)) : behind;
 }
 
 int neuzip_decompress_sequence(const neuzip_blob *const *blobs, uint32_t count, void *d_scratch,
@@ -1711,6 +1777,9 @@ int neuzip_decompress_sequence(const neuzip_blob *const *blobs, uint32_t count, 
             return NEUZIP_EINVAL;
     }
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    const int behind = follow(blobs, count, stream);
+    if (behind != NEUZIP_OK)
+        return behind;
     // Neighbouring blobs of one kind that fit the space together are placed one behind the other, each
     // at a 256-byte boundary, and share a launch (up to kBatchMax of them): tensors too small to fill
     // the chip on their own then overlap.  The next group starts at the front of the space again.
@@ -1761,6 +1830,9 @@ int neuzip_decompress_batch(const neuzip_blob *const *blobs, void *const *d_dsts
             return NEUZIP_EINVAL;
     }
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    const int behind = follow(blobs, count, stream);
+    if (behind != NEUZIP_OK)
+        return behind;
     uint64_t batch_elems = 0;
     for (uint32_t i = 0; i < count; ++i)
         batch_elems += (blobs[i]->elem == NEUZIP_F32) ? 2 * blobs[i]->n : blobs[i]->n;
@@ -1842,6 +1914,9 @@ int neuzip_export(const neuzip_blob *blob, void *h_buf, uint64_t cap, uint64_t *
     if (cap < lay.total)
         return NEUZIP_ENOMEM;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    const int behind = follow(blob, stream);
+    if (behind != NEUZIP_OK)
+        return behind;
     uint8_t *p = static_cast<uint8_t *>(h_buf);
     std::memset(p, 0, lay.total);
     auto put32 = [&](uint64_t at, uint32_t v) { std::memcpy(p + at, &v, 4); };
@@ -2107,6 +2182,9 @@ int neuzip_check(const neuzip_blob *blob, void *hip_stream)
     if (!is_blob(blob) || !on_current_device(blob))
         return NEUZIP_EINVAL;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    const int behind = follow(blob, stream);
+    if (behind != NEUZIP_OK)
+        return behind;
     uint32_t flag = 0;
     NZ_HIP(hipMemcpyAsync(&flag, table_of(blob)->status, 4, hipMemcpyDeviceToHost, stream));
     NZ_HIP(hipStreamSynchronize(stream));

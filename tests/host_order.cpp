@@ -159,7 +159,7 @@ namespace {
 
 const hipStream_t A = reinterpret_cast<hipStream_t>(0x1000), B = reinterpret_cast<hipStream_t>(0x2000);
 void *const kSomewhere = reinterpret_cast<void *>(0x100000);
-constexpr uint64_t kElems = 1000000;
+constexpr uint64_t kElems = 128 * 8000;
 
 neuzip_blob *compressed(hipStream_t s, neuzip_blob *blob = nullptr, uint64_t n = kElems)
 {
@@ -193,6 +193,101 @@ void after_a_failure()
     expect_behind("the next call", [] { compressed(B); return 0; });
 }
 
+// The calls that read blobs, on B, each with blobs that the latest compress call has filled on A.
+struct Reader { const char *what; std::function<int(neuzip_blob *, hipStream_t)> call; };
+std::vector<Reader> readers()
+{
+    auto room = [] { static uint8_t buffer[1 << 22]; return static_cast<void *>(buffer); };
+    return {
+        {"decompress", [](neuzip_blob *b, hipStream_t s) { return neuzip_decompress(b, kSomewhere, kElems, NEUZIP_BF16, s); }},
+        {"decompress_batch", [](neuzip_blob *b, hipStream_t s) {
+             void *dst = kSomewhere;
+             return neuzip_decompress_batch(&b, &dst, 1, s);
+         }},
+        {"decompress_sequence", [](neuzip_blob *b, hipStream_t s) {
+             return neuzip_decompress_sequence(&b, 1, kSomewhere, kElems, nullptr, s);
+         }},
+        {"linear", [](neuzip_blob *b, hipStream_t s) {
+             return neuzip_linear(b, kElems / 128, 128, kSomewhere, 1, nullptr,
+                                  static_cast<float *>(kSomewhere), s);
+         }},
+        {"update", [](neuzip_blob *b, hipStream_t s) {
+             const void *grad = static_cast<uint8_t *>(kSomewhere) + 256;
+             void *weight = kSomewhere;
+             return neuzip_update(&b, &grad, &weight, 1, 1.0f, NEUZIP_UPDATE_FROM_BLOB, s, nullptr);
+         }},
+        {"recompress", [](neuzip_blob *b, hipStream_t s) {
+             const void *src = kSomewhere;
+             return neuzip_recompress(&src, 1, s, &b, nullptr);
+         }},
+        {"compress_noalloc", [](neuzip_blob *b, hipStream_t s) {
+             return neuzip_compress_noalloc(kSomewhere, kElems, NEUZIP_BF16, 7, s, b);
+         }},
+        {"export", [room](neuzip_blob *b, hipStream_t s) {
+             uint64_t written = 0;
+             return neuzip_export(b, room(), 1 << 22, &written, s);
+         }},
+        {"check", [](neuzip_blob *b, hipStream_t s) { return neuzip_check(b, s); }},
+    };
+}
+
+void expect_no_wait(const char *what, const std::function<int()> &call)
+{
+    const int before = g_waits;
+    expect(call() == NEUZIP_OK, std::string(what) + " failed");
+    expect(g_waits == before, std::string(what) + " made a stream wait for nothing");
+}
+
+void read_on_another_stream()
+{
+    for (const Reader &r : readers()) {
+        neuzip_blob *blob = compressed(A);
+        expect_behind(r.what, [&] { return r.call(blob, B); });
+        neuzip_free(blob);
+    }
+}
+
+// Where there is nothing to wait for, no event gets between: the same stream, a later call that has reported, a workspace that
+// has been given back (which waits), a call that synchronises.
+void read_without_waiting()
+{
+    for (const Reader &r : readers()) {
+        const std::string what = r.what;
+        if (what == "update" || what == "recompress")   // (they use the workspace, and wait for it)
+            continue;
+        neuzip_blob *blob = compressed(A);
+        expect_no_wait(r.what, [&] { return r.call(blob, A); });
+        blob = compressed(A, blob);
+        neuzip_blob *other = compressed(A);
+        expect_no_wait(r.what, [&] { return r.call(blob, B); });
+        blob = compressed(A, blob);
+        expect(neuzip_release_workspace() == NEUZIP_OK, "release");
+        expect_no_wait(r.what, [&] { return r.call(blob, B); });
+        expect(neuzip_compress_noalloc(kSomewhere, kElems, NEUZIP_BF16, 7, A, blob) == NEUZIP_OK, "noalloc");
+        expect_no_wait(r.what, [&] { return r.call(blob, B); });
+        neuzip_free(blob);
+        neuzip_free(other);
+    }
+}
+
+void read_under_capture()
+{
+    neuzip_blob *blob = compressed(A);
+    g_capturing = true;
+    expect_no_wait("decompress", [&] { return readers()[0].call(blob, B); });
+    expect_no_wait("linear", [&] { return readers()[3].call(blob, B); });
+}
+
+// Blobs of a batch that other streams have filled: behind the latest of them.
+void read_a_batch()
+{
+    neuzip_blob *blobs[3] = {compressed(B), compressed(A), compressed(A)};
+    void *dsts[3] = {kSomewhere, kSomewhere, kSomewhere};
+    expect_behind("decompress_batch", [&] { return neuzip_decompress_batch(blobs, dsts, 3, B); });
+    blobs[0] = compressed(A, blobs[0]);
+    expect_behind("decompress_batch", [&] { return neuzip_decompress_batch(blobs, dsts, 3, B); });
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -203,6 +298,17 @@ int main(int argc, char **argv)
     } else if (s == "failure_in_a_tile") {
         expect(neuzip_set_workspace_limit(102400) == NEUZIP_OK, "limit");
         after_a_failure();
+    } else if (s == "other_stream") {
+        read_on_another_stream();
+    } else if (s == "other_stream_in_tiles") {
+        expect(neuzip_set_workspace_limit(102400) == NEUZIP_OK, "limit");
+        read_on_another_stream();
+    } else if (s == "nothing_to_wait_for") {
+        read_without_waiting();
+    } else if (s == "capture") {
+        read_under_capture();
+    } else if (s == "batch") {
+        read_a_batch();
     } else {
         wrong("unknown scenario " + s);
     }

@@ -1,0 +1,84 @@
+"""Blobs that are read on another stream than the one they were filled on, at once (-m gpu): the library orders its own calls
+behind the compress call, with no wait of the caller's.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2410_20650_amd import inputs
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def nz():
+    from paper_2410_20650_amd import binding
+    return binding
+
+
+def streams():
+    torch.cuda.synchronize()
+    return torch.cuda.Stream(DEV), torch.cuda.Stream(DEV)
+
+
+# entry points, whole states, tiles; the first call allocates the blob, the others fill the room it has
+@pytest.mark.parametrize("n, limit", [(70_001, 0), (4096 * 4096, 0), (58_720_256, 0), (3_000_001, 16 * 6400 * 20)])
+def test_decompress_and_export_on_a_second_stream(nz, n, limit):
+    ws = [inputs.gaussian_bf16(n, 6000 + i, device=DEV) * 2.0 ** i for i in range(4)]
+    outs = [torch.empty_like(ws[0]) for _ in ws]
+    first, second = streams()
+    nz.neuzip_set_workspace_limit(limit)
+    try:
+        blob = None
+        for w, out in zip(ws, outs):
+            blob = nz.neuzip_compress(w, 7, stream=first, blob=blob)
+            nz.neuzip_decompress(blob, out, stream=second)
+            if n < 1 << 23:
+                assert np.array_equal(nz.neuzip_export(blob, stream=second), O.compress(inputs.bits(w), 7, threads=4))
+            read = torch.cuda.Event()
+            read.record(second)
+            first.wait_event(read)      # (that the blob has been read before it is filled again is the caller's to order)
+        torch.cuda.synchronize()
+    finally:
+        nz.neuzip_set_workspace_limit(0)
+    for w, out in zip(ws, outs):
+        assert torch.equal(out.view(torch.int16), w.view(torch.int16))
+    nz.neuzip_check(blob)
+
+
+def test_batch_linear_update_and_noalloc_on_a_second_stream(nz):
+    shapes = [(1024, 4096), (1000, 4096), (1024, 4096)]
+    ws = [inputs.gaussian_bf16(s, 6100 + i, device=DEV) for i, s in enumerate(shapes)]
+    x = inputs.gaussian_bf16((8, 4096), 6110, std=1.0, device=DEV)
+    grads = [inputs.gaussian_bf16(w.numel(), 6120 + i, device=DEV) for i, w in enumerate(ws)]
+    outs = [torch.empty_like(w) for w in ws]
+    first, second = streams()
+    blobs = nz.neuzip_compress_guarded(ws, 7, 8, stream=first)
+    nz.neuzip_decompress_batch(blobs, outs, stream=second)
+    for w, out in zip(ws, outs):
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), w.view(torch.int16))
+    blobs = nz.neuzip_compress_guarded(ws, 7, 8, stream=first, blobs=blobs)
+    with torch.cuda.stream(second):
+        ys = nz.neuzip_linear_batch(blobs, [s[0] for s in shapes], 4096, x)
+    torch.cuda.synchronize()
+    for y, w in zip(ys, ws):
+        want, size = x.double() @ w.double().t(), x.double().abs() @ w.double().abs().t()
+        assert bool(((y.double() - want).abs() <= 2 * 4160 * 2.0 ** -24 * size).all())     # float32 sums, any order
+    blobs = nz.neuzip_compress_guarded(ws, 7, 8, stream=first, blobs=blobs)
+    spaces = [torch.empty_like(g) for g in grads]
+    nz.neuzip_update(blobs, grads, spaces, 0.125, weights_ready=0, stream=second)
+    torch.cuda.synchronize()
+    for blob, w, g in zip(blobs, ws, grads):
+        new = (w.view(-1).float() - 0.125 * g.float()).to(torch.bfloat16)
+        out = torch.empty_like(new)
+        nz.neuzip_decompress(blob, out)
+        assert torch.equal(out.view(torch.int16), new.view(torch.int16))
+    torch.cuda.synchronize()
+    blob = nz.neuzip_compress(ws[0], 7, stream=first)
+    nz.neuzip_compress_noalloc(ws[2], 7, blob, stream=second)
+    nz.neuzip_decompress(blob, outs[0])
+    assert torch.equal(outs[0].view(torch.int16), ws[2].view(torch.int16))
+    nz.neuzip_check(blob)

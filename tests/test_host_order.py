@@ -32,3 +32,13 @@ def run(driver, scenario):
 @pytest.mark.parametrize("scenario", ["failure", "failure_in_a_tile"])
 def test_a_failed_call_is_behind_the_next_one_on_another_stream(driver, scenario):
     run(driver, scenario)
+
+
+@pytest.mark.parametrize("scenario", ["other_stream", "other_stream_in_tiles", "batch"])
+def test_calls_that_read_a_blob_are_behind_the_call_that_fills_it(driver, scenario):
+    run(driver, scenario)
+
+
+@pytest.mark.parametrize("scenario", ["nothing_to_wait_for", "capture"])
+def test_no_event_where_there_is_nothing_to_wait_for(driver, scenario):
+    run(driver, scenario)

@@ -22,6 +22,7 @@
  *     below 2^32.
  *   - A compress, recompress or update call waits for the lengths of the streams, which depend on the
  *     data, and returns while its last kernels, which complete the blobs, may still run on hip_stream.
+ *     The caller's buffers are done with by then: sources have been read, new weights written.
  *     The calls of this library that read such a blob are ordered behind them, on the same stream by
  *     its own order, on another one by an event that the library makes that stream wait for (the host
  *     does not wait).  A stream under capture is not made to wait: a blob that was filled on another

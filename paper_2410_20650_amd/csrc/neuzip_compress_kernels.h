@@ -1169,7 +1169,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
         group_words_all[group] = total;
         atomicAdd(&super_words_all[it.super_base + slot_id.wg / kSuperGroups], total);
         const unsigned long long so_far = atomicAdd(&state->total[slot_id.item], kOneDone | total);
-        if (so_far / kOneDone + 1 == slot_id.wgs) {
+        if (so_far / kOneDone + 1 == slot_id.wgs && !(UPD && b.tell_late)) {
             // The tensor's last workgroup tells the host the stream's length, while the compaction is still to come:
             // what the host does next (return to its caller, launch that call's successor) takes place beside the
             // compaction and not behind it.  The record is host memory the host polls; length, flag and stamp are one
@@ -1209,7 +1209,8 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const Compress
                                                                  const CallState *__restrict__ state,
                                                                  uint32_t *__restrict__ counts_ws,
                                                                  CallState *__restrict__ state_next,
-                                                                 uint32_t *__restrict__ super_next, uint32_t super_cap)
+                                                                 uint32_t *__restrict__ super_next, uint32_t super_cap,
+                                                                 HostRecord *__restrict__ record)
 {
     const ItemSlot slot_id = item_of_workgroup<&CompressItem::compact_end>(b);
     const CompressItem &it = b.it[slot_id.item];
@@ -1233,6 +1234,10 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const Compress
                 it.offsets[n_chunks] = static_cast<uint32_t>(all_words);
                 it.offsets[n_chunks + 1] = 0;
             }
+            if (b.tell_late)
+                __hip_atomic_store(&record->item[slot_id.item].told,
+                                   told_of(state->total[slot_id.item] & (kOneDone - 1), was_stale, b.seq), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }
     // (the same decision in all workgroups of the tensor)

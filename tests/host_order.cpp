@@ -28,7 +28,7 @@ uint64_t g_words = 1000;                        // stream length that the encode
 int g_mallocs_until_failure = -1;
 int g_waits = 0;
 bool g_capturing = false;
-std::vector<std::string> g_launched;
+std::string g_told_by;                          // the kernel that told the host last
 struct { dim3 grid, block; size_t shared; hipStream_t stream; } g_call;
 
 void join(Clock &into, const Clock &from)
@@ -82,11 +82,14 @@ hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *shared, hi
 hipError_t hipLaunchKernel(const void *fn, dim3, dim3, void **args, size_t, hipStream_t stream)
 {
     const std::string &name = names()[fn];
-    g_launched.push_back(name);
     work(stream);
-    if (name.find("encode_kernel") != std::string::npos) {
+    const bool encoder = name.find("encode_kernel") != std::string::npos;
+    if (encoder || name.find("compact_kernel") != std::string::npos) {
         const nz::CompressBatch &b = *static_cast<const nz::CompressBatch *>(args[0]);
-        for (uint32_t i = 0; i < b.count && g_record; ++i)
+        const bool tells = encoder ? !b.tell_late : b.tell_late && b.tidy;
+        if (tells)
+            g_told_by = name;
+        for (uint32_t i = 0; i < b.count && g_record && tells; ++i)
             g_record->item[i].told = nz::told_of(g_words, 0, b.seq);
     }
     return hipSuccess;
@@ -278,6 +281,22 @@ void read_under_capture()
     expect_no_wait("linear", [&] { return readers()[3].call(blob, B); });
 }
 
+// A weight step that writes the new weights back returns when the kernel that writes them has ended.
+void written_weights_are_complete()
+{
+    for (int ready : {NEUZIP_UPDATE_FROM_BLOB, NEUZIP_UPDATE_WEIGHTS_READY, NEUZIP_UPDATE_WEIGHTS_READY_DISCARD,
+                      NEUZIP_UPDATE_FROM_BLOB_DISCARD}) {
+        neuzip_blob *blob = compressed(A);
+        const void *grad = static_cast<uint8_t *>(kSomewhere) + 256;
+        void *weight = kSomewhere;
+        g_told_by.clear();
+        expect(neuzip_update(&blob, &grad, &weight, 1, 1.0f, ready, A, nullptr) == NEUZIP_OK, "update");
+        const char *from = ready == NEUZIP_UPDATE_WEIGHTS_READY ? "compact_kernel" : "encode_kernel";
+        expect(g_told_by.find(from) != std::string::npos, "told by " + g_told_by + ", not by " + from);
+        neuzip_free(blob);
+    }
+}
+
 // Blobs of a batch that other streams have filled: behind the latest of them.
 void read_a_batch()
 {
@@ -307,6 +326,11 @@ int main(int argc, char **argv)
         read_without_waiting();
     } else if (s == "capture") {
         read_under_capture();
+    } else if (s == "written_weights") {
+        written_weights_are_complete();
+    } else if (s == "written_weights_in_tiles") {
+        expect(neuzip_set_workspace_limit(102400) == NEUZIP_OK, "limit");
+        written_weights_are_complete();
     } else if (s == "batch") {
         read_a_batch();
     } else {

@@ -82,3 +82,28 @@ def test_batch_linear_update_and_noalloc_on_a_second_stream(nz):
     nz.neuzip_decompress(blob, outs[0])
     assert torch.equal(outs[0].view(torch.int16), ws[2].view(torch.int16))
     nz.neuzip_check(blob)
+
+
+# the new weights that the encoder writes back, read on another stream as soon as the call has returned
+@pytest.mark.parametrize("n, limit", [(70_001, 0), (58_720_256, 0), (3_000_001, 16 * 6400 * 20)])
+def test_new_weights_are_written_when_the_call_returns(nz, n, limit):
+    w, g = inputs.gaussian_bf16(n, 6200, device=DEV), inputs.gaussian_bf16(n, 6201, device=DEV)
+    first, second = streams()
+    nz.neuzip_set_workspace_limit(limit)
+    try:
+        (blob,) = nz.neuzip_compress_guarded([w], 7, 8, stream=first)
+        for _ in range(4):
+            want = (w.float() - 0.5 * g.float()).to(torch.bfloat16)
+            seen = torch.empty_like(w)
+            torch.cuda.synchronize()
+            nz.neuzip_update([blob], [g], [w], 0.5, weights_ready=1, stream=first)
+            with torch.cuda.stream(second):
+                seen.copy_(w)
+            torch.cuda.synchronize()
+            assert torch.equal(seen.view(torch.int16), want.view(torch.int16))
+            assert torch.equal(w.view(torch.int16), want.view(torch.int16))
+        out = torch.empty_like(w)
+        nz.neuzip_decompress(blob, out)
+        assert torch.equal(out.view(torch.int16), w.view(torch.int16))
+    finally:
+        nz.neuzip_set_workspace_limit(0)

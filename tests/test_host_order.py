@@ -42,3 +42,8 @@ def test_calls_that_read_a_blob_are_behind_the_call_that_fills_it(driver, scenar
 @pytest.mark.parametrize("scenario", ["nothing_to_wait_for", "capture"])
 def test_no_event_where_there_is_nothing_to_wait_for(driver, scenario):
     run(driver, scenario)
+
+
+@pytest.mark.parametrize("scenario", ["written_weights", "written_weights_in_tiles"])
+def test_weights_written_back_are_complete_when_the_call_returns(driver, scenario):
+    run(driver, scenario)

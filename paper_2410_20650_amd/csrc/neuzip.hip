@@ -260,6 +260,14 @@ int release_workspace_locked()
     return rc;
 }
 
+// Before the kernels of call `seq` are launched: stamps come around again after 2^30 calls, so what the record holds from then,
+// or from before its first use, must not pass for this call's.
+void expect_record(uint32_t seq, uint32_t items)
+{
+    for (uint32_t i = 0; i < items; ++i)
+        __atomic_store_n(&g_ws.pinned->item[i].told, told_of(0, 0, seq + 1), __ATOMIC_RELAXED);
+}
+
 // Waits until the record of call `seq` is complete.  The stamps come from the encode kernel's last workgroups, before
 // the compaction behind it (or from that one's first, see CompressBatch::tell_late), and well before a blocking stream
 // synchronise would wake up; after a bounded spin the stream is synchronised anyway, which also surfaces errors.
@@ -947,6 +955,7 @@ int compress_tiled(neuzip_blob *b, const void *d_src, const void *d_grad, int k,
         CallState *state = ws.state + copy, *state_next = ws.state + (copy ^ 1u);
         uint32_t *super_words = ws.super_words + copy * ws.super_cap;
         uint32_t *super_next = ws.super_words + (copy ^ 1u) * ws.super_cap;
+        expect_record(batch.seq, batch.count);
         // (the workgroup that fills in the decoder's slot table rides with the first tile)
         if (!launch_encode(ws, batch, it.enc_end + (!reuse && g0 == 0 ? 1u : 0u), variant, reuse, elem, block, super_words, state,
                            stream))
@@ -1177,6 +1186,7 @@ int compress_some(const void *const *d_srcs, const uint64_t *n_elems, uint32_t c
                 return fail(rc);
             ws_used = true;
             call = ++g_calls;
+            expect_record(ws.seq + 1, batch.count);
         }
         for (uint32_t j = 0; j < batch.count; ++j) {
             work[owner[j]]->filled_by = call;

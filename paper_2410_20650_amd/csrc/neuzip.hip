@@ -444,16 +444,17 @@ inline uint64_t words_room(const neuzip_blob *b)
 // 16 chunks 10.2 / 11.7), and 16, the most a workgroup of 8 waves has lanes for (10 M binary32 elements at 8 / 12 / 16 chunks:
 // 19.7 / 16.4 / 18.1 us; 12 M bf16 13.6 / 12.6 / 12.7; 16.8 M 14.4 / 17.1 / 14.0).
 // NEUZIP_DECODE_CHUNKS_PER_WG (4..32, multiple of 4) overrides the choice for tuning runs.
-// At most so many that their words fit the LDS window (at their average length and 3 % more): a walk whose words come from
+// At most so many that their words fit the LDS window (at their average length and 1 % more): a walk whose words come from
 // memory waits for every one of them.  Exponents of 4 bits, 58.7 M elements: 32 chunks 143.7 us, 16 58.8; of 5 bits, 100 M:
 // 251.6 and, with 20, 90.5; of 8 bits, 30 M: 85.2 and, with 12, 73.7; so are weights coded with a table that they have moved away
-// from.  binary16 symbols carry 5-6 bits each (sign and two mantissa bits ride in the symbol) and never take more than 16.
-constexpr uint32_t kFitBytes = 58 * 1024;
-static_assert(kFitBytes + kFitBytes / 33 < kStageBytesOf<1> && kStageBytesOf<1> <= kStageBytesOf<0>, "the smallest window");
+// from.  The 1 %: the words of 64 K symbols and more differ by 0.1 % from workgroup to workgroup where the exponents are alike
+// throughout, and by 0.4 % among some hundred.  (With 3 % or more, 4 chunks less than fit were taken from 3.6 to 3.8 bits,
+// 30 M elements 35.5 us, 29.6 now, 100 M 83.6 / 76.0, and from 7.2 to 7.7, 16.8 M 18.9 / 16.8.)  binary16 symbols carry 5-6 bits each (sign and two mantissa bits ride in the symbol) and never take more than 16.
 inline uint32_t chunks_that_fit(const neuzip_blob *b)
 {
+    const uint32_t window = b->k == 1 ? kStageBytesOf<1> : (b->k == 0 ? kStageBytesOf<0> : kStageBytesOf<7>);
     const uint64_t bytes = b->total_words * 2 / b->n_chunks + 1;  // of a chunk's words
-    const uint64_t fit = kFitBytes / bytes / 4 * 4;
+    const uint64_t fit = (window - window / 100) / bytes / 4 * 4;
     return fit < 4 ? 4u : (fit < kDecChunksPerWg ? static_cast<uint32_t>(fit) : kDecChunksPerWg);
 }
 

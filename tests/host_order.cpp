@@ -28,6 +28,7 @@ uint64_t g_words = 1000;                        // stream length that the encode
 int g_mallocs_until_failure = -1;
 int g_waits = 0;
 bool g_capturing = false;
+uint32_t g_threads = 0;                         // of a workgroup of the last launch
 bool g_slow_kernels = false;                    // the host has to wait for the stream before it is told anything
 std::vector<std::pair<uint32_t, unsigned long long>> g_to_tell;
 std::string g_told_by;                          // the kernel that told the host last
@@ -81,9 +82,10 @@ hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *shared, hi
     *grid = g_call.grid, *block = g_call.block, *shared = g_call.shared, *stream = g_call.stream;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void *fn, dim3, dim3, void **args, size_t, hipStream_t stream)
+hipError_t hipLaunchKernel(const void *fn, dim3, dim3 block, void **args, size_t, hipStream_t stream)
 {
     const std::string &name = names()[fn];
+    g_threads = block.x;
     work(stream);
     const bool encoder = name.find("encode_kernel") != std::string::npos;
     if (encoder || name.find("compact_kernel") != std::string::npos) {
@@ -329,6 +331,27 @@ void an_old_stamp()
     }
 }
 
+// A decoder's workgroup has as many chunks as their words fit the LDS window by their average and a hundredth, four at a time.
+void chunks_of_a_workgroup()
+{
+    for (int k : {7, 3, 1, 0})
+        for (uint64_t chunks : {4096, 5000})
+            for (uint64_t bytes = 1000; bytes <= 6000; bytes += 20) {     // of a chunk's words
+                const uint32_t lanes = nz::has_entry_points(static_cast<uint32_t>(chunks)) ? 32 : 16, most = 512 / lanes;
+                const double window = 62 * 1024 - (k == 1 ? 2048 : (k == 0 ? 128 : 0));
+                g_words = chunks * bytes / 2;
+                neuzip_blob *blob = nullptr;
+                expect(neuzip_compress(kSomewhere, chunks * nz::kChunk, NEUZIP_BF16, k, A, &blob) == NEUZIP_OK, "compress");
+                expect(neuzip_decompress(blob, kSomewhere, chunks * nz::kChunk, NEUZIP_BF16, A) == NEUZIP_OK, "decompress");
+                const uint32_t per = g_threads / lanes;
+                const std::string what = std::to_string(per) + " chunks of " + std::to_string(bytes) + " bytes, k = " + std::to_string(k);
+                expect(per % 4 == 0 && per * lanes == g_threads && per >= 4 && per <= most, what);
+                expect(per * bytes * 1.005 < window, what + " do not fit");
+                expect(per == most || (per + 4) * (bytes + 2) * 1.0105 > window, what + " are fewer than fit");
+                neuzip_free(blob);
+            }
+}
+
 // Blobs of a batch that other streams have filled: behind the latest of them.
 void read_a_batch()
 {
@@ -363,6 +386,8 @@ int main(int argc, char **argv)
     } else if (s == "written_weights_in_tiles") {
         expect(neuzip_set_workspace_limit(102400) == NEUZIP_OK, "limit");
         written_weights_are_complete();
+    } else if (s == "chunks_of_a_workgroup") {
+        chunks_of_a_workgroup();
     } else if (s == "old_stamp") {
         an_old_stamp();
     } else if (s == "batch") {

@@ -1,5 +1,5 @@
-"""The order that compress calls leave between streams, without a GPU: the library's host code is driven on a double of the
-HIP runtime (host_order.cpp) that keeps what every launch and copy is ordered behind.
+"""The order that compress calls leave between streams, and the shapes of launches, without a GPU: the library's host code is
+driven on a double of the HIP runtime (host_order.cpp) that keeps what every launch and copy is ordered behind.
 """
 import os
 import subprocess
@@ -51,3 +51,7 @@ def test_weights_written_back_are_complete_when_the_call_returns(driver, scenari
 
 def test_an_old_stamp_is_not_taken_for_this_calls(driver):
     run(driver, "old_stamp")
+
+
+def test_a_decoders_workgroup_has_as_many_chunks_as_fit(driver):
+    run(driver, "chunks_of_a_workgroup")

@@ -458,6 +458,16 @@ inline uint32_t chunks_that_fit(const neuzip_blob *b)
     return fit < 4 ? 4u : (fit < kDecChunksPerWg ? static_cast<uint32_t>(fit) : kDecChunksPerWg);
 }
 
+// Symbols of 8 bits, all alike -- bits without structure -- have runs of 256 bytes (127 or 128 words), one as long as the
+// other: the lanes of a wave begin in one LDS bank and stay together, and every step of the walk without a branch, which reads
+// a word whether it consumes one or not, waits for 64 reads one after the other.  With the branch those read that consume
+// (0.05 M elements 17.3 / 13.6 us, 4 M 19.6 / 16.0, 16.8 M 50.0 / 32.0).  Any other distribution stays below 7.95 bits or has
+// runs that differ, and is better off without the branch (7.75 bits: 0.05 M 9.9 / 11.4 us, 4 M 11.3 / 12.8, 12.6 M 13.8 / 15.0).
+inline bool runs_in_step(const neuzip_blob *b)
+{
+    return b->total_words * 1600 >= 795 * b->n && b->total_words * 1600 <= 801 * b->n;
+}
+
 uint32_t decode_chunks_per_wg(const neuzip_blob *b)
 {
     static int forced = -1;
@@ -504,6 +514,7 @@ DecodeArgs decode_args(const neuzip_blob *b, void *d_dst)
     a.n_chunks = b->n_chunks;
     a.wg_end = 0;
     a.fit = b->n_chunks ? chunks_that_fit(b) : 0u;
+    a.in_step = runs_in_step(b) ? 1u : 0u;
     return a;
 }
 
@@ -527,7 +538,14 @@ int launch_decode(const neuzip_blob *b, void *d_dst, hipStream_t stream)
             return hip_ok(hipGetLastError()) ? NEUZIP_OK : NEUZIP_EHIP;
         }
     }
-    if (has_entry_points(b->n_chunks))
+    if (has_entry_points(b->n_chunks) && args.in_step) {  // (a launch of its own as a batch of one: the walk with the branch)
+        BatchArgs one;
+        one.t[0] = args;
+        one.t[0].wg_end = groups;
+        one.count = 1;
+        one.threads = block.x;
+        hipLaunchKernelGGL((decode_batch_kernel<KB, NORM, MODE, kEntries>), grid, block, 0, stream, one);
+    } else if (has_entry_points(b->n_chunks))
         hipLaunchKernelGGL((decode_kernel<KB, NORM, MODE, true>), grid, block, 0, stream, args);
     else
         hipLaunchKernelGGL((decode_kernel<KB, NORM, MODE, false>), grid, block, 0, stream, args);
@@ -606,15 +624,18 @@ template <int KB, bool NORM, int MODE = kPlain>
 void launch_batch_kernel(const BatchArgs &args, dim3 grid, dim3 block, hipStream_t stream)
 {
     bool entries = false, tables = true;
+    uint64_t all = 0, in_step = 0;
     for (uint32_t t = 0; t < args.count; ++t) {
         entries = entries || args.t[t].mid_states;
+        all += args.t[t].n;
+        in_step += args.t[t].in_step ? args.t[t].n : 0;
         tables = tables && holds_table(args.t[t].n_chunks);
     }
     // From the entry points (as place_workgroups decided), without a branch in the step where every CU has one workgroup at
     // most: 13 M elements in four tensors (205 workgroups) 13.9 us, with the branch 15.1; beyond, CUs with two have four waves
     // per SIMD, and with the branch 21 M in four tensors (321) take 19.4 instead of 23.1, 22 M (338) 18.5 instead of 21.1, 28 M in
-    // two (428) 24.3 and 23.8.
-    if (entries && !args.t[0].stream_out && grid.x <= 256)
+    // two (428) 24.3 and 23.8.  (With the branch too where most of the batch walks in step, see runs_in_step.)
+    if (entries && !args.t[0].stream_out && grid.x <= 256 && 2 * in_step <= all)
         hipLaunchKernelGGL((decode_batch_kernel<KB, NORM, MODE, kEntriesAlone>), grid, block, 0, stream, args);
     else if (entries && !args.t[0].stream_out)
         hipLaunchKernelGGL((decode_batch_kernel<KB, NORM, MODE, kEntries>), grid, block, 0, stream, args);

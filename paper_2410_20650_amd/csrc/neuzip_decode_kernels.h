@@ -603,6 +603,7 @@ struct DecodeArgs {
     uint32_t stream_out;  // non-zero: the output does not fit the last-level cache, store non-temporally
     uint32_t wg_end;      // batches: first workgroup index after this tensor's
     uint32_t fit;         // (for the host: chunks whose words fit a workgroup's LDS window)
+    uint32_t in_step;     // (for the host: the states' runs are of one length, see runs_in_step)
 };
 
 // MODE: what a decoder writes -- the decoded bf16 words (kPlain), binary32 words joined with their

@@ -29,6 +29,7 @@ int g_mallocs_until_failure = -1;
 int g_waits = 0;
 bool g_capturing = false;
 uint32_t g_threads = 0;                         // of a workgroup of the last launch
+std::string g_launched;                         // the last kernel
 bool g_slow_kernels = false;                    // the host has to wait for the stream before it is told anything
 std::vector<std::pair<uint32_t, unsigned long long>> g_to_tell;
 std::string g_told_by;                          // the kernel that told the host last
@@ -86,6 +87,7 @@ hipError_t hipLaunchKernel(const void *fn, dim3, dim3 block, void **args, size_t
 {
     const std::string &name = names()[fn];
     g_threads = block.x;
+    g_launched = name;
     work(stream);
     const bool encoder = name.find("encode_kernel") != std::string::npos;
     if (encoder || name.find("compact_kernel") != std::string::npos) {
@@ -352,6 +354,34 @@ void chunks_of_a_workgroup()
             }
 }
 
+// Blobs with entry points are walked without a branch in the step where every CU has one workgroup at most, but not those
+// whose runs all have 256 bytes.  (The last template argument: single launches' "entry points", batches' form of the walk.)
+void form_of_the_walk()
+{
+    for (double bits : {2.0, 7.75, 7.94, 7.96, 8.0, 8.005, 8.02, 11.0}) {
+        const bool in_step = bits > 7.95 && bits < 8.01;
+        for (uint64_t chunks : {3, 250, 2048}) {
+            const uint64_t n = chunks * nz::kChunk;
+            g_words = static_cast<uint64_t>(n * bits / 16);
+            neuzip_blob *blobs[2] = {compressed(A, nullptr, n), compressed(A, nullptr, n)};
+            void *dsts[2] = {kSomewhere, kSomewhere};
+            const std::string what = std::to_string(bits) + " bits: ";
+            expect(neuzip_decompress(blobs[0], kSomewhere, n, NEUZIP_BF16, A) == NEUZIP_OK, "decompress");
+            expect(g_launched.find(in_step ? "decode_batch_kernelILi7ELb0ELi0ELi2EE" : "decode_kernelILi7ELb0ELi0ELb1EE") != std::string::npos, what + g_launched);
+            expect(neuzip_decompress_batch(blobs, dsts, 2, A) == NEUZIP_OK, "decompress_batch");
+            const uint64_t per = g_threads / 32, alone = !in_step && 2 * ((chunks + per - 1) / per) <= 256;
+            expect(g_launched.find(alone ? "decode_batch_kernelILi7ELb0ELi0ELi4EE" : "decode_batch_kernelILi7ELb0ELi0ELi2EE") != std::string::npos, what + g_launched);
+            neuzip_free(blobs[0]);
+            neuzip_free(blobs[1]);
+        }
+    }
+    g_words = 4096 * 4096 / 2;  // a batch of more workgroups than CUs
+    neuzip_blob *blobs[2] = {compressed(A, nullptr, 4096 * 4096), compressed(A, nullptr, 4096 * 4096)};
+    void *dsts[2] = {kSomewhere, kSomewhere};
+    expect(neuzip_decompress_batch(blobs, dsts, 2, A) == NEUZIP_OK, "decompress_batch");
+    expect(g_launched.find("decode_batch_kernelILi7ELb0ELi0ELi2EE") != std::string::npos, g_launched);
+}
+
 // Blobs of a batch that other streams have filled: behind the latest of them.
 void read_a_batch()
 {
@@ -388,6 +418,8 @@ int main(int argc, char **argv)
         written_weights_are_complete();
     } else if (s == "chunks_of_a_workgroup") {
         chunks_of_a_workgroup();
+    } else if (s == "form_of_the_walk") {
+        form_of_the_walk();
     } else if (s == "old_stamp") {
         an_old_stamp();
     } else if (s == "batch") {

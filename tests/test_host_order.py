@@ -55,3 +55,7 @@ def test_an_old_stamp_is_not_taken_for_this_calls(driver):
 
 def test_a_decoders_workgroup_has_as_many_chunks_as_fit(driver):
     run(driver, "chunks_of_a_workgroup")
+
+
+def test_the_form_of_the_walk_from_the_entry_points(driver):
+    run(driver, "form_of_the_walk")

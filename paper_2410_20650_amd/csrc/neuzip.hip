@@ -710,10 +710,23 @@ inline LinearForm linear_form(uint32_t tokens, uint64_t in_features, const neuzi
 // Workgroups up to which the walks step without a branch (see rans_get): at most one per CU, two waves per SIMD (4096 x 4096,
 // 1 token, 15.5 us, with the branch 16.1; 1000 x 1024 17.0 / 17.7; 2048 x 4096, 16 tokens, k = 3, 15.5 / 16.4), while with more
 // (q, k and v of a Llama-3-8B attention block, 8 tokens: 20.9 / 20.0; two of 4096 x 4096, 12 tokens: 20.8 / 19.9) the vector unit has the branch's savings.
+// Not where most of the weights are symbols of 8 or of 4 bits, all alike, whose runs have 256 or 128 bytes, one as long as the
+// other: the lanes of a wave then read one or two LDS banks, at every symbol without the branch (16 exponents of one frequency,
+// 4096 x 4096, 1 token, 21.6 us).
 constexpr uint32_t kLinEager = 256;
+inline bool columns_in_step(const neuzip_blob *const *weights, uint32_t count)
+{
+    uint64_t all = 0, in_step = 0;
+    for (uint32_t i = 0; i < count; ++i) {
+        const neuzip_blob *w = weights[i];
+        all += w->n;
+        in_step += runs_in_step(w) || (w->total_words * 1600 >= 395 * w->n && w->total_words * 1600 <= 401 * w->n) ? w->n : 0;
+    }
+    return 2 * in_step > all;
+}
 
 template <int KB, bool NORM>
-void launch_linear(const LinearBatchArgs &batch, uint32_t cols, uint32_t wgs, hipStream_t stream)
+void launch_linear(const LinearBatchArgs &batch, uint32_t cols, uint32_t wgs, bool in_step, hipStream_t stream)
 {
     const dim3 grid(wgs), block(kLinThreads);
     const uint32_t tokens = batch.t[0].tokens;
@@ -724,7 +737,7 @@ void launch_linear(const LinearBatchArgs &batch, uint32_t cols, uint32_t wgs, hi
     do {                                                                                                           \
         if (read)                                                                                                  \
             hipLaunchKernelGGL((linear_batch_kernel<KB, COLS, MT, NORM, true, false>), grid, block, 0, stream, batch);  \
-        else if (wgs <= kLinEager)                                                                                 \
+        else if (wgs <= kLinEager && !in_step)                                                                                 \
             hipLaunchKernelGGL((linear_batch_kernel<KB, COLS, MT, NORM, false, true>), grid, block, 0, stream, batch);  \
         else                                                                                                       \
             hipLaunchKernelGGL((linear_batch_kernel<KB, COLS, MT, NORM, false, false>), grid, block, 0, stream, batch); \
@@ -1617,6 +1630,7 @@ int neuzip_linear_batch(const neuzip_blob *const *weights, const uint64_t *out_f
     // the kernel holds the partial sums of at most 64 tokens: larger batches go through in tiles of 64
     // (each tile decodes the weights again: beyond a few tiles decompressing once and a dense product win)
     const neuzip_blob *first = weights[0];
+    const bool in_step = columns_in_step(weights, count);
     for (uint32_t t0 = 0; t0 < tokens; t0 += kLinMaxTokens) {
         const uint32_t tile = tokens - t0 < kLinMaxTokens ? tokens - t0 : kLinMaxTokens;
         const LinearForm form = linear_form(tile, in_features, weights, count);
@@ -1636,16 +1650,16 @@ int neuzip_linear_batch(const neuzip_blob *const *weights, const uint64_t *out_f
         }
         if (first->block) {
             switch (first->k) {
-            case 3: launch_linear<3, true>(batch, cols, wgs, stream); break;
-            case 1: launch_linear<1, true>(batch, cols, wgs, stream); break;
-            default: launch_linear<0, true>(batch, cols, wgs, stream); break;
+            case 3: launch_linear<3, true>(batch, cols, wgs, in_step, stream); break;
+            case 1: launch_linear<1, true>(batch, cols, wgs, in_step, stream); break;
+            default: launch_linear<0, true>(batch, cols, wgs, in_step, stream); break;
             }
         } else {
             switch (first->k) {
-            case 7: launch_linear<7, false>(batch, cols, wgs, stream); break;
-            case 3: launch_linear<3, false>(batch, cols, wgs, stream); break;
-            case 1: launch_linear<1, false>(batch, cols, wgs, stream); break;
-            default: launch_linear<0, false>(batch, cols, wgs, stream); break;
+            case 7: launch_linear<7, false>(batch, cols, wgs, in_step, stream); break;
+            case 3: launch_linear<3, false>(batch, cols, wgs, in_step, stream); break;
+            case 1: launch_linear<1, false>(batch, cols, wgs, in_step, stream); break;
+            default: launch_linear<0, false>(batch, cols, wgs, in_step, stream); break;
             }
         }
         if (!hip_ok(hipGetLastError()))

@@ -382,6 +382,26 @@ void form_of_the_walk()
     expect(g_launched.find("decode_batch_kernelILi7ELb0ELi0ELi2EE") != std::string::npos, g_launched);
 }
 
+// The linear layer's walk in launches of few workgroups (its last template argument): without a branch unless the runs of most
+// weights are of 128 or 256 bytes.
+void form_of_the_linear_walk()
+{
+    for (double bits : {2.0, 3.94, 3.96, 4.0, 4.02, 7.94, 7.96, 8.0, 8.02}) {
+        const bool in_step = (bits > 3.95 && bits < 4.01) || (bits > 7.95 && bits < 8.01);
+        const uint64_t rows[2] = {1024, 300}, n = 1024 * 1024;
+        g_words = static_cast<uint64_t>(n * bits / 16);
+        neuzip_blob *weights[2] = {compressed(A, nullptr, n), nullptr};
+        float *const ys[2] = {static_cast<float *>(kSomewhere), static_cast<float *>(kSomewhere)};
+        auto last = [](bool eager) { return std::string(eager ? "ELb0ELb1EE" : "ELb0ELb0EE"); };
+        expect(neuzip_linear_batch(weights, rows, 1, 1024, kSomewhere, 1, nullptr, ys, A) == NEUZIP_OK, "linear");
+        expect(g_launched.find(last(!in_step)) != std::string::npos, std::to_string(bits) + " bits: " + g_launched);
+        g_words = 300 * 1024 / 8;
+        weights[1] = compressed(A, nullptr, 300 * 1024);   // (of fewer elements: it does not decide)
+        expect(neuzip_linear_batch(weights, rows, 2, 1024, kSomewhere, 1, nullptr, ys, A) == NEUZIP_OK, "linear_batch");
+        expect(g_launched.find(last(!in_step)) != std::string::npos, std::to_string(bits) + " bits: " + g_launched);
+    }
+}
+
 // Blobs of a batch that other streams have filled: behind the latest of them.
 void read_a_batch()
 {
@@ -420,6 +440,8 @@ int main(int argc, char **argv)
         chunks_of_a_workgroup();
     } else if (s == "form_of_the_walk") {
         form_of_the_walk();
+    } else if (s == "form_of_the_linear_walk") {
+        form_of_the_linear_walk();
     } else if (s == "old_stamp") {
         an_old_stamp();
     } else if (s == "batch") {

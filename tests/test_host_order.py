@@ -57,5 +57,6 @@ def test_a_decoders_workgroup_has_as_many_chunks_as_fit(driver):
     run(driver, "chunks_of_a_workgroup")
 
 
-def test_the_form_of_the_walk_from_the_entry_points(driver):
-    run(driver, "form_of_the_walk")
+@pytest.mark.parametrize("scenario", ["form_of_the_walk", "form_of_the_linear_walk"])
+def test_the_form_of_the_walk(driver, scenario):
+    run(driver, scenario)

@@ -8,6 +8,7 @@ import torch
 
 from oracle import oracle as O
 from paper_2410_20650_amd import inputs
+import wide_words
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -23,9 +24,7 @@ def nz():
 
 def words_of_a_workgroup(container, chunks):
     """The most bytes of words that `chunks` neighbouring chunks (from a multiple of that number on) hold."""
-    nc = int(container[36:40].view(np.uint32)[0])
-    offsets = container[64 + 512:64 + 512 + 4 * (nc + 1)].view(np.uint32).astype(np.int64)
-    return int(2 * np.diff(offsets[:nc // chunks * chunks + 1:chunks]).max())
+    return wide_words.widest(container, chunks)
 
 
 def random_tensor(kind, n):
@@ -37,30 +36,151 @@ def random_tensor(kind, n):
     return w.view(torch.float16) if kind == "f16" else w
 
 
-@pytest.mark.parametrize("n, chunks", [(LINE + 5000, 32), (2049 * 4096 + 77, 16)])   # whole states, halves
-@pytest.mark.parametrize("kind, k, block", [("bf16", 7, 0), ("bf16", 3, 0), ("bf16", 1, 0), ("bf16", 0, 0), ("bf16", 3, 64),
-                                            ("bf16", 0, 512), ("f32", 7, 0), ("f16", 7, 0)])
-def test_words_beyond_the_lds_window(nz, kind, k, block, n, chunks):
-    # 32 chunks of 8 bits per symbol are 128 KiB, 16 chunks 64 KiB
+def expected(w, k, block):
+    """(the decoded words' bits, the oracle's container)"""
+    if w.dtype == torch.float32:
+        return inputs.bits32(w), O.compress_f32(inputs.bits32(w), threads=8)
+    if w.dtype == torch.float16:
+        return inputs.bits16(w), O.compress_f16(inputs.bits16(w), threads=8)
+    words = inputs.bits(w)
+    decoded = O.lossy_blockwise(words, k, block) if block else O.truncate(words, k)
+    return decoded, O.compress(words, k, threads=8, block=block)
+
+
+def host_bits(w):
+    return {torch.float32: inputs.bits32, torch.float16: inputs.bits16, torch.bfloat16: inputs.bits}[w.dtype](w)
+
+
+KINDS = [("bf16", 7, 0), ("bf16", 3, 0), ("bf16", 1, 0), ("bf16", 0, 0), ("bf16", 3, 64), ("bf16", 0, 512), ("f32", 7, 0),
+         ("f16", 7, 0)]
+
+
+# whole states (32 chunks to a workgroup, 16 of binary16), and halves of them with 12 and 16 chunks
+@pytest.mark.parametrize("n", [LINE + 5000, 2500 * 4096 + 77, 3500 * 4096 + 777])
+@pytest.mark.parametrize("kind, k, block", KINDS)
+def test_words_beyond_the_lds_window(nz, kind, k, block, n):
+    w = wide_words.narrow_but_for(kind, n, 7120)
+    blob = nz.neuzip_compress_blockwise(w, k, block)
+    container = nz.neuzip_export(blob)
+    assert wide_words.exceeds(container, wide_words.chunks_of_a_workgroup(container, k, kind), k)
+    decoded, want = expected(w, k, block)
+    assert np.array_equal(container, want)
+    single, batch, again = (torch.zeros_like(w) for _ in range(3))
+    nz.neuzip_decompress(blob, single)
+    nz.neuzip_decompress_batch([blob], [batch])
+    nz.neuzip_check(blob)
+    read = nz.neuzip_import(container)      # (which walks to the entry points)
+    nz.neuzip_decompress(read, again)
+    nz.neuzip_check(read)
+    assert np.array_equal(host_bits(single), decoded)
+    assert torch.equal(wide_words.raw(single), wide_words.raw(batch)) and torch.equal(wide_words.raw(single), wide_words.raw(again))
+
+
+# wide throughout: workgroups that hold all of their words, in fewer chunks
+@pytest.mark.parametrize("n", [LINE + 5000, 2049 * 4096 + 77])
+@pytest.mark.parametrize("kind, k, block", KINDS)
+def test_words_that_fit_in_fewer_chunks(nz, kind, k, block, n):
     w = random_tensor(kind, n)
     blob = nz.neuzip_compress_blockwise(w, k, block)
     container = nz.neuzip_export(blob)
-    per = 16 if kind == "f16" else chunks
-    assert words_of_a_workgroup(container, per) > WINDOW
-    words, raw = {"bf16": (inputs.bits, torch.int16), "f16": (inputs.bits16, torch.int16), "f32": (inputs.bits32, torch.int32)}[kind]
-    want = {"f32": lambda: O.compress_f32(words(w), threads=8), "f16": lambda: O.compress_f16(words(w), threads=8),
-            "bf16": lambda: O.compress(words(w), k, threads=8, block=block)}[kind]()
+    chunks = wide_words.chunks_of_a_workgroup(container, k, kind)
+    assert not wide_words.exceeds(container, chunks, k)
+    assert wide_words.exceeds(container, 16 if kind == "f16" or n < LINE else 32, k)
+    decoded, want = expected(w, k, block)
     assert np.array_equal(container, want)
     single, batch = torch.zeros_like(w), torch.zeros_like(w)
     nz.neuzip_decompress(blob, single)
     nz.neuzip_decompress_batch([blob], [batch])
     nz.neuzip_check(blob)
-    assert torch.equal(single.view(raw), batch.view(raw))
+    assert torch.equal(wide_words.raw(single), wide_words.raw(batch))
+    assert np.array_equal(host_bits(single), decoded)
+
+
+# batches of tensors with entry points, of at most and of more workgroups than CUs (16 chunks to a workgroup), and of whole
+# walks, within the cache and beyond it; the first tensor's window is wide enough throughout
+@pytest.mark.parametrize("chunks", [(1500, 2500), (3500, 3500), (4500, 5000), (9000, 9000), (17000, 1300)])
+@pytest.mark.parametrize("kind, k, block", [c for c in KINDS if c[0] != "f16"])
+def test_words_beyond_the_lds_window_in_batches(nz, kind, k, block, chunks):
+    ns = [c * 4096 - 99 for c in chunks]
+    first = inputs.gaussian_f32(ns[0], 7130, device=DEV) if kind == "f32" else inputs.gaussian_bf16(ns[0], 7130, device=DEV)
+    ws = [first, wide_words.narrow_but_for(kind, ns[1], 7131)]
+    blobs = nz.neuzip_compress_batch(ws, k, block)
+    container = nz.neuzip_export(blobs[1])
+    assert wide_words.exceeds(container, 16 if max(chunks) <= 4096 else 32, k)
+    outs = [torch.zeros_like(w) for w in ws]
+    nz.neuzip_decompress_batch(blobs, outs)
+    for blob, out, w in zip(blobs, outs, ws):
+        nz.neuzip_check(blob)
+        alone = nz.neuzip_decompress(blob, torch.zeros_like(w))
+        assert torch.equal(wide_words.raw(alone), wide_words.raw(out))
+        if not block:
+            mask = -1 << (7 - k)
+            assert torch.equal(wide_words.raw(out), wide_words.raw(w) & (-1 if kind == "f32" else mask))
+    if block:       # (the part around the wide chunks against the oracle: blocks do not reach beyond it)
+        part = slice(990 * 4096, 1070 * 4096)
+        assert np.array_equal(inputs.bits(outs[1][part]), O.lossy_blockwise(inputs.bits(ws[1][part]), k, block))
+
+
+# launches whose words are copied straight into LDS (448 workgroups), and of one tensor beyond the cache
+@pytest.mark.parametrize("kind, k, block, chunks", [("bf16", 7, 0, 448 * 32), ("bf16", 3, 0, 448 * 32), ("bf16", 1, 0, 448 * 32),
+                                                    ("bf16", 0, 0, 448 * 32), ("bf16", 3, 512, 448 * 32), ("bf16", 7, 0, 17000),
+                                                    ("bf16", 0, 0, 17000), ("bf16", 1, 64, 17000), ("f32", 7, 0, 8300),
+                                                    ("f16", 7, 0, 17000)])
+def test_words_beyond_the_lds_window_of_large_tensors(nz, kind, k, block, chunks):
+    w = wide_words.narrow_but_for(kind, chunks * 4096 - 5, 7140)
+    blob = nz.neuzip_compress_blockwise(w, k, block)
+    container = nz.neuzip_export(blob)
+    per = wide_words.chunks_of_a_workgroup(container, k, kind)
+    assert per == (16 if kind == "f16" else 32) and wide_words.exceeds(container, per, k)
+    out = nz.neuzip_decompress(blob, torch.zeros_like(w))
+    nz.neuzip_check(blob)
     if block:
-        assert np.array_equal(words(single), O.lossy_blockwise(words(w), k, block))
+        part = slice(990 * 4096, 1070 * 4096)
+        assert np.array_equal(inputs.bits(out[part]), O.lossy_blockwise(inputs.bits(w[part]), k, block))
     else:
-        mask = -1 << (7 - k)
-        assert torch.equal(single.view(raw), w.view(raw) & (mask if kind == "bf16" else -1))
+        assert torch.equal(wide_words.raw(out), wide_words.raw(w) & (-1 << (7 - k) if kind == "bf16" else -1))
+
+
+# the decoder that applies the weight step: halves in few and in many workgroups, whole states
+@pytest.mark.parametrize("chunks", [(2500,), (3500, 3500), (5000,)])
+def test_words_beyond_the_lds_window_in_the_weight_step(nz, chunks):
+    ws = [wide_words.narrow_but_for("bf16", c * 4096 - 99, 7150 + i) for i, c in enumerate(chunks)]
+    for w in ws:        # finite, and far from the largest
+        w.view(torch.int16)[(w.view(torch.int16) >> 7 & 0xFF) > 200] &= 0x3FFF - 0x10000
+    grads = [inputs.gaussian_bf16(w.numel(), 7160 + i, device=DEV) for i, w in enumerate(ws)]
+    blobs = nz.neuzip_compress_guarded(ws, 7, 8)
+    for blob in blobs:
+        assert wide_words.exceeds(nz.neuzip_export(blob), 32 if max(chunks) > 4096 else 16, 7)
+    spaces = [torch.zeros_like(w) for w in ws]
+    nz.neuzip_update(blobs, grads, spaces, 0.125, weights_ready=0)
+    for blob, space, w, g in zip(blobs, spaces, ws, grads):
+        nz.neuzip_check(blob)
+        want = (w.float() - 0.125 * g.float()).to(torch.bfloat16)
+        assert torch.equal(wide_words.raw(space), wide_words.raw(want))
+        out = nz.neuzip_decompress(blob, torch.zeros_like(w))
+        assert torch.equal(wide_words.raw(out), wide_words.raw(want))
+
+
+# the walk with the branch of a single tensor from the entry points: a kept table's average of 8 bits, made of symbols of 7
+# and of 12 bits, the latter together in one chunk of five
+def test_words_beyond_the_lds_window_of_runs_near_256_bytes(nz):
+    n, wide = 4000 * 4096, 780
+    g = torch.Generator(device=DEV).manual_seed(7170)
+    e = torch.randint(60, 188, (n,), generator=g, device=DEV, dtype=torch.int32)
+    e[:128] = torch.arange(128, device=DEV, dtype=torch.int32) + 60
+    rare = e.clone()
+    e[1000:1064] = torch.arange(64, device=DEV, dtype=torch.int32) + 188
+    rare[1000 * 4096:(1000 + wide) * 4096] = torch.randint(188, 252, (wide * 4096,), generator=g, device=DEV, dtype=torch.int32)
+    w, moved = ((x << 7).to(torch.int16).view(torch.bfloat16) for x in (e, rare))
+    blob = nz.neuzip_compress(w, 7)
+    assert nz.neuzip_recompress([moved], [blob]) == [0]
+    container = nz.neuzip_export(blob)
+    per, bits = wide_words.chunks_of_a_workgroup(container, 7, "bf16"), 8 * wide_words.runs(container)[1] / n
+    assert 7.95 <= bits <= 8.01, bits
+    assert per == 12 and wide_words.exceeds(container, per, 7)
+    out = nz.neuzip_decompress(blob, torch.zeros_like(moved))
+    nz.neuzip_check(blob)
+    assert torch.equal(wide_words.raw(out), wide_words.raw(moved))
 
 
 def test_words_beyond_the_lds_window_in_a_batch_beyond_the_cache(nz):

@@ -53,8 +53,9 @@ def test_lossy_and_normalised_from_the_entry_points(nz, n, k, block):
 
 
 @pytest.mark.parametrize("kind", ["bf16", "f16", "f32"])
-def test_words_read_from_the_blob_from_the_entry_points(nz, kind):
-    # 16 chunks of 8 bits per symbol are 64 KiB of words, more than the window
+def test_wide_words_from_the_entry_points(nz, kind):
+    # 16 chunks of 8 bits per symbol are 64 KiB of words, more than the window: the workgroups have 12 (binary16, whose upper
+    # bytes hold 8 bits too, likewise), and all of their words in LDS
     n = 3500 * 4096 + 777
     if kind == "f32":
         g = torch.Generator(device=DEV).manual_seed(4300)
@@ -90,8 +91,8 @@ def test_both_sides_of_the_direct_copies(nz, n, k):
     assert torch.equal(decoded(nz, blob, w).view(torch.int16), w.view(torch.int16) & mask)
 
 
-def test_words_beyond_the_window_where_they_would_be_copied_directly(nz):
-    w = inputs.random_bits_bf16(420 * WG + 99, 4600, device=DEV)     # 128 KiB of words per workgroup
+def test_wide_words_at_the_size_of_the_direct_copies(nz):
+    w = inputs.random_bits_bf16(420 * WG + 99, 4600, device=DEV)     # 128 KiB of words per 32 chunks: 12 to a workgroup, no direct copies
     blob = nz.neuzip_compress(w, 7)
     assert torch.equal(decoded(nz, blob, w).view(torch.int16), w.view(torch.int16))
 

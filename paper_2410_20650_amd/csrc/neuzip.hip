@@ -518,12 +518,14 @@ DecodeArgs decode_args(const neuzip_blob *b, void *d_dst)
     return a;
 }
 
-// Whether the words of a launch of whole walks go straight into LDS: where nearly every CU is given two workgroups at once
-// and no more come behind them, so that nothing but their own requests keeps memory busy while the words are awaited (58.7 M
-// elements 46.2 us, through registers 47.8; 62 M 48.8 / 50.0; 55 M 46.6 / 46.6).  With fewer workgroups it gives nothing or
-// costs (45 M 42.3 / 42.4, 36 M 40.6 / 39.4), and in a launch of several rounds the burst of a workgroup's words is in the way
-// of those that walk (28672 x 8192, k = 3: 151 / 146; a Llama-3-8B layer 143.7 / 140.9).
-inline bool copies_directly(uint32_t workgroups) { return workgroups >= 416 && workgroups <= 512; }
+// Whether the words of a launch of whole walks go straight into LDS: where all its workgroups run at once, two on every CU at
+// most (the LDS holds two), so that nothing but their own requests keeps memory busy while the words are awaited.  Workgroups of
+// 32 chunks, k = 7: 129 of them 23.6 us, through registers 24.4; 229 27.4 / 28.5; 340 40.5 / 41.4; 416 45.3 / 46.6; 448 47.9 /
+// 49.9; 507 52.5 / 55.0; 448 with k = 3 43.5 / 44.8, k = 1 45.5 / 47.2, k = 0 43.1 / 44.7, k = 3 and blocks of 512 45.8 / 46.8;
+// the same tensor again and again 36.9 / 37.5 (k = 7) and no difference (lossy).  Smaller workgroups (see chunks_that_fit),
+// 24 chunks, 356: 35.9 / 37.4; 20, 427: 34.5 / 35.3; 16, 381: 33.7 / 33.5.  In a launch of several rounds the burst of a
+// workgroup's words is in the way of those that walk (28672 x 8192, k = 3: 151 / 146; a Llama-3-8B layer 143.7 / 140.9).
+inline bool copies_directly(uint32_t workgroups) { return workgroups <= 2 * 256; }
 
 template <int KB, bool NORM, int MODE = kPlain>
 int launch_decode(const neuzip_blob *b, void *d_dst, hipStream_t stream)
@@ -532,8 +534,8 @@ int launch_decode(const neuzip_blob *b, void *d_dst, hipStream_t stream)
     const uint32_t groups = (b->n_chunks + per - 1) / per;
     const dim3 grid(groups), block(per * lanes_per_chunk(b));
     const DecodeArgs args = decode_args(b, d_dst);
-    if constexpr (MODE == kPlain) {  // (binary32 and binary16 tensors of so many workgroups were not measured, or stream)
-        if (!has_entry_points(b->n_chunks) && !args.stream_out && per == kDecChunksPerWg && copies_directly(groups)) {
+    if constexpr (MODE == kPlain) {  // (bf16; the other types were not measured)
+        if (!has_entry_points(b->n_chunks) && !args.stream_out && copies_directly(groups)) {
             hipLaunchKernelGGL((decode_direct_kernel<KB, NORM>), grid, block, 0, stream, args);
             return hip_ok(hipGetLastError()) ? NEUZIP_OK : NEUZIP_EHIP;
         }

@@ -983,7 +983,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(const DecodeArgs a)
         decode_workgroup<KB, NORM, MODE, kReadTable>(a, blockIdx.x, lds.lut, lds.steps, lds.stage, lds.spread);
 }
 
-// The launch whose workgroups nearly all run at once, two on every CU (see copies_directly).
+// The launch whose workgroups all run at once, two on every CU at most (see copies_directly).
 template <int KB, bool NORM>
 __global__ __launch_bounds__(kDecThreads) void decode_direct_kernel(const DecodeArgs a)
 {

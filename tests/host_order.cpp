@@ -382,6 +382,23 @@ void form_of_the_walk()
     expect(g_launched.find("decode_batch_kernelILi7ELb0ELi0ELi2EE") != std::string::npos, g_launched);
 }
 
+// Whole walks have their words copied straight into LDS where all workgroups run at once, two on each of 256 CUs.
+void form_of_the_whole_walk()
+{
+    for (uint64_t bytes : {1400, 2500, 3800, 5000})        // of a chunk's words: 32, 24, 16 and 12 chunks to a workgroup
+        for (uint64_t chunks : {4097, 5000, 6144, 6145, 8192, 8193, 12288, 12289, 16383, 16384}) {
+            const uint64_t n = chunks * nz::kChunk;
+            g_words = chunks * bytes / 2;
+            neuzip_blob *blob = compressed(A, nullptr, n);
+            expect(neuzip_decompress(blob, kSomewhere, n, NEUZIP_BF16, A) == NEUZIP_OK, "decompress");
+            const uint64_t per = g_threads / 16, workgroups = (chunks + per - 1) / per;
+            const bool direct = workgroups <= 512 && n < (64ull << 20);
+            expect((g_launched.find("decode_direct_kernelILi7ELb0EE") != std::string::npos) == direct,
+                   std::to_string(workgroups) + " workgroups: " + g_launched);
+            neuzip_free(blob);
+        }
+}
+
 // The linear layer's walk in launches of few workgroups (its last template argument): without a branch unless the runs of most
 // weights are of 128 or 256 bytes.
 void form_of_the_linear_walk()
@@ -442,6 +459,8 @@ int main(int argc, char **argv)
         form_of_the_walk();
     } else if (s == "form_of_the_linear_walk") {
         form_of_the_linear_walk();
+    } else if (s == "form_of_the_whole_walk") {
+        form_of_the_whole_walk();
     } else if (s == "old_stamp") {
         an_old_stamp();
     } else if (s == "batch") {

@@ -121,6 +121,24 @@ def test_words_beyond_the_lds_window_in_batches(nz, kind, k, block, chunks):
         assert np.array_equal(inputs.bits(outs[1][part]), O.lossy_blockwise(inputs.bits(ws[1][part]), k, block))
 
 
+# a launch of more workgroups than run at once, whose words pass through registers: 16 chunks of 7.6 bits to a workgroup
+@pytest.mark.parametrize("k", [7, 3, 1, 0])
+def test_words_beyond_the_lds_window_of_many_small_workgroups(nz, k):
+    n = 9000 * 4096 + 5
+    g = torch.Generator(device=DEV).manual_seed(7145)
+    e = torch.randint(20, 220, (n,), generator=g, device=DEV, dtype=torch.int32)
+    wide = slice(1000 * 4096, 1064 * 4096)
+    e[wide] = torch.randint(220, 256, (64 * 4096,), generator=g, device=DEV, dtype=torch.int32)
+    w = ((e << 7) | torch.randint(0, 128, (n,), generator=g, device=DEV, dtype=torch.int32)).to(torch.int16).view(torch.bfloat16)
+    blob = nz.neuzip_compress(w, k)
+    container = nz.neuzip_export(blob)
+    per = wide_words.chunks_of_a_workgroup(container, k, "bf16")
+    assert 9000 / per > 512 and wide_words.exceeds(container, per, k)
+    out = nz.neuzip_decompress(blob, torch.zeros_like(w))
+    nz.neuzip_check(blob)
+    assert torch.equal(wide_words.raw(out), wide_words.raw(w) & (-1 << (7 - k)))
+
+
 # launches whose words are copied straight into LDS (448 workgroups), and of one tensor beyond the cache
 @pytest.mark.parametrize("kind, k, block, chunks", [("bf16", 7, 0, 448 * 32), ("bf16", 3, 0, 448 * 32), ("bf16", 1, 0, 448 * 32),
                                                     ("bf16", 0, 0, 448 * 32), ("bf16", 3, 512, 448 * 32), ("bf16", 7, 0, 17000),

@@ -81,8 +81,8 @@ def test_tables_with_steps_inside_pieces_and_on_their_edges(nz):
         assert np.array_equal(inputs.bits(decoded(nz, blob, w)), words)
 
 
-# workgroups on both sides of the line from which on the words are copied straight into LDS, up to the streaming sizes
-@pytest.mark.parametrize("n", [415 * WG + 4096, 416 * WG, 416 * WG - 4095, 448 * WG + 4097, 512 * WG - 8, 512 * WG])
+# launches whose words are copied straight into LDS, from the largest tensor with entry points up to the streaming sizes
+@pytest.mark.parametrize("n", [128 * WG, 128 * WG + 1, 200 * WG + 77, 256 * WG, 257 * WG - 4000, 415 * WG + 4096, 416 * WG, 416 * WG - 4095, 448 * WG + 4097, 512 * WG - 8, 512 * WG])
 @pytest.mark.parametrize("k", [7, 1])
 def test_both_sides_of_the_direct_copies(nz, n, k):
     w = inputs.gaussian_bf16(n, 4500 + n % 97, device=DEV)

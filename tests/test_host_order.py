@@ -57,6 +57,6 @@ def test_a_decoders_workgroup_has_as_many_chunks_as_fit(driver):
     run(driver, "chunks_of_a_workgroup")
 
 
-@pytest.mark.parametrize("scenario", ["form_of_the_walk", "form_of_the_linear_walk"])
+@pytest.mark.parametrize("scenario", ["form_of_the_walk", "form_of_the_whole_walk", "form_of_the_linear_walk"])
 def test_the_form_of_the_walk(driver, scenario):
     run(driver, scenario)

@@ -65,7 +65,7 @@ def test_no_kernel_spills(kernels):
         assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, name
 
 
-@pytest.mark.parametrize("prefix", ["decode_kernel<", "decode_batch_kernel<", "linear_batch_kernel<"])
+@pytest.mark.parametrize("prefix", ["decode_kernel<", "decode_direct_kernel<", "decode_batch_kernel<", "linear_batch_kernel<"])
 def test_two_workgroups_of_eight_waves_share_a_cu(kernels, prefix):
     for name, k in named(kernels, prefix).items():
         assert k[".max_flat_workgroup_size"] == 512, name

@@ -692,7 +692,7 @@ enum DecodeForm {
     kMakeTable,  // one lane per state; the blob is too small to hold the table (its entry points are not used)
     kEntries,    // two lanes per state, from the entry points; the slot table is made
     kReadDirect, // like kReadTable, cached; the words are copied straight into LDS
-    kEntriesAlone, // like kEntries, at most one workgroup per CU
+    kEntriesAlone, // like kEntries, where a SIMD has two waves or so: no branch in the step
 };
 
 template <int KB, bool NORM, int MODE, int FORM>
@@ -859,7 +859,10 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, uint32_t w
 // without a branch (see rans_get) and the table made by make_table: 4 M elements 13.5 -> 10.7 us, of which the beginning
 // 3.9 -> 2.7 and the walk 9.5 -> 7.7, 0.05 M 11.8 -> 9.5, 16.8 M 15.8 -> 14.0, 10 M binary32 elements 20.3 -> 16.4; words
 // through registers 11.8 (4 M), 15.5 (16.8 M).
-// ALONE: the launch has at most one workgroup per CU, and the step no branch (see launch_batch_kernel).
+// ALONE: the step without a branch.  A single tensor's launch has two waves per SIMD on average whatever its workgroups' size
+// (4096 chunks are 2048 waves), also where they are more than the CUs: weights that have left their kept table, 8 chunks of
+// 12-bit symbols to a workgroup, 263 workgroups 14.1 us, with the branch 15.1, 512 16.8 / 17.2; for batches see
+// launch_batch_kernel, for tensors that keep the branch all the same runs_in_step.
 template <int KB, bool NORM, int MODE, bool ALONE>
 __device__ __forceinline__ void decode_from_entries(const DecodeArgs &a, uint32_t wg, uint32_t *__restrict__ lut,
                                                     uint32_t *__restrict__ steps, uint8_t *__restrict__ stage,

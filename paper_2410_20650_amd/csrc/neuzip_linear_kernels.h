@@ -177,11 +177,13 @@ __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, co
         xrow[mt] = a.x + static_cast<uint64_t>(t) * in + ksq + kq;
     }
     uint32_t next = LONE ? 0u : src.peek(wp);
-    // The inputs of DEPTH turns are held in buffers used in rotation, each requested again once its turn is done, so that with
-    // one they travel while the next turn's eight symbols are decoded.  (Requested a whole turn earlier, or more, they only take
-    // registers and places in the queue: 4096 x 14336, 32 tokens, 43.2 us, with two buffers 48.8; 4096 x 4096, 64 tokens,
-    // 25.8 / 26.9; 9000 x 5120, 64 tokens, 86.7 / 89.3.)  A lane without turns of its own reads those of the tensor's first
-    // chunk; a turn behind the last reads the last again.
+    // A turn's inputs are requested once the turn before is done and travel while its own eight symbols are decoded.  (Requested a
+    // whole turn earlier, or more, they only take registers and places in the queue: 4096 x 14336, 32 tokens, 43.2 us, with two
+    // buffers 48.8; 4096 x 4096, 64 tokens, 25.8 / 26.9; 9000 x 5120, 64 tokens, 86.7 / 89.3.)  A lane without turns of its own
+    // reads those of the tensor's first chunk; a turn behind the last reads the last again.  The buffers are written as a
+    // rotation of DEPTH of them because of what the compiler makes of it, which is to move the request of the fields alone to
+    // the turn's beginning: with one plain buffer it does not (4096 x 4096, 1 token, 16.7 us -> 17.8), and moved there by hand
+    // normalised weights lose in the walk of 32 columns (4096 x 14336, k = 0, blocks of 64, 32 tokens, 56.1 -> 58.7).
     constexpr uint32_t DEPTH = 1;
     const uint64_t first = (turns > 0 ? base : 0u) + j * kRun;
     const uint32_t last = turns > 0 ? turns - 1 : 0u;

@@ -398,7 +398,7 @@ __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, con
 // The same walk for a binary32 tensor (lossless only): the decoded bf16 word is the upper half
 // of the element and the lower half comes from the raw plane, so a turn reads 16 B of lower
 // halves next to its 8 B of fields and writes two 128-bit pieces.
-template <bool LONE, bool STREAM, bool SPLIT, bool EAGER, class WordSrc>
+template <bool LONE, bool STREAM, bool SPLIT, bool ALONE, bool EAGER, class WordSrc>
 __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut, const WordSrc &src, uint32_t lone,
                                                 uint32_t &x, uint32_t &wp, const uint8_t *__restrict__ sm,
                                                 const uint16_t *__restrict__ low, uint32_t *__restrict__ out,
@@ -409,8 +409,9 @@ __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut
     constexpr uint32_t turns = SPLIT ? kMidTurn : kTurns;
     // Groups of turns whose inputs are held: one, and the next is requested before it is decoded and moves up behind it; or
     // two that are used in rotation, each requested again once it is merged (from the entry points, with a wave or two per
-    // SIMD to wait for memory with: 10 M elements 18.5 us with one, 17.6 with two).
-    constexpr uint32_t kDepth = SPLIT ? 2 : 1;
+    // SIMD to wait for memory with: 10 M elements 18.5 us with one, 17.6 with two).  In batches of more workgroups than CUs
+    // memory has enough to do with one (25 M elements in three tensors 50.7 us, with two 53.8; 28 M in two 51.0 / 54.6).
+    constexpr uint32_t kDepth = SPLIT && ALONE ? 2 : 1;
     static_assert(turns % (kGroup * kDepth) == 0, "whole rotations");
     uint32_t next = LONE ? 0u : src.peek(wp);
     if (__all(m == kChunk)) {
@@ -621,7 +622,7 @@ __device__ __forceinline__ void walk_mode(const uint32_t *__restrict__ lut, cons
     // (a word read from memory is fetched only when it is needed)
     constexpr bool EAGER = ALONE && !std::is_same<WordSrc, GlobalWords>::value;
     if constexpr (MODE == kWide)
-        walk_state_wide<LONE, STREAM, SPLIT, EAGER>(lut, src, lone, x, wp, a.sm, a.low, static_cast<uint32_t *>(a.out), base, m, j,
+        walk_state_wide<LONE, STREAM, SPLIT, ALONE, EAGER>(lut, src, lone, x, wp, a.sm, a.low, static_cast<uint32_t *>(a.out), base, m, j,
                                              turn0, ahead);
     else
         walk_state<KB, LONE, NORM, STREAM, MODE == kUpdate, MODE == kHalf, SPLIT, EAGER>(
@@ -950,7 +951,7 @@ __device__ __forceinline__ void decode_from_entries(const DecodeArgs &a, uint32_
     __syncthreads();
     if (!live)
         return;
-    if constexpr (MODE == kWide)  // (four times the bytes, which in front of the words are in their way: 10 M elements 18.7 / 18.1 us)
+    if constexpr (MODE == kWide && ALONE)  // (four times the bytes, which in front of the words are in their way: 10 M elements 18.7 / 18.1 us)
         request_ahead();
     uint32_t wp = 0, wp_begin = 0;
     if (lone < 256) {

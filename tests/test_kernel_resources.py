@@ -74,6 +74,12 @@ def test_two_workgroups_of_eight_waves_share_a_cu(kernels, prefix):
         assert k[".vgpr_count"] <= REGISTERS_OF_A_SIMD_LANE // 4, name
 
 
+def test_binary32_batches_of_many_workgroups_hold_one_group_of_turns(kernels):
+    # (form 4, few workgroups, holds two groups: 8 fields and 16 lower halves more; form 0 walks whole states with one)
+    of = {form: kernels[f"decode_batch_kernel<7, false, 1, {form}>"][".vgpr_count"] for form in (0, 2, 4)}
+    assert of[2] <= of[0] + 8 and of[4] >= of[2] + 16, of
+
+
 def test_decoders_that_read_the_slot_table_carry_nothing_of_making_it(kernels):
     # last template argument: entry points or not (single tensors), the form of the walk (batches)
     table_and_words, steps = 16 * 1024 + 62 * 1024, 264 * 4

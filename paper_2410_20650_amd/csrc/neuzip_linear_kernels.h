@@ -182,24 +182,36 @@ __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, co
     // buffers 48.8; 4096 x 4096, 64 tokens, 25.8 / 26.9; 9000 x 5120, 64 tokens, 86.7 / 89.3.)  A lane without turns of its own
     // reads those of the tensor's first chunk; a turn behind the last reads the last again.  The buffers are written as a
     // rotation of DEPTH of them because of what the compiler makes of it, which is to move the request of the fields alone to
-    // the turn's beginning: with one plain buffer it does not (4096 x 4096, 1 token, 16.7 us -> 17.8), and moved there by hand
-    // normalised weights lose in the walk of 32 columns (4096 x 14336, k = 0, blocks of 64, 32 tokens, 56.1 -> 58.7).
+    // the turn's beginning: with one plain buffer it does not (4096 x 4096, 1 token, 16.7 us -> 17.8).  The fields of normalised
+    // weights are one value with the coefficient and stay where they are: in the walk of 16 columns they are requested ahead by
+    // hand, apart from the coefficient (4096 x 14336, k = 3, blocks of 128, 1 token, 47.8 us -> 43.4, 10937 x 3584, 64 tokens,
+    // 134.1 -> 129.8; but not with two tiles of tokens, 32 tokens 79.4 -> 83.7, nor in the walk of 32 columns, 4096 x 14336,
+    // k = 0, blocks of 64, 32 tokens, 56.1 -> 58.7).
     constexpr uint32_t DEPTH = 1;
+    constexpr bool APART = NORM && COLS == 16 && MT != 2;
     const uint64_t first = (turns > 0 ? base : 0u) + j * kRun;
     const uint32_t last = turns > 0 ? turns - 1 : 0u;
     uint64_t fields[DEPTH];
+    uint32_t coef[DEPTH];
     uint4 xa[DEPTH][MT];
     uint32_t ahead = kk;  // the input-feature offset of the turn requested next
     auto request = [&](uint32_t d, uint32_t q) {
-        fields[d] = load_turn<KB, NORM>(sm, a.coef, a.block_shift, first + min(q, last) * kTurn);
+        const uint64_t at = first + min(q, last) * kTurn;
+        if constexpr (APART)
+            coef[d] = a.coef[at >> a.block_shift];
+        else
+            fields[d] = load_turn<KB, NORM>(sm, a.coef, a.block_shift, at);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
             xa[d][mt] = *reinterpret_cast<const uint4 *>(xrow[mt] + ahead);
         ahead = ahead + kTurn == in ? 0u : ahead + kTurn;
     };
 #pragma unroll
-    for (uint32_t d = 0; d < DEPTH; ++d)
+    for (uint32_t d = 0; d < DEPTH; ++d) {
+        if constexpr (APART)
+            fields[d] = load_fields<KB>(sm, first + min(d, last) * kTurn);
         request(d, d);
+    }
 
     // the trip count is the same for every lane of the wave (the matrix instruction needs them
     // all); a lane whose chunk is shorter or absent supplies zeros
@@ -210,6 +222,9 @@ __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, co
             const uint32_t q = q0 + d;
             const bool mine = q < turns;
             const uint32_t kk_next = kk + kTurn == in ? 0u : kk + kTurn;
+            uint64_t fields_next = 0;
+            if constexpr (APART)
+                fields_next = load_fields<KB>(sm, first + min(q + DEPTH, last) * kTurn);
 
             union {
                 uint32_t u[4];
@@ -226,7 +241,7 @@ __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, co
                 b.u[2] = merge_pair<KB>(fields[d], 2, e[4], e[5]);
                 b.u[3] = merge_pair<KB>(fields[d], 3, e[6], e[7]);
                 if constexpr (NORM) {
-                    const float c = coefficient(static_cast<uint32_t>(fields[d] >> 32) & 0x7Fu);
+                    const float c = coefficient((APART ? coef[d] : static_cast<uint32_t>(fields[d] >> 32)) & 0x7Fu);
 #pragma unroll
                     for (int p = 0; p < 4; ++p)
                         b.u[p] = denormalise_pair(b.u[p], c);
@@ -265,6 +280,8 @@ __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, co
                 ++row;
             }
             kk = kk_next;
+            if constexpr (APART)
+                fields[d] = fields_next;
         }
     }
 }

@@ -1174,8 +1174,8 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
             // what the host does next (return to its caller, launch that call's successor) takes place beside the
             // compaction and not behind it.  The record is host memory the host polls; length, flag and stamp are one
             // store past the caches, so nothing is waited for here.  (Told by the compaction, 4 tensors of an attention
-            // block with the weight step: 109.1 us per call, 99.9 now; told with a stamp of its own, behind the
-            // acknowledgements of the rest, the kernel was 2 us longer.)
+            // block with the weight step: 109.1 us per call, 99.9 now, the same four each time, or 114.5 and 105 with three
+            // sets in turn; told with a stamp of its own, behind the acknowledgements of the rest, the kernel was 2 us longer.)
             const unsigned long long own_words = (so_far & (kOneDone - 1)) + total;
             const uint32_t stale = SPLIT >= 0 ? atomicOr(&state->stale[slot_id.item], 0u) : 0u;
             __hip_atomic_store(&record->item[slot_id.item].told, told_of(own_words, stale, b.seq), __ATOMIC_RELAXED,

@@ -98,15 +98,17 @@ def test_words_that_fit_in_fewer_chunks(nz, kind, k, block, n):
 
 # batches of tensors with entry points, of at most and of more workgroups than CUs (16 chunks to a workgroup), and of whole
 # walks, within the cache and beyond it; the first tensor's window is wide enough throughout
-@pytest.mark.parametrize("chunks", [(1500, 2500), (3500, 3500), (4500, 5000), (9000, 9000), (17000, 1300)])
-@pytest.mark.parametrize("kind, k, block", [c for c in KINDS if c[0] != "f16"])
+# (binary16 batches of halves have 8 chunks to a workgroup, whose words fit whatever they are)
+@pytest.mark.parametrize("kind, k, block, chunks", [
+    (*kind, chunks) for kind in KINDS for chunks in [(1500, 2500), (3500, 3500), (4500, 5000), (9000, 9000), (17000, 1300)]
+    if kind[0] != "f16" or max(chunks) > 4096])
 def test_words_beyond_the_lds_window_in_batches(nz, kind, k, block, chunks):
     ns = [c * 4096 - 99 for c in chunks]
-    first = inputs.gaussian_f32(ns[0], 7130, device=DEV) if kind == "f32" else inputs.gaussian_bf16(ns[0], 7130, device=DEV)
+    first = {"f32": inputs.gaussian_f32, "f16": inputs.gaussian_f16, "bf16": inputs.gaussian_bf16}[kind](ns[0], 7130, device=DEV)
     ws = [first, wide_words.narrow_but_for(kind, ns[1], 7131)]
     blobs = nz.neuzip_compress_batch(ws, k, block)
     container = nz.neuzip_export(blobs[1])
-    assert wide_words.exceeds(container, 16 if max(chunks) <= 4096 else 32, k)
+    assert wide_words.exceeds(container, 16 if kind == "f16" or max(chunks) <= 4096 else 32, k)
     outs = [torch.zeros_like(w) for w in ws]
     nz.neuzip_decompress_batch(blobs, outs)
     for blob, out, w in zip(blobs, outs, ws):
@@ -115,7 +117,7 @@ def test_words_beyond_the_lds_window_in_batches(nz, kind, k, block, chunks):
         assert torch.equal(wide_words.raw(alone), wide_words.raw(out))
         if not block:
             mask = -1 << (7 - k)
-            assert torch.equal(wide_words.raw(out), wide_words.raw(w) & (-1 if kind == "f32" else mask))
+            assert torch.equal(wide_words.raw(out), wide_words.raw(w) & (mask if kind == "bf16" else -1))
     if block:       # (the part around the wide chunks against the oracle: blocks do not reach beyond it)
         part = slice(990 * 4096, 1070 * 4096)
         assert np.array_equal(inputs.bits(outs[1][part]), O.lossy_blockwise(inputs.bits(ws[1][part]), k, block))

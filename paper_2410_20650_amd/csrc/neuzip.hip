@@ -269,8 +269,7 @@ void expect_record(uint32_t seq, uint32_t items)
 }
 
 // Waits until the record of call `seq` is complete.  The stamps come from the encode kernel's last workgroups, before
-// the compaction behind it (or from that one's first, see CompressBatch::tell_late), and well before a blocking stream
-// synchronise would wake up; after a bounded spin the stream is synchronised anyway, which also surfaces errors.
+// the compaction behind it and well before a blocking stream synchronise would wake up; after a bounded spin the stream is synchronised anyway, which also surfaces errors.
 bool wait_for_record(uint32_t seq, uint32_t items, hipStream_t stream)
 {
     auto complete = [&]() {
@@ -870,7 +869,7 @@ bool launch_compaction(const Workspace &ws, const CompressBatch &batch, uint32_t
                        CallState *state, CallState *state_next, uint32_t *super_next, hipStream_t stream)
 {
     hipLaunchKernelGGL(compact_kernel, dim3(workgroups), dim3(kCompactThreads), 0, stream, batch, ws.slots, ws.chunk_words,
-                       ws.group_words, super_words, state, ws.counts, state_next, super_next, ws.super_cap, ws.pinned);
+                       ws.group_words, super_words, state, ws.counts, state_next, super_next, ws.super_cap);
     return hip_ok(hipGetLastError());
 }
 
@@ -934,7 +933,6 @@ int compress_tiled(neuzip_blob *b, const void *d_src, const void *d_grad, int k,
     batch.count = 1;
     batch.lr = lr;
     batch.keep_new = keep_new ? 1u : 0u;
-    batch.tell_late = d_grad && keep_new ? 1u : 0u;
     CompressItem &it = batch.it[0];
     it.tb = table_of(b);
     it.table_n = b->n;
@@ -1232,7 +1230,6 @@ int compress_some(const void *const *d_srcs, const uint64_t *n_elems, uint32_t c
         batch.seq = ++ws.seq;
         batch.lr = lr;
         batch.keep_new = keep_new ? 1u : 0u;
-        batch.tell_late = d_grads && keep_new ? 1u : 0u;
         touched = true;
         // the call state and the sums per 64 groups exist twice; calls alternate between the copies
         const uint32_t copy = batch.seq & 1u;

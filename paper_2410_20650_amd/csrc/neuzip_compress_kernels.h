@@ -211,6 +211,19 @@ __device__ __forceinline__ void store_to_host(uint4 *at, const uint4 &v)
     asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(at), "v"(d) : "memory");
 }
 
+// The same for device memory that others may read while the kernel runs: 16 bytes per lane at `at` bytes behind `from` (the same
+// for the wave, 32 KB of it in reach).  A store that the compiler knows, so that its waits for loads count it; whole lines leave
+// the wave, and 58.7 M weights take what they take through the caches (109.4 / 109.8 us per call; with the host told behind
+// the kernel instead, 4 M weights 41.7 us, 38.7 now).
+constexpr uint32_t kReach = 32768;
+__device__ __forceinline__ void store_through(const uint8_t *from, uint32_t at, const uint4 &v)
+{
+    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+    const u32x4_t d = {v.x, v.y, v.z, v.w};
+    const __amdgpu_buffer_rsrc_t there = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(from), 0, kReach, 0x00027000);
+    __builtin_amdgcn_raw_buffer_store_b128(d, there, static_cast<int>(at), 0, 1 | 16);  // sc0 sc1
+}
+
 // ------------------------------------------------------------------------------------------
 // Counts -> frequencies that sum to 4096, cumulative table: by ONE wave, lane l owning symbols
 // 4l .. 4l + 3, with lane shuffles only (no barrier), so that every encoder workgroup can derive
@@ -952,6 +965,13 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
     uint32_t least_mul = 1u;  // 0 once a symbol without room in the table has been met
     uint8_t *__restrict__ sm = it.sm;
 
+    // where the wave's chunks begin in the source, and this state in them (for the weights that are written back)
+    const uint32_t wave_chunk = slot_id.wg * kChunksPerGroup +
+                                static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6))) * (64 / kStates);
+    static_assert(64 / kStates * kChunk * 2 <= kReach, "a wave's chunks");
+    const uint8_t *wave_src = static_cast<const uint8_t *>(src) + static_cast<uint64_t>(wave_chunk) * (kChunk * 2);
+    const uint32_t wave_at = (c - wave_chunk) * (kChunk * 2) + j * (kRun * 2);
+
     const bool whole_wave = __all(m == kChunk || m == 0);
     if (whole_wave && m == kChunk) {
         // the words of turn q from its buffer, with what goes out along with them
@@ -964,9 +984,10 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
                 w[2] = update_pair(w[2], grads[r].z, lr);
                 w[3] = update_pair(w[3], grads[r].w, lr);
                 // if the caller wants it, the new weight replaces the old one in its buffer (same lane,
-                // same place)
+                // same place), past the caches: the call returns while this kernel may still run, and says
+                // that the weights are there
                 if (b.keep_new)
-                    reinterpret_cast<uint4 *>(const_cast<void *>(src))[vec] = make_uint4(w[0], w[1], w[2], w[3]);
+                    store_through(wave_src, wave_at + static_cast<uint32_t>(q) * (kTurn * 2), make_uint4(w[0], w[1], w[2], w[3]));
             }
             if constexpr (SPLIT >= 0) {
                 store_fields<KB>(sm, vec, fields_of<KB, HALF>(w));
@@ -1127,6 +1148,12 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
             d0 = d1;
             g0 = g1;
         }
+        // the weights written back leave the caches for memory (a fence for one workgroup per tensor, where the kernel's end
+        // would do the same; past the caches turn by turn, each request waits for the stores of the turn above: + 5 us)
+        if constexpr (UPD) {
+            if (b.keep_new)
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+        }
     }
     if constexpr (SPLIT >= 0) {
         if (least_mul == 0u) {
@@ -1159,6 +1186,10 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
     }
     if (SPLIT < 0 && slot_id.wg == 0 && threadIdx.x < 64)
         wait_for_memory_acks();  // the statistics, before this workgroup counts as done
+    if constexpr (UPD) {
+        if (b.keep_new)
+            wait_for_memory_acks();  // the weights written back, likewise
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
         // words of this workgroup: for the compaction's offsets (by group, and added up per 64 groups
@@ -1169,7 +1200,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
         group_words_all[group] = total;
         atomicAdd(&super_words_all[it.super_base + slot_id.wg / kSuperGroups], total);
         const unsigned long long so_far = atomicAdd(&state->total[slot_id.item], kOneDone | total);
-        if (so_far / kOneDone + 1 == slot_id.wgs && !(UPD && b.tell_late)) {
+        if (so_far / kOneDone + 1 == slot_id.wgs) {
             // The tensor's last workgroup tells the host the stream's length, while the compaction is still to come:
             // what the host does next (return to its caller, launch that call's successor) takes place beside the
             // compaction and not behind it.  The record is host memory the host polls; length, flag and stamp are one
@@ -1209,8 +1240,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const Compress
                                                                  const CallState *__restrict__ state,
                                                                  uint32_t *__restrict__ counts_ws,
                                                                  CallState *__restrict__ state_next,
-                                                                 uint32_t *__restrict__ super_next, uint32_t super_cap,
-                                                                 HostRecord *__restrict__ record)
+                                                                 uint32_t *__restrict__ super_next, uint32_t super_cap)
 {
     const ItemSlot slot_id = item_of_workgroup<&CompressItem::compact_end>(b);
     const CompressItem &it = b.it[slot_id.item];
@@ -1234,10 +1264,6 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const Compress
                 it.offsets[n_chunks] = static_cast<uint32_t>(all_words);
                 it.offsets[n_chunks + 1] = 0;
             }
-            if (b.tell_late)
-                __hip_atomic_store(&record->item[slot_id.item].told,
-                                   told_of(state->total[slot_id.item] & (kOneDone - 1), was_stale, b.seq), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }
     // (the same decision in all workgroups of the tensor)

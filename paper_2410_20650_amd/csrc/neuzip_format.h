@@ -154,8 +154,6 @@ struct CompressBatch {
     uint32_t keep_new;  // fused weight step: write the new weight back over the source
     uint32_t tidy;      // compaction launch: also close the offsets and tidy the workspace
     uint32_t keep_counts;  // ... but leave the histogram bins: further tiles of the tensor need them
-    uint32_t tell_late;    // the compaction tells the host, not the encoder: the new weights that the encoder writes back
-                           // are complete when the call returns, which they are behind the kernel and not in it
 };
 
 // What the encoder workgroups of a call add up for the compaction and for the host, in the workspace.  (A tensor's words

@@ -32,7 +32,6 @@ uint32_t g_threads = 0;                         // of a workgroup of the last la
 std::string g_launched;                         // the last kernel
 bool g_slow_kernels = false;                    // the host has to wait for the stream before it is told anything
 std::vector<std::pair<uint32_t, unsigned long long>> g_to_tell;
-std::string g_told_by;                          // the kernel that told the host last
 struct { dim3 grid, block; size_t shared; hipStream_t stream; } g_call;
 
 void join(Clock &into, const Clock &from)
@@ -89,13 +88,9 @@ hipError_t hipLaunchKernel(const void *fn, dim3, dim3 block, void **args, size_t
     g_threads = block.x;
     g_launched = name;
     work(stream);
-    const bool encoder = name.find("encode_kernel") != std::string::npos;
-    if (encoder || name.find("compact_kernel") != std::string::npos) {
+    if (name.find("encode_kernel") != std::string::npos) {
         const nz::CompressBatch &b = *static_cast<const nz::CompressBatch *>(args[0]);
-        const bool tells = encoder ? !b.tell_late : b.tell_late && b.tidy;
-        if (tells)
-            g_told_by = name;
-        for (uint32_t i = 0; i < b.count && g_record && tells; ++i) {
+        for (uint32_t i = 0; i < b.count && g_record; ++i) {
             const unsigned long long told = nz::told_of(g_words, 0, b.seq);
             if (g_slow_kernels)
                 g_to_tell.push_back({i, told});
@@ -299,22 +294,6 @@ void read_under_capture()
     expect_no_wait("linear", [&] { return readers()[3].call(blob, B); });
 }
 
-// A weight step that writes the new weights back returns when the kernel that writes them has ended.
-void written_weights_are_complete()
-{
-    for (int ready : {NEUZIP_UPDATE_FROM_BLOB, NEUZIP_UPDATE_WEIGHTS_READY, NEUZIP_UPDATE_WEIGHTS_READY_DISCARD,
-                      NEUZIP_UPDATE_FROM_BLOB_DISCARD}) {
-        neuzip_blob *blob = compressed(A);
-        const void *grad = static_cast<uint8_t *>(kSomewhere) + 256;
-        void *weight = kSomewhere;
-        g_told_by.clear();
-        expect(neuzip_update(&blob, &grad, &weight, 1, 1.0f, ready, A, nullptr) == NEUZIP_OK, "update");
-        const char *from = ready == NEUZIP_UPDATE_WEIGHTS_READY ? "compact_kernel" : "encode_kernel";
-        expect(g_told_by.find(from) != std::string::npos, "told by " + g_told_by + ", not by " + from);
-        neuzip_free(blob);
-    }
-}
-
 // Stamps come around again: what a call long ago has left in the record is not taken for this call's.
 void an_old_stamp()
 {
@@ -448,11 +427,6 @@ int main(int argc, char **argv)
         read_without_waiting();
     } else if (s == "capture") {
         read_under_capture();
-    } else if (s == "written_weights") {
-        written_weights_are_complete();
-    } else if (s == "written_weights_in_tiles") {
-        expect(neuzip_set_workspace_limit(102400) == NEUZIP_OK, "limit");
-        written_weights_are_complete();
     } else if (s == "chunks_of_a_workgroup") {
         chunks_of_a_workgroup();
     } else if (s == "form_of_the_walk") {

@@ -44,11 +44,6 @@ def test_no_event_where_there_is_nothing_to_wait_for(driver, scenario):
     run(driver, scenario)
 
 
-@pytest.mark.parametrize("scenario", ["written_weights", "written_weights_in_tiles"])
-def test_weights_written_back_are_complete_when_the_call_returns(driver, scenario):
-    run(driver, scenario)
-
-
 def test_an_old_stamp_is_not_taken_for_this_calls(driver):
     run(driver, "old_stamp")
 

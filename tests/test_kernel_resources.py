@@ -80,6 +80,22 @@ def test_binary32_batches_of_many_workgroups_hold_one_group_of_turns(kernels):
     assert of[2] <= of[0] + 8 and of[4] >= of[2] + 16, of
 
 
+def test_weights_that_the_encoder_writes_back_leave_the_caches(kernels, tmp_path):
+    # the call returns when the encoder has spoken, and says that the weights are there: stores at system scope in the walk of
+    # whole chunks, a release at system scope behind that of the ragged one; no other encoder has either
+    path = tmp_path / "code_object"
+    path.write_bytes(code_object())
+    of = {}
+    for updates, kernel in enumerate(("encode_kernel<false, 7, false, false, false>", "encode_kernel<false, 7, false, false, true>")):
+        name = kernels[kernel][".name"]
+        of[updates] = subprocess.run(["/opt/rocm/llvm/bin/llvm-objdump", "-d", f"--disassemble-symbols={name}", str(path)],
+                                     capture_output=True, text=True, check=True).stdout
+        assert len(of[updates].split("\n")) > 1000, name
+    through, release = r"buffer_store_dwordx4 .* sc0 sc1", r"buffer_wbl2 sc0 sc1"
+    assert re.search(through, of[1]) and re.search(release, of[1])
+    assert not re.search(through, of[0]) and not re.search(release, of[0])
+
+
 def test_decoders_that_read_the_slot_table_carry_nothing_of_making_it(kernels):
     # last template argument: entry points or not (single tensors), the form of the walk (batches)
     table_and_words, steps = 16 * 1024 + 62 * 1024, 264 * 4

@@ -319,6 +319,23 @@ int neuzip_linear_batch(const neuzip_blob *const *weights, const uint64_t *out_f
                         uint64_t in_features, const void *d_x, uint32_t tokens, const float *const *d_bias,
                         float *const *d_y, void *hip_stream);
 
+/*
+ * neuzip_linear_batch_scratch -- the same with scratch memory of the caller's, for more than 16 tokens: the
+ * activations are first laid out there in the order in which the kernel reads them, which makes a call on 64
+ * tokens a third faster.
+ *
+ *   d_scratch      device buffer of scratch_bytes bytes, 16-byte aligned (else EINVAL), in use until the call's
+ *                  work has run; or NULL.  With less than neuzip_linear_scratch_bytes() bytes the call is
+ *                  neuzip_linear_batch.
+ */
+int neuzip_linear_batch_scratch(const neuzip_blob *const *weights, const uint64_t *out_features, uint32_t count,
+                                uint64_t in_features, const void *d_x, uint32_t tokens, const float *const *d_bias,
+                                float *const *d_y, void *d_scratch, uint64_t scratch_bytes, void *hip_stream);
+
+/* The scratch memory that the call above makes use of, in bytes: about that of the activations and of one or two results, a
+ * result being at most 64 tokens of it; 0 where it needs none. */
+uint64_t neuzip_linear_scratch_bytes(const uint64_t *out_features, uint32_t count, uint64_t in_features, uint32_t tokens);
+
 /* Releases the blob and its device memory.  NULL is a no-op. */
 void neuzip_free(neuzip_blob *blob);
 

@@ -48,6 +48,9 @@ def _load():
     lib.neuzip_linear.argtypes = [vp, u64, u64, vp, u32, vp, vp, vp]
     lib.neuzip_linear.restype = i32
     lib.neuzip_linear_batch.argtypes = [vp, vp, u32, u64, vp, u32, vp, vp, vp]
+    lib.neuzip_linear_batch_scratch.argtypes = [vp, vp, u32, u64, vp, u32, vp, vp, vp, u64, vp]
+    lib.neuzip_linear_scratch_bytes.argtypes = [vp, u32, u64, u32]
+    lib.neuzip_linear_scratch_bytes.restype = u64
     lib.neuzip_linear_batch.restype = i32
     lib.neuzip_block_size.argtypes = [vp]
     lib.neuzip_block_size.restype = u32
@@ -100,8 +103,9 @@ _lib = None
 _lib = _load()
 
 EXPORTED = ["neuzip_compress", "neuzip_compress_noalloc", "neuzip_compress_blockwise", "neuzip_compress_batch", "neuzip_compress_guarded",
-            "neuzip_recompress", "neuzip_update", "neuzip_guard", "neuzip_linear", "neuzip_linear_batch", "neuzip_block_size", "neuzip_decompress", "neuzip_decompress_sequence", "neuzip_decompress_batch",
-            "neuzip_free",
+            "neuzip_recompress", "neuzip_update", "neuzip_guard", "neuzip_linear", "neuzip_linear_batch",
+            "neuzip_linear_batch_scratch", "neuzip_linear_scratch_bytes",
+            "neuzip_block_size", "neuzip_decompress", "neuzip_decompress_sequence", "neuzip_decompress_batch", "neuzip_free",
             "neuzip_compressed_bytes", "neuzip_device_bytes", "neuzip_elems", "neuzip_mantissa_bits", "neuzip_dtype",
             "neuzip_export", "neuzip_import", "neuzip_histogram", "neuzip_frequencies", "neuzip_check", "neuzip_stream_probe",
             "neuzip_workspace_bytes", "neuzip_release_workspace", "neuzip_set_workspace_limit", "neuzip_strerror", "neuzip_last_hip_error"]
@@ -313,6 +317,55 @@ def neuzip_decompress_batch(blobs, dsts, stream=None) -> None:
         raise NeuzipError(rc, "neuzip_decompress_batch")
 
 
+LINEAR_SCRATCH_TOKENS = 8   # fewer make no use of scratch memory
+
+
+def neuzip_linear_scratch_bytes(out_features, in_features: int, tokens: int) -> int:
+    """Bytes of scratch memory that neuzip_linear_batch_scratch makes use of (0: none)."""
+    outs = (ctypes.c_uint64 * len(out_features))(*[int(o) for o in out_features])
+    return int(_lib.neuzip_linear_scratch_bytes(outs, len(outs), in_features, tokens))
+
+
+def neuzip_linear_batch_scratch(weights, out_features, in_features: int, x: torch.Tensor, biases, ys, scratch=None, stream=None):
+    """neuzip_linear_batch into ys with scratch memory (a contiguous CUDA tensor of at least
+    neuzip_linear_scratch_bytes bytes, in use until the call's work has run; None: none)."""
+    return _linear_call(weights, out_features, in_features, x, x.numel() // in_features, biases, ys, stream,
+                        "neuzip_linear_batch_scratch", lambda outs: scratch)
+
+
+def _linear_scratch(outs, in_features, tokens, device, stream):
+    """Scratch memory for the linear calls below, of the stream's that the call's work runs on, or None where it needs none,
+    there is none to be had, or the stream is being captured (by whom is not known here, and an allocation could end it)."""
+    size = _lib.neuzip_linear_scratch_bytes(outs, len(outs), in_features, tokens) if tokens >= LINEAR_SCRATCH_TOKENS else 0
+    if size == 0 or not (stream is None or isinstance(stream, torch.cuda.Stream)):
+        return None
+    with torch.cuda.stream(stream):     # (None: the current one)
+        if torch.cuda.is_current_stream_capturing():
+            return None
+        try:
+            return torch.empty(size, dtype=torch.uint8, device=device)
+        except torch.cuda.OutOfMemoryError:
+            return None
+
+
+def _linear_call(weights, out_features, in_features, x, tokens, biases, ys, stream, name, scratch_of=None):
+    count = len(weights)
+    arr = (ctypes.c_void_p * count)(*[w.handle.value for w in weights])
+    outs = (ctypes.c_uint64 * count)(*[int(o) for o in out_features])
+    scratch = scratch_of(outs) if scratch_of else _linear_scratch(outs, in_features, tokens, x.device, stream)
+    yp = (ctypes.c_void_p * count)(*[y.data_ptr() for y in ys])
+    bp = None
+    if biases is not None:
+        bp = (ctypes.c_void_p * count)(*[(b.data_ptr() if b is not None else None) for b in biases])
+    rc = _lib.neuzip_linear_batch_scratch(arr, outs, count, in_features, ctypes.c_void_p(x.data_ptr()), tokens, bp, yp,
+                                          ctypes.c_void_p(scratch.data_ptr() if scratch is not None else None),
+                                          scratch.numel() * scratch.element_size() if scratch is not None else 0,
+                                          _stream_handle(stream))
+    if rc != OK:
+        raise NeuzipError(rc, name)
+    return ys
+
+
 def neuzip_linear(weight: Blob, out_features: int, in_features: int, x: torch.Tensor, bias: torch.Tensor = None,
                   y: torch.Tensor = None, stream=None) -> torch.Tensor:
     """y = x W_hat^T + bias with the weight taken straight from its compressed form (float32 result)."""
@@ -327,6 +380,9 @@ def neuzip_linear(weight: Blob, out_features: int, in_features: int, x: torch.Te
     if bias is not None and not (bias.is_cuda and bias.dtype == torch.float32 and bias.is_contiguous()
                                  and bias.numel() == out_features):
         raise TypeError("expected a contiguous float32 CUDA bias of out_features")
+    if tokens >= LINEAR_SCRATCH_TOKENS:
+        _linear_call([weight], [out_features], in_features, x, tokens, [bias], [y], stream, "neuzip_linear")
+        return y
     rc = _lib.neuzip_linear(weight.handle, out_features, in_features, ctypes.c_void_p(x.data_ptr()), tokens,
                             ctypes.c_void_p(bias.data_ptr() if bias is not None else None),
                             ctypes.c_void_p(y.data_ptr()), _stream_handle(stream))
@@ -357,16 +413,7 @@ def neuzip_linear_batch(weights, out_features, in_features: int, x: torch.Tensor
             if bias is not None and not (bias.is_cuda and bias.dtype == torch.float32 and bias.is_contiguous()
                                          and bias.numel() == o):
                 raise TypeError("expected contiguous float32 CUDA biases of out_features")
-    arr = (ctypes.c_void_p * count)(*[w.handle.value for w in weights])
-    outs = (ctypes.c_uint64 * count)(*[int(o) for o in out_features])
-    yp = (ctypes.c_void_p * count)(*[y.data_ptr() for y in ys])
-    bp = None
-    if biases is not None:
-        bp = (ctypes.c_void_p * count)(*[(b.data_ptr() if b is not None else None) for b in biases])
-    rc = _lib.neuzip_linear_batch(arr, outs, count, in_features, ctypes.c_void_p(x.data_ptr()), tokens, bp, yp,
-                                  _stream_handle(stream))
-    if rc != OK:
-        raise NeuzipError(rc, "neuzip_linear_batch")
+    _linear_call(weights, out_features, in_features, x, tokens, biases, ys, stream, "neuzip_linear_batch")
     return ys
 
 

@@ -664,48 +664,49 @@ int launch_batch(const BatchArgs &args, int variant, uint32_t groups, hipStream_
     return hip_ok(hipGetLastError()) ? NEUZIP_OK : NEUZIP_EHIP;
 }
 
+// Columns of a group whose words share a window: all the form has, or as many as fit (at their average length and 1 % more).
+inline uint32_t columns_that_fit(const neuzip_blob *w, uint32_t cols, uint32_t window)
+{
+    const uint64_t bytes = w->total_words * 2 / w->n_chunks + 16;  // of a chunk's words, and what alignment adds
+    const uint64_t fit = (window - window / 100 - 16) / bytes;
+    return fit == 0 ? 1u : (fit < cols ? static_cast<uint32_t>(fit) : cols);
+}
+
 // Which form of the linear kernel a launch takes: 16 columns (tiles of 16 tokens) or 32 columns (tiles of 32 tokens),
 // and whether weights that have entry points are walked from them (16 columns only) or whole.
-//
-// Columns, more than 16 tokens: the wide form halves the activation traffic per token but has twice the sums per
-// wave, and every row that ends inside a chunk sends them to y one by one.  It pays where at most every second chunk
-// has such an end, or none, and for rows of 2048, which end once inside each (64 tokens, 32 / 16 columns:
-// 4096 x 14336 69 / 86 us, 14336 x 4096 62 / 81, 20000 x 2048 85 / 90; 9000 x 5120 95 / 90, 18000 x 1024 106 / 77).
 //
 // Entry points: two lanes per state halve the chain and double the workgroups.  With up to 16 tokens that pays while
 // these run at once (two per CU, 512), and beyond one round of whole walks, whose last round the half ones fill
 // (1 token, halves / whole: three weights of 1000 x 8192 23.4 / 28.2 us, two of 4096 x 4096 21.0 / 26.6, four
 // 39.5 / 34.3; 4000 x 14336 with 1000 x 14336 48.3 / 55.2); the longer walk of normalised weights gains a little further
-// (three of 4096 x 4096, k = 3, block 512: 39.3 / 41.5).  With more tokens the activations weigh, and 16 columns
-// read them twice as often: weights that leave CUs empty are walked in halves, beyond that, or beside a larger one, the
-// launch whole, a little later for few tokens (4096 x 4096, 64 tokens: 26 / 30; two of them, 20 tokens: 26.2 / 26.8, 24:
-// 28.1 / 27.1, 64: 45.9 / 31.5; q, k and v of a Llama-3-8B attention block, 64 tokens: 45.6 / 31.1; 14336 x 4096 with
-// 1024 x 4096, 32 tokens: 53.7 / 38.4; 20000 x 2048 with 500 x 2048, 32 tokens: 59.1 / 54.4).  Rows shorter than a chunk end inside it, and half a walk has half the ends to send one
-// after the other: always in halves there (four weights of 16000 x 1024, 64 tokens: 173 / 200; 5000 x 2048: 70 / 90).
-// (Figures of the kernel whose words went through registers; both sides are 3-10 % lower now.)
+// (three of 4096 x 4096, k = 3, block 512: 39.3 / 41.5).  (Figures of a kernel whose words went through registers; both sides are
+// lower now.)  With more tokens, while all weights have them and they run at once (4096 x 4096, 64 tokens, halves / 32 columns
+// 20.6 / 31.6; 16000 x 512 25 / 49; q, k and v of a Llama-3-8B attention block, 32 tokens, 24.9 / 27.3, 64 29.7 / 32.4; 3000 x 4736,
+// 24 tokens, 22.4 / 31.7).  Beyond, 32 columns, which request x half as often (64 tokens, 16 / 32 columns: 4096 x 14336 86 / 69,
+// 14336 x 4096 81 / 62).
 struct LinearForm {
     uint32_t cols;
     bool entries;
+    uint32_t wgs;  // (about)
 };
-inline LinearForm linear_form(uint32_t tokens, uint64_t in_features, const neuzip_blob *const *weights, uint32_t count)
+inline LinearForm linear_form(uint32_t tokens, uint64_t in_features, const uint64_t *out_features, uint32_t count, bool normalised)
 {
     constexpr uint32_t kAtOnce = 512;  // workgroups the chip runs at once: two on each of its 256 CUs
     uint32_t whole = 0, halves = 0;    // workgroups of the launch
     bool any = false, all = true;
     for (uint32_t i = 0; i < count; ++i) {
-        const bool has = has_entry_points(weights[i]->n_chunks);
+        const uint32_t n_chunks = static_cast<uint32_t>((out_features[i] * in_features + kChunk - 1) / kChunk);
+        const bool has = has_entry_points(n_chunks);
         any = any || has;
         all = all && has;
-        whole += (weights[i]->n_chunks + kDecChunksPerWg - 1) / kDecChunksPerWg;
-        halves += (weights[i]->n_chunks + (kDecChunksPerWg >> has) - 1) / (kDecChunksPerWg >> has);
+        whole += (n_chunks + kDecChunksPerWg - 1) / kDecChunksPerWg;
+        halves += (n_chunks + (kDecChunksPerWg >> has) - 1) / (kDecChunksPerWg >> has);
     }
     if (tokens <= 16)
-        return {16u, any && (halves <= (weights[0]->block ? kAtOnce + kAtOnce / 2 : kAtOnce) || whole > kAtOnce)};
-    const bool few_ends = in_features >= 2 * kChunk || in_features == kChunk || in_features == kChunk / 2;
-    const bool worth = in_features < kChunk || halves <= (tokens <= 20 ? kAtOnce : kAtOnce / 2);
-    if (any && worth && (all || (in_features < kChunk && !few_ends)))
-        return {16u, true};
-    return {few_ends ? 32u : 16u, false};
+        return {16u, any && (halves <= (normalised ? kAtOnce + kAtOnce / 2 : kAtOnce) || whole > kAtOnce), halves};
+    if (all && halves <= kAtOnce)
+        return {16u, true, halves};
+    return {32u, false, whole};
 }
 
 // Workgroups up to which the walks step without a branch (see rans_get): at most one per CU, two waves per SIMD (4096 x 4096,
@@ -1540,6 +1541,49 @@ int neuzip_update(neuzip_blob *const *blobs, const void *const *d_grads, void *c
 
 uint32_t neuzip_guard(const neuzip_blob *blob) { return is_blob(blob) ? blob->guard : 0; }
 
+}  // extern "C"
+
+namespace {
+
+
+// Scratch memory of a linear call.
+// The sums of pieces (see LinearArgs), of one tile of tokens at a time.  The columns of a group are chunks apart that begin in the
+// same feature, 4096 / gcd(in_features, 4096) rows: 32 for an odd multiple of 128, and then every float of an atomic instruction
+// is in a cache line of its own.  Stored by themselves, the tokens of a row side by side, and added up by a launch of their own,
+// in the place of the one that sets y up (64 tokens, atomics / pieces: 12000 x 4736 94 / 56 us, 30000 x 1920 146 / 61, 90000 x 640
+// 322 / 77; 16 tokens 48.5 / 42.2, 51 / 44, 87 / 46; 5 tokens 39.1 / 39.7).  Four rows apart the atomics are the cheaper
+// ones (11000 x 5120, 64 tokens, 50.2 / 54.4; 5200 x 11264 50.2 / 59.9), eight apart about even (10000 x 5632, 16 tokens 42.3 /
+// 42.1, 64 58.9 / 55.5).
+uint64_t linear_pieces_bytes(uint64_t out_features, uint64_t in_features, uint32_t tokens)
+{
+    const uint64_t low = in_features & (0 - in_features), apart = low < kChunk ? kChunk / low : 1;  // (the gcd is the lowest bit)
+    if (tokens < 8 || kChunk % in_features == 0 || apart < 8)
+        return 0;
+    const uint64_t units = (out_features * in_features + kMidTurn * kTurn - 1) / (kMidTurn * kTurn);
+    return (units + out_features) * padded_tokens(tokens < kLinMaxTokens ? tokens : kLinMaxTokens) * sizeof(float);
+}
+
+// The activations laid out (see linear_init_kernel).  More than 32 to 36 tokens; fewer where a launch sets y up anyway, or where every
+// CU has two workgroups that request x 16 rows at a time (q, k and v of a Llama-3-8B attention block, 24 tokens, 28.4 us as x
+// lies, 24.6 laid out; 32 tokens 31.2 / 24.9): the launch takes 3 us, and otherwise gives back less (4096 x 4096, 32 tokens, 18.0 /
+// 19.1; 36 20.1 / 19.8; 14336 x 4096, 24 tokens, 36.5 / 37.9; 40 51.2 / 42.5).
+uint64_t linear_laid_out_bytes(const uint64_t *out_features, uint32_t count, uint64_t in_features, uint32_t tokens)
+{
+    if (tokens <= 16)
+        return 0;
+    if (tokens <= 36 && (kChunk % in_features == 0 || linear_pieces_bytes(1, in_features, tokens) > 0)) {
+        const LinearForm form = linear_form(tokens, in_features, out_features, count, false);
+        if (form.entries ? form.wgs <= 256 : tokens <= 32)
+            return 0;
+    }
+    const uint32_t last = tokens % kLinMaxTokens;
+    return (static_cast<uint64_t>(tokens - last) + padded_tokens(last)) * in_features * 2;
+}
+
+}  // namespace
+
+extern "C" {
+
 int neuzip_linear(const neuzip_blob *weight, uint64_t out_features, uint64_t in_features, const void *d_x,
                   uint32_t tokens, const float *d_bias, float *d_y, void *hip_stream)
 {
@@ -1550,12 +1594,29 @@ int neuzip_linear_batch(const neuzip_blob *const *weights, const uint64_t *out_f
                         uint64_t in_features, const void *d_x, uint32_t tokens, const float *const *d_bias,
                         float *const *d_y, void *hip_stream)
 {
+    return neuzip_linear_batch_scratch(weights, out_features, count, in_features, d_x, tokens, d_bias, d_y, nullptr, 0, hip_stream);
+}
+
+uint64_t neuzip_linear_scratch_bytes(const uint64_t *out_features, uint32_t count, uint64_t in_features, uint32_t tokens)
+{
+    if (!out_features || count > kLinBatchMax || in_features == 0 || in_features % kTurn != 0 || in_features >= (1ull << 31))
+        return 0;
+    uint64_t bytes = linear_laid_out_bytes(out_features, count, in_features, tokens);
+    for (uint32_t i = 0; i < count; ++i)
+        bytes += linear_pieces_bytes(out_features[i], in_features, tokens);
+    return bytes;
+}
+
+int neuzip_linear_batch_scratch(const neuzip_blob *const *weights, const uint64_t *out_features, uint32_t count,
+                                uint64_t in_features, const void *d_x, uint32_t tokens, const float *const *d_bias,
+                                float *const *d_y, void *d_scratch, uint64_t scratch_bytes, void *hip_stream)
+{
     if (count == 0)
         return NEUZIP_OK;
     if (!weights || !out_features || !d_y || !d_x || tokens == 0 || count > kLinBatchMax)
         return NEUZIP_EINVAL;
     if (in_features == 0 || in_features % kTurn != 0 || in_features >= (1ull << 31) ||
-        (reinterpret_cast<uintptr_t>(d_x) & 15u))
+        (reinterpret_cast<uintptr_t>(d_x) & 15u) || (reinterpret_cast<uintptr_t>(d_scratch) & 15u))
         return NEUZIP_EINVAL;
     for (uint32_t i = 0; i < count; ++i) {
         const neuzip_blob *w = weights[i];
@@ -1581,11 +1642,23 @@ int neuzip_linear_batch(const neuzip_blob *const *weights, const uint64_t *out_f
         gcd = r;
         r = t;
     }
+    // what the scratch memory serves for: the activations laid out, and sums of pieces
+    const uint64_t wanted = neuzip_linear_scratch_bytes(out_features, count, in_features, tokens);
+    const bool room = d_scratch && scratch_bytes >= wanted;
+    const uint64_t x_bytes = room ? linear_laid_out_bytes(out_features, count, in_features, tokens) : 0;
+    const bool in_pieces = room && wanted > x_bytes;
+    uint8_t *pieces_at = static_cast<uint8_t *>(d_scratch) + x_bytes;
     LinearBatchArgs batch;
-    LinearInitBatchArgs init;
+    LinearInitArgs init;
+    LinearSumArgs sum;
+    std::memset(&sum, 0, sizeof(sum));
+    sum.count = count;
+    sum.in_features = in_features;
     std::memset(&batch, 0, sizeof(batch));
     std::memset(&init, 0, sizeof(init));
-    batch.count = init.count = count;
+    batch.count = count;
+    for (uint32_t i = count; i < kLinBatchMax; ++i)
+        batch.wg_end[i] = init.wg_end[i] = ~0u;
     init.tokens = tokens;
     uint32_t init_wgs = 0;
     for (uint32_t i = 0; i < count; ++i) {
@@ -1602,48 +1675,66 @@ int neuzip_linear_batch(const neuzip_blob *const *weights, const uint64_t *out_f
         a.status = table_of(w)->status;
         a.n = w->n;
         a.n_chunks = w->n_chunks;
-        a.in_features = static_cast<uint32_t>(in_features);
+        a.row_turns.set(static_cast<uint32_t>(in_features / kTurn));
         a.out_features = static_cast<uint32_t>(out_features[i]);
         a.coef = coef_of(w);
         a.block_shift = 0;
         while (w->block && (1u << a.block_shift) < w->block)
             ++a.block_shift;
-        a.stride = static_cast<uint32_t>(in_features / gcd);
-        a.whole_rows = in_features == kChunk ? 1u : 0u;
+        a.stride.set(static_cast<uint32_t>(in_features / gcd));
+        a.whole_rows = kChunk % in_features == 0 ? 1u : 0u;
         a.bias = d_bias ? d_bias[i] : nullptr;
-        const uint64_t cells = static_cast<uint64_t>(tokens) * out_features[i];
         init.y[i] = d_y[i];
         init.bias[i] = d_bias ? d_bias[i] : nullptr;
         init.out_features[i] = a.out_features;
-        init_wgs += static_cast<uint32_t>((cells + 255) / 256);
+        if (in_pieces) {
+            a.pieces = reinterpret_cast<float *>(pieces_at);
+            pieces_at += linear_pieces_bytes(out_features[i], in_features, tokens);
+            sum.pieces[i] = a.pieces;
+            sum.bias[i] = a.bias;
+            sum.out_features[i] = a.out_features;
+            sum.wg_end[i] = (i ? sum.wg_end[i - 1] : 0u) + (a.out_features + kLinSumRows - 1) / kLinSumRows;
+        } else if (!a.whole_rows)
+            init_wgs += (a.out_features + kLinInitThreads - 1) / kLinInitThreads * ((tokens + kLinInitTokens - 1) / kLinInitTokens);
         init.wg_end[i] = init_wgs;
     }
-    // (a chunk that is a whole row: its sum is complete in one workgroup, which stores it)
-    if (in_features == kChunk)
-        ;
-    else if (count == 1)
-        hipLaunchKernelGGL(linear_init_kernel, dim3(init_wgs), dim3(256), 0, stream, init.y[0], init.bias[0], tokens,
-                           init.out_features[0]);
-    else
-        hipLaunchKernelGGL(linear_init_batch_kernel, dim3(init_wgs), dim3(256), 0, stream, init);
+    // (chunks of whole rows: their sums are complete in one workgroup, which stores them)
+    init.set_up = init_wgs;
+    const bool laid_out = x_bytes > 0;
+    if (laid_out) {
+        init.x = static_cast<const uint4 *>(d_x);
+        init.scratch = static_cast<uint4 *>(d_scratch);
+        init.row_pieces = static_cast<uint32_t>(in_features / kRun);
+        init_wgs += static_cast<uint32_t>((static_cast<uint64_t>(init.row_pieces) * tokens + kLinInitThreads - 1) / kLinInitThreads);
+    }
+    if (init_wgs > 0)
+        hipLaunchKernelGGL(linear_init_kernel, dim3(init_wgs), dim3(kLinInitThreads), 0, stream, init);
     // the kernel holds the partial sums of at most 64 tokens: larger batches go through in tiles of 64
     // (each tile decodes the weights again: beyond a few tiles decompressing once and a dense product win)
     const neuzip_blob *first = weights[0];
     const bool in_step = columns_in_step(weights, count);
     for (uint32_t t0 = 0; t0 < tokens; t0 += kLinMaxTokens) {
         const uint32_t tile = tokens - t0 < kLinMaxTokens ? tokens - t0 : kLinMaxTokens;
-        const LinearForm form = linear_form(tile, in_features, weights, count);
+        const LinearForm form = linear_form(tile, in_features, out_features, count, first->block != 0);
         const uint32_t cols = form.cols;  // chunks per group = columns of the matrix instruction
         uint32_t wgs = 0;
         for (uint32_t i = 0; i < count; ++i) {
             LinearArgs &a = batch.t[i];
             a.tokens = tile;
-            a.x = static_cast<const uint16_t *>(d_x) + static_cast<uint64_t>(t0) * in_features;
+            a.x = static_cast<const uint16_t *>(laid_out ? d_scratch : d_x) + static_cast<uint64_t>(t0) * in_features;
+            a.x_row = laid_out ? 2 * kRun * 2 : in_features * 2;
+            a.x_pair = laid_out ? padded_tokens(tile) * (2 * kRun * 2) : 2 * kRun * 2;
+            a.x_turn = kStates / 2 * a.x_pair;
+            a.piece_tokens = sum.piece_tokens = padded_tokens(tile);
             a.y = d_y[i] + static_cast<uint64_t>(t0) * out_features[i];
-            const uint64_t per_block = static_cast<uint64_t>(cols) * a.stride;
-            a.n_groups = static_cast<uint32_t>((weights[i]->n_chunks + per_block - 1) / per_block * a.stride);
             a.split = form.entries && a.mid_states ? 1u : 0u;
+            sum.y[i] = a.y;
+            sum.unit_shift[i] = a.split ? 11u : 12u;
+            static_assert(kChunk == 1u << 12 && kMidTurn * kTurn == 1u << 11, "log2 of a unit");
             const uint32_t groups_per_wg = (kDecChunksPerWg / cols) >> a.split;
+            a.columns = columns_that_fit(weights[i], cols, kLinStageBytes / groups_per_wg);
+            const uint64_t per_block = static_cast<uint64_t>(a.columns) * a.stride.by;
+            a.n_groups = static_cast<uint32_t>((weights[i]->n_chunks + per_block - 1) / per_block * a.stride.by);
             wgs += (a.n_groups + groups_per_wg - 1) / groups_per_wg;
             batch.wg_end[i] = wgs;
         }
@@ -1660,6 +1751,10 @@ int neuzip_linear_batch(const neuzip_blob *const *weights, const uint64_t *out_f
             case 1: launch_linear<1, false>(batch, cols, wgs, in_step, stream); break;
             default: launch_linear<0, false>(batch, cols, wgs, in_step, stream); break;
             }
+        }
+        if (in_pieces) {
+            sum.tokens = tile;
+            hipLaunchKernelGGL(linear_sum_kernel, dim3(sum.wg_end[count - 1]), dim3(kLinSumThreads), 0, stream, sum);
         }
         if (!hip_ok(hipGetLastError()))
             return NEUZIP_EHIP;

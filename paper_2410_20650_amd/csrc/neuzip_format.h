@@ -62,6 +62,38 @@ static_assert(kTableChunks <= kSplitChunks, "a blob without entry points holds t
 
 constexpr uint32_t kSteps = 264;  // occupied symbols of a table (at most 256) and what a search reads behind them
 
+// Division of 32-bit numbers by one that the host knows: exact for every n (round-up method, Granlund and Montgomery 1994).
+struct Divisor {
+    uint32_t by, mul, shift1, shift2;
+    __host__ void set(uint32_t d)
+    {
+        uint32_t l = 0;  // ceil(log2 d)
+        while (l < 32 && (1ull << l) < d)
+            ++l;
+        by = d;
+        mul = static_cast<uint32_t>(((1ull << 32) * ((1ull << l) - d)) / d + 1);
+        shift1 = l < 1 ? l : 1;
+        shift2 = l < 1 ? 0 : l - 1;
+    }
+    __host__ __device__ __forceinline__ uint32_t quotient(uint32_t n) const
+    {
+        const uint32_t t = static_cast<uint32_t>((static_cast<uint64_t>(mul) * n) >> 32);
+        return (t + ((n - t) >> shift1)) >> shift2;
+    }
+    __host__ __device__ __forceinline__ uint32_t rest(uint32_t n) const { return n - quotient(n) * by; }
+};
+
+// A launch's arguments come to a CU cache line by cache line, and a line that is first asked for when it is needed is 550
+// cycles (the first of all 1000, one that is there 80): a kernel asks for all of them with its first instructions.
+template <class Args>
+__device__ __forceinline__ void fetch_arguments(const Args &a)
+{
+    const uint32_t *at = reinterpret_cast<const uint32_t *>(&a);
+#pragma unroll
+    for (uint32_t i = 0; i < sizeof(Args); i += 64)
+        asm volatile("" ::"s"(at[i / 4]));
+}
+
 // ------------------------------------------------------------------------------------------
 // Device-side table block that sits at the start of every blob's fixed allocation.
 // ------------------------------------------------------------------------------------------

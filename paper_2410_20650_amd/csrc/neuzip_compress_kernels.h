@@ -5,6 +5,8 @@
 // described by a CompressBatch.
 #pragma once
 
+#include <type_traits>
+
 #include "neuzip_format.h"
 
 namespace nz {
@@ -820,7 +822,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
     static_assert(!(WIDE && HALF), "one element type");
     static_assert(!UPD || (SPLIT == 7 && !NORM && !WIDE && !HALF), "only lossless bf16 weights are trained");
     constexpr int KB = SPLIT >= 0 ? SPLIT : 7;
-    __shared__ uint4 enc_raw[256];
+    __shared__ uint4 enc_raw[2 * 256];  // (the second half: of no symbol)
     __shared__ __align__(32) uint16_t rings[kEncThreads * kRingWords];
     __shared__ uint32_t group_chunk[kEncThreads / kStates];
     const uint32_t all_groups = b.it[b.count - 1].enc_end;
@@ -857,6 +859,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
     // This state's first 8-element vector of the chunk; a turn later is kStates vectors on.
     const uint4 *src4 = static_cast<const uint4 *>(src) + (base / 8 + j) * (WIDE ? 2 : 1);
     // the gradients travel with the weights, one 128-bit piece per turn
+    uint64_t from = base;  // (where these begin)
     const uint4 *grad4 = UPD ? reinterpret_cast<const uint4 *>(grad) + (base / 8 + j) : nullptr;
     constexpr uint32_t kAhead = 4;  // (2: 3 % slower on tensors beyond the cache; 8: registers, 7 % slower with gradients)
     static_assert(kTurns % kAhead == 0, "whole rotations");
@@ -869,9 +872,10 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
         if constexpr (UPD)
             grads[r] = grad4[at * kStates];
         if constexpr (NORM)
-            coefs[r] = coef[(base + at * kTurn + j * kRun) >> block_shift];
+            coefs[r] = coef[(from + at * kTurn + j * kRun) >> block_shift];
     };
-    if (m == kChunk) {
+    const bool whole_wave = __all(m == kChunk || m == 0);
+    if (whole_wave && m == kChunk) {
 #pragma unroll
         for (uint32_t r = 0; r < kAhead; ++r)
             request(r, static_cast<int>(kTurns - 1 - r));
@@ -936,6 +940,8 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
         const EncSym e = encoder_constants(tb->freq[threadIdx.x], tb->cum[threadIdx.x]);
         enc_raw[threadIdx.x] = make_uint4(e.mul, e.limit_cum, e.shift_inc, e.cmpl);
     }
+    // constants that leave a state as it is (and do not look like a symbol without room), for turns that a ragged chunk does not have
+    enc_raw[256 + threadIdx.x] = make_uint4(1u, 0xFFFF0000u, 0u, 0u);
     __syncthreads();
     if (table_wg) {
         // fills in the decoder's slot table, and what decoders from the entry points need to make it, while the others
@@ -972,43 +978,70 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
     const uint8_t *wave_src = static_cast<const uint8_t *>(src) + static_cast<uint64_t>(wave_chunk) * (kChunk * 2);
     const uint32_t wave_at = (c - wave_chunk) * (kChunk * 2) + j * (kRun * 2);
 
-    const bool whole_wave = __all(m == kChunk || m == 0);
-    if (whole_wave && m == kChunk) {
-        // the words of turn q from its buffer, with what goes out along with them
-        auto prepare = [&](uint32_t r, int q, uint32_t (&w)[4]) {
-            const uint64_t vec = base / 8 + static_cast<uint32_t>(q) * kStates + j;
-            ahead[r].words(w);
-            if constexpr (UPD) {
-                w[0] = update_pair(w[0], grads[r].x, lr);
-                w[1] = update_pair(w[1], grads[r].y, lr);
-                w[2] = update_pair(w[2], grads[r].z, lr);
-                w[3] = update_pair(w[3], grads[r].w, lr);
-                // if the caller wants it, the new weight replaces the old one in its buffer (same lane,
-                // same place), past the caches: the call returns while this kernel may still run, and says
-                // that the weights are there
-                if (b.keep_new)
-                    store_through(wave_src, wave_at + static_cast<uint32_t>(q) * (kTurn * 2), make_uint4(w[0], w[1], w[2], w[3]));
-            }
-            if constexpr (SPLIT >= 0) {
+    // The words of turn q from buffer r, with what goes out along with them, as far as this lane has the turn.
+    auto prepare = [&](uint32_t r, int q, bool has, uint32_t (&w)[4]) {
+        const uint64_t vec = base / 8 + static_cast<uint32_t>(q) * kStates + j;
+        ahead[r].words(w);
+        if constexpr (UPD) {
+            w[0] = update_pair(w[0], grads[r].x, lr);
+            w[1] = update_pair(w[1], grads[r].y, lr);
+            w[2] = update_pair(w[2], grads[r].z, lr);
+            w[3] = update_pair(w[3], grads[r].w, lr);
+            // if the caller wants it, the new weight replaces the old one in its buffer (same lane,
+            // same place), past the caches: the call returns while this kernel may still run, and says
+            // that the weights are there
+            if (b.keep_new && has)
+                store_through(wave_src, wave_at + static_cast<uint32_t>(q) * (kTurn * 2), make_uint4(w[0], w[1], w[2], w[3]));
+        }
+        if constexpr (SPLIT >= 0) {
+            if (has) {
                 store_fields<KB>(sm, vec, fields_of<KB, HALF>(w));
                 if constexpr (WIDE)
                     reinterpret_cast<uint4 *>(low)[vec] = ahead[r].lows();
             }
-            // with block-wise normalisation the exponents coded are those of bf16(w / c)
-            if constexpr (NORM) {
-                const float c = coefficient(coefs[r]);
+        }
+        // with block-wise normalisation the exponents coded are those of bf16(w / c)
+        if constexpr (NORM) {
+            const float c = coefficient(coefs[r]);
 #pragma unroll
-                for (int p = 0; p < 4; ++p)
-                    w[p] = normalise_word(w[p] & 0xFFFFu, c) | (normalise_word(w[p] >> 16, c) << 16);
-            }
-        };
+            for (int p = 0; p < 4; ++p)
+                w[p] = normalise_word(w[p] & 0xFFFFu, c) | (normalise_word(w[p] >> 16, c) << 16);
+        }
+    };
+    // The walk over whole turns, back to front.  WHOLE: all chunks of the wave are whole.  Else it holds the tensor's ragged last
+    // chunk, whose lanes take the same turns: those that it does not have are coded with constants of no symbol.  (Walked by
+    // itself, element by element and a turn behind its input, that chunk and the whole ones beside it were the last to end: 4096 x
+    // 4096 weights less 1000, compressed 58.9 us, 45.9 now (45.7 without a ragged end), with the kept table 56.4 / 35.9 (34.4), with the
+    // weight step 78.4 / 57.6 (56.5); 58.7 M less 1000 107.5 / 95.1 (94.2).)
+    auto walk = [&](auto all_whole, uint32_t whole_turns) {
+        constexpr bool WHOLE = decltype(all_whole)::value;
+        // (one wave per tensor, whose registers are everybody's: four turns ahead would take 10 more; one is waited for)
+        constexpr uint32_t kBuffers = WHOLE ? kAhead : 2;
+        static_assert((kTurns - kMidTurn) % kBuffers == 0, "the middle lies between two rotations");
+        const uint32_t turns = WHOLE ? kTurns : wave_max_u32(whole_turns);
+        if (turns == 0)
+            return;
+        const int top = static_cast<int>((turns + kBuffers - 1) / kBuffers * kBuffers) - 1;
+        auto has = [&](int q) { return WHOLE || q < static_cast<int>(whole_turns); };
+        // (no branch: a lane without the turn reads another one, or, if it has none at all, the wave's first chunk's, of which
+        // nothing is used.  Behind a branch the compiler copies what has been requested, and waits for it right there.)
+        const int most = static_cast<int>(whole_turns) - 1;
+        if (!WHOLE && most < 0) {
+            const uint64_t back = (base - static_cast<uint64_t>(wave_chunk) * kChunk) / 8;
+            src4 -= back * (WIDE ? 2 : 1);
+            if constexpr (UPD)
+                grad4 -= back;
+            from -= back * 8;
+        }
+        auto request_own = [&](uint32_t r, int q) { request(r, WHOLE ? q : min(q, most)); };
         uint32_t w[4];
         // the constants of a pair of symbols are requested while the pair before it is coded: the compiler would
         // not move these LDS reads over the ring stores by itself, and every pair would wait for its own
         EncSym e_hi, e_lo;
-        auto fetch = [&](uint32_t d, EncSym &hi, EncSym &lo) {
-            hi = enc[symbol_of<HALF>(d >> 16)];
-            lo = enc[symbol_of<HALF>(d & 0xFFFFu)];
+        auto fetch = [&](uint32_t d, bool has_it, EncSym &hi, EncSym &lo) {
+            const uint32_t half = has_it ? 0u : 256u;
+            hi = enc[symbol_of<HALF>(d >> 16) | half];
+            lo = enc[symbol_of<HALF>(d & 0xFFFFu) | half];
         };
         // codes turn q from w, and makes ready the turn after it, whose source is in buffer r
         auto turn = [&](uint32_t r, int q, bool more) {
@@ -1017,11 +1050,11 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
             for (int p = 3; p >= 0; --p) {
                 EncSym n_hi = e_hi, n_lo = e_lo;
                 if (p > 0) {
-                    fetch(w[p - 1], n_hi, n_lo);
+                    fetch(w[p - 1], has(q), n_hi, n_lo);
                 } else if (more) {
-                    prepare(r, q - 1, w);
-                    fetch(w[3], n_hi, n_lo);
-                    request(r, q - 1 - static_cast<int>(kAhead));
+                    prepare(r, q - 1, has(q - 1), w);
+                    fetch(w[3], has(q - 1), n_hi, n_lo);
+                    request_own(r, q - 1 - static_cast<int>(kBuffers));
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 if constexpr (SPLIT >= 0) {
@@ -1038,118 +1071,88 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
             ring_advance(st, cur_before);
             ring_flush(wp_before, st.wp, ring_bytes, lane_ring, chunk_slots, j);
         };
-        prepare(0, static_cast<int>(kTurns) - 1, w);
-        fetch(w[3], e_hi, e_lo);
-        request(0, static_cast<int>(kTurns) - 1 - static_cast<int>(kAhead));
-        // turn q - r codes w; the turn after it is in buffer (r + 1) mod kAhead
-        int q = static_cast<int>(kTurns) - 1;
-        for (; q >= static_cast<int>(kAhead); q -= static_cast<int>(kAhead)) {
+        if constexpr (!WHOLE) {
 #pragma unroll
-            for (uint32_t r = 0; r < kAhead; ++r)
-                turn((r + 1) % kAhead, q - static_cast<int>(r), true);
-            if (q + 1 - static_cast<int>(kAhead) == static_cast<int>(kMidTurn)) {
+            for (uint32_t r = 0; r < kBuffers; ++r)
+                request_own(r, top - static_cast<int>(r));
+        }
+        prepare(0, top, has(top), w);
+        fetch(w[3], has(top), e_hi, e_lo);
+        request_own(0, top - static_cast<int>(kBuffers));
+        // turn q - r codes w; the turn after it is in buffer (r + 1) mod kBuffers
+        int q = top;
+#pragma unroll 1  // (the rotation is written out; once more of it costs registers)
+        for (; q >= static_cast<int>(kBuffers); q -= static_cast<int>(kBuffers)) {
+#pragma unroll
+            for (uint32_t r = 0; r < kBuffers; ++r)
+                turn((r + 1) % kBuffers, q - static_cast<int>(r), true);
+            // (a chunk that ends below has coded nothing so far but, perhaps, its incomplete turn, which lies below too)
+            if (q + 1 - static_cast<int>(kBuffers) == static_cast<int>(kMidTurn) && (WHOLE || m > kMidTurn * kTurn)) {
                 mid_x = st.x;
                 mid_wp = st.wp;
             }
         }
-        static_assert((kTurns - kMidTurn) % kAhead == 0, "the middle lies between two rotations");
 #pragma unroll
-        for (uint32_t r = 0; r < kAhead; ++r)
-            turn((r + 1) % kAhead, static_cast<int>(kAhead - 1 - r), r + 1 < kAhead);
-    } else if (!whole_wave && m > 0) {
-        // The wave with the tensor's ragged last chunk: every lane codes the turns its chunk has, the last
-        // one possibly with fewer than 8 elements of its own (read one by one: the source is the caller's and
-        // ends there); a turn's words are requested while the one above it is coded.
-        auto valid_of = [&](int q) -> uint32_t {
-            const uint32_t first = static_cast<uint32_t>(q) * kTurn + j * kRun;
-            return first >= m ? 0u : (m - first < kRun ? m - first : kRun);
-        };
-        auto request_some = [&](int q, SourceVec<WIDE> &d, uint4 &g) {
-            const uint32_t valid = valid_of(q);
-            const uint64_t first = base + static_cast<uint32_t>(q) * kTurn + j * kRun;
-            if (valid == kRun) {
-                d.load(src4, static_cast<uint32_t>(q) * kStates);
-                if constexpr (UPD)
-                    g = grad4[static_cast<uint32_t>(q) * kStates];
-            } else if (valid > 0) {
-                d.load_some(src, first, valid);
-                if constexpr (UPD) {
-                    SourceVec<false> some;
-                    some.load_some(grad, first, valid);
-                    g = some.a;
-                }
-            }
-        };
-        SourceVec<WIDE> d0, d1;
-        uint4 g0 = make_uint4(0, 0, 0, 0), g1 = g0;
-        d0.clear();
-        int q = static_cast<int>((m - 1) / kTurn);
-        request_some(q, d0, g0);
-        for (; q >= 0; --q) {
-            d1.clear();
-            if (q > 0)
-                request_some(q - 1, d1, g1);
-            const uint32_t valid = valid_of(q);
-            const uint64_t first = base + static_cast<uint32_t>(q) * kTurn + j * kRun;
-            uint32_t w[4];
-            d0.words(w);
-            if constexpr (UPD) {
-                w[0] = update_pair(w[0], g0.x, lr);
-                w[1] = update_pair(w[1], g0.y, lr);
-                w[2] = update_pair(w[2], g0.z, lr);
-                w[3] = update_pair(w[3], g0.w, lr);
-                if (b.keep_new) {
-                    uint16_t *back = static_cast<uint16_t *>(const_cast<void *>(src)) + first;
-                    if (valid == kRun) {
-                        *reinterpret_cast<uint4 *>(back) = make_uint4(w[0], w[1], w[2], w[3]);
-                    } else {
-#pragma unroll
-                        for (uint32_t t = 0; t < kRun; ++t)
-                            if (t < valid)
-                                back[t] = static_cast<uint16_t>(w[t >> 1] >> (16 * (t & 1)));
-                    }
-                }
-            }
-            if constexpr (SPLIT >= 0) {
-                // (the sections of the blob are padded by 256 bytes)
-                if (valid > 0) {
-                    uint64_t packed = fields_of<KB, HALF>(w);
-                    if (valid < kRun)  // nothing of the elements past the end: unused bits are zero
-                        packed &= (1ull << (valid * (KB + 1))) - 1ull;
-                    store_fields<KB>(sm, first / 8, packed);
-                    if constexpr (WIDE)
-                        *reinterpret_cast<uint4 *>(low + first) = d0.lows();
-                }
-            }
-            const uint32_t wp_before = st.wp, cur_before = st.cur;
-            float c = 1.0f;
-            if constexpr (NORM) {
-                if (valid > 0)
-                    c = coefficient(coef[first >> block_shift]);
-            }
-#pragma unroll
-            for (int t = static_cast<int>(kRun) - 1; t >= 0; --t) {
-                if (static_cast<uint32_t>(t) < valid) {
-                    const uint32_t raw = (w[t >> 1] >> (16 * (t & 1))) & 0xFFFFu;
-                    const EncSym e = enc[symbol_of<HALF>(NORM ? normalise_word(raw, c) : raw)];
-                    if constexpr (SPLIT >= 0) {
-                        least_mul = min(least_mul, e.mul);
-                        asm volatile("" : "+v"(least_mul));
-                    }
-                    rans_put(st, e, ring_bytes, lane_ring, lane_step);
-                }
-            }
-            ring_advance(st, cur_before);
-            ring_flush(wp_before, st.wp, ring_bytes, lane_ring, chunk_slots, j);
-            if (q == static_cast<int>(kMidTurn)) {
-                mid_x = st.x;
-                mid_wp = st.wp;
-            }
-            d0 = d1;
-            g0 = g1;
+        for (uint32_t r = 0; r < kBuffers; ++r)
+            turn((r + 1) % kBuffers, static_cast<int>(kBuffers - 1 - r), r + 1 < kBuffers);
+    };
+    // A ragged chunk's last turn, of which this lane has `some` elements (1..7, or all 8 while others have fewer): read one by one
+    // (the source is the caller's and ends there), coded before the others.
+    auto incomplete_turn = [&](int q, uint32_t some) {
+        const uint64_t first = base + static_cast<uint32_t>(q) * kTurn + j * kRun;
+        ahead[0].load_some(src, first, some);
+        if constexpr (NORM)
+            coefs[0] = coef[first >> block_shift];
+        if constexpr (UPD) {
+            SourceVec<false> of_grad;
+            of_grad.load_some(grad, first, some);
+            grads[0] = of_grad.a;
         }
-        // the weights written back leave the caches for memory (a fence for one workgroup per tensor, where the kernel's end
-        // would do the same; past the caches turn by turn, each request waits for the stores of the turn above: + 5 us)
+        uint32_t w[4];
+        prepare(0, q, false, w);
+        if constexpr (UPD) {
+            if (b.keep_new) {
+                uint16_t *back = static_cast<uint16_t *>(const_cast<void *>(src)) + first;
+#pragma unroll
+                for (uint32_t t = 0; t < kRun; ++t)
+                    if (t < some)
+                        back[t] = static_cast<uint16_t>(w[t >> 1] >> (16 * (t & 1)));
+            }
+        }
+        if constexpr (SPLIT >= 0) {
+            // (the sections of the blob are padded by 256 bytes; nothing of the elements past the end: unused bits are zero)
+            uint64_t packed = fields_of<KB, HALF>(w);
+            if (some < kRun)
+                packed &= (1ull << (some * (KB + 1))) - 1ull;
+            store_fields<KB>(sm, first / 8, packed);
+            if constexpr (WIDE)
+                *reinterpret_cast<uint4 *>(low + first) = ahead[0].lows();
+        }
+        const uint32_t wp_before = st.wp, cur_before = st.cur;
+#pragma unroll 1
+        for (uint32_t t = some; t-- > 0;) {
+            const EncSym e = enc[symbol_of<HALF>(((t & 2u ? (t & 4u ? w[3] : w[1]) : (t & 4u ? w[2] : w[0])) >> (16 * (t & 1u))) & 0xFFFFu)];
+            if constexpr (SPLIT >= 0)
+                least_mul = min(least_mul, e.mul);
+            rans_put(st, e, ring_bytes, lane_ring, lane_step);
+        }
+        ring_advance(st, cur_before);
+        ring_flush(wp_before, st.wp, ring_bytes, lane_ring, chunk_slots, j);
+        if (q >= static_cast<int>(kMidTurn)) {
+            mid_x = st.x;
+            mid_wp = st.wp;
+        }
+    };
+    if (whole_wave) {
+        if (m == kChunk)
+            walk(std::true_type{}, kTurns);
+    } else {
+        const uint32_t whole_turns = m / kTurn, rest = m % kTurn, some = rest > j * kRun ? min(rest - j * kRun, kRun) : 0u;
+        if (some > 0)
+            incomplete_turn(static_cast<int>(whole_turns), some);
+        walk(std::false_type{}, whole_turns);
+        // the weights that were written back one by one leave the caches for memory (a fence for one workgroup per tensor, where
+        // the kernel's end would do the same)
         if constexpr (UPD) {
             if (b.keep_new)
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");

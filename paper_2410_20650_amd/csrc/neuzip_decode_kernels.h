@@ -240,13 +240,13 @@ __device__ __forceinline__ void settle(uint64_t v)
     asm volatile("" ::"v"(static_cast<uint32_t>(v)), "v"(static_cast<uint32_t>(v >> 32)));
 }
 
-// The wave that holds a tensor's ragged last chunk: every lane walks the turns its chunk has (m elements, or
-// as many as lie before the lane's entry point; the other chunks of the wave are whole and walk beside it), the last one possibly with fewer than 8
-// elements of its own.  Fields are read a whole turn at a time and one turn ahead: the sections of the
+// The end of a tensor's ragged last chunk (and of the whole chunks that share its wave): the turns from turn0 on that the walk in
+// groups has left, fewer than a group of whole ones and one possibly with fewer than 8 elements of the lane's own; m elements, or
+// as many as lie before the lane's entry point.  Fields are read a whole turn at a time and one turn ahead: the sections of the
 // blob they come from are padded by 256 bytes, so the last read may pass the tensor's end.  The gradient is
 // the caller's, so the elements of an incomplete turn are read one by one there, as they are written.
-// (Walked element by element with a field load in front of each, the 1683 elements at the end of a
-// 10 M-element binary32 tensor took as long as the rest of the launch: 50.8 us, 25.1 us now.)
+// (Walked from its beginning a turn at a time, with the stores of a turn waited for in the next, a ragged chunk was the last to
+// end: 58.7 M elements less 1000 52.2 us, 46.8 now and without a ragged end, 45 M 45.2 / 41.3, 1 M 11.4 / 10.5.)
 template <int KB, bool LONE, bool NORM, bool UPD, bool HALF, bool EAGER, class WordSrc>
 __device__ __forceinline__ void walk_ragged(const uint32_t *__restrict__ lut, const uint2 *__restrict__ spread,
                                             const WordSrc &src, uint32_t lone, uint32_t &x, uint32_t &wp,
@@ -323,16 +323,27 @@ __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, con
 {
     static_assert(!(UPD || HALF) || (KB == 7 && !NORM), "trained weights and binary16 tensors are lossless only");
     static_assert(!(UPD && HALF), "only bf16 weights are trained");
-    // `fields` arrives holding the field bits of the state's first turns (full chunks only)
+    // `fields` arrives holding the field bits of the state's first turns (waves of full chunks only)
     constexpr uint32_t kGroup = (STREAM && KB == 7 && !UPD) ? kTurnGroupStream : kTurnGroup;
     constexpr uint32_t turns = SPLIT ? kMidTurn : kTurns;
-    if (__all(m == kChunk)) {  // all chunks of the wave are whole
+    // The whole turns, in groups: all of them where all chunks of the wave are whole (WHOLE), else as many groups as this lane has.
+    auto groups = [&](auto whole_wave) -> uint32_t {
+        constexpr bool WHOLE = decltype(whole_wave)::value;
+        const uint32_t end = turn0 + turns, have = m / kTurn < end ? m / kTurn : end;
+        const uint32_t upto = WHOLE ? turns : (have > turn0 ? (have - turn0) / kGroup * kGroup : 0u);
+        if (!WHOLE && upto == 0)
+            return 0;
         uint32_t next = LONE ? 0u : src.peek(wp);
         const uint64_t from = base + turn0 * kTurn;
         uint4 *out4 = reinterpret_cast<uint4 *>(out + from) + j;
         const uint64_t first = from + j * kRun;
         // the gradients of a turn: the 128 bits the lane's output words come from
         const uint4 *grad4 = UPD ? reinterpret_cast<const uint4 *>(grad + from) + j : nullptr;
+        if constexpr (!WHOLE) {
+#pragma unroll
+            for (uint32_t r = 0; r < kGroup; ++r)
+                fields[r] = load_turn<KB, NORM>(sm, coef, block, first + r * kTurn);
+        }
         uint4 grads[kGroup];
         if constexpr (UPD) {
 #pragma unroll
@@ -343,10 +354,10 @@ __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, con
         // the current group is decoded, and the group's 128-bit stores leave back to back, so
         // each state keeps several memory requests in flight and a chunk is written in bursts of
         // kGroup * 256 contiguous bytes.
-        for (uint32_t q0 = 0; q0 < turns; q0 += kGroup) {
+        for (uint32_t q0 = 0; q0 < upto; q0 += kGroup) {
             uint64_t fields_next[kGroup];
             // the last group re-reads its own fields (stays in bounds)
-            const uint32_t qn = q0 + kGroup < turns ? q0 + kGroup : q0;
+            const uint32_t qn = q0 + kGroup < upto ? q0 + kGroup : q0;
 #pragma unroll
             for (uint32_t r = 0; r < kGroup; ++r)
                 fields_next[r] = load_turn<KB, NORM>(sm, coef, block, first + (qn + r) * kTurn);
@@ -388,10 +399,19 @@ __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, con
                     grads[r] = grads_next[r];
             }
         }
+        if constexpr (!WHOLE) {
+#pragma unroll
+            for (uint32_t r = 0; r < kGroup; ++r)
+                settle(fields[r]);
+        }
+        return upto;
+    };
+    if (__all(m == kChunk)) {
+        groups(std::true_type{});
     } else {
-        const uint32_t end = (turn0 + turns) * kTurn;
+        const uint32_t end = (turn0 + turns) * kTurn, done = groups(std::false_type{});
         walk_ragged<KB, LONE, NORM, UPD, HALF, EAGER>(lut, spread, src, lone, x, wp, sm, coef, block, out, base, m < end ? m : end, j,
-                                               turn0, grad, lr);
+                                                      turn0 + done, grad, lr);
     }
 }
 
@@ -414,7 +434,13 @@ __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut
     constexpr uint32_t kDepth = SPLIT && ALONE ? 2 : 1;
     static_assert(turns % (kGroup * kDepth) == 0, "whole rotations");
     uint32_t next = LONE ? 0u : src.peek(wp);
-    if (__all(m == kChunk)) {
+    // (see walk_state)
+    auto groups = [&](auto whole_wave) -> uint32_t {
+        constexpr bool WHOLE = decltype(whole_wave)::value;
+        const uint32_t end = turn0 + turns, have = m / kTurn < end ? m / kTurn : end;
+        const uint32_t upto = WHOLE ? turns : (have > turn0 ? (have - turn0) / (kGroup * kDepth) * (kGroup * kDepth) : 0u);
+        if (!WHOLE && upto == 0)
+            return 0;
         // where this lane stores: its own pieces 2j and 2j + 1 of a turn's 32, or, after the exchange
         // described below, pieces (j / 8) * 16 + j % 8 and 8 further
         const uint64_t from = base + turn0 * kTurn;
@@ -436,15 +462,15 @@ __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut
         static_assert(kDepth == 1 || kDepth * kGroup == kTurnsAhead, "requested by the workgroup's beginning");
 #pragma unroll
         for (uint32_t d = 0; d < kDepth; ++d) {
-            if constexpr (kDepth == 1)
-                request(fields[d], lows[d], 0);
+            if constexpr (kDepth == 1 || !WHOLE)
+                request(fields[d], lows[d], d * kGroup);
 #pragma unroll
-            for (uint32_t r = 0; kDepth > 1 && r < kGroup; ++r) {
+            for (uint32_t r = 0; kDepth > 1 && WHOLE && r < kGroup; ++r) {
                 fields[d][r] = ahead.fields[d * kGroup + r];
                 lows[d][r] = ahead.lows[d * kGroup + r];
             }
         }
-        for (uint32_t q0 = 0; q0 < turns; q0 += kGroup * kDepth) {
+        for (uint32_t q0 = 0; q0 < upto; q0 += kGroup * kDepth) {
 #pragma unroll
             for (uint32_t d = 0; d < kDepth; ++d) {
                 const uint32_t q = q0 + d * kGroup;
@@ -453,7 +479,7 @@ __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut
                 uint64_t fields_next[kGroup];
                 uint4 lows_next[kGroup];
                 // (behind the last group: its own again, in bounds and not used)
-                const uint32_t qn = q + kDepth * kGroup < turns ? q + kDepth * kGroup : q;
+                const uint32_t qn = q + kDepth * kGroup < upto ? q + kDepth * kGroup : q;
                 if constexpr (kDepth == 1)
                     request(fields_next, lows_next, qn);
                 uint4 o[2 * kGroup];
@@ -523,11 +549,24 @@ __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut
                 }
             }
         }
+        if constexpr (!WHOLE) {
+#pragma unroll
+            for (uint32_t d = 0; d < kDepth; ++d)
+#pragma unroll
+                for (uint32_t r = 0; r < kGroup; ++r) {
+                    settle(fields[d][r]);
+                    settle(lows[d][r].x | (static_cast<uint64_t>(lows[d][r].w) << 32));
+                }
+        }
+        return upto;
+    };
+    if (__all(m == kChunk)) {
+        groups(std::true_type{});
     } else {
-        // the wave with the ragged last chunk: see walk_ragged
-        const uint32_t end = (turn0 + turns) * kTurn;
+        // what the groups have left: see walk_ragged
+        const uint32_t done = groups(std::false_type{}), end = (turn0 + turns) * kTurn;
         m = m < end ? m : end;
-        uint32_t at = turn0 * kTurn + j * kRun;
+        uint32_t at = (turn0 + done) * kTurn + j * kRun;
         uint64_t fields = 0;
         uint4 lows = make_uint4(0, 0, 0, 0);
         if (at < m) {

@@ -436,8 +436,13 @@ inline uint64_t words_room(const neuzip_blob *b)
     return b->words_bytes >= 1024 ? (b->words_bytes - 1024) / 256 * 256 / 2 : 0;
 }
 
-// Chunks per decoder workgroup.  32 (8 waves) measured best from ~16 M elements up: two such
-// workgroups fill a CU's LDS with 16 waves, and smaller workgroups lower that occupancy.  A blob with entry
+// Chunks per decoder workgroup.  32 (8 waves): two such workgroups fill a CU's LDS with 16 waves, and a launch of several rounds
+// wants them full.  One whose workgroups all run at once waits for its fullest CUs.  From 8193 to 12288 chunks they are spread over
+// two workgroups on every CU, with three waves on a SIMD where there were four on some and two on others (as 32 / spread: 34 M
+// elements 37.6 / 31.5 us, 38 M 41.3 / 32.1, 45 M 40.7 / 37.1, 50 M 43.6 / 40.5; k = 3, 36 M 36.5 / 30.9; binary32 34 M 75.6 / 53.6, 48 M
+// 81.7 / 75.2), binary32 tensors up to 8192 chunks over one (17 M 43.8 / 32.5, 25 M 50.4 / 46.1; bf16 gains nothing there up to 20 M
+// and 5 % at 24 M).  Beyond, a SIMD has four
+// either way (58.7 M 47.1 / 47.9).  A blob with entry
 // points has two lanes per state: as many chunks as spread it over the 256 CUs, between 8, below which the slot table that
 // every workgroup makes has too few threads to be made by (0.05 M elements 10.0 us at 4 chunks, 9.5 at 8; 4 M 11.5 / 10.7;
 // 16 chunks 10.2 / 11.7), and 16, the most a workgroup of 8 waves has lanes for (10 M binary32 elements at 8 / 12 / 16 chunks:
@@ -479,8 +484,13 @@ uint32_t decode_chunks_per_wg(const neuzip_blob *b)
     const uint32_t most = b->elem == NEUZIP_F16 || split ? 16u : kDecChunksPerWg;
     if (forced > 0)
         return static_cast<uint32_t>(forced) < most ? static_cast<uint32_t>(forced) : most;
-    const uint32_t spread = static_cast<uint32_t>(pad_to((b->n_chunks + 255) / 256, 4)), fit = chunks_that_fit(b);
-    const uint32_t per = split && spread < most ? (spread < 8 ? 8u : spread) : most;
+    auto over = [&](uint32_t workgroups) { return static_cast<uint32_t>(pad_to((b->n_chunks + workgroups - 1) / workgroups, 4)); };
+    uint32_t per = most;
+    if (split || (b->elem == NEUZIP_F32 && over(256) <= most))
+        per = over(256) < 8 ? 8u : (over(256) < most ? over(256) : most);
+    else if (b->elem != NEUZIP_F16 && over(256) > most && over(512) <= most / 4 * 3)
+        per = over(512);
+    const uint32_t fit = chunks_that_fit(b);
     return per < fit ? per : fit;
 }
 

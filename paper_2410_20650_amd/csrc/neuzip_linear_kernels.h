@@ -72,6 +72,12 @@ struct LinearTile<32> {
 
 constexpr uint32_t kLinThreads = 512;
 constexpr uint32_t kLinMaxTokens = 64;
+// Up to so many sums (and tokens) the waves add those of a row that ends inside the walk to y by themselves: the two barriers of
+// adding them up first cost more than the atomics, until these are too many (by themselves / added up: 16000 x 640, 1 token 18.3 /
+// 19.5 us, 2 18.9 / 19.7, 3 20.0 / 20.0; three weights of 9835 x 896 in all, 3 tokens 19.3 / 20.0; 90000 x 640, 1 token 39.7 / 41.4, 2
+// 46.4 / 41.7; 30000 x 1920, 2 tokens 37.6 / 38.4, 3 38.4 / 38.4).
+constexpr uint32_t kLinDirectTokens = 4, kLinDirectSums = 90000;
+
 struct LinearArgs {
     const TableBlock *tb;
     const uint32_t *offsets;
@@ -420,6 +426,8 @@ __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, co
     // between them in a loop of their own: with the end of a row as a branch inside one loop of turns, the compiler moved the
     // whole tile of sums from register to register in every turn, behind a wait for the matrix instruction (4096 x 14336, 1 token,
     // 38.0 -> 36.9 us, 64 tokens 67.9 -> 65.0).
+    const bool direct = COLS == 16 && MT == 1 && tokens <= kLinDirectTokens && out_features <= kLinDirectSums / tokens &&
+                        !to.whole_rows && !to.pieces;
     uint32_t q = 0, own_end = at.turns_to_end, other_end = at.other_to_end;
     for (;;) {
         const uint32_t next_end = min(all_turns, min(own_end, other_end));
@@ -460,7 +468,14 @@ __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, co
         // the end of a row of the weight inside the walk: its sums leave for y
         const bool ends = q == own_end;
         const bool col_live = q - 1 < turns && row < out_features;
-        LinearSums<COLS, MT>::template add_up<LinearSums<COLS, MT>::kFew>(acc, to, at.area, at.set, at.in_set, lane, false, ends, col_live, row, at.unit);
+        if (direct) {
+            if (ends && col_live)
+#pragma unroll
+                for (int r = 0; r < Tile::kRegs; ++r)
+                    if (Tile::row(lane, r) < tokens)
+                        atomic_add_f32((float *)(to.y + static_cast<uint64_t>(Tile::row(lane, r)) * out_features + row), acc[0][r]);
+        } else
+            LinearSums<COLS, MT>::template add_up<LinearSums<COLS, MT>::kFew>(acc, to, at.area, at.set, at.in_set, lane, false, ends, col_live, row, at.unit);
         if (ends) {
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)

@@ -336,31 +336,40 @@ def neuzip_linear_batch_scratch(weights, out_features, in_features: int, x: torc
 def _linear_scratch(outs, in_features, tokens, device, stream):
     """Scratch memory for the linear calls below, of the stream's that the call's work runs on, or None where it needs none,
     there is none to be had, or the stream is being captured (by whom is not known here, and an allocation could end it)."""
-    size = _lib.neuzip_linear_scratch_bytes(outs, len(outs), in_features, tokens) if tokens >= LINEAR_SCRATCH_TOKENS else 0
+    size = _lib.neuzip_linear_scratch_bytes(outs, len(outs), in_features, tokens)
     if size == 0 or not (stream is None or isinstance(stream, torch.cuda.Stream)):
         return None
-    with torch.cuda.stream(stream):     # (None: the current one)
-        if torch.cuda.is_current_stream_capturing():
-            return None
-        try:
-            return torch.empty(size, dtype=torch.uint8, device=device)
-        except torch.cuda.OutOfMemoryError:
-            return None
+    if stream is not None:
+        with torch.cuda.stream(stream):
+            return _linear_scratch(outs, in_features, tokens, device, None)
+    if torch.cuda.is_current_stream_capturing():
+        return None
+    try:
+        return torch.empty(size, dtype=torch.uint8, device=device)
+    except torch.cuda.OutOfMemoryError:
+        return None
 
 
 def _linear_call(weights, out_features, in_features, x, tokens, biases, ys, stream, name, scratch_of=None):
     count = len(weights)
     arr = (ctypes.c_void_p * count)(*[w.handle.value for w in weights])
     outs = (ctypes.c_uint64 * count)(*[int(o) for o in out_features])
-    scratch = scratch_of(outs) if scratch_of else _linear_scratch(outs, in_features, tokens, x.device, stream)
     yp = (ctypes.c_void_p * count)(*[y.data_ptr() for y in ys])
     bp = None
     if biases is not None:
         bp = (ctypes.c_void_p * count)(*[(b.data_ptr() if b is not None else None) for b in biases])
-    rc = _lib.neuzip_linear_batch_scratch(arr, outs, count, in_features, ctypes.c_void_p(x.data_ptr()), tokens, bp, yp,
-                                          ctypes.c_void_p(scratch.data_ptr() if scratch is not None else None),
-                                          scratch.numel() * scratch.element_size() if scratch is not None else 0,
-                                          _stream_handle(stream))
+    scratch = None
+    if scratch_of:
+        scratch = scratch_of(outs)
+    elif tokens >= LINEAR_SCRATCH_TOKENS:
+        scratch = _linear_scratch(outs, in_features, tokens, x.device, stream)
+    if scratch is None:
+        rc = _lib.neuzip_linear_batch(arr, outs, count, in_features, ctypes.c_void_p(x.data_ptr()), tokens, bp, yp,
+                                      _stream_handle(stream))
+    else:
+        rc = _lib.neuzip_linear_batch_scratch(arr, outs, count, in_features, ctypes.c_void_p(x.data_ptr()), tokens, bp, yp,
+                                              ctypes.c_void_p(scratch.data_ptr()), scratch.numel() * scratch.element_size(),
+                                              _stream_handle(stream))
     if rc != OK:
         raise NeuzipError(rc, name)
     return ys

@@ -246,17 +246,18 @@ __device__ __forceinline__ void settle(uint64_t v)
 // blob they come from are padded by 256 bytes, so the last read may pass the tensor's end.  The gradient is
 // the caller's, so the elements of an incomplete turn are read one by one there, as they are written.
 // (Walked from its beginning a turn at a time, with the stores of a turn waited for in the next, a ragged chunk was the last to
-// end: 58.7 M elements less 1000 52.2 us, 46.8 now and without a ragged end, 45 M 45.2 / 41.3, 1 M 11.4 / 10.5.)
+// end: 58.7 M elements less 1000 52.2 us, 46.8 now and without a ragged end, 45 M 45.2 / 41.3, 4 M
+// 12.3 / 11.0, binary32 2.9 M 14.0 / 13.5.)
 template <int KB, bool LONE, bool NORM, bool UPD, bool HALF, bool EAGER, class WordSrc>
 __device__ __forceinline__ void walk_ragged(const uint32_t *__restrict__ lut, const uint2 *__restrict__ spread,
                                             const WordSrc &src, uint32_t lone, uint32_t &x, uint32_t &wp,
                                             const uint8_t *__restrict__ sm, const uint8_t *__restrict__ coef,
                                             uint32_t block, uint16_t *__restrict__ out, uint64_t base, uint32_t m,
-                                            uint32_t j, uint32_t turn0, const uint16_t *__restrict__ grad, float lr)
+                                            uint32_t j, uint32_t turn0, uint64_t fields, const uint16_t *__restrict__ grad,
+                                            float lr)
 {
     uint32_t next = LONE ? 0u : src.peek(wp);
-    uint32_t at = turn0 * kTurn + j * kRun;  // this lane's run of the turn, inside the chunk
-    uint64_t fields = at < m ? load_turn<KB, NORM>(sm, coef, block, base + at) : 0;
+    uint32_t at = turn0 * kTurn + j * kRun;  // this lane's run of the turn, inside the chunk; `fields` are its
     for (; at < m; at += kTurn) {
         const uint64_t here = base + at;
         uint64_t fields_next = 0;
@@ -318,7 +319,7 @@ __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, con
                                            const uint8_t *__restrict__ coef, uint32_t block,
                                            uint64_t (&fields)[kTurnsAhead],
                                            uint16_t *__restrict__ out,
-                                           uint64_t base, uint32_t m, uint32_t j, uint32_t turn0,
+                                           uint64_t base, uint32_t m, uint32_t j, uint32_t turn0, uint64_t last_run,
                                            const uint16_t *__restrict__ grad = nullptr, float lr = 0.0f)
 {
     static_assert(!(UPD || HALF) || (KB == 7 && !NORM), "trained weights and binary16 tensors are lossless only");
@@ -327,19 +328,17 @@ __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, con
     constexpr uint32_t kGroup = (STREAM && KB == 7 && !UPD) ? kTurnGroupStream : kTurnGroup;
     constexpr uint32_t turns = SPLIT ? kMidTurn : kTurns;
     // The whole turns, in groups: all of them where all chunks of the wave are whole (WHOLE), else as many groups as this lane has.
-    auto groups = [&](auto whole_wave) -> uint32_t {
+    auto groups = [&](auto whole_wave, uint32_t upto) {
         constexpr bool WHOLE = decltype(whole_wave)::value;
-        const uint32_t end = turn0 + turns, have = m / kTurn < end ? m / kTurn : end;
-        const uint32_t upto = WHOLE ? turns : (have > turn0 ? (have - turn0) / kGroup * kGroup : 0u);
         if (!WHOLE && upto == 0)
-            return 0;
+            return;
         uint32_t next = LONE ? 0u : src.peek(wp);
         const uint64_t from = base + turn0 * kTurn;
         uint4 *out4 = reinterpret_cast<uint4 *>(out + from) + j;
         const uint64_t first = from + j * kRun;
         // the gradients of a turn: the 128 bits the lane's output words come from
         const uint4 *grad4 = UPD ? reinterpret_cast<const uint4 *>(grad + from) + j : nullptr;
-        if constexpr (!WHOLE) {
+        if constexpr (!WHOLE && !SPLIT) {  // (from the entry points they have been requested for all lanes)
 #pragma unroll
             for (uint32_t r = 0; r < kGroup; ++r)
                 fields[r] = load_turn<KB, NORM>(sm, coef, block, first + r * kTurn);
@@ -404,14 +403,19 @@ __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, con
             for (uint32_t r = 0; r < kGroup; ++r)
                 settle(fields[r]);
         }
-        return upto;
     };
     if (__all(m == kChunk)) {
-        groups(std::true_type{});
+        groups(std::true_type{}, turns);
     } else {
-        const uint32_t end = (turn0 + turns) * kTurn, done = groups(std::false_type{});
-        walk_ragged<KB, LONE, NORM, UPD, HALF, EAGER>(lut, spread, src, lone, x, wp, sm, coef, block, out, base, m < end ? m : end, j,
-                                                      turn0 + done, grad, lr);
+        // (what the groups leave is requested in front of them, where a walk is short; the address stays inside the tensor)
+        const uint32_t have = min(m / kTurn, turn0 + turns), done = have > turn0 ? (have - turn0) / kGroup * kGroup : 0u;
+        const uint64_t at = min(base + (turn0 + done) * kTurn + j * kRun, last_run);
+        uint64_t rest = SPLIT ? load_turn<KB, NORM>(sm, coef, block, at) : 0;
+        groups(std::false_type{}, done);
+        if constexpr (!SPLIT)
+            rest = load_turn<KB, NORM>(sm, coef, block, at);
+        walk_ragged<KB, LONE, NORM, UPD, HALF, EAGER>(lut, spread, src, lone, x, wp, sm, coef, block, out, base,
+                                                      min(m, (turn0 + turns) * kTurn), j, turn0 + done, rest, grad, lr);
     }
 }
 
@@ -422,7 +426,7 @@ template <bool LONE, bool STREAM, bool SPLIT, bool ALONE, bool EAGER, class Word
 __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut, const WordSrc &src, uint32_t lone,
                                                 uint32_t &x, uint32_t &wp, const uint8_t *__restrict__ sm,
                                                 const uint16_t *__restrict__ low, uint32_t *__restrict__ out,
-                                                uint64_t base, uint32_t m, uint32_t j, uint32_t turn0,
+                                                uint64_t base, uint32_t m, uint32_t j, uint32_t turn0, uint64_t last_run,
                                                 const TurnsAhead &ahead)
 {
     constexpr uint32_t kGroup = kTurnGroup;
@@ -435,12 +439,11 @@ __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut
     static_assert(turns % (kGroup * kDepth) == 0, "whole rotations");
     uint32_t next = LONE ? 0u : src.peek(wp);
     // (see walk_state)
-    auto groups = [&](auto whole_wave) -> uint32_t {
+    auto groups = [&](auto whole_wave, uint32_t upto) {
         constexpr bool WHOLE = decltype(whole_wave)::value;
-        const uint32_t end = turn0 + turns, have = m / kTurn < end ? m / kTurn : end;
-        const uint32_t upto = WHOLE ? turns : (have > turn0 ? (have - turn0) / (kGroup * kDepth) * (kGroup * kDepth) : 0u);
+        constexpr uint32_t kHeld = WHOLE ? kDepth : 1;
         if (!WHOLE && upto == 0)
-            return 0;
+            return;
         // where this lane stores: its own pieces 2j and 2j + 1 of a turn's 32, or, after the exchange
         // described below, pieces (j / 8) * 16 + j % 8 and 8 further
         const uint64_t from = base + turn0 * kTurn;
@@ -450,8 +453,8 @@ __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut
         const bool odd = lane & 1u;
         const uint4 *low4 = reinterpret_cast<const uint4 *>(low + from) + j;
         const uint64_t first = from + j * kRun;
-        uint64_t fields[kDepth][kGroup];
-        uint4 lows[kDepth][kGroup];
+        uint64_t fields[kHeld][kGroup];
+        uint4 lows[kHeld][kGroup];
         auto request = [&](uint64_t (&f)[kGroup], uint4 (&l)[kGroup], uint32_t q) {
 #pragma unroll
             for (uint32_t r = 0; r < kGroup; ++r) {
@@ -459,28 +462,28 @@ __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut
                 l[r] = low4[(q + r) * kStates];
             }
         };
-        static_assert(kDepth == 1 || kDepth * kGroup == kTurnsAhead, "requested by the workgroup's beginning");
+        static_assert(kHeld == 1 || kHeld * kGroup == kTurnsAhead, "requested by the workgroup's beginning");
 #pragma unroll
-        for (uint32_t d = 0; d < kDepth; ++d) {
-            if constexpr (kDepth == 1 || !WHOLE)
-                request(fields[d], lows[d], d * kGroup);
+        for (uint32_t d = 0; d < kHeld; ++d) {
+            if constexpr (kHeld == 1)
+                request(fields[d], lows[d], 0);
 #pragma unroll
-            for (uint32_t r = 0; kDepth > 1 && WHOLE && r < kGroup; ++r) {
+            for (uint32_t r = 0; kHeld > 1 && r < kGroup; ++r) {  // (requested for all lanes)
                 fields[d][r] = ahead.fields[d * kGroup + r];
                 lows[d][r] = ahead.lows[d * kGroup + r];
             }
         }
-        for (uint32_t q0 = 0; q0 < upto; q0 += kGroup * kDepth) {
+        for (uint32_t q0 = 0; q0 < upto; q0 += kGroup * kHeld) {
 #pragma unroll
-            for (uint32_t d = 0; d < kDepth; ++d) {
+            for (uint32_t d = 0; d < kHeld; ++d) {
                 const uint32_t q = q0 + d * kGroup;
                 uint64_t (&f)[kGroup] = fields[d];
                 uint4 (&l)[kGroup] = lows[d];
                 uint64_t fields_next[kGroup];
                 uint4 lows_next[kGroup];
                 // (behind the last group: its own again, in bounds and not used)
-                const uint32_t qn = q + kDepth * kGroup < upto ? q + kDepth * kGroup : q;
-                if constexpr (kDepth == 1)
+                const uint32_t qn = q + kHeld * kGroup < upto ? q + kHeld * kGroup : q;
+                if constexpr (kHeld == 1)
                     request(fields_next, lows_next, qn);
                 uint4 o[2 * kGroup];
 #pragma unroll
@@ -525,7 +528,7 @@ __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut
                         o[2 * r + half] = make_uint4(got[0], got[1], got[2], got[3]);
                     }
                 }
-                if constexpr (kDepth > 1)
+                if constexpr (kHeld > 1)
                     request(f, l, qn);
 #pragma unroll
                 for (uint32_t r = 0; r < kGroup; ++r) {
@@ -542,7 +545,7 @@ __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut
                             *dst = v;
                         }
                     }
-                    if constexpr (kDepth == 1) {
+                    if constexpr (kHeld == 1) {
                         f[r] = fields_next[r];
                         l[r] = lows_next[r];
                     }
@@ -551,28 +554,26 @@ __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut
         }
         if constexpr (!WHOLE) {
 #pragma unroll
-            for (uint32_t d = 0; d < kDepth; ++d)
+            for (uint32_t d = 0; d < kHeld; ++d)
 #pragma unroll
                 for (uint32_t r = 0; r < kGroup; ++r) {
                     settle(fields[d][r]);
                     settle(lows[d][r].x | (static_cast<uint64_t>(lows[d][r].w) << 32));
                 }
         }
-        return upto;
     };
     if (__all(m == kChunk)) {
-        groups(std::true_type{});
+        groups(std::true_type{}, turns);
     } else {
-        // what the groups have left: see walk_ragged
-        const uint32_t done = groups(std::false_type{}), end = (turn0 + turns) * kTurn;
-        m = m < end ? m : end;
+        // what the groups leave (see walk_ragged), requested in front of them
+        const uint32_t have = min(m / kTurn, turn0 + turns);
+        const uint32_t done = have > turn0 ? (have - turn0) / kGroup * kGroup : 0u;
         uint32_t at = (turn0 + done) * kTurn + j * kRun;
-        uint64_t fields = 0;
-        uint4 lows = make_uint4(0, 0, 0, 0);
-        if (at < m) {
-            fields = load_fields<7>(sm, base + at);
-            lows = *reinterpret_cast<const uint4 *>(low + base + at);
-        }
+        const uint64_t from = min(base + at, last_run);
+        uint64_t fields = load_fields<7>(sm, from);
+        uint4 lows = *reinterpret_cast<const uint4 *>(low + from);
+        groups(std::false_type{}, done);
+        m = min(m, (turn0 + turns) * kTurn);
         for (; at < m; at += kTurn) {
             const uint64_t here = base + at;
             uint64_t fields_next = 0;
@@ -660,12 +661,13 @@ __device__ __forceinline__ void walk_mode(const uint32_t *__restrict__ lut, cons
 {
     // (a word read from memory is fetched only when it is needed)
     constexpr bool EAGER = ALONE && !std::is_same<WordSrc, GlobalWords>::value;
+    const uint64_t last_run = (a.n - 1) & ~static_cast<uint64_t>(kRun - 1);  // where the tensor's last 8 elements, or fewer, begin
     if constexpr (MODE == kWide)
         walk_state_wide<LONE, STREAM, SPLIT, ALONE, EAGER>(lut, src, lone, x, wp, a.sm, a.low, static_cast<uint32_t *>(a.out), base, m, j,
-                                             turn0, ahead);
+                                             turn0, last_run, ahead);
     else
         walk_state<KB, LONE, NORM, STREAM, MODE == kUpdate, MODE == kHalf, SPLIT, EAGER>(
-            lut, spread, src, lone, x, wp, a.sm, a.coef, block, ahead.fields, static_cast<uint16_t *>(a.out), base, m, j, turn0,
+            lut, spread, src, lone, x, wp, a.sm, a.coef, block, ahead.fields, static_cast<uint16_t *>(a.out), base, m, j, turn0, last_run,
             a.grad, a.lr);
 }
 

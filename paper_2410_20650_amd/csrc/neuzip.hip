@@ -1563,14 +1563,34 @@ namespace {
 // in the place of the one that sets y up (64 tokens, atomics / pieces: 12000 x 4736 94 / 56 us, 30000 x 1920 146 / 61, 90000 x 640
 // 322 / 77; 16 tokens 48.5 / 42.2, 51 / 44, 87 / 46; 5 tokens 39.1 / 39.7).  Four rows apart the atomics are the cheaper
 // ones (11000 x 5120, 64 tokens, 50.2 / 54.4; 5200 x 11264 50.2 / 59.9), eight apart about even (10000 x 5632, 16 tokens 42.3 /
-// 42.1, 64 58.9 / 55.5).
-uint64_t linear_pieces_bytes(uint64_t out_features, uint64_t in_features, uint32_t tokens)
+// 42.1, 64 58.9 / 55.5).  The launch behind costs 1 us, and 5 where one in front lays the activations out too, so it takes as many sums,
+// times the rows they are apart, as atomics need that time for: up to 16 tokens (1239 x 2560, 16 tokens, 0.36 M of these, 17.4 / 18.4;
+// 3000 x 2560, 16 tokens, 0.86 M, 18.5 / 19.2; 2000 x 640, 9 tokens, 0.8 M, 19.5 / 19.5, 16 tokens, 1.3 M, 21.2 / 19.7; 10000 x 1536, 12
+// tokens, 1.7 M, 20.2 / 19.7), up to 32 (3000 x 2560, 32 tokens, 1.7 M, 20.4 / 23.0; 1000 x 4736, 24 tokens, 2.5 M, 20.1 / 21.1; 2000 x
+// 640, 32 tokens, 2.7 M, 24.7 / 24.5; 10000 x 1536, 24 tokens, 3.4 M, 23.6 / 22.2) and with more (700 x 3584, 64 tokens, 1.0 M, 20.6 / 26.8;
+// 2000 x 640, 5.4 M, 32.2 / 31.9; 1000 x 4736, 6.8 M, 26.3 / 28.7; 10000 x 1536, 9.0 M, 35.7 / 29.4).
+inline uint64_t least_piece_sums(uint32_t tokens) { return tokens <= 16 ? 1200000 : tokens <= 32 ? 3000000 : 7500000; }
+
+// pieces of rows, at most
+inline uint64_t linear_pieces(uint64_t out_features, uint64_t in_features)
+{
+    return (out_features * in_features + kMidTurn * kTurn - 1) / (kMidTurn * kTurn) + out_features;
+}
+
+bool linear_in_pieces(const uint64_t *out_features, uint32_t count, uint64_t in_features, uint32_t tokens)
 {
     const uint64_t low = in_features & (0 - in_features), apart = low < kChunk ? kChunk / low : 1;  // (the gcd is the lowest bit)
     if (tokens < 8 || kChunk % in_features == 0 || apart < 8)
-        return 0;
-    const uint64_t units = (out_features * in_features + kMidTurn * kTurn - 1) / (kMidTurn * kTurn);
-    return (units + out_features) * padded_tokens(tokens < kLinMaxTokens ? tokens : kLinMaxTokens) * sizeof(float);
+        return false;
+    uint64_t pieces = 0;
+    for (uint32_t i = 0; i < count; ++i)
+        pieces += linear_pieces(out_features[i], in_features);
+    return pieces * tokens * apart >= least_piece_sums(tokens);
+}
+
+uint64_t linear_pieces_bytes(uint64_t out_features, uint64_t in_features, uint32_t tokens)
+{
+    return linear_pieces(out_features, in_features) * padded_tokens(tokens < kLinMaxTokens ? tokens : kLinMaxTokens) * sizeof(float);
 }
 
 // The activations laid out (see linear_init_kernel).  More than 32 to 36 tokens; fewer where a launch sets y up anyway, or where every
@@ -1581,7 +1601,7 @@ uint64_t linear_laid_out_bytes(const uint64_t *out_features, uint32_t count, uin
 {
     if (tokens <= 16)
         return 0;
-    if (tokens <= 36 && (kChunk % in_features == 0 || linear_pieces_bytes(1, in_features, tokens) > 0)) {
+    if (tokens <= 36 && (kChunk % in_features == 0 || linear_in_pieces(out_features, count, in_features, tokens))) {
         const LinearForm form = linear_form(tokens, in_features, out_features, count, false);
         if (form.entries ? form.wgs <= 256 : tokens <= 32)
             return 0;
@@ -1612,8 +1632,9 @@ uint64_t neuzip_linear_scratch_bytes(const uint64_t *out_features, uint32_t coun
     if (!out_features || count > kLinBatchMax || in_features == 0 || in_features % kTurn != 0 || in_features >= (1ull << 31))
         return 0;
     uint64_t bytes = linear_laid_out_bytes(out_features, count, in_features, tokens);
-    for (uint32_t i = 0; i < count; ++i)
-        bytes += linear_pieces_bytes(out_features[i], in_features, tokens);
+    if (linear_in_pieces(out_features, count, in_features, tokens))
+        for (uint32_t i = 0; i < count; ++i)
+            bytes += linear_pieces_bytes(out_features[i], in_features, tokens);
     return bytes;
 }
 
@@ -1656,7 +1677,7 @@ int neuzip_linear_batch_scratch(const neuzip_blob *const *weights, const uint64_
     const uint64_t wanted = neuzip_linear_scratch_bytes(out_features, count, in_features, tokens);
     const bool room = d_scratch && scratch_bytes >= wanted;
     const uint64_t x_bytes = room ? linear_laid_out_bytes(out_features, count, in_features, tokens) : 0;
-    const bool in_pieces = room && wanted > x_bytes;
+    const bool in_pieces = room && linear_in_pieces(out_features, count, in_features, tokens);
     uint8_t *pieces_at = static_cast<uint8_t *>(d_scratch) + x_bytes;
     LinearBatchArgs batch;
     LinearInitArgs init;

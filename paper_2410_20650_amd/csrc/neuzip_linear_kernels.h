@@ -75,8 +75,9 @@ constexpr uint32_t kLinMaxTokens = 64;
 // Up to so many sums (and tokens) the waves add those of a row that ends inside the walk to y by themselves: the two barriers of
 // adding them up first cost more than the atomics, until these are too many (by themselves / added up: 16000 x 640, 1 token 18.3 /
 // 19.5 us, 2 18.9 / 19.7, 3 20.0 / 20.0; three weights of 9835 x 896 in all, 3 tokens 19.3 / 20.0; 90000 x 640, 1 token 39.7 / 41.4, 2
-// 46.4 / 41.7; 30000 x 1920, 2 tokens 37.6 / 38.4, 3 38.4 / 38.4).
-constexpr uint32_t kLinDirectTokens = 4, kLinDirectSums = 90000;
+// 46.4 / 41.7; 30000 x 1920, 2 tokens 37.6 / 38.4, 3 38.4 / 38.4).  Of 5 to 16 tokens the wave's 64 lanes all send, so only in the smallest
+// calls (120 x 640, 9 tokens 17.4 / 18.2; 260 x 384, 5 tokens 18.3 / 20.2; 500 x 640, 6 tokens, 3000 sums, 19.7 / 19.0).
+constexpr uint32_t kLinDirectTokens = 4, kLinDirectSums = 90000, kLinDirectFewSums = 2000;
 
 struct LinearArgs {
     const TableBlock *tb;
@@ -426,7 +427,7 @@ __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, co
     // between them in a loop of their own: with the end of a row as a branch inside one loop of turns, the compiler moved the
     // whole tile of sums from register to register in every turn, behind a wait for the matrix instruction (4096 x 14336, 1 token,
     // 38.0 -> 36.9 us, 64 tokens 67.9 -> 65.0).
-    const bool direct = COLS == 16 && MT == 1 && tokens <= kLinDirectTokens && out_features <= kLinDirectSums / tokens &&
+    const bool direct = COLS == 16 && MT == 1 && out_features <= (tokens <= kLinDirectTokens ? kLinDirectSums : kLinDirectFewSums) / tokens &&
                         !to.whole_rows && !to.pieces;
     uint32_t q = 0, own_end = at.turns_to_end, other_end = at.other_to_end;
     for (;;) {

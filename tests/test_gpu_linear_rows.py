@@ -48,6 +48,22 @@ def test_rows_with_and_without_scratch(nz, out_f, in_f, tokens):
     nz.neuzip_check(blob)
 
 
+# enough sums for the launch that adds pieces up, at each of its three limits
+@pytest.mark.parametrize("out_f,in_f", [(3600, 896), (6000, 384), (4000, 640), (11000, 1536), (2600, 1920), (1600, 4224)])
+@pytest.mark.parametrize("tokens", [8, 16, 31, 64, 66])
+def test_rows_by_pieces(nz, out_f, in_f, tokens):
+    w = inputs.gaussian_bf16((out_f, in_f), 4150 + in_f, device=DEV)
+    x = inputs.gaussian_bf16((tokens, in_f), 4250 + tokens, std=1.0, device=DEV)
+    blob = nz.neuzip_compress(w, 7)
+    size = nz.neuzip_linear_scratch_bytes([out_f], in_f, tokens)
+    assert size > 4 * out_f * min(tokens, 64)
+    room = torch.full((size + 64,), 0xFF, dtype=torch.uint8, device=DEV)
+    y = torch.full((tokens, out_f), float("nan"), dtype=torch.float32, device=DEV)
+    nz.neuzip_linear_batch_scratch([blob], [out_f], in_f, x, None, [y], room[:size])
+    within_the_bound(y, x, w, in_f)
+    assert bool((room[size:] == 0xFF).all())
+
+
 # beyond the entry points: 32 columns, several groups, the last columns without a chunk
 @pytest.mark.parametrize("out_f,in_f", [(26500, 640), (3600, 4736), (8200, 2048)])
 @pytest.mark.parametrize("tokens", [5, 20, 50])
@@ -78,7 +94,7 @@ def test_columns_as_many_as_their_words_fit(nz, out_f, in_f, tokens):
 
 
 def test_batch_by_pieces_and_under_capture(nz):
-    in_f, outs, tokens = 640, (300, 90, 41), 24
+    in_f, outs, tokens = 640, (3000, 900, 410), 24
     ws = [inputs.gaussian_bf16((o, in_f), 4700 + o, device=DEV) for o in outs]
     x = inputs.gaussian_bf16((tokens, in_f), 4701, std=1.0, device=DEV)
     biases = [torch.linspace(-1, 1, outs[0], dtype=torch.float32, device=DEV), None, None]

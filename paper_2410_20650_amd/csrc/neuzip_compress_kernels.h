@@ -397,7 +397,7 @@ __device__ inline uint32_t build_table_wave(const uint32_t (&cnt)[4], uint64_t t
 // leave the state as it is and a zero multiplier, by which the encoder recognises it.
 __device__ inline EncSym encoder_constants(uint32_t f, uint32_t cum)
 {
-    EncSym e = {0u, 0xFFFF0000u, 0u, 0u};
+    EncSym e = {0u, limit_of(0), 0u, 0u};
     if (f > 0) {
         const uint32_t s = 31u - static_cast<uint32_t>(__clz(static_cast<int>(f)));
         // floor(2^(32+s) / f): the fraction is a multiple of 1/f, so rounding the binary64 quotient (53 bits,
@@ -408,8 +408,7 @@ __device__ inline EncSym encoder_constants(uint32_t f, uint32_t cum)
         const bool single = (f & (f - 1u)) == 0u;  // a power of two: the quotient is 2^32
         const bool up = !single && 2u * rest >= f;
         e.mul = single ? 0xFFFFFFFFu : (up ? below + 1u : below);
-        // f = 4096 only for a one-symbol tensor: the state stays at 2^16 and never renormalises
-        e.limit_cum = (f >= kM ? 0xFFFF0000u : (f << 20)) | cum;
+        e.limit_cum = limit_of(f) | cum;
         e.shift_inc = s | (up ? 0u : 0x10000u);
         e.cmpl = kM - f;
     }
@@ -744,7 +743,7 @@ __device__ __forceinline__ void rans_put(EncState &st, const EncSym e, uint8_t *
     const uint32_t below = ((st.cur - lane_step) & kRingMask) | lane_ring;
     *reinterpret_cast<uint16_t *>(rings + below) = static_cast<uint16_t>(st.x);
     const uint32_t high = st.x >> 16;
-    const bool out = high >= (e.limit_cum >> 16);
+    const bool out = renormalises(st.x, e.limit_cum);
     st.cur = out ? below : st.cur;
     const uint32_t x = out ? high : st.x;
     uint32_t inc_x;  // x + inc, the upper half of shift_inc, taken by the add's operand select
@@ -940,8 +939,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
         const EncSym e = encoder_constants(tb->freq[threadIdx.x], tb->cum[threadIdx.x]);
         enc_raw[threadIdx.x] = make_uint4(e.mul, e.limit_cum, e.shift_inc, e.cmpl);
     }
-    // constants that leave a state as it is (and do not look like a symbol without room), for turns that a ragged chunk does not have
-    enc_raw[256 + threadIdx.x] = make_uint4(1u, 0xFFFF0000u, 0u, 0u);
+    enc_raw[256 + threadIdx.x] = make_uint4(kNoSymbol.mul, kNoSymbol.limit_cum, kNoSymbol.shift_inc, kNoSymbol.cmpl);
     __syncthreads();
     if (table_wg) {
         // fills in the decoder's slot table, and what decoders from the entry points need to make it, while the others

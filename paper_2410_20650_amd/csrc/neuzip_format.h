@@ -121,9 +121,10 @@ static_assert(sizeof(TableBlock) % 256 == 0, "table block keeps later sections a
 // the frequencies and cumulative frequencies of the tensor's table.
 //   The step is x <- (x / f) * M + (x mod f) + cum = q * (M - f) + x + cum with q = floor(x / f).
 //   limit_cum: the state is renormalised before the step when x >= f << 20, so q < 2^20.  f << 20
-//   has no bits in its lower half, so the test compares the upper halves only (x >> 16 against
-//   f << 4) and the lower half of the same dword carries cum (both halves are read through the
-//   sub-dword operand selects of the compare and the add, without an instruction to extract them).
+//   has no bits in its lower half, so the test compares the upper halves only (x >> 16 against the
+//   largest that stays, f << 4 less 1) and the lower half of the same dword carries cum (both halves are read
+//   through the sub-dword operand selects of the compare and the add, without an instruction to extract them).
+//   Nothing is above 0xFFFF: f = 4096 (a tensor of one symbol) and f = 0 never renormalise.
 //   mul, shift_inc: with s = floor(log2 f), q is the upper dword of (x + inc) * mul, shifted right by s
 //   (division by an invariant: Granlund and Montgomery 1994, Robison 2005).  For x < f << 20 and f < 2^12
 //   it is exact with mul = ceil(2^(32+s) / f), inc = 0 as long as (mul * f - 2^(32+s)) * f <= 2^(12+s), and
@@ -134,10 +135,17 @@ static_assert(sizeof(TableBlock) % 256 == 0, "table block keeps later sections a
 //   compare and the correction).
 struct EncSym {
     uint32_t mul;
-    uint32_t limit_cum;  // f << 20 | cum (upper half 0xFFFF: never renormalises)
+    uint32_t limit_cum;  // ((f << 4) - 1) << 16 | cum
     uint32_t shift_inc;  // s | inc << 16
     uint32_t cmpl;       // M - f
 };
+__host__ __device__ constexpr uint32_t limit_of(uint32_t f) { return ((f << 4) - 1u) << 16; }
+__host__ __device__ constexpr bool renormalises(uint32_t x, uint32_t limit_cum) { return (x >> 16) > (limit_cum >> 16); }
+
+// Of no symbol, for turns that a ragged chunk does not have: q = 0, nothing is added, nothing is renormalised, so every state
+// stays as it is, up to 2^32 - 1 (compared with >=, the limit sent the states from 0xFFFF0000 on away).  The multiplier is not
+// zero: this is no symbol without room.
+constexpr EncSym kNoSymbol = {1u, limit_of(0), 0u, 0u};
 
 // ------------------------------------------------------------------------------------------
 // Compression works on a batch of up to 8 tensors that share mantissa_bits and block size (the

@@ -329,8 +329,30 @@ def neuzip_linear_scratch_bytes(out_features, in_features: int, tokens: int) -> 
 def neuzip_linear_batch_scratch(weights, out_features, in_features: int, x: torch.Tensor, biases, ys, scratch=None, stream=None):
     """neuzip_linear_batch into ys with scratch memory (a contiguous CUDA tensor of at least
     neuzip_linear_scratch_bytes bytes, in use until the call's work has run; None: none)."""
-    return _linear_call(weights, out_features, in_features, x, x.numel() // in_features, biases, ys, stream,
+    tokens = _check_linear(weights, out_features, in_features, x, biases, ys)
+    if scratch is not None and not (scratch.is_cuda and scratch.is_contiguous()):
+        raise TypeError("expected a contiguous CUDA tensor as scratch memory")
+    return _linear_call(weights, out_features, in_features, x, tokens, biases, ys, stream,
                         "neuzip_linear_batch_scratch", lambda outs: scratch)
+
+
+def _check_linear(weights, out_features, in_features, x, biases, ys):
+    """Returns the tokens of a linear call whose tensors are what its kernels take them for."""
+    _check_tensor(x)
+    count = len(weights)
+    if len(out_features) != count or len(ys) != count or (biases is not None and len(biases) != count):
+        raise ValueError("weights, out_features, biases and ys must have one entry per weight")
+    tokens = x.numel() // in_features if in_features else 0
+    if x.numel() != tokens * in_features:
+        raise ValueError("activations must be tokens x in_features")
+    for y, o in zip(ys, out_features):
+        if not (y.is_cuda and y.dtype == torch.float32 and y.is_contiguous() and y.numel() == tokens * o):
+            raise TypeError("expected contiguous float32 CUDA tensors of tokens x out_features")
+    for bias, o in zip(biases if biases is not None else (), out_features):
+        if bias is not None and not (bias.is_cuda and bias.dtype == torch.float32 and bias.is_contiguous()
+                                     and bias.numel() == o):
+            raise TypeError("expected contiguous float32 CUDA biases of out_features")
+    return tokens
 
 
 def _linear_scratch(outs, in_features, tokens, device, stream):
@@ -405,23 +427,10 @@ def neuzip_linear_batch(weights, out_features, in_features: int, x: torch.Tensor
     """y_i = x W_hat_i^T + bias_i for several compressed weights applied to the same activations, in one
     launch (at most 4 weights).  Returns the list of float32 results."""
     _check_tensor(x)
-    count = len(weights)
-    if len(out_features) != count or (biases is not None and len(biases) != count) or \
-            (ys is not None and len(ys) != count):
-        raise ValueError("weights, out_features, biases and ys must have one entry per weight")
-    tokens = x.numel() // in_features if in_features else 0
-    if x.numel() != tokens * in_features:
-        raise ValueError("activations must be tokens x in_features")
     if ys is None:
+        tokens = x.numel() // in_features if in_features else 0
         ys = [torch.empty((tokens, o), dtype=torch.float32, device=x.device) for o in out_features]
-    for y, o in zip(ys, out_features):
-        if not (y.is_cuda and y.dtype == torch.float32 and y.is_contiguous() and y.numel() == tokens * o):
-            raise TypeError("expected contiguous float32 CUDA tensors of tokens x out_features")
-    if biases is not None:
-        for bias, o in zip(biases, out_features):
-            if bias is not None and not (bias.is_cuda and bias.dtype == torch.float32 and bias.is_contiguous()
-                                         and bias.numel() == o):
-                raise TypeError("expected contiguous float32 CUDA biases of out_features")
+    tokens = _check_linear(weights, out_features, in_features, x, biases, ys)
     _linear_call(weights, out_features, in_features, x, tokens, biases, ys, stream, "neuzip_linear_batch")
     return ys
 

@@ -145,7 +145,7 @@ struct SourceVec {
         }
     }
     __device__ __forceinline__ void clear() { a = b = make_uint4(0, 0, 0, 0); }
-    // the first `valid` (1..7) elements of a vector that passes the tensor's end, the others zero
+    // the first `valid` (1..8) elements of a vector that may pass the tensor's end, the others zero
     __device__ __forceinline__ void load_some(const void *__restrict__ src, uint64_t first, uint32_t valid)
     {
         uint32_t e[8];
@@ -706,7 +706,8 @@ __global__ __launch_bounds__(256) void sgd_update_kernel(uint16_t *__restrict__ 
 // 16-byte pieces (interleaved with the other states' of the chunk, see slot_word), so that the
 // tail of the slot read forwards is the decoder's order.  Final
 // states and run lengths go straight to their place in the blob; the chunk's word count goes to
-// the workspace for the offsets scan.  A turn's 8 bf16 words are requested four turns ahead.
+// the workspace for the offsets scan.  A turn's 8 bf16 words are requested four turns ahead (two in the
+// wave that holds a ragged last chunk).
 // ------------------------------------------------------------------------------------------
 constexpr uint32_t kEncThreads = 256;
 constexpr uint32_t kChunksPerGroup = kEncThreads / kStates;  // 16 chunks per encoder workgroup
@@ -806,8 +807,14 @@ __device__ __forceinline__ void ring_flush(uint32_t wp_before, uint32_t wp_after
 // UPD (with SPLIT = 7): the backward loop's weight step fused in.  The source holds the decompressed
 // weight, `grad` its gradient; the kernel forms W - lr * grad, writes it back over the source and
 // codes it, so the new weight is read once and never re-read from memory.
+// Waves on a SIMD, at most: beyond the cache a few that each have four turns under way ask memory for enough, and the more there are,
+// the more half-written lines of the slots are in the caches at once (235 M elements as 6 / 5 waves: kept table 222.5 / 217.8 us, k = 3
+// 205.8 / 201.0, fresh 313.6 / 311.0; binary16, 117 M, kept 133.5 / 132.1; weight step, 235 M, 5 / 4: 422 / 418).  Binary32 (117 M, fresh,
+// 4 / 5: 298.0 / 294.0) and normalised tensors (5 / 6: 595.5 / 594.1) have what their registers allow.
+constexpr int most_waves(bool norm, bool wide, bool upd) { return upd ? 4 : norm || wide ? 8 : 5; }
+
 template <bool NORM, int SPLIT, bool WIDE = false, bool HALF = false, bool UPD = false>
-__global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch b,
+__global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(1, most_waves(NORM, WIDE, UPD)))) void encode_kernel(const CompressBatch b,
                                                             const uint32_t *__restrict__ counts_ws,
                                                             uint32_t *__restrict__ chunk_words_all,
                                                             uint32_t *__restrict__ group_words_all,
@@ -851,14 +858,13 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
     const uint32_t lane_id = slot_id.wg * kEncThreads + threadIdx.x;  // = chunk * 16 + state
     const uint32_t c = lane_id / kStates, j = lane_id % kStates;
     const bool live = !table_wg && c < n_chunks;
-    const uint64_t base = static_cast<uint64_t>(c) * kChunk;
-    const uint32_t m = !live ? 0u : ((n - base) < kChunk ? static_cast<uint32_t>(n - base) : kChunk);
+    uint64_t base = static_cast<uint64_t>(c) * kChunk;
+    uint32_t m = !live ? 0u : ((n - base) < kChunk ? static_cast<uint32_t>(n - base) : kChunk);
     // The source words of a full chunk are requested kAhead turns before they are needed, in as many buffers
     // used in rotation; the first requests go out here, so that they travel while the table is made.
     // This state's first 8-element vector of the chunk; a turn later is kStates vectors on.
     const uint4 *src4 = static_cast<const uint4 *>(src) + (base / 8 + j) * (WIDE ? 2 : 1);
     // the gradients travel with the weights, one 128-bit piece per turn
-    uint64_t from = base;  // (where these begin)
     const uint4 *grad4 = UPD ? reinterpret_cast<const uint4 *>(grad) + (base / 8 + j) : nullptr;
     constexpr uint32_t kAhead = 4;  // (2: 3 % slower on tensors beyond the cache; 8: registers, 7 % slower with gradients)
     static_assert(kTurns % kAhead == 0, "whole rotations");
@@ -871,7 +877,16 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
         if constexpr (UPD)
             grads[r] = grad4[at * kStates];
         if constexpr (NORM)
-            coefs[r] = coef[(from + at * kTurn + j * kRun) >> block_shift];
+            coefs[r] = coef[(base + at * kTurn + j * kRun) >> block_shift];
+    };
+    // ... for the walk with the ragged chunk, whose inputs begin with vector `own` of the tensor
+    auto request_from = [&](uint64_t own, uint32_t r, int q) {
+        const uint64_t vec = own + static_cast<uint32_t>(q > 0 ? q : 0) * kStates;
+        ahead[r].load(static_cast<const uint4 *>(src), vec);
+        if constexpr (UPD)
+            grads[r] = reinterpret_cast<const uint4 *>(grad)[vec];
+        if constexpr (NORM)
+            coefs[r] = coef[vec * kRun >> block_shift];
     };
     const bool whole_wave = __all(m == kChunk || m == 0);
     if (whole_wave && m == kChunk) {
@@ -1013,7 +1028,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
     // weight step 78.4 / 57.6 (56.5); 58.7 M less 1000 107.5 / 95.1 (94.2).)
     auto walk = [&](auto all_whole, uint32_t whole_turns) {
         constexpr bool WHOLE = decltype(all_whole)::value;
-        // (one wave per tensor, whose registers are everybody's: four turns ahead would take 10 more; one is waited for)
+        // (one wave per tensor, whose registers are everybody's: four turns ahead would take up to 4 more; one is waited for)
         constexpr uint32_t kBuffers = WHOLE ? kAhead : 2;
         static_assert((kTurns - kMidTurn) % kBuffers == 0, "the middle lies between two rotations");
         const uint32_t turns = WHOLE ? kTurns : wave_max_u32(whole_turns);
@@ -1024,14 +1039,13 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
         // (no branch: a lane without the turn reads another one, or, if it has none at all, the wave's first chunk's, of which
         // nothing is used.  Behind a branch the compiler copies what has been requested, and waits for it right there.)
         const int most = static_cast<int>(whole_turns) - 1;
-        if (!WHOLE && most < 0) {
-            const uint64_t back = (base - static_cast<uint64_t>(wave_chunk) * kChunk) / 8;
-            src4 -= back * (WIDE ? 2 : 1);
-            if constexpr (UPD)
-                grad4 -= back;
-            from -= back * 8;
-        }
-        auto request_own = [&](uint32_t r, int q) { request(r, WHOLE ? q : min(q, most)); };
+        const uint64_t own = (most < 0 ? static_cast<uint64_t>(wave_chunk) * kChunk : base) / kRun + j;
+        auto request_own = [&](uint32_t r, int q) {
+            if constexpr (WHOLE)
+                request(r, q);
+            else
+                request_from(own, r, min(q, most));
+        };
         uint32_t w[4];
         // the constants of a pair of symbols are requested while the pair before it is coded: the compiler would
         // not move these LDS reads over the ring stores by itself, and every pair would wait for its own
@@ -1141,10 +1155,17 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const CompressBatch
             mid_wp = st.wp;
         }
     };
-    if (whole_wave) {
-        if (m == kChunk)
-            walk(std::true_type{}, kTurns);
-    } else {
+    // Nothing of either walk is held in registers through the other: they stand behind one another and not as the two sides of one
+    // branch, which the compiler lays out with the ragged side first and all that the whole chunks have requested alive through it, and
+    // the ragged one's place is worked out again (as two sides / now: 86 / 74 registers with fresh statistics, binary32 120 / 92, kept
+    // table 94 / 76, weight step 124 / 96).
+    if (whole_wave && m == kChunk)
+        walk(std::true_type{}, kTurns);
+    if (!whole_wave) {
+        uint32_t again = lane_id;
+        asm volatile("" : "+v"(again));
+        base = static_cast<uint64_t>(again / kStates) * kChunk;
+        m = again / kStates >= n_chunks ? 0u : ((n - base) < kChunk ? static_cast<uint32_t>(n - base) : kChunk);
         const uint32_t whole_turns = m / kTurn, rest = m % kTurn, some = rest > j * kRun ? min(rest - j * kRun, kRun) : 0u;
         if (some > 0)
             incomplete_turn(static_cast<int>(whole_turns), some);

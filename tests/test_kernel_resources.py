@@ -45,6 +45,26 @@ def kernel_metadata(elf):
     raise AssertionError("no kernel metadata in the code object")
 
 
+def waves_of_a_simd(elf, name):
+    """As many as the registers that the kernel's descriptor allocates leave room for (a limit that a kernel sets itself is kept by
+    allocating more than it uses, which the metadata does not say)."""
+    sections_at, = struct.unpack_from("<Q", elf, 0x28)
+    entry_size, count = struct.unpack_from("<HH", elf, 0x3A)
+    sections = [struct.unpack_from("<IIQQQQIIQQ", elf, sections_at + i * entry_size) for i in range(count)]
+    for _, kind, _, _, offset, size, link, _, _, entry in sections:
+        if kind != 11:      # SHT_DYNSYM
+            continue
+        names = sections[link][4]
+        for at in range(offset, offset + size, entry):
+            text, _, _, home, value, _ = struct.unpack_from("<IBBHQQ", elf, at)
+            begin = names + text
+            if elf[begin:elf.index(b"\0", begin)] == (name + ".kd").encode():
+                descriptor = value - sections[home][3] + sections[home][4]
+                rsrc1, = struct.unpack_from("<I", elf, descriptor + 48)
+                return REGISTERS_OF_A_SIMD_LANE // (((rsrc1 & 63) + 1) * 8)
+    raise AssertionError(name)
+
+
 @pytest.fixture(scope="module")
 def kernels():
     found = kernel_metadata(code_object())
@@ -72,6 +92,21 @@ def test_two_workgroups_of_eight_waves_share_a_cu(kernels, prefix):
         assert 2 * k[".group_segment_fixed_size"] <= LDS_OF_A_CU, name
         # two workgroups are four waves per SIMD
         assert k[".vgpr_count"] <= REGISTERS_OF_A_SIMD_LANE // 4, name
+
+
+# One wave per tensor walks a ragged last chunk, and what that takes must not be held by all of them: binary32 and normalised tensors
+# have as many waves as the walk of whole chunks allows.  The others, faster beyond the cache with fewer, have five, with gradients four.
+@pytest.mark.parametrize("kind,least,most", [("true, -1, false, false, false", 6, 8), ("false, -1, true, false, false", 5, 8),
+                                             ("false, 7, true, false, false", 5, 8), ("false, -1, false, false, false", 5, 5),
+                                             ("false, -1, false, true, false", 5, 5), ("false, 7, false, false, false", 5, 5),
+                                             ("false, 7, false, true, false", 5, 5), ("false, 3, false, false, false", 5, 5),
+                                             ("false, 1, false, false, false", 5, 5), ("false, 0, false, false, false", 5, 5),
+                                             ("false, 7, false, false, true", 4, 4)])
+def test_waves_of_the_encoders(kernels, kind, least, most):
+    k = kernels[f"encode_kernel<{kind}>"]
+    assert least <= waves_of_a_simd(code_object(), k[".name"]) <= most, k[".vgpr_count"]
+    # (workgroups of four waves: as many of them share a CU as a SIMD has waves)
+    assert least * k[".group_segment_fixed_size"] <= LDS_OF_A_CU
 
 
 def test_binary32_batches_of_many_workgroups_hold_one_group_of_turns(kernels):

@@ -223,8 +223,9 @@ __device__ __forceinline__ uint4 merge_turn(uint64_t fields, const uint32_t (&e)
     return o;
 }
 
-// What a workgroup's beginning has requested of a state's first turns (whole chunks only): the fields, and the lower halves of
-// a binary32 tensor that is walked from the entry points.
+// What a workgroup's beginning has requested of a state's first turns: the fields, and the lower halves of a binary32 tensor that is
+// walked from the entry points.  There they are requested for every lane (addresses stay inside the tensor), and waves with a
+// ragged chunk use them too; in whole walks for whole chunks only.
 constexpr uint32_t kTurnsAhead = 4;
 static_assert(kTurnsAhead >= kTurnGroup && kTurnsAhead >= kTurnGroupStream, "at least a group of turns");
 struct TurnsAhead {
@@ -324,7 +325,7 @@ __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, con
 {
     static_assert(!(UPD || HALF) || (KB == 7 && !NORM), "trained weights and binary16 tensors are lossless only");
     static_assert(!(UPD && HALF), "only bf16 weights are trained");
-    // `fields` arrives holding the field bits of the state's first turns (waves of full chunks only)
+    // `fields` arrives holding the field bits of the state's first turns (from the entry points; else of whole chunks only)
     constexpr uint32_t kGroup = (STREAM && KB == 7 && !UPD) ? kTurnGroupStream : kTurnGroup;
     constexpr uint32_t turns = SPLIT ? kMidTurn : kTurns;
     // The whole turns, in groups: all of them where all chunks of the wave are whole (WHOLE), else as many groups as this lane has.
@@ -404,7 +405,7 @@ __device__ __forceinline__ void walk_state(const uint32_t *__restrict__ lut, con
                 settle(fields[r]);
         }
     };
-    if (__all(m == kChunk)) {
+    if (__builtin_expect(__all(m == kChunk), 1)) {
         groups(std::true_type{}, turns);
     } else {
         // (what the groups leave is requested in front of them, where a walk is short; the address stays inside the tensor)
@@ -562,17 +563,21 @@ __device__ __forceinline__ void walk_state_wide(const uint32_t *__restrict__ lut
                 }
         }
     };
-    if (__all(m == kChunk)) {
+    if (__builtin_expect(__all(m == kChunk), 1)) {
         groups(std::true_type{}, turns);
     } else {
-        // what the groups leave (see walk_ragged), requested in front of them
+        // what the groups leave (see walk_ragged), requested in front of them.  In groups only where the words are in LDS: with a second
+        // copy of the group loop for the others, which hardly ever come here, the kernel is 25.7 KB of code instead of 22.5, and all waves of
+        // a launch took longer (10 M elements 16.17 us, 16.07 now, 1 M 11.81 / 11.73, mean of 42 placements).
+        constexpr bool kGroups = std::is_same<WordSrc, LdsWords>::value;
         const uint32_t have = min(m / kTurn, turn0 + turns);
-        const uint32_t done = have > turn0 ? (have - turn0) / kGroup * kGroup : 0u;
+        const uint32_t done = kGroups && have > turn0 ? (have - turn0) / kGroup * kGroup : 0u;
         uint32_t at = (turn0 + done) * kTurn + j * kRun;
         const uint64_t from = min(base + at, last_run);
         uint64_t fields = load_fields<7>(sm, from);
         uint4 lows = *reinterpret_cast<const uint4 *>(low + from);
-        groups(std::false_type{}, done);
+        if constexpr (kGroups)
+            groups(std::false_type{}, done);
         m = min(m, (turn0 + turns) * kTurn);
         for (; at < m; at += kTurn) {
             const uint64_t here = base + at;
@@ -942,7 +947,7 @@ __device__ __forceinline__ void decode_from_entries(const DecodeArgs &a, uint32_
 #pragma unroll
     for (uint32_t r = 0; r < 2; ++r)
         begins[r] = a.tb->step_of[min(tid + r * threads, kM / 8 - 1)];
-    // the first turns' inputs (addresses stay inside the tensor; a lane whose chunk is not whole makes no use of what it gets)
+    // the first turns' inputs (addresses stay inside the tensor; a lane without the turn makes no use of what it gets)
     TurnsAhead ahead = {};
     const uint32_t last_run = static_cast<uint32_t>(a.n - 1) & ~(kRun - 1);  // (such tensors have at most 2^24 elements)
     auto request_ahead = [&]() {

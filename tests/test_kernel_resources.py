@@ -45,9 +45,8 @@ def kernel_metadata(elf):
     raise AssertionError("no kernel metadata in the code object")
 
 
-def waves_of_a_simd(elf, name):
-    """As many as the registers that the kernel's descriptor allocates leave room for (a limit that a kernel sets itself is kept by
-    allocating more than it uses, which the metadata does not say)."""
+def symbol(elf, name):
+    """Where a symbol's bytes are in the file, and how many."""
     sections_at, = struct.unpack_from("<Q", elf, 0x28)
     entry_size, count = struct.unpack_from("<HH", elf, 0x3A)
     sections = [struct.unpack_from("<IIQQQQIIQQ", elf, sections_at + i * entry_size) for i in range(count)]
@@ -56,13 +55,18 @@ def waves_of_a_simd(elf, name):
             continue
         names = sections[link][4]
         for at in range(offset, offset + size, entry):
-            text, _, _, home, value, _ = struct.unpack_from("<IBBHQQ", elf, at)
+            text, _, _, home, value, length = struct.unpack_from("<IBBHQQ", elf, at)
             begin = names + text
-            if elf[begin:elf.index(b"\0", begin)] == (name + ".kd").encode():
-                descriptor = value - sections[home][3] + sections[home][4]
-                rsrc1, = struct.unpack_from("<I", elf, descriptor + 48)
-                return REGISTERS_OF_A_SIMD_LANE // (((rsrc1 & 63) + 1) * 8)
+            if elf[begin:elf.index(b"\0", begin)] == name.encode():
+                return value - sections[home][3] + sections[home][4], length
     raise AssertionError(name)
+
+
+def waves_of_a_simd(elf, name):
+    """As many as the registers that the kernel's descriptor allocates leave room for (a limit that a kernel sets itself is kept by
+    allocating more than it uses, which the metadata does not say)."""
+    rsrc1, = struct.unpack_from("<I", elf, symbol(elf, name + ".kd")[0] + 48)
+    return REGISTERS_OF_A_SIMD_LANE // (((rsrc1 & 63) + 1) * 8)
 
 
 @pytest.fixture(scope="module")
@@ -129,6 +133,11 @@ def test_weights_that_the_encoder_writes_back_leave_the_caches(kernels, tmp_path
     through, release = r"buffer_store_dwordx4 .* sc0 sc1", r"buffer_wbl2 sc0 sc1"
     assert re.search(through, of[1]) and re.search(release, of[1])
     assert not re.search(through, of[0]) and not re.search(release, of[0])
+
+
+def test_the_binary32_decoder_has_the_group_loop_of_a_ragged_chunk_once(kernels):
+    # (with a copy for every source of the words it had 25752 bytes, and every launch took longer)
+    assert symbol(code_object(), kernels["decode_kernel<7, false, 1, true>"][".name"])[1] <= 23500
 
 
 def test_decoders_that_read_the_slot_table_carry_nothing_of_making_it(kernels):

@@ -690,16 +690,22 @@ inline uint32_t columns_that_fit(const neuzip_blob *w, uint32_t cols, uint32_t w
 // (1 token, halves / whole: three weights of 1000 x 8192 23.4 / 28.2 us, two of 4096 x 4096 21.0 / 26.6, four
 // 39.5 / 34.3; 4000 x 14336 with 1000 x 14336 48.3 / 55.2); the longer walk of normalised weights gains a little further
 // (three of 4096 x 4096, k = 3, block 512: 39.3 / 41.5).  (Figures of a kernel whose words went through registers; both sides are
-// lower now.)  With more tokens, while all weights have them and they run at once (4096 x 4096, 64 tokens, halves / 32 columns
-// 20.6 / 31.6; 16000 x 512 25 / 49; q, k and v of a Llama-3-8B attention block, 32 tokens, 24.9 / 27.3, 64 29.7 / 32.4; 3000 x 4736,
-// 24 tokens, 22.4 / 31.7).  Beyond, 32 columns, which request x half as often (64 tokens, 16 / 32 columns: 4096 x 14336 86 / 69,
-// 14336 x 4096 81 / 62).
+// lower now.)  With more tokens, while all weights have them and they run at once, if the activations are laid out (4096 x 4096, 64
+// tokens, halves / 32 columns 20.6 / 31.6; 16000 x 512 25 / 49; q, k and v of a Llama-3-8B attention block, 32 tokens, 24.9 / 27.3, 64
+// 29.7 / 32.4; 3000 x 4736, 24 tokens, 22.4 / 31.7).  Beyond, 32 columns, which request x half as often (64 tokens, 16 / 32 columns:
+// 4096 x 14336 86 / 69, 14336 x 4096 81 / 62).
+// As x lies (a caller without scratch memory, a call under capture) its requests weigh more, and where CUs have two workgroups halves pay up
+// to 20 tokens only (halves / 32 columns, q, k and v: 20 tokens 23.9 / 24.5 us, 24 25.4 / 24.5, 64 42.6 / 27.5; three of 2000 x 5120, 20
+// 27.9 / 28.5, 24 29.8 / 28.7; three of 4000 x 1920, 17 32.9 / 32.9, 24 39.5 / 35.8), a little further where rows are
+// stored whole and short, which end more often in a whole walk (two of 8192 x 2048, 24 tokens 25.6 / 26.3, 32 28.5 / 26.7; 14336 x
+// 1024 with 4096 x 1024, 32 28.4 / 28.9, 48 35.7 / 32.2; two of 30000 x 512, 32 31.5 / 35.7, 64 49.8 / 49.9).
 struct LinearForm {
     uint32_t cols;
     bool entries;
     uint32_t wgs;  // (about)
 };
-inline LinearForm linear_form(uint32_t tokens, uint64_t in_features, const uint64_t *out_features, uint32_t count, bool normalised)
+inline LinearForm linear_form(uint32_t tokens, uint64_t in_features, const uint64_t *out_features, uint32_t count, bool normalised,
+                              bool laid_out)
 {
     constexpr uint32_t kAtOnce = 512;  // workgroups the chip runs at once: two on each of its 256 CUs
     uint32_t whole = 0, halves = 0;    // workgroups of the launch
@@ -714,7 +720,9 @@ inline LinearForm linear_form(uint32_t tokens, uint64_t in_features, const uint6
     }
     if (tokens <= 16)
         return {16u, any && (halves <= (normalised ? kAtOnce + kAtOnce / 2 : kAtOnce) || whole > kAtOnce), halves};
-    if (all && halves <= kAtOnce)
+    const bool short_rows = in_features < kChunk && kChunk % in_features == 0;
+    const bool few = tokens <= (short_rows ? 24u : 20u) || (short_rows && tokens * in_features <= 32 * 1024);
+    if (all && halves <= kAtOnce && (laid_out || halves <= kAtOnce / 2 || few))
         return {16u, true, halves};
     return {32u, false, whole};
 }
@@ -1602,7 +1610,7 @@ uint64_t linear_laid_out_bytes(const uint64_t *out_features, uint32_t count, uin
     if (tokens <= 16)
         return 0;
     if (tokens <= 36 && (kChunk % in_features == 0 || linear_in_pieces(out_features, count, in_features, tokens))) {
-        const LinearForm form = linear_form(tokens, in_features, out_features, count, false);
+        const LinearForm form = linear_form(tokens, in_features, out_features, count, false, true);
         if (form.entries ? form.wgs <= 256 : tokens <= 32)
             return 0;
     }
@@ -1746,7 +1754,7 @@ int neuzip_linear_batch_scratch(const neuzip_blob *const *weights, const uint64_
     const bool in_step = columns_in_step(weights, count);
     for (uint32_t t0 = 0; t0 < tokens; t0 += kLinMaxTokens) {
         const uint32_t tile = tokens - t0 < kLinMaxTokens ? tokens - t0 : kLinMaxTokens;
-        const LinearForm form = linear_form(tile, in_features, out_features, count, first->block != 0);
+        const LinearForm form = linear_form(tile, in_features, out_features, count, first->block != 0, laid_out);
         const uint32_t cols = form.cols;  // chunks per group = columns of the matrix instruction
         uint32_t wgs = 0;
         for (uint32_t i = 0; i < count; ++i) {

@@ -398,6 +398,38 @@ void form_of_the_linear_walk()
     }
 }
 
+// More than 16 tokens on weights with entry points that put two workgroups on CUs: in halves (16 columns) where the activations
+// are laid out, whole (32 columns) as they lie, up to a few tokens and but for short rows.  One workgroup per CU: in halves.
+void columns_of_the_linear_walk()
+{
+    const struct { uint64_t rows[2], in_features; uint32_t tokens; bool laid_out, as_it_lies; } cases[] = {
+        {{4096, 1024}, 4096, 17, true, true}, {{4096, 1024}, 4096, 20, true, true}, {{4096, 1024}, 4096, 21, true, false},
+        {{4096, 1024}, 4096, 64, true, false}, {{5000, 5000}, 1920, 64, true, false}, {{8192, 2048}, 2048, 24, true, true},
+        {{8192, 2048}, 2048, 25, true, false}, {{14336, 4096}, 1024, 32, true, true}, {{14336, 4096}, 1024, 33, true, false},
+        {{30000, 30000}, 512, 64, true, true}, {{2048, 1024}, 4096, 64, true, true}, {{4096, 4096}, 14336, 64, false, false}};
+    for (const auto &c : cases) {
+        neuzip_blob *weights[2] = {nullptr, nullptr};
+        float *const ys[2] = {static_cast<float *>(kSomewhere), static_cast<float *>(kSomewhere)};
+        for (int i = 0; i < 2; ++i) {
+            g_words = c.rows[i] * c.in_features / 6;
+            weights[i] = compressed(A, nullptr, c.rows[i] * c.in_features);
+        }
+        const uint64_t size = neuzip_linear_scratch_bytes(c.rows, 2, c.in_features, c.tokens);
+        for (bool room : {true, false}) {
+            g_launched.clear();
+            expect(neuzip_linear_batch_scratch(weights, c.rows, 2, c.in_features, kSomewhere, c.tokens, nullptr, ys,
+                                               room ? kSomewhere : nullptr, size, A) == NEUZIP_OK, "linear_batch_scratch");
+            const bool halves = room && size > 0 ? c.laid_out : c.as_it_lies;
+            const std::string want = halves ? "linear_batch_kernelILi7ELi16E" : "linear_batch_kernelILi7ELi32E";
+            // (sums of pieces are added up behind the walk)
+            expect(g_launched.find(want) != std::string::npos || (room && g_launched.find("linear_sum_kernel") != std::string::npos),
+                   std::to_string(c.rows[0]) + " x " + std::to_string(c.in_features) + ", " + std::to_string(c.tokens) + " tokens: " + g_launched);
+        }
+        neuzip_free(weights[0]);
+        neuzip_free(weights[1]);
+    }
+}
+
 // Blobs of a batch that other streams have filled: behind the latest of them.
 void read_a_batch()
 {
@@ -433,6 +465,8 @@ int main(int argc, char **argv)
         form_of_the_walk();
     } else if (s == "form_of_the_linear_walk") {
         form_of_the_linear_walk();
+    } else if (s == "columns_of_the_linear_walk") {
+        columns_of_the_linear_walk();
     } else if (s == "form_of_the_whole_walk") {
         form_of_the_whole_walk();
     } else if (s == "old_stamp") {

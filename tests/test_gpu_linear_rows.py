@@ -77,6 +77,22 @@ def test_rows_of_large_weights(nz, out_f, in_f, tokens):
     within_the_bound(without, x, w, in_f)
 
 
+# weights with entry points that share CUs, as x lies: in halves up to 20 tokens, whole beyond (weights that hold no slot table beside
+# ones that do)
+@pytest.mark.parametrize("in_f,outs", [(4096, (4096, 500)), (1920, (5000, 4000, 60)), (1024, (14336, 3000))])
+@pytest.mark.parametrize("tokens", [20, 21, 33, 64])
+def test_batches_without_scratch(nz, in_f, outs, tokens):
+    ws = [inputs.gaussian_bf16((o, in_f), 4350 + i, device=DEV) for i, o in enumerate(outs)]
+    x = inputs.gaussian_bf16((tokens, in_f), 4450 + tokens, std=1.0, device=DEV)
+    biases = [torch.linspace(-1, 1, o, dtype=torch.float32, device=DEV) for o in outs]
+    blobs = [nz.neuzip_compress(w, 7) for w in ws]
+    ys = [torch.full((tokens, o), float("nan"), dtype=torch.float32, device=DEV) for o in outs]
+    nz.neuzip_linear_batch_scratch(blobs, outs, in_f, x, biases, ys)
+    for y, w, b, blob in zip(ys, ws, biases, blobs):
+        within_the_bound(y, x, w, in_f, b)
+        nz.neuzip_check(blob)
+
+
 # words of 5 bits and more: groups of fewer columns than the form has, in halves and whole
 @pytest.mark.parametrize("out_f,in_f", [(96, 1024), (4100, 4736)])
 @pytest.mark.parametrize("tokens", [3, 40])

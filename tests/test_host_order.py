@@ -55,3 +55,7 @@ def test_a_decoders_workgroup_has_as_many_chunks_as_fit(driver):
 @pytest.mark.parametrize("scenario", ["form_of_the_walk", "form_of_the_whole_walk", "form_of_the_linear_walk"])
 def test_the_form_of_the_walk(driver, scenario):
     run(driver, scenario)
+
+
+def test_the_columns_of_the_linear_walk_with_and_without_scratch_memory(driver):
+    run(driver, "columns_of_the_linear_walk")

@@ -355,6 +355,19 @@ def _check_linear(weights, out_features, in_features, x, biases, ys):
     return tokens
 
 
+class _OutsideOfCaptures:
+    """An allocation in here and a capture by another thread leave each other alone.  (One in the global mode, torch's default, fails an
+    allocation by any thread and is ended by it, unless that thread's own mode is relaxed.)"""
+    RELAXED = 2     # hipStreamCaptureModeRelaxed
+
+    def __enter__(self):
+        self.mode = ctypes.c_int(self.RELAXED)
+        _lib.hipThreadExchangeStreamCaptureMode(ctypes.byref(self.mode))    # (of the runtime that the library is linked to)
+
+    def __exit__(self, *_):
+        _lib.hipThreadExchangeStreamCaptureMode(ctypes.byref(self.mode))
+
+
 def _linear_scratch(outs, in_features, tokens, device, stream):
     """Scratch memory for the linear calls below, of the stream's that the call's work runs on, or None where it needs none,
     there is none to be had, or the stream is being captured (by whom is not known here, and an allocation could end it)."""
@@ -367,7 +380,8 @@ def _linear_scratch(outs, in_features, tokens, device, stream):
     if torch.cuda.is_current_stream_capturing():
         return None
     try:
-        return torch.empty(size, dtype=torch.uint8, device=device)
+        with _OutsideOfCaptures():
+            return torch.empty(size, dtype=torch.uint8, device=device)
     except torch.cuda.OutOfMemoryError:
         return None
 

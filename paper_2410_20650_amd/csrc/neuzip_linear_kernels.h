@@ -72,12 +72,16 @@ struct LinearTile<32> {
 
 constexpr uint32_t kLinThreads = 512;
 constexpr uint32_t kLinMaxTokens = 64;
-// Up to so many sums (and tokens) the waves add those of a row that ends inside the walk to y by themselves: the two barriers of
-// adding them up first cost more than the atomics, until these are too many (by themselves / added up: 16000 x 640, 1 token 18.3 /
-// 19.5 us, 2 18.9 / 19.7, 3 20.0 / 20.0; three weights of 9835 x 896 in all, 3 tokens 19.3 / 20.0; 90000 x 640, 1 token 39.7 / 41.4, 2
-// 46.4 / 41.7; 30000 x 1920, 2 tokens 37.6 / 38.4, 3 38.4 / 38.4).  Of 5 to 16 tokens the wave's 64 lanes all send, so only in the smallest
-// calls (120 x 640, 9 tokens 17.4 / 18.2; 260 x 384, 5 tokens 18.3 / 20.2; 500 x 640, 6 tokens, 3000 sums, 19.7 / 19.0).
-constexpr uint32_t kLinDirectTokens = 4, kLinDirectSums = 90000, kLinDirectFewSums = 2000;
+// Up to so many sums the waves add those of a row that ends inside the walk to y by themselves: the two barriers of adding them up
+// first cost more than the atomics, until these are too many, the sooner the more of a wave's 64 lanes send (by themselves / added up:
+// 16000 x 640, 1 token, 16.9 / 17.9 us, 90000 x 640 35.3 / 38.1; 40000 x 640, 2 tokens, 27.7 / 30.5; 15000 x 640, 3 tokens, 18.1 / 18.5,
+// 25000 x 640 23.8 / 19.1; 5000 x 1152, 4 tokens, 17.1 / 17.8, 13000 x 640 19.2 / 18.6; 5 tokens: 900 x 384 17.9 / 19.3, 2000 x 1152
+// 17.1 / 17.6, 3000 x 640 18.5 / 18.3; 6 tokens: 600 x 1152 17.2 / 18.0, 1000 x 640 18.9 / 18.5; 260 x 384, 10 tokens, 18.1 / 18.9; 500 x
+// 384, 8 tokens, 21.5 / 20.1; 120 x 1152, 16 tokens, 15.9 / 17.0, 300 x 640, 12 tokens, 19.1 / 18.4).
+constexpr uint32_t direct_sums(uint32_t tokens)
+{
+    return tokens <= 2 ? 90000 : tokens <= 4 ? 45000 : tokens == 5 ? 10000 : tokens == 6 ? 5000 : 2500;
+}
 
 struct LinearArgs {
     const TableBlock *tb;
@@ -427,9 +431,14 @@ __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, co
     // between them in a loop of their own: with the end of a row as a branch inside one loop of turns, the compiler moved the
     // whole tile of sums from register to register in every turn, behind a wait for the matrix instruction (4096 x 14336, 1 token,
     // 38.0 -> 36.9 us, 64 tokens 67.9 -> 65.0).
-    const bool direct = COLS == 16 && MT == 1 && out_features <= (tokens <= kLinDirectTokens ? kLinDirectSums : kLinDirectFewSums) / tokens &&
-                        !to.whole_rows && !to.pieces;
-    uint32_t q = 0, own_end = at.turns_to_end, other_end = at.other_to_end;
+    const bool direct = COLS == 16 && MT == 1 && out_features <= direct_sums(tokens) / tokens && !to.whole_rows && !to.pieces;
+    // (sums that leave by themselves meet at no barrier: the other set's ends are nothing to this one)
+    uint32_t q = 0, own_end = at.turns_to_end, other_end = direct ? ~0u : at.other_to_end;
+    // The fields of the turn behind an end are waited for in front of it.  Behind it, it would be for the acknowledgements of the sums
+    // that leave there, too, at every end (300 x 640, 4 tokens, 17.4 us, 16.1 now; 260 x 384, 5 tokens, 18.5 / 16.7; 2000 x 640, 6
+    // tokens, 19.2 / 18.5; 57344 x 1024, 16 tokens, 36.0 / 35.2).  The compiler waits behind it if there is a way there without.
+    if constexpr (EARLY)
+        settle(fields);
     for (;;) {
         const uint32_t next_end = min(all_turns, min(own_end, other_end));
         for (; q < next_end; ++q) {
@@ -464,6 +473,8 @@ __device__ __forceinline__ void linear_walk(const uint32_t *__restrict__ lut, co
                 acc[mt] = Tile::mma(xa[mt], b.v, acc[mt]);
             request_coef(q + 1);
         }
+        if constexpr (EARLY)
+            settle(fields);
         if (q == all_turns)
             break;
         // the end of a row of the weight inside the walk: its sums leave for y

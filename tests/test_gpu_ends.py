@@ -1,5 +1,5 @@
-"""GPU parity at the ragged end of a tensor (-m gpu): the wave that holds an incomplete last chunk takes a
-walk of its own in the decoder and in the encoders.  Every remainder class of a turn (128 elements) and of a
+"""GPU parity at the ragged end of a tensor (-m gpu): the wave that holds an incomplete last chunk has
+branches of its own in the decoder and in the encoders.  Every remainder class of a turn (128 elements) and of a
 lane's run (8), alone in the tensor and beside whole chunks of the same wave, for each element type, width
 and direction, against the oracle; nothing is written behind the tensor.
 """

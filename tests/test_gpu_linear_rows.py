@@ -93,6 +93,20 @@ def test_batches_without_scratch(nz, in_f, outs, tokens):
         nz.neuzip_check(blob)
 
 
+# the last calls whose waves add their sums to the result by themselves, and the first whose do not; two sets whose rows end in
+# other turns
+@pytest.mark.parametrize("in_f", [384, 640])
+@pytest.mark.parametrize("tokens,most", [(3, 15000), (5, 2000), (6, 833), (7, 357), (16, 156)])
+def test_sums_by_themselves_and_added_up(nz, in_f, tokens, most):
+    x = inputs.gaussian_bf16((tokens, in_f), 4460 + tokens, std=1.0, device=DEV)
+    for out_f in (most, most + 1):
+        w = inputs.gaussian_bf16((out_f, in_f), 4470 + out_f, device=DEV)
+        bias = torch.linspace(-1, 1, out_f, dtype=torch.float32, device=DEV)
+        blob = nz.neuzip_compress(w, 7)
+        within_the_bound(nz.neuzip_linear(blob, out_f, in_f, x, bias), x, w, in_f, bias)
+        nz.neuzip_check(blob)
+
+
 # words of 5 bits and more: groups of fewer columns than the form has, in halves and whole
 @pytest.mark.parametrize("out_f,in_f", [(96, 1024), (4100, 4736)])
 @pytest.mark.parametrize("tokens", [3, 40])

@@ -41,3 +41,24 @@ def test_shared_turns(nz, whole, end):
         (rebuilt,) = nz.neuzip_update([blob], [g], [space], 1e-2, weights_ready=mode)
         assert rebuilt == want_rebuilt and np.array_equal(nz.neuzip_export(blob), container), (n, mode)
         assert np.array_equal(inputs.bits(space), want_words), (n, mode)
+
+
+@pytest.mark.parametrize("whole", [1, 18])
+@pytest.mark.parametrize("end", [5, 129, 1920, 2047, 2049, 2048 + 127, 2048 + 128, 2304 + 3, 3968])
+def test_shared_turns_of_other_types_and_kept_tables(nz, whole, end):
+    n = whole * 4096 + end
+    for w, bits, compress in ((inputs.gaussian_f32(n, 5100 + n, device=DEV), inputs.bits32, O.compress_f32),
+                              (inputs.gaussian_f16(n, 5101 + n, device=DEV), inputs.bits16, O.compress_f16),
+                              (inputs.gaussian_bf16(n, 5102 + n, device=DEV), inputs.bits,
+                               lambda words, **kw: O.compress(words, 7, **kw))):
+        (blob,) = nz.neuzip_compress_guarded([w], 7, 8)
+        assert np.array_equal(nz.neuzip_export(blob), compress(bits(w), threads=8, guard=8)), (n, w.dtype)
+        for v in (w, inputs.synthetic_update(w, 5103 + n)):
+            table = nz.neuzip_frequencies(blob).copy()
+            (rebuilt,) = nz.neuzip_recompress([v], [blob])
+            want = compress(bits(v), threads=8, guard=8, **({} if rebuilt else {"freq": table}))
+            assert np.array_equal(nz.neuzip_export(blob), want), (n, w.dtype, "kept table")
+            out = torch.zeros_like(v)
+            nz.neuzip_decompress(blob, out)
+            nz.neuzip_check(blob)
+            assert np.array_equal(bits(out), bits(v)), (n, w.dtype)

@@ -320,9 +320,11 @@ int neuzip_linear_batch(const neuzip_blob *const *weights, const uint64_t *out_f
                         float *const *d_y, void *hip_stream);
 
 /*
- * neuzip_linear_batch_scratch -- the same with scratch memory of the caller's, for more than 16 tokens: the
- * activations are first laid out there in the order in which the kernel reads them, which makes a call on 64
- * tokens a third faster.
+ * neuzip_linear_batch_scratch -- the same with scratch memory of the caller's, which serves for two things.
+ * From 17 tokens on, most calls first lay the activations out there in the order in which the kernel reads them,
+ * which makes a call on 64 tokens a third faster.  From 8 tokens on, calls whose rows end inside chunks in many
+ * places store the sums of pieces of rows there (a piece lies inside one chunk or half of one) and add them up in a
+ * launch of their own.
  *
  *   d_scratch      device buffer of scratch_bytes bytes, 16-byte aligned (else EINVAL), in use until the call's
  *                  work has run; or NULL.  With less than neuzip_linear_scratch_bytes() bytes the call is
@@ -332,8 +334,10 @@ int neuzip_linear_batch_scratch(const neuzip_blob *const *weights, const uint64_
                                 uint64_t in_features, const void *d_x, uint32_t tokens, const float *const *d_bias,
                                 float *const *d_y, void *d_scratch, uint64_t scratch_bytes, void *hip_stream);
 
-/* The scratch memory that the call above makes use of, in bytes: about that of the activations and of one or two results, a
- * result being at most 64 tokens of it; 0 where it needs none. */
+/* The scratch memory that the call above makes use of, in bytes; 0 where it needs none.  At most the activations', their
+ * last 64 tokens or fewer rounded up to a multiple of 4, and for every weight that of out_features * (in_features /
+ * 2048 + 1) + 1 sums of min(tokens, 64) tokens, rounded up like that, of 4 bytes each: in_features / 2048 + 1 results
+ * (14.6 for rows of 27776). */
 uint64_t neuzip_linear_scratch_bytes(const uint64_t *out_features, uint32_t count, uint64_t in_features, uint32_t tokens);
 
 /* Releases the blob and its device memory.  NULL is a no-op. */

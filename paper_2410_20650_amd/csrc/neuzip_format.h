@@ -84,7 +84,7 @@ struct Divisor {
 };
 
 // A launch's arguments come to a CU cache line by cache line, and a line that is first asked for when it is needed is 550
-// cycles (the first of all 1000, one that is there 80): a kernel asks for all of them with its first instructions.
+// cycles (the first of all 1000, one that is there 80): a kernel asks for all lines of `a` with its first instructions.
 template <class Args>
 __device__ __forceinline__ void fetch_arguments(const Args &a)
 {

@@ -151,8 +151,8 @@ constexpr uint32_t kLinInitThreads = 256, kLinInitTokens = 4;
 __host__ __device__ constexpr uint32_t padded_tokens(uint32_t tokens) { return (tokens + 3) / 4 * 4; }  // 128 bytes
 __global__ void linear_init_kernel(const LinearInitArgs b)
 {
-    // which weight's y this workgroup sets up (all candidates at once: the launch is a chain of latencies, and an argument
-    // that waits for another one is a link of it)
+    // which weight's y this workgroup sets up (a grid of outputs x tokens x weights, where this is known without a look at the ends
+    // and without a division, gave nothing: 300 x 1152, 9 tokens, 17.7 us either way)
     float *y = nullptr;
     const float *bias = nullptr;
     uint32_t out_features = 1, first = 0;
@@ -679,7 +679,8 @@ __global__ __launch_bounds__(kLinThreads, 4) void linear_batch_kernel(const Line
         float area[kLinAreaBytes / 4];
         uint32_t steps[READ ? 4 : kSteps];
     } lds;
-    fetch_arguments(b.t[0]);  // (and the ends)
+    // (the first weight's, with the ends, which lie in its first line; workgroups of the others wait for theirs as they come to them)
+    fetch_arguments(b.t[0]);
     uint32_t i = 0, first = 0;
 #pragma unroll
     for (uint32_t n = 0; n + 1 < kLinBatchMax; ++n) {  // (behind the last weight: no workgroup has these numbers)
